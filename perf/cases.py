@@ -4,8 +4,9 @@ A case is one call pattern of the public entry points (`paper_2605_08123_amd.bin
 forward for inference, a forward and a backward as two calls (an autograd function around the
 library), or the one-call step for a cotangent known beforehand.  `listed()` names the cases that are
 quoted, `draw(rng)` gives another one of the same ranges, `prepare(case, seed)` makes what a program
-holds before the call, `run(state)` is one pass, `work(case)` what the pass cannot do without and
-`tolerance(case)` what another implementation of the same precision may differ by.
+holds before the call, `run(state)` is one pass, `work(case)` what the pass cannot do without,
+`tolerance(case)` what another implementation of the same precision may differ by and `exact(case, seed)` the
+outputs in 64 bits, from plain torch.
 
 Fields of a case:
   call   "step" (one call, caller's buffers), "fwd" or "fwd_bwd" (results allocated per call)
@@ -183,3 +184,144 @@ def tolerance(case):
     if case["dtype"] == "f32":
         return {"rel": 1e-5}
     return {"rel": 2e-2 if case["kind"] == "token" else 1e-2}
+
+
+def _win(x, w):
+    """[..., L] -> view [L, 2w+1] with entry (i, k) = x[i + k - w], zeros outside."""
+    return torch.nn.functional.pad(x, (w, w)).unfold(0, 2 * w + 1, 1)
+
+
+def _chunks(x, w, c):
+    """[L, d] -> [n, c + 2w, d]: the rows that rows [ic, ic + c) meet in the band, zeros outside."""
+    n = -(-x.shape[0] // c)
+    return torch.nn.functional.pad(x, (0, 0, w, w + n * c - x.shape[0])).unfold(0, c + 2 * w, c).transpose(1, 2).contiguous()
+
+
+def _diag(dense, w):
+    """The band of dense chunks [n, c, c + 2w] as a view [n, c, 2w + 1]."""
+    n, c, m = dense.shape
+    return dense.as_strided((n, c, 2 * w + 1), (c * m, m + 1, 1))
+
+
+def _band(x, y, w):
+    """[L, 2w+1] with entry (i, k) = <x_i, y_{i + k - w}>."""
+    L, c = x.shape[0], max(64, min(w, 1024))
+    yc = _chunks(y, w, c)
+    xc = torch.nn.functional.pad(x, (0, 0, 0, yc.shape[0] * c - L)).view(-1, c, x.shape[1])
+    return _diag(torch.bmm(xc, yc.transpose(1, 2).contiguous()), w).reshape(-1, 2 * w + 1)[:L]
+
+
+def _apply(m, y, w):
+    """sum over the band of m[i, k] y_{i + k - w}."""
+    L, c = m.shape[0], max(64, min(w, 1024))
+    yc = _chunks(y, w, c)
+    dense = m.new_zeros((yc.shape[0], c, c + 2 * w))
+    _diag(dense, w).copy_(torch.nn.functional.pad(m, (0, 0, 0, yc.shape[0] * c - L)).view(-1, c, 2 * w + 1))
+    return torch.bmm(dense, yc).view(-1, y.shape[1])[:L]
+
+
+def _flip(m, w):
+    """The transposed band matrix: (j, k) -> m[j + k - w, 2w - k]."""
+    return torch.nn.functional.pad(m, (0, 0, w, w)).as_strided(m.shape, (2 * w + 1, 2 * w), 2 * w)
+
+
+def _exact_one(Q, K, V, G, c, ok_q, ok_k, la, lb, tok):
+    """One problem in fp64: the solve as written, then the reverse sweep over the unrolled tail.  tok: (q, k, v) of
+    the dustbin tokens, or None; a scalar dustbin (score and payload zero) is three zero tokens."""
+    L, d = Q.shape
+    w, R, sc = min(c["W"], L - 1), c["R"], 1.0 / (c["eps"] * math.sqrt(Q.shape[1]))
+    inf = float("inf")
+    S = _band(Q, K, w) * sc
+    i, k = torch.arange(L, device=Q.device)[:, None], torch.arange(2 * w + 1, device=Q.device)[None]
+    j = i + k - w
+    S.masked_fill_((j < 0) | (j >= L) | ~ok_q[:, None] | ~(_win(ok_k.double(), w) > 0), -inf)
+    del j
+    St = _flip(S, w).contiguous()
+    St.masked_fill_((i + k - w < 0) | (i + k - w >= L), -inf)
+    if tok is not None:
+        q_db, k_db, v_db = tok
+        sq, sk, scc = sc * (Q @ k_db), sc * (K @ q_db), sc * (q_db @ k_db)
+
+    def half(M, y, yL, spoke, spoke_oth, target):
+        s = torch.logsumexp(M + _win(y, w), 1)
+        xL = None
+        if tok is not None:
+            s = torch.logaddexp(s, spoke + yL)
+            xL = -torch.logaddexp(torch.logsumexp(spoke_oth + y, 0), scc + yL)
+        return torch.where(s > -inf, target - s, 0.0), xL
+
+    sq_, sk_ = (sq, sk) if tok is not None else (None, None)
+    v, vL, us, vs = torch.zeros_like(Q[:, 0]), Q.new_zeros(()), [], []
+    for t in range(c["T"] + R):
+        if t == 0 and not c["T"]:
+            us, vs = [(torch.zeros_like(v), vL)], [(v, vL)]
+        u, uL = half(S, v, vL, sq_, sk_, la)
+        v, vL = half(St, u, uL, sk_, sq_, lb)
+        if t >= c["T"] - 1:
+            us.append((u, uL))
+            vs.append((v, vL))
+    del St
+    cat = (lambda x: torch.cat([x[0], x[1].reshape(1)])) if tok is not None else (lambda x: x[0])
+    out = {"UV": torch.stack([cat(x) for p in zip(us, vs) for x in p])}
+
+    plan = lambda u, v: torch.exp(S + u[0][:, None] + _win(v[0], w))
+    spokes = lambda u, v: (torch.exp(sq + u[0] + v[1]), torch.exp(sk + u[1] + v[0]), torch.exp(scc + u[1] + v[1]))
+    P = plan(us[R], vs[R])
+    out["O"] = _apply(P, V, w)
+    if tok is not None:
+        pr, _, _ = spokes(us[R], vs[R])
+        out["O"] = out["O"] + pr[:, None] * v_db
+    if c["call"] == "fwd":
+        return out
+    out["dV"] = _apply(_flip(P, w), G, w)
+    Sb = P * _band(G, V, w)
+    ub, vb, ubL, vbL = Sb.sum(1), _flip(Sb, w).sum(1), Q.new_zeros(()), Q.new_zeros(())
+    if tok is not None:
+        sqb, skb, scb = pr * (G @ v_db), torch.zeros_like(pr), Q.new_zeros(())
+        ub, vbL = ub + sqb, sqb.sum()
+        out["dv_db"] = pr @ G
+    ea, eb = torch.exp(-la), torch.exp(-lb)
+    for t in range(R, 0, -1):
+        M = plan(us[t], vs[t]) * _win(vb * eb, w)   # v_t from u_t
+        Sb -= M
+        ub = ub - M.sum(1)
+        if tok is not None:
+            a, b, x = spokes(us[t], vs[t])
+            sqb, skb, scb = sqb - a * vbL, skb - b * vb, scb - x * vbL
+            ub, ubL = ub - a * vbL, ubL - (b * vb).sum() - x * vbL
+        M = plan(us[t], vs[t - 1]) * (ub * ea)[:, None]   # u_t from v_{t-1}
+        Sb -= M
+        vb = -_flip(M, w).sum(1)
+        if tok is not None:
+            a, b, x = spokes(us[t], vs[t - 1])
+            sqb, skb, scb = sqb - a * ub, skb - b * ubL, scb - x * ubL
+            vb, vbL = vb - b * ubL, -(a * ub).sum() - x * ubL
+        ub, ubL = torch.zeros_like(ub), torch.zeros_like(ubL)
+    del M, P
+    out["dQ"], out["dK"] = sc * _apply(Sb, K, w), sc * _apply(_flip(Sb, w), Q, w)
+    if tok is not None:
+        out["dQ"] = out["dQ"] + sc * sqb[:, None] * k_db
+        out["dK"] = out["dK"] + sc * skb[:, None] * q_db
+        out["dk_db"], out["dq_db"] = sc * (sqb @ Q + scb * q_db), sc * (skb @ K + scb * k_db)
+    return out
+
+
+def exact(case, seed):
+    c, s = case, prepare(case, seed)
+    B, H, L, d = s["Q"].shape
+    kind, dev = c["kind"], s["Q"].device
+    pos, every, zero = torch.arange(L, device=dev), torch.ones(L, dtype=torch.bool, device=dev), torch.zeros(L, device=dev).double()
+    res = []
+    for n in range(B * H):
+        b, h = divmod(n, H)
+        ok_q = ok_k = every
+        if kind == "varlen":
+            ok_q, ok_k = pos < s["len_q"][b], pos < s["len_k"][b]
+        if kind == "masked":
+            ok_q, ok_k = s["mask_q"][b] != 0, s["mask_k"][b] != 0
+        la, lb = (s["log_a"][b, h].double(), s["log_b"][b, h].double()) if kind == "marginals" else (zero, zero)
+        tok = [t[b, h].double() for t in s["tok"]] if kind == "token" else [zero[:d]] * 3 if kind == "dustbin" else None
+        res.append(_exact_one(*(s[x][b, h].double() for x in ("Q", "K", "V", "dO")), c, ok_q, ok_k, la, lb, tok))
+    names = ["O"] + (["UV"] if kind != "masked" else []) + (["dQ", "dK", "dV"] if c["call"] != "fwd" else [])
+    names += ["dq_db", "dk_db", "dv_db"] if kind == "token" and c["call"] == "fwd_bwd" else []
+    return {x: torch.stack([r[x] for r in res]).view((B, H) + tuple(res[0][x].shape)) for x in names}
