@@ -382,7 +382,7 @@ __global__ __launch_bounds__(NTHREADS) void vsweep_kernel(const SweepArgs a)
     // a.lead workgroups come first (a multiple of 8, so the XCD of a sweep block is unchanged): one
     // per problem for the dustbin element, started first so that it ends under the sweep
     if ((int)blockIdx.x < a.lead) {
-        if ((int)blockIdx.x < a.nb_total / a.nbp) dustbin_element(a, blockIdx.x, MODE == M_MATVEC);
+        if ((int)blockIdx.x < a.nb_total / a.nbp) dustbin_element<MODE == M_MATVEC>(a, blockIdx.x);
         return;
     }
     const int lb = xcd_block((int)blockIdx.x - a.lead, a.nb_total, a.rev);
