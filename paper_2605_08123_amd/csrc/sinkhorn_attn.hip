@@ -722,7 +722,7 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         if (hipGetLastError() != hipSuccess) return SKA_EHIP;
         if (p.token()) {
             // dv_db = sum_i P_RR(i, d_k) dO_i and vbar_R at the dustbin column = <v_db, dv_db>
-            hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(256), 0, st, reinterpret_cast<const T *>(G),
+            hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(WS_THREADS), 0, st, reinterpret_cast<const T *>(G),
                                Vec{nullptr, 0}, SQ, uv(2 * R), uv(2 * R + 1), partial, L);
             hipLaunchKernelGGL((wsum_final_kernel<D>), dim3(N), dim3(D), 0, st, partial, nchunk, Vec{nullptr, 0}, 0,
                                nullptr, 1.f, p.dv_db, p.v_db, wo(vbar(R)), L);
@@ -834,11 +834,11 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         hipLaunchKernelGGL((spoke_axpy_kernel<T, D>), agrid, dim3(256), 0, st, reinterpret_cast<T *>(dK), wv(sbc),
                            p.q_db, cs, L);
         // dk_db = c (sum_i sbr_i q_i + sbr_L q_db), dq_db = c (sum_j sbc_j k_j + sbc_L k_db)
-        hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(256), 0, st, reinterpret_cast<const T *>(Qin),
+        hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(WS_THREADS), 0, st, reinterpret_cast<const T *>(Qin),
                            wv(sbr), Vec{nullptr, 0}, Vec{nullptr, 0}, Vec{nullptr, 0}, partial, L);
         hipLaunchKernelGGL((wsum_final_kernel<D>), dim3(N), dim3(D), 0, st, partial, nchunk, wv(sbr), L, p.q_db, cs,
                            p.dk_db, nullptr, VecOut{nullptr, 0}, 0);
-        hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(256), 0, st, reinterpret_cast<const T *>(K),
+        hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(WS_THREADS), 0, st, reinterpret_cast<const T *>(K),
                            wv(sbc), Vec{nullptr, 0}, Vec{nullptr, 0}, Vec{nullptr, 0}, partial, L);
         hipLaunchKernelGGL((wsum_final_kernel<D>), dim3(N), dim3(D), 0, st, partial, nchunk, wv(sbc), L, p.k_db, cs,
                            p.dq_db, nullptr, VecOut{nullptr, 0}, 0);

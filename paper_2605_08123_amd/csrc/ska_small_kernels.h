@@ -143,19 +143,23 @@ __global__ void spoke_scores_kernel(const T *M, const float *x, const float *xc,
 //   plan : w_o = exp(spoke[o] + x[o] + yL)   (plan entries of the spokes (o, dustbin); yL = y[L])
 //   given: w_o = wv[o]
 // partial[n][chunk][dv] = sum over the chunk's rows o of w_o M[n][o][dv]; rows in chunks of WS_ROWS.
-constexpr int WS_ROWS = 1024;
+// A workgroup takes one chunk.  The rows are few and their loads independent, so latency is what bounds
+// it: 1024 threads and eight rows requested before the first is used (256 threads, row after row:
+// 21 us per sum at L = 5000; eight problems of that length 522 -> 463 us per forward and backward).
+constexpr int WS_ROWS = 1024, WS_THREADS = 1024;
 template <typename T, int D>
-__global__ __launch_bounds__(256) void wsum_kernel(const T *M, Vec wv, Vec spoke, Vec x, Vec y, float *partial, int L)
+__global__ __launch_bounds__(WS_THREADS) void wsum_kernel(const T *M, Vec wv, Vec spoke, Vec x, Vec y, float *partial, int L)
 {
     constexpr int TPR = D / 4;            // threads per row, four columns each
-    constexpr int RPI = 256 / TPR;        // rows per iteration
-    __shared__ float red[256][4];
+    constexpr int RPI = WS_THREADS / TPR; // rows per iteration
+    __shared__ float red[WS_THREADS / 64][TPR][4];
     const int n = blockIdx.y, chunk = blockIdx.x, tid = threadIdx.x;
     const int col = (tid % TPR) * 4, r0 = tid / TPR;
     const int o_end = min(L, (chunk + 1) * WS_ROWS);
     float yL = 0.f;
     if (!wv.p) yL = y.p[n * y.stride + L];
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
     for (int o = chunk * WS_ROWS + r0; o < o_end; o += RPI) {
         const float w = wv.p ? wv.p[n * wv.stride + o]
                              : __expf(spoke.p[n * spoke.stride + o] + x.p[n * x.stride + o] + yL);
@@ -164,14 +168,21 @@ __global__ __launch_bounds__(256) void wsum_kernel(const T *M, Vec wv, Vec spoke
         acc[0] = fmaf(w, m4[0], acc[0]); acc[1] = fmaf(w, m4[1], acc[1]);
         acc[2] = fmaf(w, m4[2], acc[2]); acc[3] = fmaf(w, m4[3], acc[3]);
     }
+    // the 64 / TPR rows of a wavefront, then the wavefronts
 #pragma unroll
-    for (int k = 0; k < 4; ++k) red[tid][k] = acc[k];
+    for (int s = TPR; s < 64; s <<= 1)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[k] += __shfl_xor(acc[k], s);
+    if ((tid & 63) < TPR)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) red[tid >> 6][tid & 63][k] = acc[k];
     __syncthreads();
     if (tid < TPR) {
         float t4[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int r = 0; r < RPI; ++r)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) t4[k] += red[r * TPR + tid][k];
+        for (int r = 0; r < WS_THREADS / 64; ++r)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) t4[k] += red[r][tid][k];
         float *dst = partial + ((long)n * gridDim.x + chunk) * D + col;
         dst[0] = t4[0]; dst[1] = t4[1]; dst[2] = t4[2]; dst[3] = t4[3];
     }
@@ -184,19 +195,19 @@ __global__ void wsum_final_kernel(const float *partial, int nchunk, Vec wc, int 
 {
     const int n = blockIdx.x, dv = threadIdx.x;   // D threads
     float acc = 0.f;
+#pragma unroll 8
     for (int c = 0; c < nchunk; ++c) acc += partial[((long)n * nchunk + c) * D + dv];
     if (wc.p) acc = fmaf(wc.p[n * wc.stride + wc_at], xc[(long)n * D + dv], acc);
     acc *= scale;
     out[(long)n * D + dv] = acc;
     if (dotv) {
-        __shared__ float red[D];
-        red[dv] = acc * dotv[(long)n * D + dv];
+        __shared__ float red[2];
+        float t = acc * dotv[(long)n * D + dv];
+#pragma unroll
+        for (int s = (D < 64 ? D : 64) / 2; s >= 1; s >>= 1) t += __shfl_xor(t, s);
+        if ((dv & 63) == 0) red[dv >> 6] = t;
         __syncthreads();
-        if (dv == 0) {
-            float t = 0.f;
-            for (int k = 0; k < D; ++k) t += red[k];
-            dot_out.p[n * dot_out.stride + dot_at] = t;
-        }
+        if (dv == 0) dot_out.p[n * dot_out.stride + dot_at] = D > 64 ? red[0] + red[1] : t;
     }
 }
 

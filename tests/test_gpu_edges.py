@@ -19,3 +19,27 @@ def work(name, L, d, W, T, dtype, H=1, R=2, **kw):
 def test_dustbin_element_batches(dtype, L):
     """L + 1 values in batches of 8192 (half-steps) or 4096 (mat-vecs), then single ones."""
     check(work("dustbin_edge", L, 32, 5, 2, dtype, dustbin=True, dustbin_score=0.3))
+
+
+@pytest.mark.parametrize("dtype,d,L", [("f32", 32, 1024), ("bf16", 64, 1025), ("bf16", 128, 2047), ("bf16", 32, 65),
+                                       ("f32", 128, 130), ("f32", 64, 8200)])
+def test_token_sums_chunks(dtype, d, L):
+    """Weighted row sums in chunks of 1024 rows: whole, one row over, one short, less than a pass."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    w = work("token_edge", L, d, 9, 3, dtype, dustbin=True)
+    print(f"\n[case] {w} learned tokens", flush=True)
+    arrays = make_inputs(w, 5)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V, G = (torch.from_numpy(x).cuda().to(td) for x in arrays)
+    toks = [np.random.default_rng(7 + i).standard_normal((1, 1, d)).astype(np.float32) for i in range(3)]
+    tq, tk, tv = (torch.from_numpy(t).cuda() for t in toks)
+    O, UV = ska.sinkhorn_attn_fwd_dustbin_token(Q, K, V, tq, tk, tv, w.W, w.T, w.R, w.eps)
+    res = ska.sinkhorn_attn_bwd_dustbin_token(Q, K, V, tq, tk, tv, O, G, UV, w.W, w.T, w.R, w.eps)
+    q, k, v, g = (t[0, 0].float().cpu().numpy().astype(np.float64) for t in (Q, K, V, G))
+    ref = oracle.band_dustbin_token(q, k, v, g, *(t[0, 0] for t in toks), w.W, w.T, w.R, w.eps)
+    for name, t in zip(("O", "dQ", "dK", "dV", "dq_db", "dk_db", "dv_db"), (O, *res)):
+        e = rel(t[0, 0].float().cpu().numpy().astype(np.float64), ref[name])
+        print(f"   {name} {e:.2e}", flush=True)
+        assert e <= TOL[dtype], (name, e)
