@@ -43,3 +43,14 @@ def test_token_sums_chunks(dtype, d, L):
         e = rel(t[0, 0].float().cpu().numpy().astype(np.float64), ref[name])
         print(f"   {name} {e:.2e}", flush=True)
         assert e <= TOL[dtype], (name, e)
+
+
+@pytest.mark.parametrize("d,H,L", [(64, 3, 22000), (32, 2, 32769), (64, 1, 65536)])
+def test_output_map_block_sizes(d, H, L):
+    """128-row blocks up to 65536 rows in a launch, 256-row blocks above."""
+    w = work("apply_edge", L, d, 21, 2, "bf16", H=H)
+    print(f"\n[case] {w}", flush=True)
+    arrays = make_inputs(w, 3)
+    got = run_gpu(w, arrays, one_call=True)
+    ref = oracle.band_batched(*arrays, w.W, w.T, w.R, w.eps)
+    assert_per_tensor(got, ref, w.dtype, floors(w.dtype, *arrays, ref["O"], w.eps), where=w.name)
