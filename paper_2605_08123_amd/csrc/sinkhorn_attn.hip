@@ -146,7 +146,7 @@ int check_common(const Problem &p)
     return SKA_OK;
 }
 
-template <typename T, int D, int MODE, int FR, bool DIRECT = false>
+template <typename T, int D, int MODE, int FR, int PK = PK_TERMS>
 int launch_sweep(SweepArgs a, int N, hipStream_t st, int dev)
 {
     constexpr int BM = NWAVES * FR * 32;
@@ -156,13 +156,13 @@ int launch_sweep(SweepArgs a, int N, hipStream_t st, int dev)
     constexpr int LDS = 2 * Stage<T, D, MODE>::BYTES;
     static bool raised[MAX_DEVICES];    // static LDS tops out at 64 KB; the CU has 160 KB (an attribute per device)
     if (LDS > 48 * 1024 && !raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_kernel<T, D, MODE, FR, DIRECT>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&sweep_kernel<T, D, MODE, FR, PK>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
     }
     a.lead = 0;
-    hipLaunchKernelGGL((sweep_kernel<T, D, MODE, FR, DIRECT>), dim3(chunk * 8), dim3(NTHREADS), LDS, st, a);
+    hipLaunchKernelGGL((sweep_kernel<T, D, MODE, FR, PK>), dim3(chunk * 8), dim3(NTHREADS), LDS, st, a);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
 
@@ -241,10 +241,11 @@ template <typename T, int D> int sweep_one(int mode, const SweepArgs &a, int N, 
             return launch_msweep<D, M_APPLY, 2>(a, N, st, dev);
         }
         else return launch_sweep<T, D, M_APPLY, 1>(a, N, st, dev);
-    case M_FINAL_DIRECT: return launch_sweep<T, D, M_FINAL, 1, true>(a, N, st, dev);
+    case M_FINAL_DIRECT: return launch_sweep<T, D, M_FINAL, 1, PK_DIRECT>(a, N, st, dev);
     default:
-        if constexpr (sizeof(T) == 2 && D <= 64) {
-            if (a.poB) return launch_msweep<D, M_FINAL, 1>(a, N, st, dev);   // packs as bf16 columns (R <= 2)
+        if constexpr (sizeof(T) == 2) {   // packs as bf16 columns (R <= 2)
+            if constexpr (D <= 64) { if (a.poB) return launch_msweep<D, M_FINAL, 1>(a, N, st, dev); }
+            else if (a.poB) return launch_sweep<T, D, M_FINAL, 1, PK_COLUMNS>(a, N, st, dev);
         }
         return launch_sweep<T, D, M_FINAL, 1>(a, N, st, dev);
     }
@@ -676,8 +677,8 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     auto ubar = [&](int t) { return wf + (2 + 2 * (R - t)) * nldp; };
     float4 *rowp = reinterpret_cast<float4 *>(wf + (long)ws_vecs(R) * nldp);
     float4 *colp = rowp + nldp * R;   // (room for R groups per side)
-    // the ring kernel (R <= 2) takes the packs as bf16 columns (rowA, rowB, colA, colB)
-    const bool AUG = (sizeof(T) == 2 && D <= 64 && R <= 2 && !seed && p.variant == SKA_BWD_ONE_REFERENCE);   // (that kernel always adds Z)
+    // bf16 storage, R <= 2: the packs are bf16 columns (rowA, rowB, colA, colB)
+    const bool AUG = (sizeof(T) == 2 && R <= 2 && !seed && p.variant == SKA_BWD_ONE_REFERENCE);   // (that kernel always adds Z)
     __bf16 *aug = reinterpret_cast<__bf16 *>(colp + nldp * R);
     const int final_mode = p.direct() ? M_FINAL_DIRECT : M_FINAL;
     auto wv = [&](float *q) { return Vec{q, ldw}; };

@@ -129,24 +129,26 @@ __device__ __forceinline__ bf16x8 pack8(const float *e)
 }
 
 // LDS layouts -------------------------------------------------------------------
-// bf16 row-major tile [32][D]: 16-byte chunks XOR-swizzled so that the 32 lanes of
-// an A-fragment read (one chunk per lane, consecutive rows) spread over all banks.
+// bf16 row-major tile [32][D]: 16-byte chunks XOR-swizzled so that both ways of reading it touch all 64 banks:
+// an A-fragment read (one chunk per lane, 16 consecutive rows) and a transposing read (8-byte pieces of
+// four adjacent chunks in four consecutive rows).  256 bytes hold 16 / CH rows; what is left of the low
+// two row bits picks the group of four chunks, the next two bits the chunk inside it.
+template <int D> __device__ __forceinline__ int bf16_swizzle(int row)
+{
+    if constexpr (D == 128) return ((row & 3) << 2) | ((row >> 2) & 3);
+    else if constexpr (D == 64) return (((row >> 1) & 1) << 2) | ((row >> 2) & 3);
+    else return (row >> 2) & 3;
+}
 template <int D> __device__ __forceinline__ int bf16_chunk_off(int row, int chunk)
 {
-    constexpr int CH = D / 8;                       // chunks per row
-    constexpr int RPB = (CH >= 8) ? 1 : 8 / CH;     // rows per 128-byte line
-    constexpr int MASK = (CH >= 8) ? 7 : CH - 1;
-    return (row * CH + (chunk ^ ((row / RPB) & MASK))) * 16;
+    return (row * (D / 8) + (chunk ^ bf16_swizzle<D>(row))) * 16;
 }
-// bf16 transposed payload tile [D][32 + 4] (t contiguous, 72-byte rows)
-constexpr int PT_STRIDE = 72;
 // fp32 row-major tile [32][D + 4]
 template <int D> constexpr int f32_row_floats() { return D + 4; }
 
 template <typename T, int D> struct Tile {
     static constexpr bool IS_BF16 = (Elem<T>::BYTES == 2);
     static constexpr int RM_BYTES = IS_BF16 ? 32 * D * 2 : 32 * f32_row_floats<D>() * 4;
-    static constexpr int PT_BYTES = IS_BF16 ? D * PT_STRIDE : RM_BYTES;
     static constexpr int CHUNKS = 32 * D * Elem<T>::BYTES / 16;       // 16-byte pieces per tile
     static constexpr int CPT = (CHUNKS + NTHREADS - 1) / NTHREADS;    // per thread
     static constexpr int CPR = D * Elem<T>::BYTES / 16;               // per row
@@ -155,27 +157,29 @@ template <typename T, int D> struct Tile {
 template <typename T, int D> using TileRegs = uint4[Tile<T, D>::CPT];
 
 // ------------------------------------------------------------------ staging
-// Global -> registers for one 32-row tile of a [L][D] matrix (rows beyond L read as 0).
+// Global -> registers for one 32-row tile of a [L][D] matrix with at least one row inside it.  Rows beyond
+// L are clamped, and zeroed by tile_store_rm: a load under a condition is waited for at once.
 template <typename T, int D>
 __device__ __forceinline__ void tile_load(TileRegs<T, D> &reg, const T *base, int t0, int L)
 {
     using TL = Tile<T, D>;
+    const unsigned char *tb = reinterpret_cast<const unsigned char *>(base) + (long)t0 * (D * Elem<T>::BYTES);
+    const unsigned lim = min(TT, L - t0) * (D * Elem<T>::BYTES) - 16;
 #pragma unroll
-    for (int c = 0; c < TL::CPT; ++c) {
-        int idx = threadIdx.x + c * NTHREADS;
-        int row = idx / TL::CPR, ch = idx % TL::CPR;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (idx < TL::CHUNKS && t0 + row < L)
-            v = *reinterpret_cast<const uint4 *>(base + (long)(t0 + row) * D + ch * (16 / Elem<T>::BYTES));
-        reg[c] = v;
-    }
+    for (int c = 0; c < TL::CPT; ++c)
+        reg[c] = *reinterpret_cast<const uint4 *>(tb + min((threadIdx.x + c * NTHREADS) * 16u, lim));
 }
 
-// registers -> LDS, row-major (A-operand of the score / Z products)
+// registers -> LDS, row-major; the first `rows` rows of the tile exist (uniform)
 template <typename T, int D>
-__device__ __forceinline__ void tile_store_rm(const TileRegs<T, D> &reg, unsigned char *lds)
+__device__ __forceinline__ void tile_store_rm(TileRegs<T, D> &reg, unsigned char *lds, int rows)
 {
     using TL = Tile<T, D>;
+    if (rows < TT) {
+#pragma unroll
+        for (int c = 0; c < TL::CPT; ++c)
+            if ((int)(threadIdx.x + c * NTHREADS) / TL::CPR >= rows) reg[c] = make_uint4(0, 0, 0, 0);
+    }
 #pragma unroll
     for (int c = 0; c < TL::CPT; ++c) {
         int idx = threadIdx.x + c * NTHREADS;
@@ -185,31 +189,6 @@ __device__ __forceinline__ void tile_store_rm(const TileRegs<T, D> &reg, unsigne
                 *reinterpret_cast<uint4 *>(lds + bf16_chunk_off<D>(row, ch)) = reg[c];
             else
                 *reinterpret_cast<uint4 *>(lds + (row * f32_row_floats<D>() + ch * 4) * 4) = reg[c];
-        }
-    }
-}
-
-// registers -> LDS in the layout the second product wants: bf16 transposed [dv][t],
-// fp32 row-major.
-template <typename T, int D>
-__device__ __forceinline__ void tile_store_pay(const TileRegs<T, D> &reg, unsigned char *lds)
-{
-    using TL = Tile<T, D>;
-    if constexpr (!TL::IS_BF16) {
-        tile_store_rm<T, D>(reg, lds);
-    } else {
-#pragma unroll
-        for (int c = 0; c < TL::CPT; ++c) {
-            int idx = threadIdx.x + c * NTHREADS;
-            if (idx < TL::CHUNKS) {
-                int row = idx / TL::CPR, ch = idx % TL::CPR;
-                const unsigned int wds[4] = {reg[c].x, reg[c].y, reg[c].z, reg[c].w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    unsigned short v = (unsigned short)(wds[e >> 1] >> ((e & 1) * 16));
-                    *reinterpret_cast<unsigned short *>(lds + (ch * 8 + e) * PT_STRIDE + row * 2) = v;
-                }
-            }
         }
     }
 }
@@ -298,23 +277,28 @@ __device__ __forceinline__ void ring_dot_multi(const unsigned char *tile, const 
     for (int f = 0; f < FR; ++f) acc[f] = tile_dot<D>(tile, x[f], lane, acc[f]);
 }
 
-// out[dvt][dv, o] += sum_t pay[t][dv] * e[t, o]   (e in the accumulator layout)
+// out[dvt][dv, o] += sum_t pay[t][dv] * e[t, o]   (e in the accumulator layout, pay row-major)
 template <typename T, int D>
 __device__ __forceinline__ void tile_accum(f32x16 (&out)[D / 32], const unsigned char *pay,
                                            const float (&e)[16], int lane)
 {
     const int c = lane & 31, h = lane >> 5;
     if constexpr (Elem<T>::BYTES == 2) {
+        // transposing reads of the row-major tile: within 16 lanes, lane i receives element (i & 3) of the
+        // 8-byte pieces addressed by lanes (i >> 2) + 4 e, e = 0..3
+        typedef __bf16 bf16x4v __attribute__((ext_vector_type(4)));
+        const int row = 4 * h + ((lane & 15) >> 2), ch = 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1);
+        const unsigned char *sub = pay + (lane & 1) * 8;
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             bf16x8 pf = pack8(&e[8 * m]);
 #pragma unroll
             for (int dvt = 0; dvt < D / 32; ++dvt) {
-                const unsigned char *rowp = pay + (32 * dvt + c) * PT_STRIDE;
-                uint2 lo = *reinterpret_cast<const uint2 *>(rowp + (16 * m + 4 * h) * 2);
-                uint2 hi = *reinterpret_cast<const uint2 *>(rowp + (16 * m + 8 + 4 * h) * 2);
-                uint4 both = make_uint4(lo.x, lo.y, hi.x, hi.y);
-                bf16x8 af = *reinterpret_cast<bf16x8 *>(&both);
+                bf16x4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4v __attribute__((address_space(3))) *)(
+                    sub + bf16_chunk_off<D>(row + 16 * m, ch + 4 * dvt)));
+                bf16x4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((bf16x4v __attribute__((address_space(3))) *)(
+                    sub + bf16_chunk_off<D>(row + 16 * m + 8, ch + 4 * dvt)));
+                bf16x8 af = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
                 out[dvt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, pf, out[dvt], 0, 0, 0);
             }
         }

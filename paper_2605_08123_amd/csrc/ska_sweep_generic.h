@@ -7,29 +7,39 @@ namespace {
 
 // ------------------------------------------------------------------ the generic sweep kernel
 // Double-buffered LDS staging, one other-side tile per barrier.  It serves every fp32-storage
-// matrix sweep and the bf16 matrix sweeps at d = 128; the ring kernels take the rest.
+// matrix sweep and the bf16 matrix sweeps at d = 128; the ring kernels take the rest.  (A ring of d = 128 tile
+// pairs takes 86 KB, which leaves one workgroup per CU and every LDS and MFMA latency exposed; two buffers
+// take 35 KB, and registers allow two workgroups.)
+//   At d = 128 a transposed copy of the payload (2-byte LDS writes) and the
+// modifier terms on the plain ALUs bounded it; with the second product's operand read from the row-major tile by
+// transposing reads, the terms inside the Z product and loads under no condition, eight problems of
+// L = 16384, W = 256 went from 2031 to 1722 us per step (20 half-step pairs included).  fp32, which had
+// only the conditions and an empty group of terms to lose: 815 to 807 us, eight of L = 4096.
+enum Pack { PK_TERMS, PK_DIRECT, PK_COLUMNS };
 template <typename T, int D, int MODE> struct Stage {
     using TL = Tile<T, D>;
-    static constexpr bool HAS_B = (MODE == M_FINAL);
-    static constexpr bool HAS_PAY = (MODE == M_APPLY) || (MODE == M_FINAL && TL::IS_BF16);
     static constexpr int OFF_Y = 0;
-    static constexpr int OFF_B = OFF_Y + TL::RM_BYTES;
-    static constexpr int OFF_PAY = OFF_B + (HAS_B ? TL::RM_BYTES : 0);
-    static constexpr int OFF_VY = OFF_PAY + (HAS_PAY ? TL::PT_BYTES : 0);
+    static constexpr int OFF_B = OFF_Y + TL::RM_BYTES;     // Z factor (M_FINAL) or payload (M_APPLY)
+    static constexpr int OFF_VY = OFF_B + TL::RM_BYTES;
     static constexpr int OFF_VQ = OFF_VY + TT * 4;
-    static constexpr int BYTES = ((OFF_VQ + TT * 16 * MAXNQ) + 15) / 16 * 16;
+    static constexpr int BYTES = ((OFF_VQ + (MODE == M_FINAL ? TT * 16 * MAXNQ : 0)) + 15) / 16 * 16;
 };
 
-// DIRECT (M_FINAL only): the comparator that forms every staircase plan factor by an
+// PK (M_FINAL only) says how the rank-1 modifier terms come.  PK_TERMS: float4 groups, four terms each,
+// on the plain ALUs.  PK_COLUMNS (bf16, R <= 2): 16 bf16 columns per side that extend the Z product by one K = 16
+// MFMA step, as in the ring kernel.  PK_DIRECT: the comparator that forms every staircase plan factor by an
 // exponential of its own, exp(S + u_t + v_t'), instead of scaling the one reference tile
 // (Prop. 2 versus the plain evaluation of Prop. 1).  A pack group then holds two terms as
 // (log2 modifier, weight) pairs: the term is exp2(score + l_row + l_col) w_row w_col.
-template <typename T, int D, int MODE, int FR, bool DIRECT = false>
+template <typename T, int D, int MODE, int FR, int PK = PK_TERMS>
 __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
 {
     using TL = Tile<T, D>;
     using ST = Stage<T, D, MODE>;
     constexpr int BM = NWAVES * FR * 32;
+    constexpr bool PRE = (sizeof(T) == 2);   // bf16 storage: the score operand is prescaled, c2 == 1
+    constexpr bool DIRECT = (PK == PK_DIRECT), COLUMNS = (PK == PK_COLUMNS);
+    static_assert(!COLUMNS || PRE, "pack columns go with bf16 tiles");
     static_assert(MODE == M_APPLY || MODE == M_FINAL, "matrix sweeps only");
 
     extern __shared__ __align__(16) unsigned char smem[];   // two stages of ST::BYTES
@@ -45,7 +55,7 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
     const int n = lb / a.nbp;
     const int o_blk = (lb % a.nbp) * BM;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 31, h = lane >> 5;
     const int L = a.L, W = a.W;
     const Lens ln = problem_lens(a, n);
@@ -82,6 +92,7 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
     OwnerFrag<T, D> xf[FR];
     OwnerFrag<T, D> af[MODE == M_FINAL ? FR : 1];
     float4 pof[FR][MAXNQ];
+    bf16x8 pob[FR];   // COLUMNS: this lane's half of the owner row's 16 pack columns
     int o_frag[FR];
 #pragma unroll
     for (int f = 0; f < FR; ++f) {
@@ -89,6 +100,11 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
         xf[f].load(Xb, o_frag[f] + c, Le, h);
         if constexpr (MODE == M_FINAL) {
             af[f].load(reinterpret_cast<const T *>(a.A) + moff, o_frag[f] + c, Le, h);
+            if constexpr (COLUMNS) {
+                uint4 z = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a.poB) +
+                                                           (n * a.ldp + min(o_frag[f] + c, Le - 1)) * 32 + h * 16);
+                pob[f] = *reinterpret_cast<bf16x8 *>(&z);
+            } else
 #pragma unroll
             for (int g = 0; g < MAXNQ; ++g)
                 pof[f][g] = (o_frag[f] + c < Le && g < a.nq) ? a.po[(n * a.ldp + o_frag[f] + c) * a.pstride + g]
@@ -112,48 +128,52 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
     if (hi > Lt - 1) hi = Lt - 1;   // (lo <= hi: the block has a row below Le <= Lt + W)
     const int k_lo = lo / TT, k_hi = hi / TT;
 
-    // staging registers
-    uint4 ry[TL::CPT], rb[ST::HAS_B ? TL::CPT : 1], rp[MODE == M_APPLY ? TL::CPT : 1];
+    // Staging registers.  Everything is requested without a condition (indices clamped into the matrix, absent
+    // rows neutralised at the store): a load under a condition is waited for at once.
+    uint4 ry[TL::CPT], rb[TL::CPT], rk = make_uint4(0, 0, 0, 0);
     float rvy = 0.f;
     float4 rvq[MAXNQ] = {make_float4(0, 0, 0, 0), make_float4(0, 0, 0, 0)};
+    const T *Bb = reinterpret_cast<const T *>(MODE == M_FINAL ? a.Bm : a.Pay) + moff;
 
     auto g_load = [&](int k) {
         const int t0 = k * TT;
         tile_load<T, D>(ry, Yb, t0, Lt);
-        if constexpr (ST::HAS_B) tile_load<T, D>(rb, reinterpret_cast<const T *>(a.Bm) + moff, t0, Lt);
-        if constexpr (MODE == M_APPLY) tile_load<T, D>(rp, reinterpret_cast<const T *>(a.Pay) + moff, t0, Lt);
-        if (tid < TT) {
-            const int t = t0 + tid;
-            rvy = (t < Lt) ? ytp[t] * LOG2E + m2 : -INFINITY;
-            if constexpr (MODE == M_FINAL) {
+        tile_load<T, D>(rb, Bb, t0, Lt);
+        const int t = min(t0 + (tid & (TT - 1)), Lt - 1);
+        rvy = ytp[t];
+        if constexpr (COLUMNS) {   // 64 pieces of 16 bytes
+            rk = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a.qtA) +
+                                                  (n * a.ldp + t) * 32 + h * 16);
+        } else if constexpr (MODE == M_FINAL) {
 #pragma unroll
-                for (int g = 0; g < MAXNQ; ++g)
-                    rvq[g] = (t < Lt && g < a.nq) ? a.qt[(n * a.ldp + t) * a.pstride + g] : make_float4(0, 0, 0, 0);
-            }
+            for (int g = 0; g < MAXNQ; ++g) rvq[g] = a.qt[(n * a.ldp + t) * a.pstride + min(g, a.nq - 1)];
         }
     };
-    auto s_store = [&](int buf) {
+    auto s_store = [&](int buf, int k) {
         unsigned char *s = smem + buf * ST::BYTES;
-        tile_store_rm<T, D>(ry, s + ST::OFF_Y);
-        if constexpr (ST::HAS_B) tile_store_rm<T, D>(rb, s + ST::OFF_B);
-        if constexpr (MODE == M_APPLY) tile_store_pay<T, D>(rp, s + ST::OFF_PAY);
-        if constexpr (MODE == M_FINAL && TL::IS_BF16) tile_store_pay<T, D>(ry, s + ST::OFF_PAY);
+        const int rows = Lt - k * TT;
+        tile_store_rm<T, D>(ry, s + ST::OFF_Y, rows);
+        tile_store_rm<T, D>(rb, s + ST::OFF_B, rows);
         if (tid < TT) {
-            reinterpret_cast<float *>(s + ST::OFF_VY)[tid] = rvy;
-            if constexpr (MODE == M_FINAL) {
+            reinterpret_cast<float *>(s + ST::OFF_VY)[tid] = tid < rows ? rvy * LOG2E + m2 : -INFINITY;
+            if constexpr (MODE == M_FINAL && !COLUMNS) {
 #pragma unroll
-                for (int g = 0; g < MAXNQ; ++g) reinterpret_cast<float4 *>(s + ST::OFF_VQ)[tid * MAXNQ + g] = rvq[g];
+                for (int g = 0; g < MAXNQ; ++g)
+                    reinterpret_cast<float4 *>(s + ST::OFF_VQ)[tid * MAXNQ + g] =
+                        tid < rows && g < a.nq ? rvq[g] : make_float4(0, 0, 0, 0);
             }
         }
+        if constexpr (COLUMNS)   // (halves apart: a read is one 16-byte piece per lane, rows in sequence)
+            if (tid < 64) *reinterpret_cast<uint4 *>(s + ST::OFF_VQ + tid * 16) = c < rows ? rk : make_uint4(0, 0, 0, 0);
     };
 
     g_load(k_lo);
-    s_store(0);
+    s_store(0, k_lo);
     __syncthreads();
 
     for (int k = k_lo; k <= k_hi; ++k) {
         const int buf = (k - k_lo) & 1;
-        if (k < k_hi) g_load(k + 1);
+        g_load(min(k + 1, k_hi));
         const unsigned char *s = smem + buf * ST::BYTES;
         const int t0 = k * TT;
 
@@ -164,20 +184,29 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
             if (of >= Le || (long)t0 + TT - 1 < (long)of - W || (long)t0 > (long)of + 31 + W) continue;
             const bool interior = ((long)of + 31 - t0 <= W) && ((long)t0 + TT - 1 - of <= W);
 
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-            acc = tile_dot<D>(s + ST::OFF_Y, xf[f], lane, acc);
-
             float yv[16];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float4 v4 = *reinterpret_cast<const float4 *>(s + ST::OFF_VY + (8 * q + 4 * h) * 4);
                 yv[4 * q + 0] = v4.x; yv[4 * q + 1] = v4.y; yv[4 * q + 2] = v4.z; yv[4 * q + 3] = v4.w;
             }
+            f32x16 acc, z;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { acc[r] = PRE ? yv[r] : 0.f; z[r] = 0.f; }
+            acc = tile_dot<D>(s + ST::OFF_Y, xf[f], lane, acc);
+            if constexpr (MODE == M_FINAL) {   // the Z product runs beside the exponentials
+                if constexpr (COLUMNS) {
+                    z = tile_dot<D>(s + ST::OFF_B, af[f], lane, z);
+                    const bf16x8 qpk = *reinterpret_cast<const bf16x8 *>(s + ST::OFF_VQ + lane * 16);
+                    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qpk, pob[f], z, 0, 0, 0);   // - sum_k po_k qt_k
+                } else if (!a.skipz) {
+                    z = tile_dot<D>(s + ST::OFF_B, af[f], lane, z);
+                }
+            }
+
             float e[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) e[r] = fmaf(acc[r], a.c2, yv[r]);
+            for (int r = 0; r < 16; ++r) e[r] = PRE ? acc[r] : fmaf(acc[r], a.c2, yv[r]);
             if (!interior) {
                 const int o = of + c;
 #pragma unroll
@@ -196,46 +225,37 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) e[r] = fast_exp2(e[r]);
                 if constexpr (MODE == M_APPLY) {
-                    tile_accum<T, D>(outm[f], s + ST::OFF_PAY, e, lane);
+                    tile_accum<T, D>(outm[f], s + ST::OFF_B, e, lane);
                 } else {  // M_FINAL
-                    f32x16 z;
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) z[r] = 0.f;
-                    if (!a.skipz) z = tile_dot<D>(s + ST::OFF_B, af[f], lane, z);
+                    for (int g = 0; g < MAXNQ; ++g) {
+                        if (COLUMNS || g >= a.nq) break;   // (uniform; R <= 2 has one group)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int tl = 8 * (r >> 2) + 4 * h + (r & 3);
-                        float md = z[r];
-                        if constexpr (DIRECT) {
-                            float sb = e[r] * md;
-#pragma unroll
-                            for (int g = 0; g < MAXNQ; ++g) {   // (an absent group has zero weights)
-                                float4 q4 = *reinterpret_cast<const float4 *>(s + ST::OFF_VQ + (tl * MAXNQ + g) * 16);
-                                const float p0 = (g == 0 && a.refterm) ? e[r]
-                                                                       : fast_exp2(el[r] + pof[f][g].x + q4.x);
+                        for (int r = 0; r < 16; ++r) {
+                            const int tl = 8 * (r >> 2) + 4 * h + (r & 3);
+                            const float4 q4 = *reinterpret_cast<const float4 *>(s + ST::OFF_VQ + (tl * MAXNQ + g) * 16);
+                            if constexpr (DIRECT) {
+                                if (g == 0) z[r] *= e[r];
+                                const float p0 = (g == 0 && a.refterm) ? e[r] : fast_exp2(el[r] + pof[f][g].x + q4.x);
                                 const float p1 = fast_exp2(el[r] + pof[f][g].z + q4.z);
-                                sb = fmaf(-p0 * pof[f][g].y, q4.y, sb);
-                                sb = fmaf(-p1 * pof[f][g].w, q4.w, sb);
+                                z[r] = fmaf(-p0 * pof[f][g].y, q4.y, z[r]);
+                                z[r] = fmaf(-p1 * pof[f][g].w, q4.w, z[r]);
+                            } else {
+                                z[r] = fmaf(-pof[f][g].x, q4.x, z[r]);
+                                z[r] = fmaf(-pof[f][g].y, q4.y, z[r]);
+                                z[r] = fmaf(-pof[f][g].z, q4.z, z[r]);
+                                z[r] = fmaf(-pof[f][g].w, q4.w, z[r]);
                             }
-                            e[r] = sb;
-                        } else {
-#pragma unroll
-                            for (int g = 0; g < MAXNQ; ++g) {   // (an absent group is all zeros)
-                                float4 q4 = *reinterpret_cast<const float4 *>(s + ST::OFF_VQ + (tl * MAXNQ + g) * 16);
-                                md = fmaf(-pof[f][g].x, q4.x, md);
-                                md = fmaf(-pof[f][g].y, q4.y, md);
-                                md = fmaf(-pof[f][g].z, q4.z, md);
-                                md = fmaf(-pof[f][g].w, q4.w, md);
-                            }
-                            e[r] *= md;
                         }
                     }
-                    tile_accum<T, D>(outm[f], TL::IS_BF16 ? s + ST::OFF_PAY : s + ST::OFF_Y, e, lane);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) e[r] = DIRECT ? z[r] : e[r] * z[r];
+                    tile_accum<T, D>(outm[f], s + ST::OFF_Y, e, lane);
                 }
             }
         }
 
-        if (k < k_hi) s_store(buf ^ 1);
+        s_store(buf ^ 1, min(k + 1, k_hi));   // (after the last tile nobody reads it)
         __syncthreads();
     }
 

@@ -54,3 +54,10 @@ def test_output_map_block_sizes(d, H, L):
     got = run_gpu(w, arrays, one_call=True)
     ref = oracle.band_batched(*arrays, w.W, w.T, w.R, w.eps)
     assert_per_tensor(got, ref, w.dtype, floors(w.dtype, *arrays, ref["O"], w.eps), where=w.name)
+
+
+@pytest.mark.parametrize("L,W,R", [(31, 7, 2), (33, 40, 1), (127, 31, 2), (129, 32, 3), (161, 64, 2), (1000, 95, 5)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_double_buffered_matrix_sweeps(dtype, d, L, W, R):
+    """Ragged last tiles and band edges; modifier terms as pack columns (bf16, R <= 2), in one group of four or in two."""
+    check(work("generic_edge", L, d, W, 3, dtype, H=2, R=R))
