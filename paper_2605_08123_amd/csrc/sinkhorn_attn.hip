@@ -210,6 +210,22 @@ int launch_msweep(SweepArgs a, int N, hipStream_t st, int dev)
 //                                         first half-step is its running-maximum variant
 //   output map / dV, final sweeps         msweep_kernel for bf16 storage with d <= 64,
 //                                         sweep_kernel otherwise
+// Block size of a vector sweep over `rows` owner rows: 32 rows per wavefront (blocks of 128) or 64.
+template <typename T, int D> bool small_blocks(long rows)
+{
+    constexpr long BLOCK_PER_CU = 256L * 256;   // rows of one 256-row block per CU
+    if (sizeof(T) == 4) return true;
+    // 64 rows per wavefront reuse every tile fragment twice, but a launch then has half the workgroups.
+    // d <= 64: a CU holds four; up to three per CU (measured: two per CU gains 4-7 %, four per CU loses
+    // 3 %) halve the block instead.
+    if (D <= 64) return rows <= 3 * BLOCK_PER_CU;
+    // d = 128: the rings of two workgroups fill a CU's LDS.  Up to one 256-row block per CU, twice as many of
+    // 128 rows are resident together just the same; up to two, the large blocks are one round and the small
+    // ones two; with a remainder beyond that the small ones fill it better.  Forward of eight problems,
+    // W = 256, us with 128 / 256 rows: 729 / 892 at 65536 rows, 1126 / 1122 at 81920, 1386 / 1321 at
+    // 131072, 1795 / 1869 at 163840; two launches of 98304 side by side 1854 / 1638.
+    return rows <= BLOCK_PER_CU || (rows > 2 * BLOCK_PER_CU && rows <= 3 * BLOCK_PER_CU);
+}
 template <typename T, int D> int sweep_one(int mode, const SweepArgs &a, int N, hipStream_t st, int dev)
 {
     constexpr int FRV = (sizeof(T) == 2) ? 2 : 1;   // vector sweeps: owner rows per wavefront / 32
@@ -217,12 +233,8 @@ template <typename T, int D> int sweep_one(int mode, const SweepArgs &a, int N, 
     case M_LSE_FIRST:
     case M_LSE:
     case M_MATVEC: {
-        // 64 rows per wavefront reuse every tile fragment twice, but a launch then has N L / 256
-        // workgroups.  The 256 CUs hold four of them each; up to three per CU (measured: two per CU
-        // gains 4-7 %, four per CU loses 3 %) halve the block instead: twice the workgroups
-        constexpr long SMALL_ROWS = 3L * 256 * 256;
         if constexpr (sizeof(T) == 2) {
-            if ((long)N * a.L <= SMALL_ROWS)
+            if (small_blocks<T, D>((long)N * a.L))
                 return mode == M_LSE         ? launch_vsweep<T, D, M_LSE, 1>(a, N, st, dev)
                        : mode == M_MATVEC    ? launch_vsweep<T, D, M_MATVEC, 1>(a, N, st, dev)
                                              : launch_vsweep<T, D, M_LSE_FIRST, 1>(a, N, st, dev);
@@ -522,14 +534,12 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         if (g_fuse && !cx.noalloc && !capturing && !p.dustbin && !p.n_stages && ws && p.ws_given >= off + ws_chain_bytes(p))
             chain_done = reinterpret_cast<int *>(reinterpret_cast<unsigned char *>(ws) + off);
     }
-    // the block size of the separate launches (sweep_one: 128 rows while a dispatch has few rows, else
-    // 256) is taken per dispatch; the chain is one launch, so it needs the two halves of a split call
-    // to agree (they differ only for an odd number of problems around the threshold): results stay
+    // the block size of the separate launches (small_blocks) is taken per dispatch; the chain is one
+    // launch, so it needs the two halves of a split call to agree (they differ only for an odd number of problems around the threshold): results stay
     // those of the separate launches bit for bit
-    constexpr long SMALL_ROWS = 3L * 256 * 256;
     const int n_half = (cx.side && N >= 2) ? N / 2 : N;
-    const bool chain_fr1 = sizeof(T) == 4 || (long)n_half * L <= SMALL_ROWS;
-    if (chain_fr1 != (sizeof(T) == 4 || (long)(N - n_half ? N - n_half : N) * L <= SMALL_ROWS)) chain_done = nullptr;
+    const bool chain_fr1 = small_blocks<T, D>((long)n_half * L);
+    if (chain_fr1 != small_blocks<T, D>((long)(N - n_half ? N - n_half : N) * L)) chain_done = nullptr;
     auto flush_chain = [&]() -> int {
         if (chain.nsteps == 0) return SKA_OK;
         SKA_TRY(cx.join());   // the chain takes all problems on the caller's stream

@@ -61,3 +61,14 @@ def test_output_map_block_sizes(d, H, L):
 def test_double_buffered_matrix_sweeps(dtype, d, L, W, R):
     """Ragged last tiles and band edges; modifier terms as pack columns (bf16, R <= 2), in one group of four or in two."""
     check(work("generic_edge", L, d, W, 3, dtype, H=2, R=R))
+
+
+@pytest.mark.parametrize("H,L", [(1, 65536), (3, 21846), (1, 131072), (2, 65600)])
+def test_vector_sweep_block_sizes_wide_heads(H, L):
+    """d = 128: 128-row blocks up to 65536 rows in a launch, 256-row ones up to 131072, 128-row ones again."""
+    w = work("block_edge", L, 128, 9, 2, "bf16", H=H)
+    print(f"\n[case] {w}", flush=True)
+    arrays = make_inputs(w, 3)
+    got = run_gpu(w, arrays, one_call=True)
+    ref = oracle.band_batched(*arrays, w.W, w.T, w.R, w.eps)
+    assert_per_tensor(got, ref, w.dtype, floors(w.dtype, *arrays, ref["O"], w.eps), where=w.name)
