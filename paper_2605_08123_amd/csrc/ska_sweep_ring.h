@@ -546,18 +546,11 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
     const float *ytp = a.yt.p + n * a.yt.stride;
     const float *xsp = a.xs.p + n * a.xs.stride;
 
-    float mblk, m2;
-    {
-        float m = -INFINITY;
-        for (int i = tid; i < BM; i += NTHREADS) m = fmaxf(m, xsp[min(o_blk + i, Le - 1)]);
-#pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
-        if (lane == 0) red[wave] = m;
-        __syncthreads();
-        mblk = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        if (mblk == -INFINITY) mblk = 0.f;   // a block of inactive tokens only
-    }
-    m2 = mblk * LOG2E;
+    // Everything the prologue needs from memory is requested before anything is waited for: the potentials
+    // the stabiliser is taken from, the owner rows, the first tiles of the ring.
+    static_assert(BM <= NTHREADS, "one owner-side potential per thread");
+    const float mraw = xsp[min(o_blk + min(tid, BM - 1), Le - 1)];   // clamped repeats are harmless
+    float mblk = 0.f, m2 = 0.f;
 
     // owner side: score rows, and for M_FINAL the owner factor of Z and the modifier pack.
     // Rows beyond Le are clamped: they compute garbage that is never stored.
@@ -594,65 +587,76 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
     const int S = kend - kbase + 1;
     const int klast = (Lt - 1) / TT;
 
-    // one tile pair in flight between global memory and LDS (plain arrays: a struct holding
-    // them ends up in scratch memory)
-    auto g_load = [&](uint4 (&gy)[RG::CPT], uint4 (&gb)[RG::CPT], float &gvy, uint4 &gpk, int k) {
+    // One tile pair in flight between global memory and LDS (plain arrays of a native vector type: a struct
+    // holding them, or the uint4 class, ends up in scratch memory).  As in the vector sweeps a piece sits at a fixed offset from the tile's start, a scalar.
+    // Loads and the stores of the pieces are under no condition, neither on the step nor on the thread: threads
+    // without a piece of their own repeat the tile's last one.  The compiler moves a load whose only use
+    // is a conditional store down to that store, and the prologue then waited for its tiles one after another:
+    // 32 problems of L = 4096, W = 128 613 -> 606 us per step, two of L = 262144, W = 256 2875 -> 2857 us.
+    // (The potentials and pack columns are stored by the threads that have one: stored by all of them, which
+    // writes a third more LDS per step in the final sweeps, the large case lost 1 % instead.)
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int ROW_BYTES = D * 2, TILE_BYTES = TT * ROW_BYTES;
+    unsigned goff[RG::CPT], soff[RG::CPT];   // piece offsets: in memory, in the LDS tile
+#pragma unroll
+    for (int q = 0; q < RG::CPT; ++q) {
+        const int idx = min(tid + q * NTHREADS, RG::CHUNKS - 1);
+        goff[q] = idx * 16;
+        soff[q] = (idx / RG::CPR) * RG::ROWB + (idx % RG::CPR) * 16;
+    }
+    const int vrow = tid & (TT - 1);
+    auto g_load = [&](u32x4 (&gy)[RG::CPT], u32x4 (&gb)[RG::CPT], float &gvy, u32x4 &gpk, int k) {
+        const int kc = min(max(k, 0), klast);   // a tile outside the matrix is never used
+        const int rows = min(TT, Lt - kc * TT);
+        const long t_off = (long)kc * TILE_BYTES;
+        const unsigned lim = rows * ROW_BYTES - 16;
 #pragma unroll
         for (int q = 0; q < RG::CPT; ++q) {
-            int idx = tid + q * NTHREADS;
-            if (idx >= RG::CHUNKS) idx = RG::CHUNKS - 1;
-            const unsigned row = (unsigned)min(max(k * TT + idx / RG::CPR, 0), Lt - 1);
-            const unsigned off = row * (unsigned)(D * 2) + (unsigned)(idx % RG::CPR) * 16u;
-            gy[q] = *reinterpret_cast<const uint4 *>(Yb + off);
-            gb[q] = *reinterpret_cast<const uint4 *>(Bb + off);
+            const unsigned off = min(goff[q], lim);
+            gy[q] = *reinterpret_cast<const u32x4 *>(Yb + t_off + off);
+            gb[q] = *reinterpret_cast<const u32x4 *>(Bb + t_off + off);
         }
-        const unsigned tv = (unsigned)min(max(k * TT + (tid & (TT - 1)), 0), Lt - 1);
-        gvy = ytp[tv];
-        if constexpr (MODE == M_FINAL) {
-            // 64 pieces of 16 bytes per tile: every wavefront requests them (same addresses; a
-            // request under a condition would cost a full wait), the first one stores them
-            const unsigned tp = (unsigned)min(max(k * TT + ((tid & 63) >> 1), 0), Lt - 1);
-            gpk = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a.qtA) +
-                                                   ((long)n * a.ldp + tp) * 32 + (tid & 1) * 16);
-        }
+        gvy = (ytp + kc * TT)[(unsigned)min(vrow, rows - 1)];
+        if constexpr (MODE == M_FINAL)   // 64 pieces of 16 bytes per tile, the same for every wavefront
+            gpk = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const unsigned char *>(a.qtA) +
+                                                   ((long)n * a.ldp + kc * TT) * 32 +
+                                                   min((unsigned)(tid & 63) * 16u, (unsigned)rows * 32u - 16u));
     };
     // rows outside [0, Lt) keep whatever the clamped fetch brought: their potential is -inf,
     // so their plan entries are exactly zero and finite data times zero adds nothing
-    auto s_store = [&](const uint4 (&gy)[RG::CPT], const uint4 (&gb)[RG::CPT], float gvy, uint4 gpk, int j, int k) {
-        unsigned char *sl = smem + (j % RG::NSLOT) * RG::SLOT;
+    const int pk_off = ((tid & 1) ? RG::OFF_B : RG::OFF_Y) + ((tid & 63) >> 1) * RG::ROWB + RG::OFF_PK;
+    auto s_store = [&](const u32x4 (&gy)[RG::CPT], const u32x4 (&gb)[RG::CPT], float gvy, u32x4 gpk, int j, int k) {
+        unsigned char *sl = smem + ((unsigned)j % RG::NSLOT) * RG::SLOT;
 #pragma unroll
         for (int q = 0; q < RG::CPT; ++q) {
-            const int idx = tid + q * NTHREADS;
-            if (idx < RG::CHUNKS) {
-                const int off = (idx / RG::CPR) * RG::ROWB + (idx % RG::CPR) * 16;
-                *reinterpret_cast<uint4 *>(sl + RG::OFF_Y + off) = gy[q];
-                *reinterpret_cast<uint4 *>(sl + RG::OFF_B + off) = gb[q];
-            }
+            *reinterpret_cast<u32x4 *>(sl + RG::OFF_Y + soff[q]) = gy[q];
+            *reinterpret_cast<u32x4 *>(sl + RG::OFF_B + soff[q]) = gb[q];
         }
-        if (tid < TT) {
-            const bool live = k >= 0 && k * TT + tid < Lt;
-            reinterpret_cast<float *>(sl + RG::OFF_VY)[tid] = live ? fmaf(gvy, LOG2E, m2) : -INFINITY;
-        }
-        if constexpr (MODE == M_FINAL) {
-            if (tid < 64)   // (rows outside the matrix: clamped data, multiplied by a zero plan entry)
-                *reinterpret_cast<uint4 *>(sl + ((tid & 1) ? RG::OFF_B : RG::OFF_Y) + (tid >> 1) * RG::ROWB +
-                                           RG::OFF_PK) = gpk;
-        }
+        if (tid < TT) reinterpret_cast<float *>(sl + RG::OFF_VY)[vrow] = k * TT + vrow < Lt ? fmaf(gvy, LOG2E, m2) : -INFINITY;
+        if constexpr (MODE == M_FINAL) if (tid < 64) *reinterpret_cast<u32x4 *>(sl + pk_off) = gpk;
     };
 
     {
-        uint4 fy[RG::LEAD + 1][RG::CPT], fb[RG::LEAD + 1][RG::CPT];
+        u32x4 fy[RG::LEAD + 1][RG::CPT], fb[RG::LEAD + 1][RG::CPT];
         float fvy[RG::LEAD + 1];
-        uint4 fvq[RG::LEAD + 1];
+        u32x4 fvq[RG::LEAD + 1];
 #pragma unroll
         for (int j = 0; j <= RG::LEAD; ++j) g_load(fy[j], fb[j], fvy[j], fvq[j], kbase + j);
+        float m = mraw;
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
+        if (lane == 0) red[wave] = m;
+        __syncthreads();
+        mblk = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+        if (mblk == -INFINITY) mblk = 0.f;   // a block of inactive tokens only
+        m2 = mblk * LOG2E;
 #pragma unroll
         for (int j = 0; j <= RG::LEAD; ++j) s_store(fy[j], fb[j], fvy[j], fvq[j], j, kbase + j);
     }
     __syncthreads();
-    uint4 ny[RG::CPT], nb[RG::CPT];
+    u32x4 ny[RG::CPT], nb[RG::CPT];
     float nvy = 0.f;
-    uint4 nvq = make_uint4(0, 0, 0, 0);
+    u32x4 nvq = u32x4{0, 0, 0, 0};
 
     // per-lane LDS offsets: fragment rows for the score / Z products, and the 8-byte pieces
     // this lane addresses in a transposing read (row 4h + (lane & 15) / 4 of a 16-row block,
@@ -663,13 +667,12 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
 
     for (int s = 0; s < S; ++s) {
         const int jnew = s + 1 + RG::LEAD;
-        const bool more = (s + 1 < S);
-        if (more) g_load(ny, nb, nvy, nvq, kbase + jnew);
+        g_load(ny, nb, nvy, nvq, kbase + jnew);
 
         const int j = s + wave * FR;
         const int k = kbase + j;
         if (k >= 0 && k <= klast) {
-            const unsigned char *sl = smem + (j % RG::NSLOT) * RG::SLOT;
+            const unsigned char *sl = smem + ((unsigned)j % RG::NSLOT) * RG::SLOT;
             const int t0 = k * TT;
             // this tile's fragments (score rows, Z rows) and staged potentials, read once for
             // all FR owner fragments
@@ -749,7 +752,7 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
                         outm[f][dvt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, pf[f][m], outm[f][dvt], 0, 0, 0);
                 }
         }
-        if (more) s_store(ny, nb, nvy, nvq, jnew, kbase + jnew);
+        s_store(ny, nb, nvy, nvq, jnew, kbase + jnew);   // (its slot is free, also when no later step reads it)
         __syncthreads();
     }
 
