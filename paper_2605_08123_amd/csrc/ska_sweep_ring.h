@@ -548,8 +548,12 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
 
     // Everything the prologue needs from memory is requested before anything is waited for: the potentials
     // the stabiliser is taken from, the owner rows, the first tiles of the ring.
-    static_assert(BM <= NTHREADS, "one owner-side potential per thread");
-    const float mraw = xsp[min(o_blk + min(tid, BM - 1), Le - 1)];   // clamped repeats are harmless
+    // The stabiliser belongs to the rows, not to the block: the output map takes it over 256 aligned rows with
+    // either block size, so that its bf16 plan entries, and with them O and dV, do not depend on
+    // how a call is cut into launches.
+    constexpr int GROUP = MODE == M_APPLY ? 256 : BM;
+    static_assert(GROUP <= NTHREADS && GROUP % BM == 0, "one owner-side potential per thread");
+    const float mraw = xsp[min(o_blk / GROUP * GROUP + min(tid, GROUP - 1), Le - 1)];   // clamped repeats are harmless
     float mblk = 0.f, m2 = 0.f;
 
     // owner side: score rows, and for M_FINAL the owner factor of Z and the modifier pack.

@@ -69,6 +69,18 @@ def test_static_scratch_step_matches_workspace_step():
     _compare(lib, Workload("static_db", 23, 1, 2, 1500, 64, 33, 3, 2, 0.5, "bf16", dustbin=True, dustbin_score=0.3))
 
 
+# Calls that sinkhorn_attn_step splits over two streams (50 M band edges and more per half) and the static
+# entry does not, where the halves and the whole take blocks of different sizes.
+SPLIT = [
+    Workload("static_split_output_map", 25, 1, 2, 40000, 64, 700, 4, 2, 0.5, "bf16"),   # 2 x 40000 rows or 80000
+]
+
+
+@pytest.mark.parametrize("w", SPLIT, ids=[w.name for w in SPLIT])
+def test_static_scratch_step_matches_a_split_step(w):
+    _compare(binding.load(), w)
+
+
 def test_static_scratch_step_refuses_what_does_not_fit():
     import torch
     lib = binding.load()
