@@ -247,7 +247,8 @@ template <typename T, int D> int sweep_one(int mode, const SweepArgs &a, int N, 
         if constexpr (sizeof(T) == 2 && D <= 64) {
             // 64 rows per wavefront read every streamed tile half as often, but a launch of at most one
             // 256-row block per CU is faster as twice as many of 128 rows: 65536 rows 424 -> 417 us per
-            // step, 48016 rows 416 -> 411 us; at two per CU (131072 rows) 613 -> 625 us the other way
+            // step, 48016 rows 416 -> 411 us; at two per CU (131072 rows) 613 -> 625 us the other way.  Two launches
+            // of 65536 rows side by side take the same time with either (1196 us, W = 400)
             constexpr long ONE_BLOCK_PER_CU = 256L * 256;
             if ((long)N * a.L <= ONE_BLOCK_PER_CU) return launch_msweep<D, M_APPLY, 1>(a, N, st, dev);
             return launch_msweep<D, M_APPLY, 2>(a, N, st, dev);
