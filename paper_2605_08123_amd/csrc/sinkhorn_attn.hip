@@ -210,15 +210,20 @@ int launch_msweep(SweepArgs a, int N, hipStream_t st, int dev)
 //                                         first half-step is its running-maximum variant
 //   output map / dV, final sweeps         msweep_kernel for bf16 storage with d <= 64,
 //                                         sweep_kernel otherwise
+// Rows of a vector sweep that share a stabiliser, from the rows of a launch.  It decides how wide the potentials
+// may spread before a sum leaves fp32, and the last bits of a result, so it is a rule of its own: whatever blocks
+// a launch takes, its results are those of blocks of this size.
+constexpr long BLOCK_PER_CU = 256L * 256;   // rows of one 256-row block per CU
+template <typename T> int stab_rows(long rows) { return sizeof(T) == 4 || rows <= 3 * BLOCK_PER_CU ? 128 : 256; }
+
 // Block size of a vector sweep over `rows` owner rows: 32 rows per wavefront (blocks of 128) or 64.
 template <typename T, int D> bool small_blocks(long rows)
 {
-    constexpr long BLOCK_PER_CU = 256L * 256;   // rows of one 256-row block per CU
     if (sizeof(T) == 4) return true;
     // 64 rows per wavefront reuse every tile fragment twice, but a launch then has half the workgroups.
     // d <= 64: a CU holds four; up to three per CU (measured: two per CU gains 4-7 %, four per CU loses
     // 3 %) halve the block instead.
-    if (D <= 64) return rows <= 3 * BLOCK_PER_CU;
+    if (D <= 64) return stab_rows<T>(rows) == 128;
     // d = 128: the rings of two workgroups fill a CU's LDS.  Up to one 256-row block per CU, twice as many of
     // 128 rows are resident together just the same; up to two, the large blocks are one round and the small
     // ones two; with a remainder beyond that the small ones fill it better.  Forward of eight problems,
@@ -226,8 +231,10 @@ template <typename T, int D> bool small_blocks(long rows)
     // 131072, 1795 / 1869 at 163840; two launches of 98304 side by side 1854 / 1638.
     return rows <= BLOCK_PER_CU || (rows > 2 * BLOCK_PER_CU && rows <= 3 * BLOCK_PER_CU);
 }
-template <typename T, int D> int sweep_one(int mode, const SweepArgs &a, int N, hipStream_t st, int dev)
+template <typename T, int D> int sweep_one(int mode, const SweepArgs &a_in, int N, hipStream_t st, int dev)
 {
+    SweepArgs a = a_in;
+    a.stab = stab_rows<T>((long)N * a.L);
     constexpr int FRV = (sizeof(T) == 2) ? 2 : 1;   // vector sweeps: owner rows per wavefront / 32
     switch (mode) {
     case M_LSE_FIRST:
@@ -535,16 +542,18 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         if (g_fuse && !cx.noalloc && !capturing && !p.dustbin && !p.n_stages && ws && p.ws_given >= off + ws_chain_bytes(p))
             chain_done = reinterpret_cast<int *>(reinterpret_cast<unsigned char *>(ws) + off);
     }
-    // the block size of the separate launches (small_blocks) is taken per dispatch; the chain is one
-    // launch, so it needs the two halves of a split call to agree (they differ only for an odd number of problems around the threshold): results stay
-    // those of the separate launches bit for bit
+    // the stabiliser of the separate launches (stab_rows) is taken per dispatch; the chain is one launch, so it
+    // needs the two halves of a split call to agree (they differ only for an odd number of problems around
+    // the threshold): results stay those of the separate launches bit for bit
     const int n_half = (cx.side && N >= 2) ? N / 2 : N;
     const bool chain_fr1 = small_blocks<T, D>((long)n_half * L);
-    if (chain_fr1 != small_blocks<T, D>((long)(N - n_half ? N - n_half : N) * L)) chain_done = nullptr;
+    const int chain_stab = stab_rows<T>((long)n_half * L);
+    if (chain_stab != stab_rows<T>((long)(N - n_half) * L) && N > n_half) chain_done = nullptr;
     auto flush_chain = [&]() -> int {
         if (chain.nsteps == 0) return SKA_OK;
         SKA_TRY(cx.join());   // the chain takes all problems on the caller's stream
         chain.base = base;
+        chain.base.stab = chain_stab;
         chain.base.c2 = stage_c2; chain.base.sdb2 = stage_sdb2;
         chain.Q = Q; chain.K = K; chain.UV = UV; chain.us = us; chain.Lp = Lp;
         chain.log_a = p.log_a; chain.log_b = p.log_b; chain.len_q = p.len_q; chain.len_k = p.len_k;

@@ -78,6 +78,7 @@ struct SweepArgs {
     int nbp;          // workgroups per problem
     int nb_total;
     int lead;         // workgroups in front of the sweep's own (dustbin elements; a multiple of 8)
+    int stab;         // vector sweeps at d = 128: owner rows that share a stabiliser (128 or 256)
     int rev;          // walk each XCD's share of the blocks backwards (alternates between launches)
 };
 

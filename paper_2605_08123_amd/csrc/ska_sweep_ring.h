@@ -21,8 +21,12 @@ template <typename T, int D, int MODE, int FR> struct VRing {
     // read touches then fall on distinct banks, and the chunks of one row sit at fixed
     // distances: one address register per step); fp32 rows are padded by four floats
     static constexpr int ROWB = TL::IS_BF16 ? D * 2 + 16 : f32_row_floats<D>() * 4;
+    // Two stabilisers in a block, rows 0 .. 127 and 128 .. 255: the potentials are staged twice.  Only d = 128 takes
+    // 256-row blocks in launches whose stabiliser spans 128 rows (see small_blocks).
+    static constexpr bool TWO = TL::IS_BF16 && D == 128 && FR == 2 && MODE != M_LSE_FIRST;
+    static constexpr int NVY = TWO ? 2 * TT : TT;
     static constexpr int OFF_VY = 32 * ROWB;
-    static constexpr int OFF_VW = OFF_VY + TT * 4;
+    static constexpr int OFF_VW = OFF_VY + NVY * 4;
     static constexpr int SLOT = OFF_VW + TT * 4;
     static constexpr int BYTES = NSLOT * SLOT;
 };
@@ -79,7 +83,7 @@ __device__ __forceinline__ void vsweep_block(const SweepArgs &a, const int lb, u
     // stabiliser input first, so that waiting for it waits for nothing else
     static_assert(BM <= NTHREADS, "one owner-side potential per thread");
     float mraw = FIRST ? 0.f : ld_pot<COH>(xsp + min(o_blk + min(tid, BM - 1), Le - 1));   // clamped repeats are harmless
-    float mblk = 0.f, m2 = 0.f;
+    float mblk = 0.f, m2 = 0.f, m2s = 0.f;   // m2: of this wavefront's rows; m2s: what this thread stages with
     OwnerFrag<T, D> xf[FR];
     int o_frag[FR];
     float sum[FR], mx[FR];
@@ -140,10 +144,8 @@ __device__ __forceinline__ void vsweep_block(const SweepArgs &a, const int lb, u
         for (int q = 0; q < TL::CPT; ++q)
             if (TL::CHUNKS % NTHREADS == 0 || tid + q * NTHREADS < TL::CHUNKS)
                 *reinterpret_cast<uint4 *>(sl + soff[q]) = g.y[q];
-        if (tid < TT) {
-            reinterpret_cast<float *>(sl + RG::OFF_VY)[tid] = fmaf(g.vy, LOG2E, m2);
-            if constexpr (MODE == M_MATVEC) reinterpret_cast<float *>(sl + RG::OFF_VW)[tid] = g.vw;
-        }
+        if (tid < RG::NVY) reinterpret_cast<float *>(sl + RG::OFF_VY)[tid] = fmaf(g.vy, LOG2E, m2s);
+        if constexpr (MODE == M_MATVEC) if (tid < TT) reinterpret_cast<float *>(sl + RG::OFF_VW)[tid] = g.vw;
     };
     auto g_load = [&](Inflight &g, int k) {
         const int kc = min(max(k, 0), klast);
@@ -171,11 +173,9 @@ __device__ __forceinline__ void vsweep_block(const SweepArgs &a, const int lb, u
         for (int q = 0; q < TL::CPT; ++q)
             if (TL::CHUNKS % NTHREADS == 0 || tid + q * NTHREADS < TL::CHUNKS)
                 *reinterpret_cast<uint4 *>(sl + soff[q]) = g.y[q];
-        if (tid < TT) {
-            const bool ok = (int)vrow < g.rows;
-            reinterpret_cast<float *>(sl + RG::OFF_VY)[tid] = ok ? fmaf(g.vy, LOG2E, m2) : -INFINITY;
-            if constexpr (MODE == M_MATVEC) reinterpret_cast<float *>(sl + RG::OFF_VW)[tid] = ok ? g.vw : 0.f;
-        }
+        const bool ok = (int)vrow < g.rows;
+        if (tid < RG::NVY) reinterpret_cast<float *>(sl + RG::OFF_VY)[tid] = ok ? fmaf(g.vy, LOG2E, m2s) : -INFINITY;
+        if constexpr (MODE == M_MATVEC) if (tid < TT) reinterpret_cast<float *>(sl + RG::OFF_VW)[tid] = ok ? g.vw : 0.f;
     };
 
     // fill the ring with the tiles of step 0.  Everything the prologue needs from memory is
@@ -190,10 +190,21 @@ __device__ __forceinline__ void vsweep_block(const SweepArgs &a, const int lb, u
         for (int s = 32; s >= 1; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
         if (lane == 0) red[wave] = m;
         __syncthreads();
-        mblk = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+        if constexpr (RG::TWO) {   // (a wavefront's maximum is over the 64 rows it owns)
+            const float lo = fmaxf(red[0], red[1]), hi = fmaxf(red[2], red[3]), both = fmaxf(lo, hi);
+            const float m_lo = a.stab == 128 ? lo : both, m_hi = a.stab == 128 ? hi : both;
+            mblk = wave < 2 ? m_lo : m_hi;
+            m2s = (tid & TT) ? m_hi : m_lo;
+            if (m2s == -INFINITY) m2s = 0.f;
+            m2s *= LOG2E;
+        } else {
+            mblk = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+        }
         if (mblk == -INFINITY) mblk = 0.f;   // a block of inactive tokens only
     }
     m2 = mblk * LOG2E;
+    if constexpr (!RG::TWO) m2s = m2;
+    const int off_vy = RG::OFF_VY + (RG::TWO ? (wave >> 1) * (TT * 4) : 0);   // the copy staged with this wavefront's stabiliser
 #pragma unroll
     for (int j = 0; j <= RG::LEAD; ++j) s_store(fill[j], j);
     __syncthreads();
@@ -231,7 +242,7 @@ __device__ __forceinline__ void vsweep_block(const SweepArgs &a, const int lb, u
                 float yv[16];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    float4 v4 = *reinterpret_cast<const float4 *>(sl + RG::OFF_VY + (8 * q + 4 * h) * 4);
+                    float4 v4 = *reinterpret_cast<const float4 *>(sl + off_vy + (8 * q + 4 * h) * 4);
                     yv[4 * q + 0] = v4.x; yv[4 * q + 1] = v4.y; yv[4 * q + 2] = v4.z; yv[4 * q + 3] = v4.w;
                 }
 #pragma unroll

@@ -72,3 +72,21 @@ def test_vector_sweep_block_sizes_wide_heads(H, L):
     got = run_gpu(w, arrays, one_call=True)
     ref = oracle.band_batched(*arrays, w.W, w.T, w.R, w.eps)
     assert_per_tensor(got, ref, w.dtype, floors(w.dtype, *arrays, ref["O"], w.eps), where=w.name)
+
+
+@pytest.mark.parametrize("L", [65536, 66000])
+def test_potentials_that_jump_between_blocks_of_128_rows(L):
+    """One partner per token and row targets of 1 and e^50 in turn, 128 rows each, against column targets of 1: after two
+    steps the potentials of neighbouring groups are 100 apart, more than one stabiliser for both could carry, and
+    the plan is the identity all the same.  256-row blocks (L = 66000) have to take one per 128 rows."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    print(f"\n[case] stabiliser range L={L}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    Q, K, V = (torch.randn((1, 1, L, 128), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    log_a = 50.0 * ((torch.arange(L, device="cuda") // 128) % 2).float().view(1, 1, L)
+    O, UV = ska.sinkhorn_attn_fwd_marginals(Q, K, V, log_a, torch.zeros_like(log_a), 0, 1, 1, 1.0)
+    assert torch.isfinite(UV).all()
+    assert float((O.float() - V.float()).norm() / V.float().norm()) < TOL["bf16"]

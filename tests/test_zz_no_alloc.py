@@ -73,6 +73,7 @@ def test_static_scratch_step_matches_workspace_step():
 # entry does not, where the halves and the whole take blocks of different sizes.
 SPLIT = [
     Workload("static_split_output_map", 25, 1, 2, 40000, 64, 700, 4, 2, 0.5, "bf16"),   # 2 x 40000 rows or 80000
+    Workload("static_split_half_steps", 26, 1, 2, 34000, 128, 800, 4, 2, 0.5, "bf16"),  # 2 x 34000 rows or 68000
 ]
 
 
