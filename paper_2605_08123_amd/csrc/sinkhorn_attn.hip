@@ -216,20 +216,29 @@ int launch_msweep(SweepArgs a, int N, hipStream_t st, int dev)
 constexpr long BLOCK_PER_CU = 256L * 256;   // rows of one 256-row block per CU
 template <typename T> int stab_rows(long rows) { return sizeof(T) == 4 || rows <= 3 * BLOCK_PER_CU ? 128 : 256; }
 
-// Block size of a vector sweep over `rows` owner rows: 32 rows per wavefront (blocks of 128) or 64.
-template <typename T, int D> bool small_blocks(long rows)
+// Block size of a vector sweep over N problems of L owner rows: 32 rows per wavefront (blocks of 128) or 64.
+template <typename T, int D> bool small_blocks(int N, int L, int W)
 {
     if (sizeof(T) == 4) return true;
     // 64 rows per wavefront reuse every tile fragment twice, but a launch then has half the workgroups.
     // d <= 64: a CU holds four; up to three per CU (measured: two per CU gains 4-7 %, four per CU loses
     // 3 %) halve the block instead.
-    if (D <= 64) return stab_rows<T>(rows) == 128;
-    // d = 128: the rings of two workgroups fill a CU's LDS.  Up to one 256-row block per CU, twice as many of
-    // 128 rows are resident together just the same; up to two, the large blocks are one round and the small
-    // ones two; with a remainder beyond that the small ones fill it better.  Forward of eight problems,
-    // W = 256, us with 128 / 256 rows: 729 / 892 at 65536 rows, 1126 / 1122 at 81920, 1386 / 1321 at
-    // 131072, 1795 / 1869 at 163840; two launches of 98304 side by side 1854 / 1638.
-    return rows <= BLOCK_PER_CU || (rows > 2 * BLOCK_PER_CU && rows <= 3 * BLOCK_PER_CU);
+    const bool few = stab_rows<T>((long)N * L) == 128;
+    if (D <= 64) return few;
+    // d = 128: the rings of two workgroups fill a CU's LDS, so 512 are resident.  Where the large blocks are one
+    // round and the small ones more, the large ones win if the second round costs them most of another one:
+    // with a band of W >= 192, or beyond one and a half rounds.  (A narrow band's block is mostly its start
+    // and end, which a short second round hides.)  us per step or forward with 128 / 256 rows:
+    //   W = 64:  70000 rows 636 / 683, 98304 689 / 730, 104000 787 / 758;   W = 128: 84000 rows 852 / 890
+    //   W = 192: 82000 rows 1035 / 1040, 70 problems of L = 1000 1031 / 992;  W = 256: the same 1211 / 1163
+    //   W = 256, forward of eight problems: 729 / 892 at 65536 rows, 1126 / 1122 at 81920, 1386 / 1321 at
+    //   131072, 1795 / 1869 at 163840; two launches of 98304 side by side 1854 / 1638
+    // It is the blocks that are counted, not the rows: 400 problems of L = 300 (W = 64) are 800 large ones, 946 /
+    // 1182 us per step.  The dustbin elements do not count: they end long before the blocks (eight problems of
+    // L = 16384 with one, 512 large blocks: 1839 / 1763).
+    constexpr long RESIDENT = 512;
+    const long large = (long)N * ((L + 255) / 256), small = (long)N * ((L + 127) / 128);
+    return few && (large > RESIDENT || small <= RESIDENT || (W < 192 && 2 * small <= 3 * RESIDENT));
 }
 template <typename T, int D> int sweep_one(int mode, const SweepArgs &a_in, int N, hipStream_t st, int dev)
 {
@@ -241,7 +250,7 @@ template <typename T, int D> int sweep_one(int mode, const SweepArgs &a_in, int 
     case M_LSE:
     case M_MATVEC: {
         if constexpr (sizeof(T) == 2) {
-            if (small_blocks<T, D>((long)N * a.L))
+            if (small_blocks<T, D>(N, a.L, a.W))
                 return mode == M_LSE         ? launch_vsweep<T, D, M_LSE, 1>(a, N, st, dev)
                        : mode == M_MATVEC    ? launch_vsweep<T, D, M_MATVEC, 1>(a, N, st, dev)
                                              : launch_vsweep<T, D, M_LSE_FIRST, 1>(a, N, st, dev);
@@ -546,7 +555,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // needs the two halves of a split call to agree (they differ only for an odd number of problems around
     // the threshold): results stay those of the separate launches bit for bit
     const int n_half = (cx.side && N >= 2) ? N / 2 : N;
-    const bool chain_fr1 = small_blocks<T, D>((long)n_half * L);
+    const bool chain_fr1 = small_blocks<T, D>(n_half, L, base.W);
     const int chain_stab = stab_rows<T>((long)n_half * L);
     if (chain_stab != stab_rows<T>((long)(N - n_half) * L) && N > n_half) chain_done = nullptr;
     auto flush_chain = [&]() -> int {

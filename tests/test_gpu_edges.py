@@ -63,10 +63,11 @@ def test_double_buffered_matrix_sweeps(dtype, d, L, W, R):
     check(work("generic_edge", L, d, W, 3, dtype, H=2, R=R))
 
 
-@pytest.mark.parametrize("H,L", [(1, 65536), (3, 21846), (1, 131072), (2, 65600)])
-def test_vector_sweep_block_sizes_wide_heads(H, L):
-    """d = 128: 128-row blocks up to 65536 rows in a launch, 256-row ones up to 131072, 128-row ones again."""
-    w = work("block_edge", L, 128, 9, 2, "bf16", H=H)
+@pytest.mark.parametrize("H,L,W", [(1, 65536, 9), (1, 65537, 200), (1, 98304, 9), (1, 98305, 9), (400, 300, 9), (1, 131072, 192),
+                                   (2, 65600, 9)])
+def test_vector_sweep_block_sizes_wide_heads(H, L, W):
+    """d = 128: 128-row blocks while 512 of them hold a launch (768 with a narrow band), 256-row ones while 512 of those do."""
+    w = work("block_edge", L, 128, W, 2, "bf16", H=H)
     print(f"\n[case] {w}", flush=True)
     arrays = make_inputs(w, 3)
     got = run_gpu(w, arrays, one_call=True)
@@ -74,11 +75,11 @@ def test_vector_sweep_block_sizes_wide_heads(H, L):
     assert_per_tensor(got, ref, w.dtype, floors(w.dtype, *arrays, ref["O"], w.eps), where=w.name)
 
 
-@pytest.mark.parametrize("L", [65536, 66000])
+@pytest.mark.parametrize("L", [65536, 100000])
 def test_potentials_that_jump_between_blocks_of_128_rows(L):
     """One partner per token and row targets of 1 and e^50 in turn, 128 rows each, against column targets of 1: after two
     steps the potentials of neighbouring groups are 100 apart, more than one stabiliser for both could carry, and
-    the plan is the identity all the same.  256-row blocks (L = 66000) have to take one per 128 rows."""
+    the plan is the identity all the same.  256-row blocks (L = 100000) have to take one per 128 rows."""
     import torch
 
     import paper_2605_08123_amd as ska
