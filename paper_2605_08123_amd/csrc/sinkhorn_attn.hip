@@ -272,9 +272,8 @@ template <typename T, int D> int sweep_one(int mode, const SweepArgs &a_in, int 
         else return launch_sweep<T, D, M_APPLY, 1>(a, N, st, dev);
     case M_FINAL_DIRECT: return launch_sweep<T, D, M_FINAL, 1, PK_DIRECT>(a, N, st, dev);
     default:
-        if constexpr (sizeof(T) == 2) {   // packs as bf16 columns (R <= 2)
-            if constexpr (D <= 64) { if (a.poB) return launch_msweep<D, M_FINAL, 1>(a, N, st, dev); }
-            else if (a.poB) return launch_sweep<T, D, M_FINAL, 1, PK_COLUMNS>(a, N, st, dev);
+        if constexpr (sizeof(T) == 2 && D <= 64) {
+            if (a.poB) return launch_msweep<D, M_FINAL, 1>(a, N, st, dev);   // packs as bf16 columns (R <= 2)
         }
         return launch_sweep<T, D, M_FINAL, 1>(a, N, st, dev);
     }
@@ -706,8 +705,8 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     auto ubar = [&](int t) { return wf + (2 + 2 * (R - t)) * nldp; };
     float4 *rowp = reinterpret_cast<float4 *>(wf + (long)ws_vecs(R) * nldp);
     float4 *colp = rowp + nldp * R;   // (room for R groups per side)
-    // bf16 storage, R <= 2: the packs are bf16 columns (rowA, rowB, colA, colB)
-    const bool AUG = (sizeof(T) == 2 && R <= 2 && !seed && p.variant == SKA_BWD_ONE_REFERENCE);   // (that kernel always adds Z)
+    // the ring kernel (R <= 2) takes the packs as bf16 columns (rowA, rowB, colA, colB)
+    const bool AUG = (sizeof(T) == 2 && D <= 64 && R <= 2 && !seed && p.variant == SKA_BWD_ONE_REFERENCE);   // (that kernel always adds Z)
     __bf16 *aug = reinterpret_cast<__bf16 *>(colp + nldp * R);
     const int final_mode = p.direct() ? M_FINAL_DIRECT : M_FINAL;
     auto wv = [&](float *q) { return Vec{q, ldw}; };

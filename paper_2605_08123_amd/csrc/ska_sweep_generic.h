@@ -10,12 +10,13 @@ namespace {
 // matrix sweep and the bf16 matrix sweeps at d = 128; the ring kernels take the rest.  (A ring of d = 128 tile
 // pairs takes 86 KB, which leaves one workgroup per CU and every LDS and MFMA latency exposed; two buffers
 // take 35 KB, and registers allow two workgroups.)
-//   At d = 128 a transposed copy of the payload (2-byte LDS writes) and the
-// modifier terms on the plain ALUs bounded it; with the second product's operand read from the row-major tile by
-// transposing reads, the terms inside the Z product and loads under no condition, eight problems of
-// L = 16384, W = 256 went from 2031 to 1722 us per step (20 half-step pairs included).  fp32, which had
-// only the conditions and an empty group of terms to lose: 815 to 807 us, eight of L = 4096.
-enum Pack { PK_TERMS, PK_DIRECT, PK_COLUMNS };
+//   At d = 128 a transposed copy of the payload (2-byte LDS writes) and the modifier terms on the plain ALUs (64
+// multiply-adds and sixteen 16-byte LDS reads per lane and tile) bounded it; the second product's operand now
+// comes from the row-major tile by transposing reads, the terms are fp32 matrix products (two 4-byte reads
+// per group, the same bits as the multiply-adds: terms in order, each product fused and rounded), loads
+// are under no condition.  A step of eight problems of L = 16384, W = 256, half-steps included: 2031 -> 1661 us
+// together with the vector sweeps' 256-row blocks.  fp32, eight of L = 4096, W = 128: 812 -> 801 us.
+enum Pack { PK_TERMS, PK_DIRECT };
 template <typename T, int D, int MODE> struct Stage {
     using TL = Tile<T, D>;
     static constexpr int OFF_Y = 0;
@@ -25,11 +26,11 @@ template <typename T, int D, int MODE> struct Stage {
     static constexpr int BYTES = ((OFF_VQ + (MODE == M_FINAL ? TT * 16 * MAXNQ : 0)) + 15) / 16 * 16;
 };
 
-// PK (M_FINAL only) says how the rank-1 modifier terms come.  PK_TERMS: float4 groups, four terms each,
-// on the plain ALUs.  PK_COLUMNS (bf16, R <= 2): 16 bf16 columns per side that extend the Z product by one K = 16
-// MFMA step, as in the ring kernel.  PK_DIRECT: the comparator that forms every staircase plan factor by an
-// exponential of its own, exp(S + u_t + v_t'), instead of scaling the one reference tile
-// (Prop. 2 versus the plain evaluation of Prop. 1).  A pack group then holds two terms as
+// PK (M_FINAL only) says how the rank-1 modifier terms come, always in fp32.  PK_TERMS: float4 groups, four terms
+// each.  (As bf16 columns, the ring kernel's form, they keep 16 bits: Z minus the terms is where the score
+// cotangent cancels, and at d = 128 the terms have always been fp32.)  PK_DIRECT: the comparator that forms every
+// staircase plan factor by an exponential of its own, exp(S + u_t + v_t'), instead of scaling the one
+// reference tile (Prop. 2 versus the plain evaluation of Prop. 1).  A pack group then holds two terms as
 // (log2 modifier, weight) pairs: the term is exp2(score + l_row + l_col) w_row w_col.
 template <typename T, int D, int MODE, int FR, int PK = PK_TERMS>
 __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
@@ -37,9 +38,7 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
     using TL = Tile<T, D>;
     using ST = Stage<T, D, MODE>;
     constexpr int BM = NWAVES * FR * 32;
-    constexpr bool PRE = (sizeof(T) == 2);   // bf16 storage: the score operand is prescaled, c2 == 1
-    constexpr bool DIRECT = (PK == PK_DIRECT), COLUMNS = (PK == PK_COLUMNS);
-    static_assert(!COLUMNS || PRE, "pack columns go with bf16 tiles");
+    constexpr bool DIRECT = (PK == PK_DIRECT);
     static_assert(MODE == M_APPLY || MODE == M_FINAL, "matrix sweeps only");
 
     extern __shared__ __align__(16) unsigned char smem[];   // two stages of ST::BYTES
@@ -92,7 +91,7 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
     OwnerFrag<T, D> xf[FR];
     OwnerFrag<T, D> af[MODE == M_FINAL ? FR : 1];
     float4 pof[FR][MAXNQ];
-    bf16x8 pob[FR];   // COLUMNS: this lane's half of the owner row's 16 pack columns
+    float po[FR][MAXNQ][2];   // PK_TERMS: terms h and 2 + h of each group, negated
     int o_frag[FR];
 #pragma unroll
     for (int f = 0; f < FR; ++f) {
@@ -100,15 +99,13 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
         xf[f].load(Xb, o_frag[f] + c, Le, h);
         if constexpr (MODE == M_FINAL) {
             af[f].load(reinterpret_cast<const T *>(a.A) + moff, o_frag[f] + c, Le, h);
-            if constexpr (COLUMNS) {
-                uint4 z = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a.poB) +
-                                                           (n * a.ldp + min(o_frag[f] + c, Le - 1)) * 32 + h * 16);
-                pob[f] = *reinterpret_cast<bf16x8 *>(&z);
-            } else
 #pragma unroll
-            for (int g = 0; g < MAXNQ; ++g)
+            for (int g = 0; g < MAXNQ; ++g) {
                 pof[f][g] = (o_frag[f] + c < Le && g < a.nq) ? a.po[(n * a.ldp + o_frag[f] + c) * a.pstride + g]
                                                             : make_float4(0, 0, 0, 0);
+                po[f][g][0] = h ? -pof[f][g].y : -pof[f][g].x;
+                po[f][g][1] = h ? -pof[f][g].w : -pof[f][g].z;
+            }
         }
     }
 
@@ -130,7 +127,7 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
 
     // Staging registers.  Everything is requested without a condition (indices clamped into the matrix, absent
     // rows neutralised at the store): a load under a condition is waited for at once.
-    uint4 ry[TL::CPT], rb[TL::CPT], rk = make_uint4(0, 0, 0, 0);
+    uint4 ry[TL::CPT], rb[TL::CPT];
     float rvy = 0.f;
     float4 rvq[MAXNQ] = {make_float4(0, 0, 0, 0), make_float4(0, 0, 0, 0)};
     const T *Bb = reinterpret_cast<const T *>(MODE == M_FINAL ? a.Bm : a.Pay) + moff;
@@ -141,10 +138,7 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
         tile_load<T, D>(rb, Bb, t0, Lt);
         const int t = min(t0 + (tid & (TT - 1)), Lt - 1);
         rvy = ytp[t];
-        if constexpr (COLUMNS) {   // 64 pieces of 16 bytes
-            rk = *reinterpret_cast<const uint4 *>(reinterpret_cast<const unsigned char *>(a.qtA) +
-                                                  (n * a.ldp + t) * 32 + h * 16);
-        } else if constexpr (MODE == M_FINAL) {
+        if constexpr (MODE == M_FINAL) {
 #pragma unroll
             for (int g = 0; g < MAXNQ; ++g) rvq[g] = a.qt[(n * a.ldp + t) * a.pstride + min(g, a.nq - 1)];
         }
@@ -156,15 +150,13 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
         tile_store_rm<T, D>(rb, s + ST::OFF_B, rows);
         if (tid < TT) {
             reinterpret_cast<float *>(s + ST::OFF_VY)[tid] = tid < rows ? rvy * LOG2E + m2 : -INFINITY;
-            if constexpr (MODE == M_FINAL && !COLUMNS) {
+            if constexpr (MODE == M_FINAL) {
 #pragma unroll
                 for (int g = 0; g < MAXNQ; ++g)
                     reinterpret_cast<float4 *>(s + ST::OFF_VQ)[tid * MAXNQ + g] =
                         tid < rows && g < a.nq ? rvq[g] : make_float4(0, 0, 0, 0);
             }
         }
-        if constexpr (COLUMNS)   // (halves apart: a read is one 16-byte piece per lane, rows in sequence)
-            if (tid < 64) *reinterpret_cast<uint4 *>(s + ST::OFF_VQ + tid * 16) = c < rows ? rk : make_uint4(0, 0, 0, 0);
     };
 
     g_load(k_lo);
@@ -192,21 +184,24 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
             }
             f32x16 acc, z;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) { acc[r] = PRE ? yv[r] : 0.f; z[r] = 0.f; }
+            for (int r = 0; r < 16; ++r) { acc[r] = 0.f; z[r] = 0.f; }
             acc = tile_dot<D>(s + ST::OFF_Y, xf[f], lane, acc);
             if constexpr (MODE == M_FINAL) {   // the Z product runs beside the exponentials
-                if constexpr (COLUMNS) {
-                    z = tile_dot<D>(s + ST::OFF_B, af[f], lane, z);
-                    const bf16x8 qpk = *reinterpret_cast<const bf16x8 *>(s + ST::OFF_VQ + lane * 16);
-                    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qpk, pob[f], z, 0, 0, 0);   // - sum_k po_k qt_k
-                } else if (!a.skipz) {
-                    z = tile_dot<D>(s + ST::OFF_B, af[f], lane, z);
+                if (!a.skipz) z = tile_dot<D>(s + ST::OFF_B, af[f], lane, z);
+                if constexpr (!DIRECT) {   // - sum_k po_k qt_k, in fp32 on the matrix cores: two terms a product
+#pragma unroll
+                    for (int g = 0; g < MAXNQ; ++g) {
+                        if (g >= a.nq) break;   // (uniform; R <= 2 has one group)
+                        const float *qg = reinterpret_cast<const float *>(s + ST::OFF_VQ) + (c * MAXNQ + g) * 4 + h;
+                        z = __builtin_amdgcn_mfma_f32_32x32x2f32(qg[0], po[f][g][0], z, 0, 0, 0);
+                        z = __builtin_amdgcn_mfma_f32_32x32x2f32(qg[2], po[f][g][1], z, 0, 0, 0);
+                    }
                 }
             }
 
             float e[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) e[r] = PRE ? acc[r] : fmaf(acc[r], a.c2, yv[r]);
+            for (int r = 0; r < 16; ++r) e[r] = fmaf(acc[r], a.c2, yv[r]);
             if (!interior) {
                 const int o = of + c;
 #pragma unroll
@@ -227,25 +222,19 @@ __global__ __launch_bounds__(NTHREADS) void sweep_kernel(const SweepArgs a)
                 if constexpr (MODE == M_APPLY) {
                     tile_accum<T, D>(outm[f], s + ST::OFF_B, e, lane);
                 } else {  // M_FINAL
+                    if constexpr (DIRECT)
 #pragma unroll
                     for (int g = 0; g < MAXNQ; ++g) {
-                        if (COLUMNS || g >= a.nq) break;   // (uniform; R <= 2 has one group)
+                        if (g >= a.nq) break;
 #pragma unroll
                         for (int r = 0; r < 16; ++r) {
                             const int tl = 8 * (r >> 2) + 4 * h + (r & 3);
                             const float4 q4 = *reinterpret_cast<const float4 *>(s + ST::OFF_VQ + (tl * MAXNQ + g) * 16);
-                            if constexpr (DIRECT) {
-                                if (g == 0) z[r] *= e[r];
-                                const float p0 = (g == 0 && a.refterm) ? e[r] : fast_exp2(el[r] + pof[f][g].x + q4.x);
-                                const float p1 = fast_exp2(el[r] + pof[f][g].z + q4.z);
-                                z[r] = fmaf(-p0 * pof[f][g].y, q4.y, z[r]);
-                                z[r] = fmaf(-p1 * pof[f][g].w, q4.w, z[r]);
-                            } else {
-                                z[r] = fmaf(-pof[f][g].x, q4.x, z[r]);
-                                z[r] = fmaf(-pof[f][g].y, q4.y, z[r]);
-                                z[r] = fmaf(-pof[f][g].z, q4.z, z[r]);
-                                z[r] = fmaf(-pof[f][g].w, q4.w, z[r]);
-                            }
+                            if (g == 0) z[r] *= e[r];
+                            const float p0 = (g == 0 && a.refterm) ? e[r] : fast_exp2(el[r] + pof[f][g].x + q4.x);
+                            const float p1 = fast_exp2(el[r] + pof[f][g].z + q4.z);
+                            z[r] = fmaf(-p0 * pof[f][g].y, q4.y, z[r]);
+                            z[r] = fmaf(-p1 * pof[f][g].w, q4.w, z[r]);
                         }
                     }
 #pragma unroll

@@ -91,3 +91,28 @@ def test_potentials_that_jump_between_blocks_of_128_rows(L):
     O, UV = ska.sinkhorn_attn_fwd_marginals(Q, K, V, log_a, torch.zeros_like(log_a), 0, 1, 1, 1.0)
     assert torch.isfinite(UV).all()
     assert float((O.float() - V.float()).norm() / V.float().norm()) < TOL["bf16"]
+
+
+@pytest.mark.parametrize("R", [1, 2])
+def test_wide_heads_keep_modifier_terms_in_fp32(R):
+    """One partner per token, all queries and all keys alike: the plan is the identity with entries that bf16 holds
+    exactly, Z and the modifier terms are equal, and dQ = dK = 0.  What is left is the rounding of Z minus the
+    terms: sums of 128 products of order one in fp32, below 2^-20 of Z with room to spare (2^-23 each); terms kept
+    to 16 bits leave 2^-18.8 (with fp32 terms 2^-22.7)."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    L, d, eps = 300, 128, 0.8
+    print(f"\n[case] modifier terms d={d} R={R}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(9)
+    q, k = (torch.randn((1, 1, 1, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    Q, K = (x.expand(1, 1, L, d).contiguous() for x in (q, k))
+    V, G = (torch.randn((1, 1, L, d), generator=gen, device="cuda").bfloat16() for _ in range(2))
+    O, UV, dQ, dK, dV = ska.sinkhorn_attn_step(Q, K, V, G, 0, 3, R, eps)
+    assert torch.equal(O, V) and torch.equal(dV, G)
+    z = (G.double() * V.double()).sum(-1, keepdim=True) / (eps * d ** 0.5)
+    for got, other in ((dQ, K), (dK, Q)):
+        left = float(got.double().norm() / (z * other.double()).norm())
+        print(f"   left of Z: 2^{np.log2(max(left, 1e-30)):.1f}", flush=True)
+        assert left <= 2.0 ** -20
