@@ -619,12 +619,14 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
         goff[q] = idx * 16;
         soff[q] = (idx / RG::CPR) * RG::ROWB + (idx % RG::CPR) * 16;
     }
+    static_assert(NTHREADS % RG::CPR == 0 && (RG::CPT == 1 || RG::CHUNKS % NTHREADS == 0), "a thread's pieces share their columns");
+    const unsigned gcol = goff[0] % ROW_BYTES;
     const int vrow = tid & (TT - 1);
     auto g_load = [&](u32x4 (&gy)[RG::CPT], u32x4 (&gb)[RG::CPT], float &gvy, u32x4 &gpk, int k) {
         const int kc = min(max(k, 0), klast);   // a tile outside the matrix is never used
         const int rows = min(TT, Lt - kc * TT);
         const long t_off = (long)kc * TILE_BYTES;
-        const unsigned lim = rows * ROW_BYTES - 16;
+        const unsigned lim = (rows - 1) * ROW_BYTES + gcol;   // this thread's columns of the last row
 #pragma unroll
         for (int q = 0; q < RG::CPT; ++q) {
             const unsigned off = min(goff[q], lim);
@@ -635,10 +637,11 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
         if constexpr (MODE == M_FINAL)   // 64 pieces of 16 bytes per tile, the same for every wavefront
             gpk = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const unsigned char *>(a.qtA) +
                                                    ((long)n * a.ldp + kc * TT) * 32 +
-                                                   min((unsigned)(tid & 63) * 16u, (unsigned)rows * 32u - 16u));
+                                                   min((tid & 63) * 16, (rows - 1) * 32 + (tid & 1) * 16));
     };
-    // rows outside [0, Lt) keep whatever the clamped fetch brought: their potential is -inf,
-    // so their plan entries are exactly zero and finite data times zero adds nothing
+    // Rows at or past Lt repeat the last row, column by column: their potential is -inf, so their plan
+    // entries are exactly zero and finite data times zero adds nothing; an infinity in the last row stays in
+    // its own column.  (Tiles before the sequence, k < 0, are skipped below.)
     const int pk_off = ((tid & 1) ? RG::OFF_B : RG::OFF_Y) + ((tid & 63) >> 1) * RG::ROWB + RG::OFF_PK;
     auto s_store = [&](const u32x4 (&gy)[RG::CPT], const u32x4 (&gb)[RG::CPT], float gvy, u32x4 gpk, int j, int k) {
         unsigned char *sl = smem + ((unsigned)j % RG::NSLOT) * RG::SLOT;

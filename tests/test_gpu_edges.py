@@ -116,3 +116,25 @@ def test_wide_heads_keep_modifier_terms_in_fp32(R):
         left = float(got.double().norm() / (z * other.double()).norm())
         print(f"   left of Z: 2^{np.log2(max(left, 1e-30)):.1f}", flush=True)
         assert left <= 2.0 ** -20
+
+
+@pytest.mark.parametrize("N,L", [(1, 70), (2, 33), (1000, 70)])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_an_infinity_in_the_last_row_stays_in_its_column(d, N, L):
+    """Rows past the end of a ragged last tile are stand-ins for the last row, times a plan entry of zero: an infinite
+    value of V there may not reach any other column of O, nor one of dO any other column of dV (both block sizes)."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    print(f"\n[case] infinite payload N={N} L={L} d={d}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    Q, K, V, G = (torch.randn((1, N, L, d), generator=gen, device="cuda").bfloat16() for _ in range(4))
+    V[..., L - 1, d - 2] = float("inf")
+    O, UV = ska.sinkhorn_attn_fwd(Q, K, V, 5, 3, 2, 0.8)
+    V[..., L - 1, d - 2] = 1.0
+    G[..., L - 1, d - 3] = float("inf")
+    dQ, dK, dV = ska.sinkhorn_attn_bwd(Q, K, V, O, G, UV, 5, 3, 2, 0.8)
+    for got, at in ((O, d - 2), (dV, d - 3)):
+        cols = (~torch.isfinite(got)).flatten(0, 2).any(0).nonzero().flatten().tolist()
+        assert cols == [at], cols
