@@ -639,9 +639,9 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
                                                    ((long)n * a.ldp + kc * TT) * 32 +
                                                    min((tid & 63) * 16, (rows - 1) * 32 + (tid & 1) * 16));
     };
-    // Rows at or past Lt repeat the last row, column by column: their potential is -inf, so their plan
-    // entries are exactly zero and finite data times zero adds nothing; an infinity in the last row stays in
-    // its own column.  (Tiles before the sequence, k < 0, are skipped below.)
+    // Rows outside [0, Lt) repeat a row of the matrix, past the end the last row, column by column: their
+    // potential is -inf, so their plan entries are exactly zero and finite data times zero adds nothing; an
+    // infinity in the last row stays in its own column.
     const int pk_off = ((tid & 1) ? RG::OFF_B : RG::OFF_Y) + ((tid & 63) >> 1) * RG::ROWB + RG::OFF_PK;
     auto s_store = [&](const u32x4 (&gy)[RG::CPT], const u32x4 (&gb)[RG::CPT], float gvy, u32x4 gpk, int j, int k) {
         unsigned char *sl = smem + ((unsigned)j % RG::NSLOT) * RG::SLOT;
@@ -650,7 +650,7 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
             *reinterpret_cast<u32x4 *>(sl + RG::OFF_Y + soff[q]) = gy[q];
             *reinterpret_cast<u32x4 *>(sl + RG::OFF_B + soff[q]) = gb[q];
         }
-        if (tid < TT) reinterpret_cast<float *>(sl + RG::OFF_VY)[vrow] = k * TT + vrow < Lt ? fmaf(gvy, LOG2E, m2) : -INFINITY;
+        if (tid < TT) reinterpret_cast<float *>(sl + RG::OFF_VY)[vrow] = (unsigned)(k * TT + vrow) < (unsigned)Lt ? fmaf(gvy, LOG2E, m2) : -INFINITY;
         if constexpr (MODE == M_FINAL) if (tid < 64) *reinterpret_cast<u32x4 *>(sl + pk_off) = gpk;
     };
 
