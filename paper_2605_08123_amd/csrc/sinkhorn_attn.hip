@@ -166,8 +166,8 @@ int launch_sweep(SweepArgs a, int N, hipStream_t st, int dev)
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
 
-template <typename T, int D, int MODE, int FR>
-int launch_vsweep(SweepArgs a, int N, hipStream_t st, int dev)
+template <typename T, int D, int MODE, int FR, int NV>
+int launch_vsweep_nv(SweepArgs a, int N, hipStream_t st, int dev)
 {
     constexpr int BM = NWAVES * FR * 32;
     a.nbp = (a.L + BM - 1) / BM;
@@ -176,14 +176,28 @@ int launch_vsweep(SweepArgs a, int N, hipStream_t st, int dev)
     constexpr int LDS = VRing<T, D, MODE, FR>::BYTES;
     static bool raised[MAX_DEVICES];
     if (LDS > 48 * 1024 && !raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vsweep_kernel<T, D, MODE, FR>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vsweep_kernel<T, D, MODE, FR, NV>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
     }
     a.lead = a.dustbin ? (N + 7) / 8 * 8 : 0;   // one workgroup per problem in front: the dustbin element
-    hipLaunchKernelGGL((vsweep_kernel<T, D, MODE, FR>), dim3(chunk * 8 + a.lead), dim3(NTHREADS), LDS, st, a);
+    hipLaunchKernelGGL((vsweep_kernel<T, D, MODE, FR, NV>), dim3(chunk * 8 + a.lead), dim3(NTHREADS), LDS, st, a);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
+}
+
+// Loads in flight of a dustbin element: eight, four of a mat-vec, which reads a third stream.  At bf16 d = 32 the rings of
+// seven workgroups fit a CU's LDS, which the registers of eight loads would cut to four: four problems of
+// L = 65536, W = 256 1147 us per step, 1066 with four loads; eight of L = 16384 with a dustbin 881 / 820.  Beyond 65536
+// the element itself is what a launch with a dustbin waits for: one problem of L = 131072, W = 64 905 with eight, 1080
+// with four; two of L = 262144, W = 256 2065 / 2595.  Elsewhere LDS holds four workgroups or fewer.
+template <typename T, int D, int MODE, int FR>
+int launch_vsweep(const SweepArgs &a, int N, hipStream_t st, int dev)
+{
+    constexpr int NV = MODE == M_MATVEC || (sizeof(T) == 2 && D == 32) ? 4 : 8;
+    if constexpr (MODE != M_MATVEC && NV == 4)
+        if (a.dustbin && a.L > 65536) return launch_vsweep_nv<T, D, MODE, FR, 8>(a, N, st, dev);
+    return launch_vsweep_nv<T, D, MODE, FR, NV>(a, N, st, dev);
 }
 
 template <int D, int MODE, int FR>

@@ -346,7 +346,7 @@ template <> __device__ __forceinline__ void load4<__bf16>(const __bf16 *src, flo
 // is a learned token).
 //   half-steps: out[L] = -log sum_{t<=L} exp(s_t + y_t)
 //   mat-vec   : out[L] = -exp(x[L]) sum_{t<=L} exp(s_t + y_t) w_t    (its additive term is 0)
-template <bool MATVEC> __device__ __forceinline__ void dustbin_element(const SweepArgs &a, int n)
+template <bool MATVEC, int NV> __device__ __forceinline__ void dustbin_element(const SweepArgs &a, int n)
 {
     __shared__ float sm[NWAVES], ss[NWAVES];
     const int L = a.L, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -355,13 +355,10 @@ template <bool MATVEC> __device__ __forceinline__ void dustbin_element(const Swe
     const float *wp = MATVEC ? a.w.p + n * a.w.stride : nullptr;
     const float sdb = sp ? 0.f : a.sdb2 * LN2;
     // One pass: running maximum m and sum of exp(. - m) (times the weight), merged pairwise.  One
-    // workgroup reads a whole vector, so loads in flight are what bounds it: a thread requests 32 values
-    // (half-steps; 16 of a mat-vec, which reads a third stream and would otherwise cost the sweep a
-    // workgroup per CU in registers) by 16-byte loads (the vectors start on any float, which global
-    // loads allow) and rescales its sum once for all of them.  A value per load and two exponentials per
-    // value made the element the longest workgroup of the launch: eight problems of L = 16384, W = 256
-    // 1.19 -> 1.08 ms per step.
-    constexpr int NV = MATVEC ? 4 : 8;              // 16-byte loads per thread, batch and stream
+    // workgroup reads a whole vector, so loads in flight are what bounds it: a thread requests 4 NV values by
+    // NV 16-byte loads per stream (the vectors start on any float, which global loads allow) and rescales
+    // its sum once for all of them.  A value per load and two exponentials per value made the element the
+    // longest workgroup of the launch: eight problems of L = 16384, W = 256 1133 -> 1018 us per step.
     constexpr int STEP = NTHREADS * 4, BATCH = NV * STEP;
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     float m = -INFINITY, acc = 0.f;

@@ -385,7 +385,10 @@ __device__ __forceinline__ int xcd_block(int bx, int nb_total, int rev)
     return (bx & 7) * chunk + (rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
 }
 
-template <typename T, int D, int MODE, int FR>
+// NV: 16-byte loads in flight of a dustbin element.  The element shares the sweep's kernel, and a kernel's registers are
+// those of its hungriest path, with a dustbin or without: a half-step has 56 at bf16 d = 32 with four loads, 104 with
+// eight (launch_vsweep chooses).
+template <typename T, int D, int MODE, int FR, int NV>
 __global__ __launch_bounds__(NTHREADS) void vsweep_kernel(const SweepArgs a)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -393,7 +396,7 @@ __global__ __launch_bounds__(NTHREADS) void vsweep_kernel(const SweepArgs a)
     // a.lead workgroups come first (a multiple of 8, so the XCD of a sweep block is unchanged): one
     // per problem for the dustbin element, started first so that it ends under the sweep
     if ((int)blockIdx.x < a.lead) {
-        if ((int)blockIdx.x < a.nb_total / a.nbp) dustbin_element<MODE == M_MATVEC>(a, blockIdx.x);
+        if ((int)blockIdx.x < a.nb_total / a.nbp) dustbin_element<MODE == M_MATVEC, NV>(a, blockIdx.x);
         return;
     }
     const int lb = xcd_block((int)blockIdx.x - a.lead, a.nb_total, a.rev);
