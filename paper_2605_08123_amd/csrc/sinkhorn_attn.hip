@@ -320,7 +320,6 @@ Side g_side[MAX_DEVICES];
 int g_streams = 2;            // sinkhorn_attn_set_streams: 1 = everything on the caller's stream
 int g_fuse = 0;               // sinkhorn_attn_set_fused_half_steps: 0 off, 1 the tail, 2 all but the first half-step
 unsigned g_spin_limit = 1u << 18;   // polls of a chain's wait before it gives up (a poll is a few hundred cycles: about 0.1 s)
-int g_chain_cap[MAX_DEVICES][8];    // workgroups of a chain kernel the device holds at once (0: not asked yet)
 double g_split_min_edges = 50e6;   // sinkhorn_attn_set_split_min_edges
 
 Side *side_for_device(int dev)   // (g_mutex held)
@@ -382,7 +381,7 @@ struct Call {
 
 // A chain of half-steps in one cooperative launch (vchain_kernel); returns SKA_EUNSUPPORTED if the
 // device cannot hold a useful grid, so that the caller launches the half-steps one by one instead.
-template <typename T, int D, int FR> int launch_vchain(ChainArgs &c, int N, hipStream_t st, int dev, int slot)
+template <typename T, int D, int FR> int launch_vchain(ChainArgs &c, int N, hipStream_t st, int dev)
 {
     constexpr int BM = NWAVES * FR * 32;
     c.base.nbp = (c.base.L + BM - 1) / BM;
@@ -395,7 +394,8 @@ template <typename T, int D, int FR> int launch_vchain(ChainArgs &c, int N, hipS
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, LDS) != hipSuccess) return SKA_EHIP;
         raised[dev] = true;
     }
-    int &cap = g_chain_cap[dev][slot];
+    static int caps[MAX_DEVICES];   // workgroups of this instance the device holds at once (0: not asked yet; g_mutex held)
+    int &cap = caps[dev];
     if (cap == 0) {
         int per_cu = 0, cus = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, NTHREADS, LDS) != hipSuccess ||
@@ -587,8 +587,8 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
                            reinterpret_cast<float *>(chain_done), nflag, nflag, 1, 0.f);
         if (hipGetLastError() != hipSuccess) return SKA_EHIP;
         int rc;
-        if constexpr (sizeof(T) == 2) rc = fr1 ? launch_vchain<T, D, 1>(chain, N, st, cx.dev, 0) : launch_vchain<T, D, 2>(chain, N, st, cx.dev, 1);
-        else rc = launch_vchain<T, D, 1>(chain, N, st, cx.dev, 0);
+        if constexpr (sizeof(T) == 2) rc = fr1 ? launch_vchain<T, D, 1>(chain, N, st, cx.dev) : launch_vchain<T, D, 2>(chain, N, st, cx.dev);
+        else rc = launch_vchain<T, D, 1>(chain, N, st, cx.dev);
         if (rc == SKA_EUNSUPPORTED) {   // the device cannot hold the grid: one launch per half-step after all
             for (int i = 0; i < chain.nsteps; ++i) {
                 const unsigned code = chain.code[i];

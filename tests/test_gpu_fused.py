@@ -24,6 +24,8 @@ CASES = [
     ("f32_marginals", 1, 2, 900, 32, 40, 5, 2, 1.0, "f32", "marginals"),
     ("bf16_masks", 2, 1, 1500, 64, 31, 4, 2, 0.6, "bf16", "masked"),
     ("bf16_d128", 1, 1, 1300, 128, 64, 3, 1, 0.5, "bf16", "plain"),
+    ("bf16_d128_more_blocks_than_fit", 1, 2, 40000, 128, 40, 3, 1, 0.5, "bf16", "plain"),   # 626 blocks, 512 at once (d = 64: 1024)
+    ("bf16_d128_256_rows", 1, 1, 100000, 128, 200, 3, 1, 0.5, "bf16", "plain"),
 ]
 
 
