@@ -615,36 +615,35 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
     // writes a third more LDS per step in the final sweeps, the large case lost 1 % instead.)
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
     constexpr int ROW_BYTES = D * 2, TILE_BYTES = TT * ROW_BYTES;
-    unsigned goff[RG::CPT], soff[RG::CPT];   // piece offsets: in memory, in the LDS tile
+    // piece offsets: in memory (in the last tile absent rows repeat the last one, column by column), in the LDS tile
+    unsigned goff[RG::CPT], glast[RG::CPT], soff[RG::CPT];
+    const int last_rows = Lt - klast * TT;   // 1 .. 32
 #pragma unroll
     for (int q = 0; q < RG::CPT; ++q) {
-        const int idx = min(tid + q * NTHREADS, RG::CHUNKS - 1);
+        const int idx = min(tid + q * NTHREADS, RG::CHUNKS - 1), row = idx / RG::CPR, col = idx % RG::CPR;
         goff[q] = idx * 16;
-        soff[q] = (idx / RG::CPR) * RG::ROWB + (idx % RG::CPR) * 16;
+        glast[q] = min(row, last_rows - 1) * ROW_BYTES + col * 16;
+        soff[q] = row * RG::ROWB + col * 16;
     }
-    static_assert(NTHREADS % RG::CPR == 0 && (RG::CPT == 1 || RG::CHUNKS % NTHREADS == 0), "a thread's pieces share their columns");
-    const unsigned gcol = goff[0] % ROW_BYTES;
     const int vrow = tid & (TT - 1);
+    const unsigned pkoff = (tid & 63) * 16, pklast = min((tid & 63) >> 1, last_rows - 1) * 32 + (tid & 1) * 16;
     auto g_load = [&](u32x4 (&gy)[RG::CPT], u32x4 (&gb)[RG::CPT], float &gvy, u32x4 &gpk, int k) {
         const int kc = min(max(k, 0), klast);   // a tile outside the matrix is never used
-        const int rows = min(TT, Lt - kc * TT);
+        const bool last = kc == klast;
         const long t_off = (long)kc * TILE_BYTES;
-        const unsigned lim = (rows - 1) * ROW_BYTES + gcol;   // this thread's columns of the last row
 #pragma unroll
         for (int q = 0; q < RG::CPT; ++q) {
-            const unsigned off = min(goff[q], lim);
+            const unsigned off = last ? glast[q] : goff[q];
             gy[q] = *reinterpret_cast<const u32x4 *>(Yb + t_off + off);
             gb[q] = *reinterpret_cast<const u32x4 *>(Bb + t_off + off);
         }
-        gvy = (ytp + kc * TT)[(unsigned)min(vrow, rows - 1)];
+        gvy = (ytp + kc * TT)[(unsigned)min(vrow, Lt - 1 - kc * TT)];
         if constexpr (MODE == M_FINAL)   // 64 pieces of 16 bytes per tile, the same for every wavefront
             gpk = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const unsigned char *>(a.qtA) +
-                                                   ((long)n * a.ldp + kc * TT) * 32 +
-                                                   min((tid & 63) * 16, (rows - 1) * 32 + (tid & 1) * 16));
+                                                   ((long)n * a.ldp + kc * TT) * 32 + (last ? pklast : pkoff));
     };
-    // Rows outside [0, Lt) repeat a row of the matrix, past the end the last row, column by column: their
-    // potential is -inf, so their plan entries are exactly zero and finite data times zero adds nothing; an
-    // infinity in the last row stays in its own column.
+    // Rows outside [0, Lt) repeat a row of the matrix: their potential is -inf, so their plan entries are exactly
+    // zero and finite data times zero adds nothing; an infinity in the last row stays in its own column.
     const int pk_off = ((tid & 1) ? RG::OFF_B : RG::OFF_Y) + ((tid & 63) >> 1) * RG::ROWB + RG::OFF_PK;
     auto s_store = [&](const u32x4 (&gy)[RG::CPT], const u32x4 (&gb)[RG::CPT], float gvy, u32x4 gpk, int j, int k) {
         unsigned char *sl = smem + ((unsigned)j % RG::NSLOT) * RG::SLOT;
