@@ -25,7 +25,7 @@ constexpr int MAXR = 32;     // deepest differentiable tail (T = 0 with R = T' +
 constexpr int MAXNQ = 2;     // float4 groups of modifier terms one final sweep takes (8 terms);
                              // deeper tails take several sweeps that accumulate
 enum Mode { M_LSE_FIRST = 0, M_LSE = 1, M_MATVEC = 2, M_APPLY = 3, M_FINAL = 4,
-            M_FINAL_DIRECT = 5 /* dispatch only: M_FINAL of the generic kernel with DIRECT = true */ };
+            M_FINAL_DIRECT = 5 /* dispatch only: M_FINAL of the generic kernel with PK_DIRECT */ };
 
 struct Vec {          // one fp32 vector per problem
     const float *p;
@@ -358,7 +358,7 @@ template <bool MATVEC, int NV> __device__ __forceinline__ void dustbin_element(c
     // workgroup reads a whole vector, so loads in flight are what bounds it: a thread requests 4 NV values by
     // NV 16-byte loads per stream (the vectors start on any float, which global loads allow) and rescales
     // its sum once for all of them.  A value per load and two exponentials per value made the element the
-    // longest workgroup of the launch: eight problems of L = 16384, W = 256 1133 -> 1018 us per step.
+    // longest workgroup of the launch: eight problems of L = 16384, W = 256 1179 -> 1055 us per step.
     constexpr int STEP = NTHREADS * 4, BATCH = NV * STEP;
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     float m = -INFINITY, acc = 0.f;

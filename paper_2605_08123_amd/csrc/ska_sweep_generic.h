@@ -14,8 +14,8 @@ namespace {
 // multiply-adds and sixteen 16-byte LDS reads per lane and tile) bounded it; the second product's operand now
 // comes from the row-major tile by transposing reads, the terms are fp32 matrix products (two 4-byte reads
 // per group, the same bits as the multiply-adds: terms in order, each product fused and rounded), loads
-// are under no condition.  A step of eight problems of L = 16384, W = 256, half-steps included: 2031 -> 1661 us
-// together with the vector sweeps' 256-row blocks.  fp32, eight of L = 4096, W = 128: 812 -> 801 us.
+// are under no condition.  A step of eight problems of L = 16384, W = 256, half-steps included: 2038 -> 1702 us
+// together with the vector sweeps' 256-row blocks.  fp32, eight of L = 4096, W = 128: 815 -> 803 us.
 enum Pack { PK_TERMS, PK_DIRECT };
 template <typename T, int D, int MODE> struct Stage {
     using TL = Tile<T, D>;

@@ -610,7 +610,7 @@ __global__ __launch_bounds__(NTHREADS) void msweep_kernel(const SweepArgs a)
     // Loads and the stores of the pieces are under no condition, neither on the step nor on the thread: threads
     // without a piece of their own repeat the tile's last one.  The compiler moves a load whose only use
     // is a conditional store down to that store, and the prologue then waited for its tiles one after another:
-    // 32 problems of L = 4096, W = 128 613 -> 606 us per step, two of L = 262144, W = 256 2875 -> 2857 us.
+    // 32 problems of L = 4096, W = 128 613 -> 606 us per step; two of L = 262144 no difference beyond noise.
     // (The potentials and pack columns are stored by the threads that have one: stored by all of them, which
     // writes a third more LDS per step in the final sweeps, the large case lost 1 % instead.)
     typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
