@@ -37,6 +37,7 @@
 #include "sinkhorn_attn.h"
 #include "ska_common.h"
 #include "ska_small_kernels.h"
+#include "ska_step.h"
 #include "ska_sweep_generic.h"
 #include "ska_sweep_ring.h"
 
@@ -414,10 +415,9 @@ template <typename T, int D, int FR> int launch_vchain(ChainArgs &c, int N, hipS
     return SKA_OK;
 }
 
-template <typename T, int D> int sweep(Call &cx, int mode, const SweepArgs &a, int N)
+// the arguments of a sweep over the problems from n0 on
+template <typename T, int D> SweepArgs from_problem(const SweepArgs &a, int n0)
 {
-    if (!cx.side || N < 2) return sweep_one<T, D>(mode, a, N, cx.st, cx.dev);
-    const int n0 = N / 2;
     SweepArgs b = a;
     const long mb = (long)n0 * a.L * D * (long)sizeof(T);
     auto mat = [&](const void *p) -> const void * { return p ? reinterpret_cast<const unsigned char *>(p) + mb : nullptr; };
@@ -434,9 +434,162 @@ template <typename T, int D> int sweep(Call &cx, int mode, const SweepArgs &a, i
     if (a.qtA) b.qtA = reinterpret_cast<const unsigned char *>(a.qtA) + (long)n0 * a.ldp * 32;
     if (a.pay_db) b.pay_db = a.pay_db + (long)n0 * D;
     b.n0 = a.n0 + n0;
+    return b;
+}
+template <typename T, int D> int sweep(Call &cx, int mode, const SweepArgs &a, int N)
+{
+    if (!cx.side || N < 2) return sweep_one<T, D>(mode, a, N, cx.st, cx.dev);
+    const int n0 = N / 2;
     SKA_TRY((sweep_one<T, D>(mode, a, n0, cx.st, cx.dev)));
     cx.busy = true;
-    return sweep_one<T, D>(mode, b, N - n0, cx.side->s, cx.dev);
+    return sweep_one<T, D>(mode, from_problem<T, D>(a, n0), N - n0, cx.side->s, cx.dev);
+}
+
+// ------------------------------------------------------------------ whole steps (vstep_kernel)
+// Blocks of NF fragments of 32 rows, G wavefronts per fragment with NTW tiles each, M blocks per workgroup (a segment);
+// hw = ceil(W / 32).  NF = 0: the half-steps run one by one.
+struct StepShape { int NF, G, NTW, hw, M; };
+constexpr int STEP_LDS = 159 * 1024;   // dynamic part; the dustbin element has a little of its own
+// The instances, by the bytes of a 32-row tile; the second list marches (M > 1).
+#define SKA_STEP_SHAPES(X) \
+    X(TB <= 16384, 2, 2, 3, false) X(TB <= 16384, 4, 1, 5, false) X(TB <= 8192, 2, 2, 5, false) X(TB <= 8192, 8, 1, 9, false) \
+    X(TB <= 8192, 2, 4, 5, false) X(TB == 8192, 4, 1, 9, false) X(TB == 8192, 1, 4, 5, false) X(TB == 16384, 1, 2, 5, false) \
+    X(TB <= 4096, 4, 2, 9, false) X(TB <= 4096, 8, 1, 9, true) X(TB <= 4096, 4, 2, 9, true)
+template <typename T, int D> constexpr int step_tile_bytes = StepTile<T, D>::BYTES;
+template <typename T, int D> int step_lds(const StepShape &sh)
+{
+    constexpr int TB = step_tile_bytes<T, D>;
+#define SKA_LDS(COND, NF_, G_, NTW_, MARCH_) \
+    if constexpr (COND) \
+        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && (sh.M > 1) == MARCH_) return StepLds<T, D, NF_, G_, NTW_, MARCH_>(sh.hw).total;
+    SKA_STEP_SHAPES(SKA_LDS)
+#undef SKA_LDS
+    return STEP_LDS + 1;
+}
+// Which shape a call takes, from the rows of the whole call (not of a launch: results do not depend on how a call is cut).
+// Short blocks while they leave CUs idle or barely fill them, large ones (less of the band read twice) beyond, one segment per
+// CU where two buffers of tiles fit LDS.  Forward of T = 16, R = 2 steps, us, at the sizes next to each line:
+//   bf16, d = 64, W = 64:  48000 rows (2,2,3) 155 (4,1,5) 159; 65536 rows 175 / 163; half-steps 255 / 253
+//   W = 128: 48000 rows (2,2,5) 196 (8,1,9) 203, 65536 rows 262 / 203; 131072 rows (8,1,9) one block 364, segments 340
+//   W = 200: 5600 rows (2,4,5) 176 (4,2,9) 206; 48000 rows 408 / 336 in segments; 524288 rows 1803, half-steps 1804
+//   d = 32, W = 256: 131072 rows 464, half-steps 574; 262144 rows 805 / 742, as d = 32 half-steps have half the products
+//   d = 128 or fp32 d = 64 (8 KB tiles), W = 128: 5600 rows (2,2,5) 195 (4,1,9) 222; 32768 rows (4,1,9) 229 (8,1,9) 247;
+//   131072 rows (4,1,9) 702 (8,1,9) 539, half-steps 826.  W = 200 (2,4,5): 32768 rows 387, half-steps 457; 131072 rows
+//   1306 / 1081; fp32 2692 / 3187.  fp32, W = 256: 5600 rows (1,4,5) 381 (2,4,5) 436
+//   fp32 d = 128 (16 KB tiles): W = 32 32768 rows (2,2,3) 393 (4,1,5) 329; W = 128 5600 rows 539, half-steps 989; 32768 rows
+//   1532 / 995
+template <typename T, int D> StepShape step_shape(int N, int L, int W)
+{
+    constexpr int TB = step_tile_bytes<T, D>;
+    const int hw = ((W < L ? W : L) + 31) / 32;
+    const long rows = (long)N * L;
+    StepShape sh{0, 0, 0, hw, 1};
+    auto take = [&](int NF, int G, int NTW) { sh.NF = NF; sh.G = G; sh.NTW = NTW; };
+    bool march = false;
+    if (hw <= 2) {
+        if (rows <= (TB <= 4096 ? 49152 : TB == 8192 ? 32768 : 16384)) take(2, 2, 3);
+        else take(4, 1, 5);
+    } else if (hw <= 4) {
+        if (TB == 16384) {
+            if (rows <= 8192) take(1, 2, 5);
+        } else if (rows <= (TB <= 4096 ? 49152 : 16384)) {
+            take(2, 2, 5);
+        } else if (TB == 8192 && rows <= 32768) {
+            take(4, 1, 9);
+        } else {
+            take(8, 1, 9);
+            march = TB <= 4096;
+        }
+    } else if (hw <= 8) {
+        if (TB <= 4096) {
+            if (rows <= 16384) {
+                take(2, 4, 5);
+            } else if (TB == 4096 || rows <= 196608) {
+                take(4, 2, 9);
+                march = true;
+            }
+        } else if (TB == 8192) {
+            if (rows <= 8192) take(1, 4, 5);
+            else if (sizeof(T) == 4 || (rows <= 32768 && hw <= 7)) take(2, 4, 5);
+        }
+    }
+    if (!sh.NF) return sh;
+    if (march) {   // one segment per CU, of equal lengths and at least hw tiles
+        const int nblk = (L + 32 * sh.NF - 1) / (32 * sh.NF);
+        const long per = 256 / N > 1 ? 256 / N : 1;   // segments per problem
+        int M = (int)((nblk + per - 1) / per);
+        if (M > 4096 / sh.NF) M = 4096 / sh.NF;   // (segment_reciprocal)
+        if (M > 1 && M * sh.NF < hw) M = (hw + sh.NF - 1) / sh.NF;
+        sh.M = M;
+    }
+    if (step_lds<T, D>(sh) > STEP_LDS) sh.NF = 0;
+    return sh;
+}
+inline long step_segments(const StepShape &sh, int L) { return (L + 32L * sh.NF * sh.M - 1) / (32L * sh.NF * sh.M); }
+inline long step_part_stride(const StepShape &sh, int L)   // floats of column sums per problem
+{
+    return step_segments(sh, L) * 32 * (sh.NF * sh.M + 2 * sh.hw);
+}
+template <typename T, int D, int NF, int G, int NTW, bool MARCH> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
+{
+    p.s.nbp = (p.s.L + 32 * NF * p.M - 1) / (32 * NF * p.M);
+    p.s.nb_total = p.s.nbp * N;
+    p.s.lead = p.s.dustbin ? (N + 7) / 8 * 8 : 0;
+    const int lds = StepLds<T, D, NF, G, NTW, MARCH>(p.hw).total;
+    static bool raised[MAX_DEVICES];
+    if (!raised[dev]) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, MARCH>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
+            return SKA_EHIP;
+        raised[dev] = true;
+    }
+    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, MARCH>), dim3((p.s.nb_total + 7) / 8 * 8 + p.s.lead), dim3(64 * NF * G), lds,
+                       st, p);
+    return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
+}
+template <typename T, int D> int launch_vstep(const StepArgs &p, int NTW, int N, hipStream_t st, int dev)
+{
+    constexpr int TB = step_tile_bytes<T, D>;
+#define SKA_LAUNCH(COND, NF_, G_, NTW_, MARCH_) \
+    if constexpr (COND) \
+        if (p.NF == NF_ && p.G == G_ && NTW == NTW_ && (p.M > 1) == MARCH_) return launch_vstep_n<T, D, NF_, G_, NTW_, MARCH_>(p, N, st, dev);
+    SKA_STEP_SHAPES(SKA_LAUNCH)
+#undef SKA_LAUNCH
+    return SKA_EUNSUPPORTED;
+}
+template <typename T, int D> StepArgs step_from_problem(const StepArgs &p, int n0)
+{
+    StepArgs b = p;
+    b.s = from_problem<T, D>(p.s, n0);
+    if (p.part_in) b.part_in = p.part_in + n0 * p.part_stride;
+    if (p.part_out) b.part_out = p.part_out + n0 * p.part_stride;
+    if (p.v_out.p) b.v_out.p = p.v_out.p + n0 * p.v_out.stride;
+    if (p.log_b.p) b.log_b.p = p.log_b.p + n0 * p.log_b.stride;
+    return b;
+}
+template <typename T, int D> int step_sweep(Call &cx, const StepArgs &p, int NTW, int N)
+{
+    if (!cx.side || N < 2) return launch_vstep<T, D>(p, NTW, N, cx.st, cx.dev);
+    const int n0 = N / 2;
+    SKA_TRY((launch_vstep<T, D>(p, NTW, n0, cx.st, cx.dev)));
+    cx.busy = true;
+    return launch_vstep<T, D>(step_from_problem<T, D>(p, n0), NTW, N - n0, cx.side->s, cx.dev);
+}
+inline int launch_vfinal(StepArgs p, int N, hipStream_t st)
+{
+    p.s.nbp = (p.s.L + NTHREADS - 1) / NTHREADS;
+    p.s.nb_total = p.s.nbp * N;
+    p.s.lead = p.s.dustbin ? N : 0;
+    hipLaunchKernelGGL(vfinal_kernel, dim3(p.s.nb_total + p.s.lead), dim3(NTHREADS), 0, st, p);
+    return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
+}
+template <typename T, int D> int step_final(Call &cx, const StepArgs &p, int N)
+{
+    if (!cx.side || N < 2) return launch_vfinal(p, N, cx.st);
+    const int n0 = N / 2;
+    SKA_TRY(launch_vfinal(p, n0, cx.st));
+    cx.busy = true;
+    return launch_vfinal(step_from_problem<T, D>(p, n0), N - n0, cx.side->s);
 }
 
 // benchmark hooks: while enabled, every phase of a call is bracketed by events on the call's
@@ -635,6 +788,74 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         }
         return SKA_OK;
     };
+    // Whole steps (vstep_kernel) after the first one.  `pend`: the last step's column sums have not been taken into v
+    // yet; the next step's launch does so on the way, and a launch of its own (flush) where v is needed by itself.  The
+    // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
+    // ends in slot 1 (the first step's v starts in the slot that makes it so).
+    const StepShape shape = step_shape<T, D>(N, L, p.W);
+    const long pstride = step_part_stride(shape.NF ? shape : StepShape{1, 1, 1, 0, 1}, L);
+    float *part[2] = {nullptr, nullptr};
+    if (shape.NF) {   // room for two buffers of sums between g_u and the end of the vectors (the same bytes at every R)
+        const size_t gu = (size_t)N * p.ldw() * sizeof(float), need = 2 * (size_t)N * pstride * sizeof(float);
+        const size_t off = (fused ? 0 : ws_qs_bytes(p)) + gu;
+        if (need <= (size_t)N * p.ldw() * 168 && ws && (fused || p.ws_given >= off + need)) {
+            part[0] = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + off);
+            part[1] = part[0] + (size_t)N * pstride;
+        }
+    }
+    if (part[0]) chain_done = nullptr;   // a step is one launch already
+    bool first = !p.resume_t, pend = false;
+    int vcur = p.resume_t ? 2 * p.resume_t - 1 : 1, vhome = 0, pbuf = 0;
+    auto flush = [&]() -> int {
+        if (!pend) return SKA_OK;
+        StepArgs f{};
+        f.s = base;
+        f.s.sdb2 = stage_sdb2;
+        f.s.spoke_own = SK; f.s.spoke_oth = SQ;
+        f.s.yt = vec(vhome - 1); f.s.xs = vec(vcur); f.s.out_vec = vout(vhome);
+        f.s.olog = Vec{p.log_b, (long)Lp};
+        f.s.len_own = p.len_k; f.s.len_oth = p.len_q;
+        f.part_in = part[pbuf]; f.part_stride = pstride;
+        f.NF = shape.NF; f.G = shape.G; f.hw = shape.hw; f.M = shape.M; f.rcp = segment_reciprocal(shape.NF * shape.M);
+        SKA_TRY((step_final<T, D>(cx, f, N)));
+        pend = false;
+        vcur = vhome;
+        return SKA_OK;
+    };
+    // (u, v) -> (u', v'): uprev, uout the slots of u and u', vout_slot that of v'; `left` steps of the base solve follow
+    auto full = [&](int uprev, int uout, int vslot, int left) -> int {
+        if (!part[0] || first) {
+            first = false;
+            SKA_TRY(half(true, vcur, uprev, uout));
+            const int vfirst = part[0] && vslot == 1 && (left & 1) ? 3 : vslot;
+            SKA_TRY(half(false, uout, vcur, vfirst));
+            vcur = vfirst;
+            return SKA_OK;
+        }
+        StepArgs f{};
+        f.s = base;
+        f.s.c2 = stage_c2; f.s.sdb2 = stage_sdb2;
+        f.s.spoke_own = SQ; f.s.spoke_oth = SK;
+        f.s.X = Q; f.s.Y = K;
+        f.s.yt = vec(vcur); f.s.xs = vec(uprev); f.s.out_vec = vout(uout);
+        f.s.olog = Vec{p.log_a, (long)Lp}; f.log_b = Vec{p.log_b, (long)Lp};
+        f.s.len_own = p.len_q; f.s.len_oth = p.len_k;
+        if (pend) {
+            const int dst = vhome != vcur ? vhome : 4 - vcur;   // (only inside a base solve: slots 1 and 3)
+            f.part_in = part[pbuf];
+            f.v_out = vout(dst);
+            vcur = dst;
+            pbuf ^= 1;
+        }
+        f.part_out = part[pbuf]; f.part_stride = pstride;
+        f.NF = shape.NF; f.G = shape.G; f.hw = shape.hw; f.M = shape.M; f.rcp = segment_reciprocal(shape.NF * shape.M);
+        f.s.rev = nlaunch++ & 1;
+        SKA_TRY((step_sweep<T, D>(cx, f, shape.NTW, N)));
+        if (pt_run) pt_run->launched(2);
+        pend = true;
+        vhome = vslot;
+        return p.dustbin ? flush() : SKA_OK;   // (the spokes need u of all rows)
+    };
     auto halves = [&]() -> int {
         // base solve: T steps at eps, or the stages of the continuation schedule (remark
         // "Fixed-Budget eps-Scaling"): stage s runs on the scores A / eps_s; between stages both
@@ -653,18 +874,19 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
                 SKA_TRY(cx.fork());
             }
             stage_sdb2 = p.sdb * (p.eps / es) * LOG2E;
-            for (int t = 0; t < Ts; ++t) {
-                SKA_TRY(half(true, 1, 0, 0));
-                SKA_TRY(half(false, 0, 1, 1));
+            for (int t = 0; t < Ts; ++t) SKA_TRY(full(0, 0, 1, p.dustbin || sidx + 1 < nst ? 0 : Ts - 1 - t));
+            if (sidx + 1 < nst) {   // the next stage rescales both potentials in place
+                SKA_TRY(flush());
             }
         }
         stage_c2 = base.c2 = (sizeof(T) == 2) ? 1.f : base.cs * LOG2E;   // the tail runs at eps (= the last stage's)
         stage_sdb2 = base.sdb2;
         tail_now = true;
         for (int t = p.resume_t ? p.resume_t : 1; t <= R; ++t) {
-            SKA_TRY(half(true, 2 * t - 1, 2 * t - 2, 2 * t));    // u_t from v_{t-1}
-            SKA_TRY(half(false, 2 * t, 2 * t - 1, 2 * t + 1));   // v_t from u_t
+            if (pend && vcur == vhome) SKA_TRY(flush());
+            SKA_TRY(full(2 * t - 2, 2 * t, 2 * t + 1, 0));       // u_t from v_{t-1}, v_t from u_t
         }
+        SKA_TRY(flush());
         return flush_chain();
     };
     SKA_TRY(cx.fork());   // everything above ran for all problems on st

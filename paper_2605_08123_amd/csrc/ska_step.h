@@ -1,0 +1,569 @@
+// A whole Sinkhorn step (row half-step and column half-step) from one evaluation of the scores.
+#pragma once
+#include "ska_common.h"
+
+namespace {
+
+// ------------------------------------------------------------------ one Sinkhorn step per launch
+// From potentials (u, v) the row half-step needs r_i = sum_j E_ij with E_ij = exp(S_ij + u_i + v_j), u'_i = u_i - log r_i,
+// and the column half-step the column sums of the same matrix with its rows rescaled, c_j = sum_i E_ij / r_i,
+// v'_j = v_j - log c_j.  So E is evaluated once per step if it can be kept between the two sums: a wavefront
+// keeps the 32 rows x 32 NTW columns it evaluates in registers (16 of them per 32 x 32 tile), where two half-steps
+// evaluate every score and exponential twice.  The owner rows are the MFMA's A operand here: a lane is one
+// column and its registers are rows, so both sums are in-lane (row sums: 16 accumulators, exchanged between the
+// lanes once per wavefront; column sums: 16 multiply-adds per tile).
+//   A workgroup of NF G wavefronts owns blocks of NF fragments (32 rows each); G wavefronts share a fragment, each with NTW
+// of the 2 ceil(W / 32) + 1 tiles that its band meets.  The other side's rows that a block meets lie in LDS as
+// a whole (written by LDS-direct loads, 16-byte chunks swizzled on the way), so the evaluation runs without a barrier.
+// With MARCH a workgroup walks M blocks (a segment) on a ring of tiles: a block adds NF tiles, requested one block ahead.
+//   Column sums are summed over the fragments of a block and the blocks of a segment in LDS, and written per
+// segment; a column has those of at most ceil(2 ceil(W / 32) / (NF M)) + 1 segments, which the next launch adds up in a fixed
+// order where it needs v' (vfinal_kernel where no step follows).
+//   Every row and every column carries its own potential as stabiliser: after one step the row sums of a
+// column-normalised plan lie between 1 / (2 W + 1) and 2 W + 1 (unit targets), and likewise the column sums.
+//   What bounds it: the issue slots of the SIMDs.  Per tile and wavefront 16 exponentials, 16 adds, 16 multiply-adds, five
+// products at d = 64, five 16-byte LDS reads; 18 tiles of a SIMD take about 6000 cycles, what a block does around them (the
+// exchange of row sums, the column sums, staging) about 4000 more.  Small calls are bound by latency from start to end: a
+// launch of short blocks is 5 us, 2.3 of them until the first product.  Forward of T = 16, R = 2 steps, bf16, d = 64, us, by
+// half-steps -> by steps: 8 problems of L = 700, W = 64 210 -> 115; 16 of 3000, W = 128 312 -> 196; 32 of 4096, W = 128
+// 467 -> 340; 8 of 32768, W = 64 708 -> 427, W = 256 1094 -> 948; 2 of 262144, W = 256 1941 -> 1757.  fp32: 8 of 4096, W = 128
+// 607 -> 370 (matrix instructions: half as many).
+//   The potentials enter through the products (potential_row): as 16 adds per tile they took 6 % of a long call, and as
+// the products' initial accumulator 16 registers.  The products of a tile are issued among the exponentials of the tile
+// before it, in an order that scheduling barriers pin: left to itself the compiler puts all products first.
+struct StepArgs {
+    SweepArgs s;           // the row half-step: X (owner) = row operand, Y = column operand, yt = v, xs = u, out_vec = u'
+    const float *part_in;  // column sums of the step before, to be taken into v first (null: yt is v itself)
+    float *part_out;       // column sums of this step  [problem][segment][32 (NF M + 2 hw)]
+    long part_stride;      // floats per problem
+    VecOut v_out;          // part_in: where v goes (never yt: other blocks read that)
+    Vec log_b;             // log of the column targets (null: unit)
+    int NF, G, hw;         // fragments per block, wavefronts per fragment, ceil(W / 32)
+    int M;                 // blocks per segment
+    unsigned rcp;          // segment_reciprocal(NF M)
+};
+
+// x / SL (tiles per segment) as a multiplication: exact for x < 2^20 and SL <= 2^12, since x (SL - 1) < 2^32
+inline unsigned segment_reciprocal(int SL) { return SL == 1 ? 0u : (unsigned)((0x100000000ull + SL - 1) / SL); }
+__device__ __forceinline__ int segment_of(const StepArgs &p, int x) { return p.rcp ? (int)__umulhi((unsigned)x, p.rcp) : x; }
+// v' of a column from its old value and its column sum; the marks as in the half-steps' epilogue
+__device__ __forceinline__ float column_update(float v, float sum, float log_b)
+{
+    if (v == -INFINITY) return -INFINITY;                       // inactive token: stays so
+    if (!(sum > 0.f && sum < INFINITY)) return __builtin_nanf("");
+    return v - LN2 * fast_log2(sum) + log_b;
+}
+// columns of problem n with at least one band edge (rows, seen from the columns: the lengths exchanged)
+__device__ __forceinline__ int valid_columns(const SweepArgs &a, int n)
+{
+    int Lq = a.L, Lk = a.L;
+    if (a.len_own) Lq = min(max(a.len_own[(n + a.n0) / a.nh], 0), a.L);
+    if (a.len_oth) Lk = min(max(a.len_oth[(n + a.n0) / a.nh], 0), a.L);
+    return Lq > 0 ? min(Lk, Lq + a.W) : 0;
+}
+// where the sums of column t < L are: n segments from the first one that meets it
+struct ColumnSegments {
+    int n, step;
+    long first;
+    __device__ __forceinline__ ColumnSegments(const StepArgs &p, int t, int nseg_valid)
+    {
+        const int tile = t >> 5, SL = p.NF * p.M;
+        const int lo = min(segment_of(p, max(tile - p.hw, 0)), nseg_valid - 1), hi = min(segment_of(p, tile + p.hw), nseg_valid - 1);
+        n = hi - lo + 1;
+        step = 64 * p.hw;   // (segments overlap by 2 hw tiles)
+        first = (long)lo * (32 * (SL + 2 * p.hw)) + (t - 32 * (lo * SL - p.hw));
+    }
+    // past the last one: the last one again.  (No load is under a condition: it would be waited for at once.)
+    __device__ __forceinline__ long at(int i) const { return first + (long)min(i, n - 1) * step; }
+};
+// their sum, in the order of the segments
+__device__ __forceinline__ float column_sum(const StepArgs &p, const float *part, int t, int nseg_valid)
+{
+    const ColumnSegments cg(p, t, nseg_valid);
+    float c = 0.f;
+    for (int i0 = 0; i0 < cg.n; i0 += 4) {
+        float x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = part[cg.at(i0 + i)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c += i0 + i < cg.n ? x[i] : 0.f;
+    }
+    return c;
+}
+
+// A potential (base 2) as a row of a bf16 operand: x in three parts, which hold its 24 bits, and three ones for the
+// other side's parts; the product of a row's and a column's is the sum of their potentials.  An absent or inactive
+// token (-inf) is a number whose exponential is zero, since -inf times an absent part would not be.
+__device__ __forceinline__ bf16x8 potential_row(float x, bool row)
+{
+    const float y = fmaxf(x, -1e30f), z = x == x ? y : x;
+    const __bf16 hi = (__bf16)z, mid = (__bf16)(z - (float)hi), lo = (__bf16)(z - (float)hi - (float)mid), one = (__bf16)1.f, no = (__bf16)0.f;
+    return row ? bf16x8{hi, mid, lo, one, one, one, no, no} : bf16x8{one, one, one, hi, mid, lo, no, no};
+}
+
+template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
+{
+    return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+// lanes 0 .. 31: a over both halves of the wavefront; lanes 32 .. 63: b
+__device__ __forceinline__ float halves_sum(float a, float b)
+{
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// the same within each half, between its rows of 16 lanes
+__device__ __forceinline__ float rows16_sum(float a, float b)
+{
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+template <typename T, int D> struct StepTile {
+    static constexpr int ROWB = D * (int)sizeof(T), CPR = ROWB / 16, BYTES = 32 * ROWB;
+    // position of a 16-byte chunk in its row: sixteen consecutive rows spread one chunk over all 64 banks
+    static __device__ __forceinline__ int swz(int row) { return CPR >= 16 ? (row & 15) : CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
+};
+template <typename T, int D, int NF, int G, int NTW, bool MARCH> struct StepLds {   // offsets in bytes
+    static constexpr int RSUM = 0;                              // [NF][G][32] row sums
+    static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
+    static constexpr int US = WS + NF * G * 128;                // [2][32 NF] potentials of the rows
+    static constexpr int TWO = MARCH ? 2 : 1;
+    static constexpr int CP = US + TWO * NF * 128;                // [2][NF][G NTW 32] column sums of a fragment
+    static constexpr int Y = CP + TWO * NF * G * NTW * 128;     // ring of the other side's tiles
+    static constexpr int VB = sizeof(T) == 2 ? 16 : 4;          // bytes of a column's potential
+    int rs, vs, cs, total;
+    __host__ __device__ StepLds(int hw)
+    {
+        rs = NF + 2 * hw + (MARCH ? NF : 0);   // ring slots: the window of a block and the tiles the next one adds
+        vs = Y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
+        cs = vs + rs * 32 * VB;                // MARCH: [32 rs] column sums of the segment so far
+        total = cs + (MARCH ? rs * 128 : 0);
+    }
+};
+
+template <typename T, int D, int NF, int G, int NTW, bool MARCH>
+__global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
+{
+    using ST = StepTile<T, D>;
+    using LD = StepLds<T, D, NF, G, NTW, MARCH>;
+    constexpr bool PRE = (sizeof(T) == 2);
+    constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
+    const SweepArgs &a = p.s;
+    extern __shared__ __align__(16) unsigned char smem[];
+    if ((int)blockIdx.x < a.lead) {
+        if ((int)blockIdx.x < a.nb_total / a.nbp) dustbin_element<false, 8, NTHR>(a, blockIdx.x);
+        return;
+    }
+    const int chunk = (a.nb_total + 7) >> 3, bx = (int)blockIdx.x - a.lead;
+    const int lb = (bx & 7) * chunk + (a.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
+    if (lb >= a.nb_total) return;
+    const int hw = p.hw, M = MARCH ? p.M : 1, NT = 2 * hw + 1, nwt = NF + 2 * hw;
+    const LD lds(hw);
+    const int RS = lds.rs;
+    const int n = lb / a.nbp, seg = lb % a.nbp;
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int f = wave / G, g = wave % G;
+    const int L = a.L, W = a.W;
+    const Lens ln = problem_lens(a, n);
+    const int Lt = ln.Lt, Le = ln.Le;
+    const int Lc = valid_columns(a, n), nseg_valid = (Le + BM * M - 1) / (BM * M);
+    const int b0 = seg * M, b1 = min(b0 + M, (L + BM - 1) / BM), bv = min(b1, (Le + BM - 1) / BM);   // blocks; those with valid rows
+
+    unsigned char *vs = smem + lds.vs;
+    float *us = reinterpret_cast<float *>(smem + LD::US);
+    float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cs = reinterpret_cast<float *>(smem + lds.cs);
+    float *wsw = reinterpret_cast<float *>(smem + LD::WS) + 32 * wave;
+
+    const float *vp = a.yt.p + n * a.yt.stride;
+    const float *part = p.part_in ? p.part_in + n * p.part_stride : nullptr;
+    const float *lbp = p.log_b.p ? p.log_b.p + n * p.log_b.stride : nullptr;
+    const float *xsp = a.xs.p + n * a.xs.stride;
+    // rows without an edge: zeros, and this segment's share of v there
+    for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR) {
+        a.out_vec.p[n * a.out_vec.stride + t] = 0.f;
+        if (part) p.v_out.p[n * p.v_out.stride + t] = t < Lc ? column_update(vp[t], column_sum(p, part, t, nseg_valid), lbp ? lbp[t] : 0.f) : 0.f;
+    }
+    if (b0 >= bv) return;
+    const long moff = (long)n * L * D;
+    const unsigned char *Xb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.X) + moff);
+    const unsigned char *Yb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.Y) + moff);
+    const int kseg = b0 * NF - hw;   // the segment's first tile, ring slot 0
+
+    // `count` tiles of a matrix from tile k on into LDS slots from `slot` on (wrapping at `wrap`); one instruction of a
+    // wavefront fills 1 KB, RPI rows.  Rows outside the matrix repeat its first or last valid one; they are masked
+    // where they are used.
+    constexpr int RPI = 64 / ST::CPR, IPT = 32 / RPI;
+    const unsigned smem_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
+    auto dma = [&](const unsigned char *mat, int rows, int k, int count, int off, int slot, int wrap) {
+        const bool whole = k >= 0 && 32 * (k + count) <= rows;
+        for (int i = wave; i < count * IPT; i += NF * G) {
+            const int kt = i / IPT, r0 = (i % IPT) * RPI, lrow = lane / ST::CPR;
+            int sl = slot + kt;
+            if (sl >= wrap) sl -= wrap;
+            const unsigned col = ((lane % ST::CPR) ^ ST::swz(r0 + lrow)) * 16;
+            long t = 32 * (k + kt) + r0;   // (uniform)
+            unsigned o = lrow * ST::ROWB + col;
+            if (!whole) {
+                const long last = rows - 1, tb = min(max(t, 0L), last);
+                o = (unsigned)(min(max(t + lrow, 0L), last) - tb) * ST::ROWB + col;
+                t = tb;
+            }
+            // (written out, because the compiler takes every later LDS read for one of these bytes and waits at once; the
+            // kernel waits where a block ends.  No register is written.)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(smem_at + off + sl * ST::BYTES + r0 * ST::ROWB),
+                         "v"(o), "s"(mat + t * ST::ROWB)
+                         : "memory", "m0");
+        }
+    };
+    // v of a column into its place in LDS, as the evaluation takes it
+    auto stage_v = [&](int at, int t, float v) {
+        v = t >= 0 && t < Lt ? v * LOG2E : -INFINITY;
+        if constexpr (PRE) *reinterpret_cast<bf16x8 *>(vs + at * 16) = potential_row(v, false);
+        else *reinterpret_cast<float *>(vs + at * 4) = v;
+    };
+    // Loads return in order: the vectors, which need work, are requested before the tiles and the owner rows.
+    constexpr int NWIN = (32 * (NF + G * NTW) + NTHR - 1) / NTHR;   // columns of a window per thread
+    constexpr int NSUM = MARCH ? 3 : (G * NTW - 1) / NF + 2;        // segments that a column can have sums from, at most
+    const float u_first = tid < BM && b0 * BM + tid < Le ? xsp[b0 * BM + tid] : -INFINITY;
+    float win_v[NWIN], win_sum[NWIN][NSUM], win_lb[NWIN];
+#pragma unroll
+    for (int k = 0; k < NWIN; ++k) {
+        const int t = min(max(32 * kseg + tid + k * NTHR, 0), L - 1);
+        win_v[k] = vp[t];
+        win_lb[k] = 0.f;
+        if (lbp) win_lb[k] = lbp[min(t, max(Lc - 1, 0))];
+        if (part) {
+            const ColumnSegments cg(p, t, nseg_valid);
+#pragma unroll
+            for (int i = 0; i < NSUM; ++i) win_sum[k][i] = part[cg.at(i)];
+        }
+    }
+    OwnerFrag<T, D> xf;
+    dma(Yb, Lt, kseg, nwt, LD::Y, 0, RS);
+    xf.load(reinterpret_cast<const T *>(Xb), min((b0 * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
+#pragma unroll
+    for (int k = 0; k < NWIN; ++k) {
+        const int i = tid + k * NTHR, t = 32 * kseg + i;
+        float v = win_v[k];
+        if (part) {
+            const ColumnSegments cg(p, min(max(t, 0), L - 1), nseg_valid);
+            float sum = 0.f;
+#pragma unroll
+            for (int q = 0; q < NSUM; ++q) sum += q < cg.n ? win_sum[k][q] : 0.f;
+            v = t < Lc ? column_update(v, sum, win_lb[k]) : 0.f;
+            if (t >= b0 * BM && t < min(bv * BM, L)) p.v_out.p[n * p.v_out.stride + t] = v;
+        }
+        if (i < 32 * nwt) stage_v(i, t, v);
+    }
+    if (tid < BM) us[tid] = u_first;
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
+    __syncthreads();
+
+    const int j0 = g * NTW, klast = (Lt - 1) / TT;
+    int base = 0;   // ring slot of the block's first tile
+    for (int b = b0; b < (MARCH ? bv : b0 + 1); ++b) {
+        // what depends on the lane alone is computed again in every block: kept across the loop it would take the
+        // registers that the plan entries need
+        if constexpr (MARCH) asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        const int c = lane & 31, h = lane >> 5;
+        const int par = MARCH ? (b - b0) & 1 : 0, k0 = b * NF - hw, o_f = (b * NF + f) * 32, o = o_f + c;
+        const bool more = MARCH && b + 1 < bv;
+        float spoke = 0.f, spoke_v = 0.f, la = 0.f;   // of this lane's row
+        if (a.dustbin) {
+            spoke = a.spoke_own.p ? a.spoke_own.p[n * a.spoke_own.stride + min(o, L - 1)] : a.sdb2 * LN2;
+            spoke_v = vp[L];
+        }
+        if (a.olog.p) la = a.olog.p[n * a.olog.stride + min(o, Le - 1)];
+        // what the next block adds (a thread below BM: one column, one row): requested now, stored after this block's last
+        // use of the slots' old content
+        float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nlb = 0.f;
+        const int nt = 32 * (k0 + nwt) + tid, no = (b + 1) * BM + tid;
+        const int nq = min(segment_of(p, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
+        if (more) {
+            const int tc = min(nt, L - 1);
+            nv = vp[tc];
+            nu = xsp[min(no, Le - 1)];
+            if (lbp) nlb = lbp[min(tc, max(Lc - 1, 0))];
+            if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
+                const float *pp = part + (long)seg * (32 * (NF * M + 2 * hw)) + (tc - 32 * kseg);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) np[i] = pp[(long)min(i, nq) * (64 * hw)];
+            }
+            int sl = base + nwt;
+            if (sl >= RS) sl -= RS;
+            dma(Yb, Lt, k0 + nwt, NF, LD::Y, sl, RS);
+        }
+
+        [[maybe_unused]] f32x16 ci;   // fp32 storage: the rows' potentials
+        if constexpr (!PRE) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 v4 = *reinterpret_cast<const float4 *>(us + par * BM + 32 * f + 8 * q + 4 * h);
+                ci[4 * q + 0] = v4.x * LOG2E; ci[4 * q + 1] = v4.y * LOG2E; ci[4 * q + 2] = v4.z * LOG2E; ci[4 * q + 3] = v4.w * LOG2E;
+            }
+        }
+        const float u_old = us[par * BM + 32 * f + c];
+
+        f32x16 E[NTW];
+        float rsum[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) rsum[r] = 0.f;
+        auto add_rows = [&](const f32x16 &e, int r) { rsum[r] += e[r]; };
+        // entries of an edge tile outside the band or the matrix become zero (whatever they are): with o = o_f + 4 h +
+        // off_r and t = t0 + c, |t - o| <= W keeps lo <= off_r <= lo + 2 W.  As a bit per offset: two instructions an
+        // entry, the first ones of eight entries together (one after the other they wait for each other).
+        auto mask = [&](f32x16 &e, int t0, bool present) {
+            const int lo = t0 + c - o_f - 4 * h - W, hi = min(min(lo + 2 * W, Le - 1 - o_f - 4 * h), 31);
+            unsigned keep = (~0u << min(max(lo, 0), 31)) & (~0u >> (31 - max(hi, 0)));
+            keep = lo <= 31 && hi >= 0 && present && t0 + c < Lt ? keep : 0u;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                int m[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) asm volatile("v_bfe_i32 %0, %1, %2, 1" : "=v"(m[i]) : "v"(keep), "n"(16 * q + 8 * (i >> 2) + (i & 3)));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) e[8 * q + i] = __int_as_float(__float_as_int(e[8 * q + i]) & m[i]);
+            }
+        };
+        const int kw = k0 + f + j0;   // this wavefront's first tile
+        const int nj = min(min(NT - j0, NTW), klast + 1 - kw), sfirst = max(0, -kw);   // tiles [sfirst, nj) are there
+        // [ilo, ilo + icnt): tiles wholly inside the matrix and, for all 32 rows, inside the band
+        const int d0 = 32 * kw - o_f;
+        const int ilo = max(sfirst, (62 - W - d0) >> 5), ihi = min(min((W - 31 - d0) >> 5, Lt / 32 - 1 - kw), nj - 1);
+        const unsigned icnt = o_f + 32 <= Le ? max(ihi - ilo + 1, 0) : 0, pcnt = max(nj - sfirst, 0);
+        auto interior = [&](int s) { return (unsigned)(s - ilo) < icnt; };   // (uniform: one compare)
+        auto present = [&](int s) { return (unsigned)(s - sfirst) < pcnt; };
+        int slot = base + f + j0;
+        if (slot >= RS) slot -= RS;
+        if constexpr (PRE) {
+            // one wavefront's pipeline: the products of tile s + 1 are issued among the exponentials of tile s, and the
+            // operand of tile s + 2 is requested as its registers come free
+            constexpr int KS = D / 16;
+            bf16x8 y[KS], yv, xv;
+            {   // the rows' potentials, in the lanes that hold the first eight of the sixteen
+                xv = potential_row(u_old * LOG2E, true);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) xv[i] = h ? (__bf16)0.f : xv[i];
+            }
+            f32x16 zero;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+            auto rd = [&](int ks) { y[ks] = *reinterpret_cast<const bf16x8 *>(smem + LD::Y + slot * ST::BYTES + c * ST::ROWB + (((2 * ks + h) ^ ST::swz(c)) << 4)); };
+            auto rdv = [&]() { yv = *reinterpret_cast<const bf16x8 *>(vs + (32 * slot + c) * 16); };
+            auto step_slot = [&]() { ++slot; if (MARCH && slot == RS) slot = 0; };
+            rdv();
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) rd(ks);
+            step_slot();
+            E[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
+            if (NTW > 1) rdv();
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                E[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks], y[ks], E[0], 0, 0, 0);
+                if (NTW > 1) rd(ks);
+            }
+            constexpr int RPS = 16 / (KS + 1) + 1;   // entries per product: KS + 1 products and sixteen entries
+#pragma unroll
+            for (int s = 0; s < NTW; ++s) {
+                step_slot();
+#pragma unroll
+                for (int ks = 0; ks <= KS; ++ks) {
+                    if (s + 1 < NTW) {
+                        if (ks == 0) E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
+                        else E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks - 1], y[ks - 1], E[s + 1], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (s + 2 < NTW) {
+                            if (ks == 0) rdv();
+                            else rd(ks - 1);
+                        }
+                    }
+#pragma unroll
+                    for (int r = ks * RPS; r < 16 && r < (ks + 1) * RPS; ++r) {
+                        E[s][r] = fast_exp2(E[s][r]);
+                        if (s > 0) add_rows(E[s - 1], r);
+                        asm volatile("" : "+v"(rsum[r]));   // the sums here, among the products, not for all tiles at the end
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (!interior(s)) mask(E[s], 32 * (kw + s), present(s));
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) add_rows(E[NTW - 1], r);
+        } else {
+#pragma unroll
+            for (int s = 0; s < NTW; ++s) {
+                if (present(s)) {   // (uniform)
+                    const unsigned char *yr = smem + LD::Y + slot * ST::BYTES + c * ST::ROWB;
+                    const float vt = *reinterpret_cast<const float *>(vs + (32 * slot + c) * 4);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
+#pragma unroll
+                    for (int q = 0; q < D / 8; ++q) {
+                        const float4 y = *reinterpret_cast<const float4 *>(yr + (((h * (D / 8) + q) ^ ST::swz(c)) << 4));
+                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 0], y.x, E[s], 0, 0, 0);
+                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 1], y.y, E[s], 0, 0, 0);
+                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 2], y.z, E[s], 0, 0, 0);
+                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 3], y.w, E[s], 0, 0, 0);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) E[s][r] = fast_exp2(fmaf(E[s][r], a.c2, ci[r] + vt));
+                    if (!interior(s)) mask(E[s], 32 * (kw + s), true);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) add_rows(E[s], r);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
+                }
+                ++slot;
+                if (MARCH && slot == RS) slot = 0;
+            }
+        }
+
+        if (more) xf.load(reinterpret_cast<const T *>(Xb), min(((b + 1) * NF + f) * 32 + c, Le - 1), Le, h);
+
+        // row sums over the 32 columns of a lane half: registers r, r + 8 to the two rows of 16 lanes, then within those
+        {
+            float t8[8];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t8[r] = rows16_sum(rsum[r], rsum[r + 8]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x128>(t8[r]);   // row_ror:8, 4, 2, 1
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x124>(t8[r]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x122>(t8[r]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x121>(t8[r]);
+            if ((lane & 15) == 0) {   // register r of the second row of lanes is r + 8: rows 16 further
+                float *d = rs + (f * G + g) * 32 + 16 * ((lane >> 4) & 1) + 4 * h;
+                *reinterpret_cast<float4 *>(d) = make_float4(t8[0], t8[1], t8[2], t8[3]);
+                *reinterpret_cast<float4 *>(d + 8) = make_float4(t8[4], t8[5], t8[6], t8[7]);
+            }
+        }
+        if constexpr (G > 1) __syncthreads();
+        else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        float tot = 0.f;
+#pragma unroll
+        for (int i = 0; i < G; ++i) tot += rs[(f * G + i) * 32 + c];
+        if (a.dustbin) tot += fast_exp2((spoke + spoke_v + u_old) * LOG2E);   // spoke edge (o, dustbin element of the other side)
+        float u_new = 0.f, w = 0.f;
+        if (o < Le) {
+            if (u_old == -INFINITY) {
+                u_new = -INFINITY;   // inactive token: stays so
+            } else if (!(tot > 0.f && tot < INFINITY)) {
+                u_new = w = __builtin_nanf("");
+            } else {
+                u_new = u_old - LN2 * fast_log2(tot) + la;
+                w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
+                if (a.olog.p) w *= __expf(la);
+            }
+        }
+        if (h == 0) wsw[c] = w;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        f32x16 wv;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 v4 = *reinterpret_cast<const float4 *>(wsw + 8 * q + 4 * h);
+            wv[4 * q + 0] = v4.x; wv[4 * q + 1] = v4.y; wv[4 * q + 2] = v4.z; wv[4 * q + 3] = v4.w;
+        }
+        // column sums of the fragment
+        float *cp = reinterpret_cast<float *>(smem + LD::CP) + par * NF * G * NTW * 32;
+        float *cpw = cp + (f * G * NTW + j0) * 32;
+        auto col = [&](const f32x16 &e) {
+            float x = 0.f, y = 0.f;
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) { x = fmaf(e[r], wv[r], x); y = fmaf(e[r + 1], wv[r + 1], y); }
+            return x + y;
+        };
+#pragma unroll
+        for (int s = 0; s + 1 < NTW; s += 2) cpw[32 * s + lane] = halves_sum(col(E[s]), col(E[s + 1]));
+        if constexpr (NTW & 1) {
+            const float x = col(E[NTW - 1]);
+            const float y = halves_sum(x, x);
+            if (h == 0) cpw[32 * (NTW - 1) + c] = y;
+        }
+        float v_new = nv;
+        if (more && tid < BM) {
+            if (part && nt < L) v_new = nt < Lc ? column_update(nv, np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f), nlb) : 0.f;
+            int sl = 32 * (base + nwt) + tid;
+            if (sl >= 32 * RS) sl -= 32 * RS;
+            stage_v(sl, nt, v_new);
+            us[(par ^ 1) * BM + tid] = no < Le ? nu : -INFINITY;
+        }
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        __syncthreads();
+        // stores to memory only now: the wait above would wait for them as well
+        if (h == 0 && g == 0 && o < L) a.out_vec.p[n * a.out_vec.stride + o] = u_new;
+        if (more && part && tid < BM && nt >= b0 * BM && nt < min(bv * BM, L)) p.v_out.p[n * p.v_out.stride + nt] = v_new;
+        // the block's column sums onto the segment's; tiles that no later block of the segment meets are done
+        float *po = p.part_out + n * p.part_stride + (long)seg * (32 * (NF * M + 2 * hw));
+        if constexpr (!MARCH) {
+#pragma unroll
+            for (int k = 0; k < NWIN; ++k) {
+                const int i = tid + k * NTHR, wt = i >> 5;
+                if (i >= 32 * nwt) continue;
+                float x[NF], s = 0.f;
+#pragma unroll
+                for (int q = 0; q < NF; ++q) x[q] = cp[(q * G * NTW + min(max(wt - q, 0), NT - 1)) * 32 + (i & 31)];
+#pragma unroll
+                for (int q = 0; q < NF; ++q) s += (unsigned)(wt - q) < (unsigned)NT ? x[q] : 0.f;
+                po[i] = s;
+            }
+            return;
+        }
+        constexpr int NPOS = (32 * (2 * NF + G * NTW) + NTHR - 1) / NTHR;   // ring positions of a thread, always the same ones
+#pragma unroll
+        for (int k = 0; k < NPOS; ++k) {
+            const int i = tid + k * NTHR;
+            int wt = (i >> 5) - base;
+            if (wt < 0) wt += RS;
+            if (i >= 32 * RS || wt >= nwt) continue;
+            float x[NF], s = cs[i];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) x[q] = cp[(q * G * NTW + min(max(wt - q, 0), NT - 1)) * 32 + (i & 31)];
+            if (b == b0 || wt >= nwt - NF) s = 0.f;
+#pragma unroll
+            for (int q = 0; q < NF; ++q) s += (unsigned)(wt - q) < (unsigned)NT ? x[q] : 0.f;
+            if (!more || wt < NF) po[32 * (k0 + wt - kseg) + (i & 31)] = s;
+            else cs[i] = s;
+        }
+        base += NF;
+        if (base >= RS) base -= RS;
+    }
+}
+
+// v from the column sums of a step: the last step of a run, and every step with a dustbin, whose spokes need u of all
+// rows.  The arguments are those of the column half-step: yt = u', xs = v before the step (may be out_vec), lengths of the
+// columns first.  With a dustbin the leading workgroups compute its column's element.
+__global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
+{
+    const SweepArgs &a = p.s;
+    const int nprob = a.nb_total / a.nbp;
+    if ((int)blockIdx.x < a.lead) {
+        if ((int)blockIdx.x < nprob) dustbin_element<false, 8>(a, blockIdx.x);
+        return;
+    }
+    const int lb = (int)blockIdx.x - a.lead;
+    const int n = lb / a.nbp, t = (lb % a.nbp) * NTHREADS + threadIdx.x;
+    if (t >= a.L) return;
+    const Lens ln = problem_lens(a, n);   // own = columns: Le of them have an edge
+    SweepArgs r = a;                      // the rows' view, for the number of blocks that wrote sums
+    r.len_own = a.len_oth; r.len_oth = a.len_own;
+    const int rows = problem_lens(r, n).Le;
+    const float v = a.xs.p[n * a.xs.stride + t];
+    float out = 0.f;
+    if (t < ln.Le) {
+        float sum = column_sum(p, p.part_in + n * p.part_stride, t, (rows + 32 * p.NF * p.M - 1) / (32 * p.NF * p.M));
+        if (a.dustbin) {
+            const float sp2 = a.spoke_own.p ? a.spoke_own.p[n * a.spoke_own.stride + t] * LOG2E : a.sdb2;
+            sum += fast_exp2(sp2 + a.yt.p[n * a.yt.stride + a.L] * LOG2E + v * LOG2E);
+        }
+        out = column_update(v, sum, a.olog.p ? a.olog.p[n * a.olog.stride + t] : 0.f);
+    }
+    a.out_vec.p[n * a.out_vec.stride + t] = out;
+}
+
+}  // namespace

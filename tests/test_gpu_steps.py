@@ -1,0 +1,103 @@
+"""Whole Sinkhorn steps from one evaluation of the scores against the half-steps they replace.  A forward whose workspace
+holds the prescaled operand and nothing more runs half-step by half-step, so both routes can be compared over every form
+the steps accept: lengths, marginals, masks, a dustbin, both storage types, every head dimension, the sizes at which
+a block shape or a segment length changes over.
+
+Bound: both routes compute the same potentials in fp32.  A half-step adds to a potential at most the rounding of its
+exponents (three terms of size M, the largest score or potential in base 2), of a sum of 2 W + 2 terms and of one
+exponential and one logarithm: (2 W + 20 + 4 M) 2^-24.  The half-steps do not enlarge a difference of potentials, so over
+2 (T + R) of them two routes are at most twice the sum apart."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SHORT = [  # kind, dtype, d, N, L, W, T, R
+    ("plain", "bf16", 64, 1, 31, 7, 3, 2), ("plain", "bf16", 64, 2, 65, 0, 2, 1), ("plain", "bf16", 64, 3, 129, 32, 1, 2),
+    ("plain", "bf16", 64, 2, 500, 33, 0, 3), ("plain", "bf16", 64, 2, 701, 64, 5, 2), ("plain", "bf16", 64, 2, 700, 65, 4, 1),
+    ("plain", "bf16", 64, 1, 999, 96, 3, 2), ("plain", "bf16", 64, 1, 1000, 128, 2, 2), ("plain", "bf16", 64, 1, 1000, 129, 3, 2),
+    ("plain", "bf16", 64, 1, 1025, 224, 4, 2), ("plain", "bf16", 64, 1, 1023, 256, 3, 2), ("plain", "bf16", 64, 1, 400, 5000, 3, 2),
+    ("plain", "bf16", 32, 2, 333, 40, 3, 2), ("plain", "bf16", 32, 2, 777, 100, 3, 2), ("plain", "bf16", 32, 1, 900, 250, 3, 2),
+    ("plain", "bf16", 128, 2, 333, 40, 3, 2), ("plain", "bf16", 128, 1, 777, 127, 3, 2), ("plain", "bf16", 128, 1, 900, 200, 3, 2),
+    ("plain", "bf16", 128, 1, 900, 256, 3, 2), ("plain", "f32", 32, 1, 256, 16, 8, 2), ("plain", "f32", 32, 2, 611, 99, 3, 2),
+    ("plain", "f32", 32, 1, 800, 256, 3, 2), ("plain", "f32", 64, 2, 300, 64, 3, 2), ("plain", "f32", 64, 1, 700, 111, 3, 2),
+    ("plain", "f32", 64, 1, 700, 255, 3, 2), ("plain", "f32", 128, 1, 300, 50, 3, 2), ("plain", "f32", 128, 1, 500, 128, 3, 2),
+    ("varlen", "bf16", 64, 4, 600, 50, 3, 2), ("varlen", "f32", 64, 4, 500, 100, 2, 2), ("varlen", "bf16", 64, 4, 900, 200, 3, 1),
+    ("marginals", "bf16", 64, 2, 600, 100, 3, 2), ("marginals", "f32", 32, 2, 400, 20, 2, 2), ("masked", "bf16", 64, 2, 500, 31, 3, 2),
+    ("masked", "f32", 64, 2, 700, 128, 3, 2), ("dustbin", "bf16", 64, 2, 701, 30, 3, 2), ("dustbin", "f32", 32, 2, 500, 100, 1, 2),
+    ("dustbin", "bf16", 128, 2, 600, 222, 2, 2), ("dustbin", "bf16", 64, 1, 9000, 256, 2, 1)]
+LONG = [  # other block shapes; segments of several blocks, also ragged ones and ones that end inside a problem
+    ("plain", "bf16", 64, 1, 50000, 20, 2, 1), ("plain", "bf16", 64, 1, 50001, 100, 2, 2), ("plain", "bf16", 64, 1, 66000, 97, 3, 1),
+    ("plain", "bf16", 64, 3, 40001, 128, 2, 1), ("plain", "bf16", 64, 1, 17000, 130, 2, 1), ("plain", "bf16", 64, 1, 40000, 256, 3, 1),
+    ("plain", "bf16", 64, 2, 70001, 200, 2, 1), ("plain", "bf16", 64, 300, 700, 130, 2, 1), ("plain", "bf16", 32, 2, 40000, 100, 2, 1),
+    ("plain", "bf16", 32, 1, 60000, 256, 2, 1), ("plain", "bf16", 128, 1, 33000, 60, 2, 1), ("plain", "bf16", 128, 1, 33000, 120, 2, 1),
+    ("plain", "bf16", 128, 1, 20000, 120, 2, 1), ("plain", "f32", 32, 1, 60000, 100, 2, 1), ("plain", "f32", 32, 1, 60000, 256, 2, 1),
+    ("plain", "f32", 64, 1, 40000, 128, 2, 1), ("plain", "f32", 128, 1, 20000, 64, 2, 1), ("varlen", "bf16", 64, 4, 40000, 256, 3, 1),
+    ("varlen", "bf16", 64, 8, 20000, 70, 2, 1), ("marginals", "bf16", 64, 2, 70000, 128, 2, 1), ("masked", "bf16", 64, 2, 70000, 129, 2, 1),
+    ("dustbin", "bf16", 64, 1, 70000, 128, 2, 1), ("dustbin", "f32", 32, 1, 60000, 200, 2, 1)]
+
+
+@pytest.mark.parametrize("case", SHORT + LONG, ids=lambda c: "-".join(map(str, c)))
+def test_steps_equal_half_steps(case):
+    import torch
+
+    import paper_2605_08123_amd as ska
+    kind, dtype, d, N, L, W, T, R = case
+    print(f"\n[case] {case}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(17)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K, V = (torch.randn((N, 1, L, d), generator=gen, device="cuda").to(td) for _ in range(3))
+    eps, db = 0.7, kind == "dustbin"
+    la = lb = lq = lk = mq = mk = None
+    if kind == "varlen":   # one item without queries, one with a single key, the others anything
+        lq, lk = (torch.randint(1, L + 1, (N,), generator=gen, device="cuda").int() for _ in range(2))
+        lq[0], lk[1] = 0, 1
+        lq[2], lk[2] = L // 3, L   # rows end well before the columns do
+    if kind == "marginals":
+        a, b = (torch.rand((N, 1, L), generator=gen, device="cuda") + 0.5 for _ in range(2))
+        la, lb = a.log(), (b * a.sum(-1, keepdim=True) / b.sum(-1, keepdim=True)).log()
+    if kind == "masked":
+        mq, mk = ((torch.rand((N, L), generator=gen, device="cuda") > 0.3).to(torch.uint8) for _ in range(2))
+
+    def forward(nbytes):
+        ws = None if nbytes is None else torch.empty(nbytes, device="cuda", dtype=torch.uint8)
+        if kind == "masked":
+            return ska.sinkhorn_attn_fwd_masked(Q, K, V, mq, mk, W, T, R, eps, workspace=ws)
+        return ska.sinkhorn_attn_fwd_varlen(Q, K, V, la, lb, lq, lk, W, T, R, eps, db, 0.3, workspace=ws)
+
+    O, UV = forward(None)
+    O0, UV0 = forward(max(16, Q.numel() * 2 if dtype == "bf16" else 16))   # room for the prescaled operand alone
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isneginf(UV), torch.isneginf(UV0))
+    x, y = (torch.where(torch.isneginf(z), 0.0, z.double()) for z in (UV, UV0))
+    assert torch.isfinite(x).all() and torch.isfinite(y).all()
+    score = float((Q.double().norm(dim=-1).max() * K.double().norm(dim=-1).max()) / (eps * d ** 0.5))
+    M = 1.4427 * max(score, float(y.abs().max()))
+    terms = 2 * min(W, L) + 1 + (L if db else 0)
+    bound = 2 * 2 * (T + R) * (terms + 20 + 4 * M) * 2.0 ** -24
+    err = float((x - y).abs().max())
+    print(f"   |UV - UV0| {err:.1e} (bound {bound:.1e}), M {M:.0f}", flush=True)
+    assert err <= bound
+    # a plan entry moves by at most the two potentials' differences, and (bf16) to the other neighbour
+    rel = float((O.double() - O0.double()).norm() / O0.double().norm())
+    assert rel <= 2 * bound + (2.0 ** -8 if dtype == "bf16" else 0.0), rel
+
+
+def test_steps_take_spread_potentials():
+    """Row targets of 1 and e^60 in turn, row by row, against a column target of 1: the potentials inside one block are
+    60 apart, which a stabiliser per row carries in either direction (one partner per token: the plan is the identity)."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    L = 3000
+    Q, K, V = (torch.randn((1, 1, L, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    la = 60.0 * (torch.arange(L, device="cuda") % 2).float().view(1, 1, L)
+    O, UV = ska.sinkhorn_attn_fwd_marginals(Q, K, V, la, torch.zeros_like(la), 0, 3, 2, 1.0)
+    assert torch.isfinite(UV).all()
+    u, v = UV[0, 0, 4].double(), UV[0, 0, 5].double()
+    s = (Q.double() * K.double()).sum(-1)[0, 0] / 8.0
+    # after a column step the column sums are one; scores from a bf16 copy of Q: 2^-9 of the terms' sizes
+    assert float((u + v + s).abs().max()) <= 2.0 ** -9 * float((Q.double() * K.double()).abs().sum(-1).max() / 8.0) + 1e-4
