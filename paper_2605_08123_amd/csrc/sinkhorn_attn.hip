@@ -448,20 +448,22 @@ template <typename T, int D> int sweep(Call &cx, int mode, const SweepArgs &a, i
 // ------------------------------------------------------------------ whole steps (vstep_kernel)
 // Blocks of NF fragments of 32 rows, G wavefronts per fragment with NTW tiles each, M blocks per workgroup (a segment);
 // hw = ceil(W / 32).  NF = 0: the half-steps run one by one.
-struct StepShape { int NF, G, NTW, hw, M; };
+struct StepShape { int NF, G, NTW, hw, M, kind; };
 constexpr int STEP_LDS = 159 * 1024;   // dynamic part; the dustbin element has a little of its own
-// The instances, by the bytes of a 32-row tile; the second list marches (M > 1).
+// The instances, by the bytes of a 32-row tile (TB).
 #define SKA_STEP_SHAPES(X) \
-    X(TB <= 16384, 2, 2, 3, false) X(TB <= 16384, 4, 1, 5, false) X(TB <= 8192, 2, 2, 5, false) X(TB <= 8192, 8, 1, 9, false) \
-    X(TB <= 8192, 2, 4, 5, false) X(TB == 8192, 4, 1, 9, false) X(TB == 8192, 1, 4, 5, false) X(TB == 16384, 1, 2, 5, false) \
-    X(TB <= 4096, 4, 2, 9, false) X(TB <= 4096, 8, 1, 9, true) X(TB <= 4096, 4, 2, 9, true)
+    X(TB <= 16384, 2, 2, 3, STEP_BLOCK) X(TB <= 16384, 4, 1, 5, STEP_BLOCK) X(TB <= 8192, 2, 2, 5, STEP_BLOCK) \
+    X(TB <= 8192, 8, 1, 9, STEP_BLOCK) X(TB <= 8192, 2, 4, 5, STEP_BLOCK) X(TB == 8192, 4, 1, 9, STEP_BLOCK) \
+    X(TB == 8192 && sizeof(T) == 4, 1, 4, 5, STEP_BLOCK) X(TB == 16384, 1, 2, 5, STEP_BLOCK) X(TB <= 4096, 4, 2, 9, STEP_BLOCK) \
+    X(TB <= 4096, 8, 1, 9, STEP_MARCH) X(TB <= 4096, 4, 2, 9, STEP_MARCH) X(TB == 8192, 2, 4, 5, STEP_TIGHT) \
+    X(TB <= 4096, 2, 4, 9, STEP_BLOCK)
 template <typename T, int D> constexpr int step_tile_bytes = StepTile<T, D>::BYTES;
 template <typename T, int D> int step_lds(const StepShape &sh)
 {
     constexpr int TB = step_tile_bytes<T, D>;
-#define SKA_LDS(COND, NF_, G_, NTW_, MARCH_) \
+#define SKA_LDS(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
-        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && (sh.M > 1) == MARCH_) return StepLds<T, D, NF_, G_, NTW_, MARCH_>(sh.hw).total;
+        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) return StepLds<T, D, NF_, G_, NTW_, KIND_>(sh.hw).total;
     SKA_STEP_SHAPES(SKA_LDS)
 #undef SKA_LDS
     return STEP_LDS + 1;
@@ -474,16 +476,19 @@ template <typename T, int D> int step_lds(const StepShape &sh)
 //   W = 200: 5600 rows (2,4,5) 176 (4,2,9) 206; 48000 rows 408 / 336 in segments; 524288 rows 1803, half-steps 1804
 //   d = 32, W = 256: 131072 rows 464, half-steps 574; 262144 rows 805 / 742, as d = 32 half-steps have half the products
 //   d = 128 or fp32 d = 64 (8 KB tiles), W = 128: 5600 rows (2,2,5) 195 (4,1,9) 222; 32768 rows (4,1,9) 229 (8,1,9) 247;
-//   131072 rows (4,1,9) 702 (8,1,9) 539, half-steps 826.  W = 200 (2,4,5): 32768 rows 387, half-steps 457; 131072 rows
-//   1306 / 1081; fp32 2692 / 3187.  fp32, W = 256: 5600 rows (1,4,5) 381 (2,4,5) 436
+//   131072 rows (4,1,9) 702 (8,1,9) 539, half-steps 826.  W = 256 (2,4,5): 5600 rows 236, half-steps 481; 32768 rows block by
+//   block 401, in segments 481, half-steps 481; 131072 rows 1321 / 916 / 1115; 262144 rows 2502 / 1625 / 1786.  fp32: 131072
+//   rows 2701 / 2253 / 3181; 5600 rows (1,4,5) 381 (2,4,5) 436
 //   fp32 d = 128 (16 KB tiles): W = 32 32768 rows (2,2,3) 393 (4,1,5) 329; W = 128 5600 rows 539, half-steps 989; 32768 rows
 //   1532 / 995
+//   W = 300 .. 480 (2,4,9): 16384 rows 244 .. 271, half-steps 469 .. 618; 32768 rows 414 .. 456 / 470 .. 619; beyond, the 36
+//   tiles that a block of 64 rows reads are what bounds it
 template <typename T, int D> StepShape step_shape(int N, int L, int W)
 {
     constexpr int TB = step_tile_bytes<T, D>;
     const int hw = ((W < L ? W : L) + 31) / 32;
     const long rows = (long)N * L;
-    StepShape sh{0, 0, 0, hw, 1};
+    StepShape sh{0, 0, 0, hw, 1, STEP_BLOCK};
     auto take = [&](int NF, int G, int NTW) { sh.NF = NF; sh.G = G; sh.NTW = NTW; };
     bool march = false;
     if (hw <= 2) {
@@ -509,9 +514,12 @@ template <typename T, int D> StepShape step_shape(int N, int L, int W)
                 march = true;
             }
         } else if (TB == 8192) {
-            if (rows <= 8192) take(1, 4, 5);
-            else if (sizeof(T) == 4 || (rows <= 32768 && hw <= 7)) take(2, 4, 5);
+            if (sizeof(T) == 4 && rows <= 8192) take(1, 4, 5);
+            else take(2, 4, 5);
+            march = rows > 32768;
         }
+    } else if (hw <= 15 && TB <= 4096 && rows <= 32768) {
+        take(2, 4, 9);
     }
     if (!sh.NF) return sh;
     if (march) {   // one segment per CU, of equal lengths and at least hw tiles
@@ -521,6 +529,7 @@ template <typename T, int D> StepShape step_shape(int N, int L, int W)
         if (M > 4096 / sh.NF) M = 4096 / sh.NF;   // (segment_reciprocal)
         if (M > 1 && M * sh.NF < hw) M = (hw + sh.NF - 1) / sh.NF;
         sh.M = M;
+        if (M > 1) sh.kind = TB <= 4096 ? STEP_MARCH : STEP_TIGHT;
     }
     if (step_lds<T, D>(sh) > STEP_LDS) sh.NF = 0;
     return sh;
@@ -530,29 +539,29 @@ inline long step_part_stride(const StepShape &sh, int L)   // floats of column s
 {
     return step_segments(sh, L) * 32 * (sh.NF * sh.M + 2 * sh.hw);
 }
-template <typename T, int D, int NF, int G, int NTW, bool MARCH> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
+template <typename T, int D, int NF, int G, int NTW, int KIND> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
     p.s.nbp = (p.s.L + 32 * NF * p.M - 1) / (32 * NF * p.M);
     p.s.nb_total = p.s.nbp * N;
     p.s.lead = p.s.dustbin ? (N + 7) / 8 * 8 : 0;
-    const int lds = StepLds<T, D, NF, G, NTW, MARCH>(p.hw).total;
+    const int lds = StepLds<T, D, NF, G, NTW, KIND>(p.hw).total;
     static bool raised[MAX_DEVICES];
     if (!raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, MARCH>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, MARCH>), dim3((p.s.nb_total + 7) / 8 * 8 + p.s.lead), dim3(64 * NF * G), lds,
+    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND>), dim3((p.s.nb_total + 7) / 8 * 8 + p.s.lead), dim3(64 * NF * G), lds,
                        st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
-template <typename T, int D> int launch_vstep(const StepArgs &p, int NTW, int N, hipStream_t st, int dev)
+template <typename T, int D> int launch_vstep(const StepArgs &p, int NTW, int kind, int N, hipStream_t st, int dev)
 {
     constexpr int TB = step_tile_bytes<T, D>;
-#define SKA_LAUNCH(COND, NF_, G_, NTW_, MARCH_) \
+#define SKA_LAUNCH(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
-        if (p.NF == NF_ && p.G == G_ && NTW == NTW_ && (p.M > 1) == MARCH_) return launch_vstep_n<T, D, NF_, G_, NTW_, MARCH_>(p, N, st, dev);
+        if (p.NF == NF_ && p.G == G_ && NTW == NTW_ && kind == KIND_) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_>(p, N, st, dev);
     SKA_STEP_SHAPES(SKA_LAUNCH)
 #undef SKA_LAUNCH
     return SKA_EUNSUPPORTED;
@@ -567,13 +576,13 @@ template <typename T, int D> StepArgs step_from_problem(const StepArgs &p, int n
     if (p.log_b.p) b.log_b.p = p.log_b.p + n0 * p.log_b.stride;
     return b;
 }
-template <typename T, int D> int step_sweep(Call &cx, const StepArgs &p, int NTW, int N)
+template <typename T, int D> int step_sweep(Call &cx, const StepArgs &p, int NTW, int kind, int N)
 {
-    if (!cx.side || N < 2) return launch_vstep<T, D>(p, NTW, N, cx.st, cx.dev);
+    if (!cx.side || N < 2) return launch_vstep<T, D>(p, NTW, kind, N, cx.st, cx.dev);
     const int n0 = N / 2;
-    SKA_TRY((launch_vstep<T, D>(p, NTW, n0, cx.st, cx.dev)));
+    SKA_TRY((launch_vstep<T, D>(p, NTW, kind, n0, cx.st, cx.dev)));
     cx.busy = true;
-    return launch_vstep<T, D>(step_from_problem<T, D>(p, n0), NTW, N - n0, cx.side->s, cx.dev);
+    return launch_vstep<T, D>(step_from_problem<T, D>(p, n0), NTW, kind, N - n0, cx.side->s, cx.dev);
 }
 inline int launch_vfinal(StepArgs p, int N, hipStream_t st)
 {
@@ -793,7 +802,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
     const StepShape shape = step_shape<T, D>(N, L, p.W);
-    const long pstride = step_part_stride(shape.NF ? shape : StepShape{1, 1, 1, 0, 1}, L);
+    const long pstride = step_part_stride(shape.NF ? shape : StepShape{1, 1, 1, 0, 1, 0}, L);
     float *part[2] = {nullptr, nullptr};
     if (shape.NF) {   // room for two buffers of sums between g_u and the end of the vectors (the same bytes at every R)
         const size_t gu = (size_t)N * p.ldw() * sizeof(float), need = 2 * (size_t)N * pstride * sizeof(float);
@@ -850,7 +859,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         f.part_out = part[pbuf]; f.part_stride = pstride;
         f.NF = shape.NF; f.G = shape.G; f.hw = shape.hw; f.M = shape.M; f.rcp = segment_reciprocal(shape.NF * shape.M);
         f.s.rev = nlaunch++ & 1;
-        SKA_TRY((step_sweep<T, D>(cx, f, shape.NTW, N)));
+        SKA_TRY((step_sweep<T, D>(cx, f, shape.NTW, shape.kind, N)));
         if (pt_run) pt_run->launched(2);
         pend = true;
         vhome = vslot;

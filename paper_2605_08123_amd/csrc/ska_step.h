@@ -91,14 +91,14 @@ __device__ __forceinline__ float column_sum(const StepArgs &p, const float *part
     return c;
 }
 
-// A potential (base 2) as a row of a bf16 operand: x in three parts, which hold its 24 bits, and three ones for the
-// other side's parts; the product of a row's and a column's is the sum of their potentials.  An absent or inactive
+// A potential (base 2) in three bf16 parts, which hold its 24 bits.  A column's operand row is (its parts, 0, 1, 1, 1, 0),
+// a row's (1, 1, 1, 0, its parts, 0): their product is the sum of the two potentials.  An absent or inactive
 // token (-inf) is a number whose exponential is zero, since -inf times an absent part would not be.
-__device__ __forceinline__ bf16x8 potential_row(float x, bool row)
+__device__ __forceinline__ bf16x4 potential_parts(float x)
 {
     const float y = fmaxf(x, -1e30f), z = x == x ? y : x;
-    const __bf16 hi = (__bf16)z, mid = (__bf16)(z - (float)hi), lo = (__bf16)(z - (float)hi - (float)mid), one = (__bf16)1.f, no = (__bf16)0.f;
-    return row ? bf16x8{hi, mid, lo, one, one, one, no, no} : bf16x8{one, one, one, hi, mid, lo, no, no};
+    const __bf16 hi = (__bf16)z, mid = (__bf16)(z - (float)hi), lo = (__bf16)(z - (float)hi - (float)mid);
+    return bf16x4{hi, mid, lo, (__bf16)0.f};
 }
 
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
@@ -124,29 +124,41 @@ template <typename T, int D> struct StepTile {
     // position of a 16-byte chunk in its row: sixteen consecutive rows spread one chunk over all 64 banks
     static __device__ __forceinline__ int swz(int row) { return CPR >= 16 ? (row & 15) : CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
 };
-template <typename T, int D, int NF, int G, int NTW, bool MARCH> struct StepLds {   // offsets in bytes
+// How a workgroup goes over its rows: one block; a segment of blocks on a ring of tiles, the next block's requested at a
+// block's start; the same on a ring that holds one block's window and no more (LDS): requested once a block's
+// products are done, into the slots that it leaves.  (8 KB tiles: a forward of eight problems of L = 16384, d = 128,
+// W = 256 1321 us block by block, 916 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
+// window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
+enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
+template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds {   // offsets in bytes
     static constexpr int RSUM = 0;                              // [NF][G][32] row sums
     static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
     static constexpr int US = WS + NF * G * 128;                // [2][32 NF] potentials of the rows
+    static constexpr bool MARCH = KIND != STEP_BLOCK;
     static constexpr int TWO = MARCH ? 2 : 1;
+    static_assert(KIND != STEP_TIGHT || G > 1, "the exchange of row sums says that the products are done");
     static constexpr int CP = US + TWO * NF * 128;                // [2][NF][G NTW 32] column sums of a fragment
-    static constexpr int Y = CP + TWO * NF * G * NTW * 128;     // ring of the other side's tiles
-    static constexpr int VB = sizeof(T) == 2 ? 16 : 4;          // bytes of a column's potential
+    // two buffers where a wavefront can write its sums of the next block while others read these: with G > 1 the exchange
+    // of row sums lies in between
+    static constexpr int CP2 = MARCH && G == 1 ? 2 : 1;
+    static constexpr int Y = CP + CP2 * NF * G * NTW * 128;     // ring of the other side's tiles
+    static constexpr int VB = sizeof(T) == 2 ? 8 : 4;           // bytes of a column's potential
     int rs, vs, cs, total;
     __host__ __device__ StepLds(int hw)
     {
-        rs = NF + 2 * hw + (MARCH ? NF : 0);   // ring slots: the window of a block and the tiles the next one adds
+        rs = NF + 2 * hw + (KIND == STEP_MARCH ? NF : 0);   // ring slots: the window of a block (and the tiles the next one adds)
         vs = Y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
         cs = vs + rs * 32 * VB;                // MARCH: [32 rs] column sums of the segment so far
         total = cs + (MARCH ? rs * 128 : 0);
     }
 };
 
-template <typename T, int D, int NF, int G, int NTW, bool MARCH>
+template <typename T, int D, int NF, int G, int NTW, int KIND>
 __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 {
     using ST = StepTile<T, D>;
-    using LD = StepLds<T, D, NF, G, NTW, MARCH>;
+    using LD = StepLds<T, D, NF, G, NTW, KIND>;
+    constexpr bool MARCH = KIND != STEP_BLOCK, TIGHT = KIND == STEP_TIGHT;
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
     const SweepArgs &a = p.s;
@@ -191,36 +203,37 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     const unsigned char *Yb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.Y) + moff);
     const int kseg = b0 * NF - hw;   // the segment's first tile, ring slot 0
 
-    // `count` tiles of a matrix from tile k on into LDS slots from `slot` on (wrapping at `wrap`); one instruction of a
-    // wavefront fills 1 KB, RPI rows.  Rows outside the matrix repeat its first or last valid one; they are masked
+    // LDS-direct loads of the other side's tiles: one instruction of a wavefront fills 1 KB, RPI rows.  Rows outside the matrix repeat its first or last valid one; they are masked
     // where they are used.
     constexpr int RPI = 64 / ST::CPR, IPT = 32 / RPI;
     const unsigned smem_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    auto dma = [&](const unsigned char *mat, int rows, int k, int count, int off, int slot, int wrap) {
-        const bool whole = k >= 0 && 32 * (k + count) <= rows;
+    auto dma_rows = [&](long t, int lds_at, bool whole) {   // rows t ... t + RPI - 1 (t uniform)
+        const int lrow = lane / ST::CPR;
+        const unsigned col = ((lane % ST::CPR) ^ ST::swz((int)(t & 31) + lrow)) * 16;
+        unsigned o = lrow * ST::ROWB + col;
+        if (!whole) {
+            const long last = Lt - 1, tb = min(max(t, 0L), last);
+            o = (unsigned)(min(max(t + lrow, 0L), last) - tb) * ST::ROWB + col;
+            t = tb;
+        }
+        // (written out, because the compiler takes every later LDS read for one of these bytes and waits at once; the
+        // kernel waits where it needs them.  No register is written.)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(smem_at + lds_at), "v"(o), "s"(Yb + t * ST::ROWB)
+                     : "memory", "m0");
+    };
+    // `count` tiles from tile k on into the ring from `slot` on, by the whole workgroup
+    auto dma = [&](int k, int count, int slot) {
+        const bool whole = k >= 0 && 32 * (k + count) <= Lt;
         for (int i = wave; i < count * IPT; i += NF * G) {
-            const int kt = i / IPT, r0 = (i % IPT) * RPI, lrow = lane / ST::CPR;
-            int sl = slot + kt;
-            if (sl >= wrap) sl -= wrap;
-            const unsigned col = ((lane % ST::CPR) ^ ST::swz(r0 + lrow)) * 16;
-            long t = 32 * (k + kt) + r0;   // (uniform)
-            unsigned o = lrow * ST::ROWB + col;
-            if (!whole) {
-                const long last = rows - 1, tb = min(max(t, 0L), last);
-                o = (unsigned)(min(max(t + lrow, 0L), last) - tb) * ST::ROWB + col;
-                t = tb;
-            }
-            // (written out, because the compiler takes every later LDS read for one of these bytes and waits at once; the
-            // kernel waits where a block ends.  No register is written.)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(smem_at + off + sl * ST::BYTES + r0 * ST::ROWB),
-                         "v"(o), "s"(mat + t * ST::ROWB)
-                         : "memory", "m0");
+            int sl = slot + i / IPT;
+            if (sl >= RS) sl -= RS;
+            dma_rows(32L * (k + i / IPT) + (i % IPT) * RPI, LD::Y + sl * ST::BYTES + (i % IPT) * 1024, whole);
         }
     };
     // v of a column into its place in LDS, as the evaluation takes it
     auto stage_v = [&](int at, int t, float v) {
         v = t >= 0 && t < Lt ? v * LOG2E : -INFINITY;
-        if constexpr (PRE) *reinterpret_cast<bf16x8 *>(vs + at * 16) = potential_row(v, false);
+        if constexpr (PRE) *reinterpret_cast<bf16x4 *>(vs + at * 8) = potential_parts(v);
         else *reinterpret_cast<float *>(vs + at * 4) = v;
     };
     // Loads return in order: the vectors, which need work, are requested before the tiles and the owner rows.
@@ -241,7 +254,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         }
     }
     OwnerFrag<T, D> xf;
-    dma(Yb, Lt, kseg, nwt, LD::Y, 0, RS);
+    dma(kseg, nwt, 0);
     xf.load(reinterpret_cast<const T *>(Xb), min((b0 * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
@@ -282,6 +295,11 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nlb = 0.f;
         const int nt = 32 * (k0 + nwt) + tid, no = (b + 1) * BM + tid;
         const int nq = min(segment_of(p, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
+        auto request_tiles = [&]() {
+            int sl = base + nwt;
+            if (sl >= RS) sl -= RS;
+            dma(k0 + nwt, NF, sl);
+        };
         if (more) {
             const int tc = min(nt, L - 1);
             nv = vp[tc];
@@ -292,9 +310,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 #pragma unroll
                 for (int i = 0; i < 3; ++i) np[i] = pp[(long)min(i, nq) * (64 * hw)];
             }
-            int sl = base + nwt;
-            if (sl >= RS) sl -= RS;
-            dma(Yb, Lt, k0 + nwt, NF, LD::Y, sl, RS);
+            if constexpr (!TIGHT) request_tiles();
         }
 
         [[maybe_unused]] f32x16 ci;   // fp32 storage: the rows' potentials
@@ -344,15 +360,24 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             constexpr int KS = D / 16;
             bf16x8 y[KS], yv, xv;
             {   // the rows' potentials, in the lanes that hold the first eight of the sixteen
-                xv = potential_row(u_old * LOG2E, true);
+                const bf16x4 u3 = potential_parts(u_old * LOG2E);
+                const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
+                xv = bf16x8{one, one, one, no, u3[0], u3[1], u3[2], no};
 #pragma unroll
-                for (int i = 0; i < 8; ++i) xv[i] = h ? (__bf16)0.f : xv[i];
+                for (int i = 0; i < 8; ++i) xv[i] = h ? no : xv[i];
             }
             f32x16 zero;
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-            auto rd = [&](int ks) { y[ks] = *reinterpret_cast<const bf16x8 *>(smem + LD::Y + slot * ST::BYTES + c * ST::ROWB + (((2 * ks + h) ^ ST::swz(c)) << 4)); };
-            auto rdv = [&]() { yv = *reinterpret_cast<const bf16x8 *>(vs + (32 * slot + c) * 16); };
+            const unsigned char *ybase = smem + LD::Y + c * ST::ROWB;
+            auto rd = [&](int ks) {
+                y[ks] = *reinterpret_cast<const bf16x8 *>(ybase + slot * ST::BYTES + (((2 * ks + h) ^ ST::swz(c)) << 4));
+            };
+            auto rdv = [&]() {
+                const bf16x4 v3 = *reinterpret_cast<const bf16x4 *>(vs + (32 * slot + c) * 8);
+                const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
+                yv = bf16x8{v3[0], v3[1], v3[2], v3[3], one, one, one, no};
+            };
             auto step_slot = [&]() { ++slot; if (MARCH && slot == RS) slot = 0; };
             rdv();
 #pragma unroll
@@ -445,6 +470,8 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         }
         if constexpr (G > 1) __syncthreads();
         else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (TIGHT)
+            if (more) request_tiles();   // (every wavefront is done with this block's)
         float tot = 0.f;
 #pragma unroll
         for (int i = 0; i < G; ++i) tot += rs[(f * G + i) * 32 + c];
@@ -470,7 +497,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             wv[4 * q + 0] = v4.x; wv[4 * q + 1] = v4.y; wv[4 * q + 2] = v4.z; wv[4 * q + 3] = v4.w;
         }
         // column sums of the fragment
-        float *cp = reinterpret_cast<float *>(smem + LD::CP) + par * NF * G * NTW * 32;
+        float *cp = reinterpret_cast<float *>(smem + LD::CP) + (LD::CP2 == 2 ? par : 0) * NF * G * NTW * 32;
         float *cpw = cp + (f * G * NTW + j0) * 32;
         auto col = [&](const f32x16 &e) {
             float x = 0.f, y = 0.f;
@@ -487,13 +514,16 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         }
         float v_new = nv;
         if (more && tid < BM) {
-            if (part && nt < L) v_new = nt < Lc ? column_update(nv, np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f), nlb) : 0.f;
+            if (part && nt < L) {
+                const float sum = np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f);
+                v_new = nt < Lc ? column_update(nv, sum, nlb) : 0.f;
+            }
             int sl = 32 * (base + nwt) + tid;
             if (sl >= 32 * RS) sl -= 32 * RS;
             stage_v(sl, nt, v_new);
             us[(par ^ 1) * BM + tid] = no < Le ? nu : -INFINITY;
         }
-        __builtin_amdgcn_s_waitcnt(0x0070);
+        __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
         __syncthreads();
         // stores to memory only now: the wait above would wait for them as well
         if (h == 0 && g == 0 && o < L) a.out_vec.p[n * a.out_vec.stride + o] = u_new;

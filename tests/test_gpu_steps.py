@@ -19,7 +19,9 @@ SHORT = [  # kind, dtype, d, N, L, W, T, R
     ("plain", "bf16", 64, 1, 1025, 224, 4, 2), ("plain", "bf16", 64, 1, 1023, 256, 3, 2), ("plain", "bf16", 64, 1, 400, 5000, 3, 2),
     ("plain", "bf16", 32, 2, 333, 40, 3, 2), ("plain", "bf16", 32, 2, 777, 100, 3, 2), ("plain", "bf16", 32, 1, 900, 250, 3, 2),
     ("plain", "bf16", 128, 2, 333, 40, 3, 2), ("plain", "bf16", 128, 1, 777, 127, 3, 2), ("plain", "bf16", 128, 1, 900, 200, 3, 2),
-    ("plain", "bf16", 128, 1, 900, 256, 3, 2), ("plain", "f32", 32, 1, 256, 16, 8, 2), ("plain", "f32", 32, 2, 611, 99, 3, 2),
+    ("plain", "bf16", 128, 1, 900, 256, 3, 2), ("plain", "bf16", 64, 2, 1100, 300, 3, 2), ("plain", "bf16", 32, 1, 1500, 480, 3, 1),
+    ("plain", "bf16", 64, 1, 1500, 481, 2, 1), ("plain", "f32", 32, 1, 1200, 400, 2, 2), ("varlen", "bf16", 64, 4, 900, 350, 3, 1),
+    ("plain", "f32", 32, 1, 256, 16, 8, 2), ("plain", "f32", 32, 2, 611, 99, 3, 2),
     ("plain", "f32", 32, 1, 800, 256, 3, 2), ("plain", "f32", 64, 2, 300, 64, 3, 2), ("plain", "f32", 64, 1, 700, 111, 3, 2),
     ("plain", "f32", 64, 1, 700, 255, 3, 2), ("plain", "f32", 128, 1, 300, 50, 3, 2), ("plain", "f32", 128, 1, 500, 128, 3, 2),
     ("varlen", "bf16", 64, 4, 600, 50, 3, 2), ("varlen", "f32", 64, 4, 500, 100, 2, 2), ("varlen", "bf16", 64, 4, 900, 200, 3, 1),
@@ -31,7 +33,9 @@ LONG = [  # other block shapes; segments of several blocks, also ragged ones and
     ("plain", "bf16", 64, 3, 40001, 128, 2, 1), ("plain", "bf16", 64, 1, 17000, 130, 2, 1), ("plain", "bf16", 64, 1, 40000, 256, 3, 1),
     ("plain", "bf16", 64, 2, 70001, 200, 2, 1), ("plain", "bf16", 64, 300, 700, 130, 2, 1), ("plain", "bf16", 32, 2, 40000, 100, 2, 1),
     ("plain", "bf16", 32, 1, 60000, 256, 2, 1), ("plain", "bf16", 128, 1, 33000, 60, 2, 1), ("plain", "bf16", 128, 1, 33000, 120, 2, 1),
-    ("plain", "bf16", 128, 1, 20000, 120, 2, 1), ("plain", "f32", 32, 1, 60000, 100, 2, 1), ("plain", "f32", 32, 1, 60000, 256, 2, 1),
+    ("plain", "bf16", 128, 1, 20000, 120, 2, 1), ("plain", "bf16", 128, 1, 33000, 256, 2, 1), ("plain", "bf16", 128, 3, 30001, 200, 3, 1),
+    ("plain", "f32", 64, 1, 40001, 256, 2, 1), ("varlen", "bf16", 128, 4, 30000, 130, 3, 1), ("dustbin", "bf16", 128, 1, 40000, 250, 2, 1),
+    ("plain", "bf16", 128, 600, 100, 130, 2, 1), ("plain", "f32", 32, 1, 60000, 100, 2, 1), ("plain", "f32", 32, 1, 60000, 256, 2, 1),
     ("plain", "f32", 64, 1, 40000, 128, 2, 1), ("plain", "f32", 128, 1, 20000, 64, 2, 1), ("varlen", "bf16", 64, 4, 40000, 256, 3, 1),
     ("varlen", "bf16", 64, 8, 20000, 70, 2, 1), ("marginals", "bf16", 64, 2, 70000, 128, 2, 1), ("masked", "bf16", 64, 2, 70000, 129, 2, 1),
     ("dustbin", "bf16", 64, 1, 70000, 128, 2, 1), ("dustbin", "f32", 32, 1, 60000, 200, 2, 1)]
