@@ -535,70 +535,64 @@ template <typename T, int D> StepShape step_shape(int N, int L, int W)
     return sh;
 }
 inline long step_segments(const StepShape &sh, int L) { return (L + 32L * sh.NF * sh.M - 1) / (32L * sh.NF * sh.M); }
-inline long step_part_stride(const StepShape &sh, int L)   // floats of column sums per problem
+inline long step_part_stride(const StepShape &sh, int L, bool dustbin)   // floats of column sums per problem
 {
-    return step_segments(sh, L) * 32 * (sh.NF * sh.M + 2 * sh.hw);
+    const long nseg = step_segments(sh, L);
+    return nseg * 32 * (sh.NF * sh.M + 2 * sh.hw) + (dustbin ? 2 * nseg + 2 : 0);
 }
-template <typename T, int D, int NF, int G, int NTW, int KIND> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
+template <typename T, int D, int NF, int G, int NTW, int KIND, bool DUST> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
-    p.s.nbp = (p.s.L + 32 * NF * p.M - 1) / (32 * NF * p.M);
-    p.s.nb_total = p.s.nbp * N;
-    p.s.lead = p.s.dustbin ? (N + 7) / 8 * 8 : 0;
+    p.nb_total = p.nseg * N;
     const int lds = StepLds<T, D, NF, G, NTW, KIND>(p.hw).total;
     static bool raised[MAX_DEVICES];
     if (!raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, DUST>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND>), dim3((p.s.nb_total + 7) / 8 * 8 + p.s.lead), dim3(64 * NF * G), lds,
-                       st, p);
+    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, DUST>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
-template <typename T, int D> int launch_vstep(const StepArgs &p, int NTW, int kind, int N, hipStream_t st, int dev)
+template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape &sh, int N, hipStream_t st, int dev)
 {
     constexpr int TB = step_tile_bytes<T, D>;
 #define SKA_LAUNCH(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
-        if (p.NF == NF_ && p.G == G_ && NTW == NTW_ && kind == KIND_) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_>(p, N, st, dev);
+        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) \
+            return p.dustbin ? launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, true>(p, N, st, dev) : launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, false>(p, N, st, dev);
     SKA_STEP_SHAPES(SKA_LAUNCH)
 #undef SKA_LAUNCH
     return SKA_EUNSUPPORTED;
 }
-template <typename T, int D> StepArgs step_from_problem(const StepArgs &p, int n0)
+inline int launch_vfinal(const StepArgs &p, int N, hipStream_t st)
 {
-    StepArgs b = p;
-    b.s = from_problem<T, D>(p.s, n0);
-    if (p.part_in) b.part_in = p.part_in + n0 * p.part_stride;
-    if (p.part_out) b.part_out = p.part_out + n0 * p.part_stride;
-    if (p.v_out.p) b.v_out.p = p.v_out.p + n0 * p.v_out.stride;
-    if (p.log_b.p) b.log_b.p = p.log_b.p + n0 * p.log_b.stride;
-    return b;
-}
-template <typename T, int D> int step_sweep(Call &cx, const StepArgs &p, int NTW, int kind, int N)
-{
-    if (!cx.side || N < 2) return launch_vstep<T, D>(p, NTW, kind, N, cx.st, cx.dev);
-    const int n0 = N / 2;
-    SKA_TRY((launch_vstep<T, D>(p, NTW, kind, n0, cx.st, cx.dev)));
-    cx.busy = true;
-    return launch_vstep<T, D>(step_from_problem<T, D>(p, n0), NTW, kind, N - n0, cx.side->s, cx.dev);
-}
-inline int launch_vfinal(StepArgs p, int N, hipStream_t st)
-{
-    p.s.nbp = (p.s.L + NTHREADS - 1) / NTHREADS;
-    p.s.nb_total = p.s.nbp * N;
-    p.s.lead = p.s.dustbin ? N : 0;
-    hipLaunchKernelGGL(vfinal_kernel, dim3(p.s.nb_total + p.s.lead), dim3(NTHREADS), 0, st, p);
+    hipLaunchKernelGGL(vfinal_kernel, dim3((unsigned)((p.L + NTHREADS - 1) / NTHREADS * N)), dim3(NTHREADS), 0, st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
-template <typename T, int D> int step_final(Call &cx, const StepArgs &p, int N)
+// a step's launch, or (shape null) the one that takes the last step's sums into v: the two halves of a split call
+template <typename T, int D> int step_sweep(Call &cx, const StepArgs &p, const StepShape *sh, int N)
 {
-    if (!cx.side || N < 2) return launch_vfinal(p, N, cx.st);
+    auto launch = [&](const StepArgs &q, int cnt, hipStream_t st) {
+        return sh ? launch_vstep<T, D>(q, *sh, cnt, st, cx.dev) : launch_vfinal(q, cnt, st);
+    };
+    if (!cx.side || N < 2) return launch(p, N, cx.st);
     const int n0 = N / 2;
-    SKA_TRY(launch_vfinal(p, n0, cx.st));
+    SKA_TRY(launch(p, n0, cx.st));
     cx.busy = true;
-    return launch_vfinal(step_from_problem<T, D>(p, n0), N - n0, cx.side->s);
+    StepArgs b = p;
+    auto mat = [&](const void *q) -> const void * {
+        return q ? reinterpret_cast<const unsigned char *>(q) + (long)n0 * p.L * D * (long)sizeof(T) : nullptr;
+    };
+    auto skip = [&](auto *q, long stride) { return q ? q + n0 * stride : q; };
+    b.X = mat(p.X); b.Y = mat(p.Y);
+    b.v = skip(p.v, p.us); b.u = skip(p.u, p.us);
+    b.u_out = skip(p.u_out, p.us); b.v_out = skip(p.v_out, p.us); b.u_fin = skip(p.u_fin, p.us);
+    b.part_in = skip(p.part_in, p.part_stride); b.part_out = skip(p.part_out, p.part_stride);
+    b.log_a = skip(p.log_a, p.lstride); b.log_b = skip(p.log_b, p.lstride);
+    b.spoke_r = skip(p.spoke_r, p.sstride); b.spoke_c = skip(p.spoke_c, p.sstride);
+    b.n0 = p.n0 + n0;
+    return launch(b, N - n0, cx.side->s);
 }
 
 // benchmark hooks: while enabled, every phase of a call is bracketed by events on the call's
@@ -802,7 +796,8 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
     const StepShape shape = step_shape<T, D>(N, L, p.W);
-    const long pstride = step_part_stride(shape.NF ? shape : StepShape{1, 1, 1, 0, 1, 0}, L);
+    const int nseg = shape.NF ? (int)step_segments(shape, L) : 0;
+    const long pstride = step_part_stride(shape.NF ? shape : StepShape{1, 1, 1, 0, 1, 0}, L, p.dustbin);
     float *part[2] = {nullptr, nullptr};
     if (shape.NF) {   // room for two buffers of sums between g_u and the end of the vectors (the same bytes at every R)
         const size_t gu = (size_t)N * p.ldw() * sizeof(float), need = 2 * (size_t)N * pstride * sizeof(float);
@@ -815,23 +810,28 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     if (part[0]) chain_done = nullptr;   // a step is one launch already
     bool first = !p.resume_t, pend = false;
     int vcur = p.resume_t ? 2 * p.resume_t - 1 : 1, vhome = 0, pbuf = 0;
+    auto slot = [&](int k) { return UV + (long)k * Lp; };
+    StepArgs step{};
+    step.Y = K;
+    step.log_a = p.log_a; step.log_b = p.log_b; step.lstride = Lp;
+    step.spoke_r = SQ.p; step.spoke_c = SK.p; step.sstride = (int)p.ldw();
+    step.len_q = p.len_q; step.len_k = p.len_k;
+    step.us = us; step.part_stride = pstride;
+    step.L = L; step.W = base.W; step.NF = shape.NF; step.M = shape.M; step.hw = shape.hw; step.nseg = nseg;
+    step.rcp = shape.NF ? segment_reciprocal(shape.NF * shape.M) : 0;
+    step.nh = p.H; step.dustbin = p.dustbin;
     auto flush = [&]() -> int {
         if (!pend) return SKA_OK;
-        StepArgs f{};
-        f.s = base;
-        f.s.sdb2 = stage_sdb2;
-        f.s.spoke_own = SK; f.s.spoke_oth = SQ;
-        f.s.yt = vec(vhome - 1); f.s.xs = vec(vcur); f.s.out_vec = vout(vhome);
-        f.s.olog = Vec{p.log_b, (long)Lp};
-        f.s.len_own = p.len_k; f.s.len_oth = p.len_q;
-        f.part_in = part[pbuf]; f.part_stride = pstride;
-        f.NF = shape.NF; f.G = shape.G; f.hw = shape.hw; f.M = shape.M; f.rcp = segment_reciprocal(shape.NF * shape.M);
-        SKA_TRY((step_final<T, D>(cx, f, N)));
+        StepArgs f = step;
+        f.sdb = stage_sdb2 * LN2;
+        f.v = slot(vcur); f.v_out = slot(vhome); f.u_fin = slot(vhome - 1);
+        f.part_in = part[pbuf];
+        SKA_TRY((step_sweep<T, D>(cx, f, nullptr, N)));
         pend = false;
         vcur = vhome;
         return SKA_OK;
     };
-    // (u, v) -> (u', v'): uprev, uout the slots of u and u', vout_slot that of v'; `left` steps of the base solve follow
+    // (u, v) -> (u', v'): uprev, uout the slots of u and u', vslot that of v'; `left` steps of the base solve follow
     auto full = [&](int uprev, int uout, int vslot, int left) -> int {
         if (!part[0] || first) {
             first = false;
@@ -841,29 +841,25 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
             vcur = vfirst;
             return SKA_OK;
         }
-        StepArgs f{};
-        f.s = base;
-        f.s.c2 = stage_c2; f.s.sdb2 = stage_sdb2;
-        f.s.spoke_own = SQ; f.s.spoke_oth = SK;
-        f.s.X = Q; f.s.Y = K;
-        f.s.yt = vec(vcur); f.s.xs = vec(uprev); f.s.out_vec = vout(uout);
-        f.s.olog = Vec{p.log_a, (long)Lp}; f.log_b = Vec{p.log_b, (long)Lp};
-        f.s.len_own = p.len_q; f.s.len_oth = p.len_k;
+        StepArgs f = step;
+        f.c2 = stage_c2; f.sdb = stage_sdb2 * LN2;
+        f.X = Q;
+        f.v = slot(vcur); f.u = slot(uprev); f.u_out = slot(uout);
+        f.v_out = slot(vcur);   // (not written without part_in)
         if (pend) {
             const int dst = vhome != vcur ? vhome : 4 - vcur;   // (only inside a base solve: slots 1 and 3)
             f.part_in = part[pbuf];
-            f.v_out = vout(dst);
+            f.v_out = slot(dst); f.u_fin = slot(uprev);
             vcur = dst;
             pbuf ^= 1;
         }
-        f.part_out = part[pbuf]; f.part_stride = pstride;
-        f.NF = shape.NF; f.G = shape.G; f.hw = shape.hw; f.M = shape.M; f.rcp = segment_reciprocal(shape.NF * shape.M);
-        f.s.rev = nlaunch++ & 1;
-        SKA_TRY((step_sweep<T, D>(cx, f, shape.NTW, shape.kind, N)));
+        f.part_out = part[pbuf];
+        f.rev = nlaunch++ & 1;
+        SKA_TRY((step_sweep<T, D>(cx, f, &shape, N)));
         if (pt_run) pt_run->launched(2);
         pend = true;
         vhome = vslot;
-        return p.dustbin ? flush() : SKA_OK;   // (the spokes need u of all rows)
+        return SKA_OK;
     };
     auto halves = [&]() -> int {
         // base solve: T steps at eps, or the stages of the continuation schedule (remark
@@ -883,7 +879,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
                 SKA_TRY(cx.fork());
             }
             stage_sdb2 = p.sdb * (p.eps / es) * LOG2E;
-            for (int t = 0; t < Ts; ++t) SKA_TRY(full(0, 0, 1, p.dustbin || sidx + 1 < nst ? 0 : Ts - 1 - t));
+            for (int t = 0; t < Ts; ++t) SKA_TRY(full(0, 0, 1, sidx + 1 < nst ? 0 : Ts - 1 - t));
             if (sidx + 1 < nst) {   // the next stage rescales both potentials in place
                 SKA_TRY(flush());
             }

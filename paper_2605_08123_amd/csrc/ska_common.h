@@ -346,12 +346,9 @@ template <> __device__ __forceinline__ void load4<__bf16>(const __bf16 *src, flo
 // is a learned token).
 //   half-steps: out[L] = -log sum_{t<=L} exp(s_t + y_t)
 //   mat-vec   : out[L] = -exp(x[L]) sum_{t<=L} exp(s_t + y_t) w_t    (its additive term is 0)
-// NTH: threads of the launch (0: any whole number of wavefronts up to 16).
-template <bool MATVEC, int NV, int NTH = NTHREADS> __device__ __forceinline__ void dustbin_element(const SweepArgs &a, int n)
+template <bool MATVEC, int NV> __device__ __forceinline__ void dustbin_element(const SweepArgs &a, int n)
 {
-    constexpr int MAXW = NTH ? NTH / 64 : 16;
-    __shared__ float sm[MAXW], ss[MAXW];
-    const int nth = NTH ? NTH : blockDim.x;
+    __shared__ float sm[NWAVES], ss[NWAVES];
     const int L = a.L, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float *yp = a.yt.p + n * a.yt.stride;
     const float *sp = a.spoke_oth.p ? a.spoke_oth.p + n * a.spoke_oth.stride : nullptr;
@@ -362,7 +359,7 @@ template <bool MATVEC, int NV, int NTH = NTHREADS> __device__ __forceinline__ vo
     // NV 16-byte loads per stream (the vectors start on any float, which global loads allow) and rescales
     // its sum once for all of them.  A value per load and two exponentials per value made the element the
     // longest workgroup of the launch: eight problems of L = 16384, W = 256 1179 -> 1055 us per step.
-    const int STEP = nth * 4, BATCH = NV * STEP;
+    constexpr int STEP = NTHREADS * 4, BATCH = NV * STEP;
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     float m = -INFINITY, acc = 0.f;
     auto batch = [&](const float (&v)[NV * 4], const float (&wt)[NV * 4]) {
@@ -398,13 +395,13 @@ template <bool MATVEC, int NV, int NTH = NTHREADS> __device__ __forceinline__ vo
         float v[NV * 4], wt[NV * 4];
 #pragma unroll
         for (int i = 0; i < NV * 4; ++i) {
-            const int t = min(t0 + i * nth + tid, L);
+            const int t = min(t0 + i * NTHREADS + tid, L);
             v[i] = yp[t] + (sp ? sp[t] : 0.f);
             wt[i] = wp ? wp[t] : 1.f;
         }
 #pragma unroll
         for (int i = 0; i < NV * 4; ++i)
-            if (t0 + i * nth + tid > L) { v[i] = -INFINITY; wt[i] = 0.f; }
+            if (t0 + i * NTHREADS + tid > L) { v[i] = -INFINITY; wt[i] = 0.f; }
         batch(v, wt);
     }
     auto merge = [](float &m0, float &s0, float m1, float s1) {
@@ -417,7 +414,7 @@ template <bool MATVEC, int NV, int NTH = NTHREADS> __device__ __forceinline__ vo
     __syncthreads();
     if (tid == 0) {
         m = sm[0]; acc = ss[0];
-        for (int i = 1; i < nth / 64; ++i) merge(m, acc, sm[i], ss[i]);
+        for (int i = 1; i < NWAVES; ++i) merge(m, acc, sm[i], ss[i]);
         a.out_vec.p[n * a.out_vec.stride + L] =
             MATVEC ? -__expf(a.xs.p[n * a.xs.stride + L] + sdb + m) * acc : -(sdb + m + __logf(acc));
     }

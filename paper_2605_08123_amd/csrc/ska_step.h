@@ -31,17 +31,47 @@ namespace {
 //   The potentials enter through the products (potential_row): as 16 adds per tile they took 6 % of a long call, and as
 // the products' initial accumulator 16 registers.  The products of a tile are issued among the exponentials of the tile
 // before it, in an order that scheduling barriers pin: left to itself the compiler puts all products first.
+//   DUST: every segment also writes what the dustbin's row and its column get from it, and the next launch makes the dustbin's
+// two potentials of them (dustbin_pair), each workgroup for itself.  A launch between the steps (the column sums and
+// the dustbin's elements, one long workgroup each) took a fifth of the step: forward and backward of 8 problems of L = 16384,
+// W = 256, T = 20 1022 -> 863 us, 16 of 1501, W = 64 with learned tokens 396 -> 356.  A template parameter, since
+// its branches and registers cost calls without a dustbin 4 % (2 problems of 262144: 2730 -> 2650 us).
+//   The arguments are a struct of their own, read as a whole at a kernel's start (take_args): fetched where they are first
+// used they cost a short launch one wait of some hundred cycles after another.
 struct StepArgs {
-    SweepArgs s;           // the row half-step: X (owner) = row operand, Y = column operand, yt = v, xs = u, out_vec = u'
-    const float *part_in;  // column sums of the step before, to be taken into v first (null: yt is v itself)
-    float *part_out;       // column sums of this step  [problem][segment][32 (NF M + 2 hw)]
-    long part_stride;      // floats per problem
-    VecOut v_out;          // part_in: where v goes (never yt: other blocks read that)
-    Vec log_b;             // log of the column targets (null: unit)
-    int NF, G, hw;         // fragments per block, wavefronts per fragment, ceil(W / 32)
-    int M;                 // blocks per segment
-    unsigned rcp;          // segment_reciprocal(NF M)
+    const void *X, *Y;             // row (owner) and column operand
+    const float *v, *u;            // potentials before the step (with part_in: v before the step before)
+    float *u_out;                  // u'
+    float *v_out;                  // part_in: where v goes (never p.v: other blocks read that)
+    float *u_fin;                  // part_in and a dustbin: the step before's u', whose dustbin element is known only now
+    const float *part_in;          // column sums of the step before, to be taken into v first (null: v is final)
+    float *part_out;               // column sums of this step  [problem][segment][32 (NF M + 2 hw)]; with a dustbin, what its
+                                   // row and its column got from each segment, and the potentials those refer to [2 nseg + 2]
+    const float *log_a, *log_b;    // logs of the row and column targets (null: unit)
+    const float *spoke_r, *spoke_c;   // learned dustbin token: scores of the spokes of the rows and of the columns (null: sdb)
+    const int *len_q, *len_k;      // valid lengths per batch item (null: L)
+    long us, part_stride;          // floats between problems: potentials; part_in, part_out
+    int lstride, sstride;          // ... targets, spokes
+    int L, W, NF, M, hw, nseg;     // fragments per block, blocks per segment, ceil(W / 32), segments per problem
+    unsigned rcp;                  // segment_reciprocal(NF M)
+    int nb_total, rev, nh, n0, dustbin;   // (as in SweepArgs)
+    float c2, sdb;                 // score scale in base 2 (fp32 storage); scalar dustbin score
 };
+__device__ __forceinline__ void take_args(const StepArgs &p)
+{
+    asm volatile("" ::"s"(p.X), "s"(p.Y), "s"(p.v), "s"(p.u), "s"(p.u_out), "s"(p.v_out), "s"(p.part_in), "s"(p.part_out),
+                 "s"(p.log_a), "s"(p.log_b), "s"(p.len_q), "s"(p.len_k), "s"(p.spoke_c), "s"(p.us), "s"(p.part_stride), "s"(p.L),
+                 "s"(p.W), "s"(p.M), "s"(p.hw), "s"(p.nseg), "s"(p.rcp), "s"(p.nb_total), "s"(p.rev), "s"(p.lstride));
+}
+// Valid lengths of problem n: Lt columns, Le rows and Lc columns with at least one band edge.
+struct StepLens { int Lt, Le, Lc; };
+__device__ __forceinline__ StepLens step_lens(const StepArgs &p, int n)
+{
+    int Lq = p.L, Lk = p.L;
+    if (p.len_q) Lq = min(max(p.len_q[(n + p.n0) / p.nh], 0), p.L);
+    if (p.len_k) Lk = min(max(p.len_k[(n + p.n0) / p.nh], 0), p.L);
+    return StepLens{Lk, Lk > 0 ? min(Lq, Lk + p.W) : 0, Lq > 0 ? min(Lk, Lq + p.W) : 0};
+}
 
 // x / SL (tiles per segment) as a multiplication: exact for x < 2^20 and SL <= 2^12, since x (SL - 1) < 2^32
 inline unsigned segment_reciprocal(int SL) { return SL == 1 ? 0u : (unsigned)((0x100000000ull + SL - 1) / SL); }
@@ -52,14 +82,6 @@ __device__ __forceinline__ float column_update(float v, float sum, float log_b)
     if (v == -INFINITY) return -INFINITY;                       // inactive token: stays so
     if (!(sum > 0.f && sum < INFINITY)) return __builtin_nanf("");
     return v - LN2 * fast_log2(sum) + log_b;
-}
-// columns of problem n with at least one band edge (rows, seen from the columns: the lengths exchanged)
-__device__ __forceinline__ int valid_columns(const SweepArgs &a, int n)
-{
-    int Lq = a.L, Lk = a.L;
-    if (a.len_own) Lq = min(max(a.len_own[(n + a.n0) / a.nh], 0), a.L);
-    if (a.len_oth) Lk = min(max(a.len_oth[(n + a.n0) / a.nh], 0), a.L);
-    return Lq > 0 ? min(Lk, Lq + a.W) : 0;
 }
 // where the sums of column t < L are: n segments from the first one that meets it
 struct ColumnSegments {
@@ -99,6 +121,27 @@ __device__ __forceinline__ bf16x4 potential_parts(float x)
     const float y = fmaxf(x, -1e30f), z = x == x ? y : x;
     const __bf16 hi = (__bf16)z, mid = (__bf16)(z - (float)hi), lo = (__bf16)(z - (float)hi - (float)mid);
     return bf16x4{hi, mid, lo, (__bf16)0.f};
+}
+
+// The dustbin's own potentials after the step before, from what its row and its column got from each segment (in the order
+// of the segments, the same in every workgroup).  The column half-step follows the row half-step.  All threads call it;
+// red: 2 * 16 floats of LDS.
+struct DustbinPair { float u, v; };
+template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_pair(const StepArgs &p, const float *part, float corner, float *red)
+{
+    const float *q = part + (long)p.nseg * (32 * (p.NF * p.M + 2 * p.hw));
+    float r = 0.f, c = 0.f;
+    for (int i = threadIdx.x; i < p.nseg; i += NTHR) { r += q[i]; c += q[p.nseg + i]; }
+    const float u0 = q[2 * p.nseg], v0 = q[2 * p.nseg + 1];
+#pragma unroll
+    for (int s = 32; s >= 1; s >>= 1) { r += __shfl_xor(r, s); c += __shfl_xor(c, s); }
+    if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = r; red[16 + (threadIdx.x >> 6)] = c; }
+    __syncthreads();
+    r = c = 0.f;
+#pragma unroll
+    for (int i = 0; i < NTHR / 64; ++i) { r += red[i]; c += red[16 + i]; }
+    const float u = column_update(u0, r + fast_exp2((corner + v0 + u0) * LOG2E), 0.f);
+    return DustbinPair{u, column_update(v0, c + fast_exp2((corner + u + v0) * LOG2E), 0.f)};
 }
 
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
@@ -153,7 +196,7 @@ template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds { 
     }
 };
 
-template <typename T, int D, int NF, int G, int NTW, int KIND>
+template <typename T, int D, int NF, int G, int NTW, int KIND, bool DUST>
 __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 {
     using ST = StepTile<T, D>;
@@ -161,26 +204,22 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     constexpr bool MARCH = KIND != STEP_BLOCK, TIGHT = KIND == STEP_TIGHT;
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
-    const SweepArgs &a = p.s;
     extern __shared__ __align__(16) unsigned char smem[];
-    if ((int)blockIdx.x < a.lead) {
-        if ((int)blockIdx.x < a.nb_total / a.nbp) dustbin_element<false, 8, NTHR>(a, blockIdx.x);
-        return;
-    }
-    const int chunk = (a.nb_total + 7) >> 3, bx = (int)blockIdx.x - a.lead;
-    const int lb = (bx & 7) * chunk + (a.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
-    if (lb >= a.nb_total) return;
+    __shared__ float red[32];
+    take_args(p);
+    const int chunk = (p.nb_total + 7) >> 3, bx = (int)blockIdx.x;
+    const int lb = (bx & 7) * chunk + (p.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
+    if (lb >= p.nb_total) return;
     const int hw = p.hw, M = MARCH ? p.M : 1, NT = 2 * hw + 1, nwt = NF + 2 * hw;
     const LD lds(hw);
     const int RS = lds.rs;
-    const int n = lb / a.nbp, seg = lb % a.nbp;
+    const int n = lb / p.nseg, seg = lb % p.nseg;
     int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int f = wave / G, g = wave % G;
-    const int L = a.L, W = a.W;
-    const Lens ln = problem_lens(a, n);
-    const int Lt = ln.Lt, Le = ln.Le;
-    const int Lc = valid_columns(a, n), nseg_valid = (Le + BM * M - 1) / (BM * M);
+    const int L = p.L, W = p.W;
+    const StepLens ln = step_lens(p, n);
+    const int Lt = ln.Lt, Le = ln.Le, Lc = ln.Lc, nseg_valid = (Le + BM * M - 1) / (BM * M);
     const int b0 = seg * M, b1 = min(b0 + M, (L + BM - 1) / BM), bv = min(b1, (Le + BM - 1) / BM);   // blocks; those with valid rows
 
     unsigned char *vs = smem + lds.vs;
@@ -188,23 +227,24 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cs = reinterpret_cast<float *>(smem + lds.cs);
     float *wsw = reinterpret_cast<float *>(smem + LD::WS) + 32 * wave;
 
-    const float *vp = a.yt.p + n * a.yt.stride;
+    const float *vp = p.v + n * p.us, *xsp = p.u + n * p.us;
+    float *u_out = p.u_out + n * p.us, *v_out = p.v_out + n * p.us;
     const float *part = p.part_in ? p.part_in + n * p.part_stride : nullptr;
-    const float *lbp = p.log_b.p ? p.log_b.p + n * p.log_b.stride : nullptr;
-    const float *xsp = a.xs.p + n * a.xs.stride;
+    const float *lap = p.log_a ? p.log_a + (long)n * p.lstride : nullptr, *lbp = p.log_b ? p.log_b + (long)n * p.lstride : nullptr;
+    const float *spr = p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr, *spc = p.spoke_c ? p.spoke_c + (long)n * p.sstride : nullptr;
     // rows without an edge: zeros, and this segment's share of v there
     for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR) {
-        a.out_vec.p[n * a.out_vec.stride + t] = 0.f;
-        if (part) p.v_out.p[n * p.v_out.stride + t] = t < Lc ? column_update(vp[t], column_sum(p, part, t, nseg_valid), lbp ? lbp[t] : 0.f) : 0.f;
+        u_out[t] = 0.f;
+        if (part) v_out[t] = t < Lc ? column_update(vp[t], column_sum(p, part, t, nseg_valid), lbp ? lbp[t] : 0.f) : 0.f;
     }
     if (b0 >= bv) return;
     const long moff = (long)n * L * D;
-    const unsigned char *Xb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.X) + moff);
-    const unsigned char *Yb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(a.Y) + moff);
+    const unsigned char *Xb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(p.X) + moff);
+    const unsigned char *Yb = reinterpret_cast<const unsigned char *>(reinterpret_cast<const T *>(p.Y) + moff);
     const int kseg = b0 * NF - hw;   // the segment's first tile, ring slot 0
 
-    // LDS-direct loads of the other side's tiles: one instruction of a wavefront fills 1 KB, RPI rows.  Rows outside the matrix repeat its first or last valid one; they are masked
-    // where they are used.
+    // LDS-direct loads of the other side's tiles: one instruction of a wavefront fills 1 KB, RPI rows.  Rows outside the
+    // matrix repeat its first or last valid one; they are masked where they are used.
     constexpr int RPI = 64 / ST::CPR, IPT = 32 / RPI;
     const unsigned smem_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
     auto dma_rows = [&](long t, int lds_at, bool whole) {   // rows t ... t + RPI - 1 (t uniform)
@@ -240,12 +280,13 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     constexpr int NWIN = (32 * (NF + G * NTW) + NTHR - 1) / NTHR;   // columns of a window per thread
     constexpr int NSUM = MARCH ? 3 : (G * NTW - 1) / NF + 2;        // segments that a column can have sums from, at most
     const float u_first = tid < BM && b0 * BM + tid < Le ? xsp[b0 * BM + tid] : -INFINITY;
-    float win_v[NWIN], win_sum[NWIN][NSUM], win_lb[NWIN];
+    float win_v[NWIN], win_sum[NWIN][NSUM], win_lb[NWIN], win_sp[NWIN];
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
         const int t = min(max(32 * kseg + tid + k * NTHR, 0), L - 1);
         win_v[k] = vp[t];
         win_lb[k] = 0.f;
+        win_sp[k] = (DUST && spc ? spc : vp)[t];   // (v, which is requested anyway, where nobody asks)
         if (lbp) win_lb[k] = lbp[min(t, max(Lc - 1, 0))];
         if (part) {
             const ColumnSegments cg(p, t, nseg_valid);
@@ -253,22 +294,48 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             for (int i = 0; i < NSUM; ++i) win_sum[k][i] = part[cg.at(i)];
         }
     }
+    // Dustbin: its potentials as this step's rows see them (uL is a reference only: the row half-step replaces it)
+    float uL = 0.f, vL = 0.f, to_row = 0.f, to_col = 0.f;   // this thread's share of what its row and its column get
+    float *dust = p.part_out + n * p.part_stride + (long)p.nseg * (32 * (NF * M + 2 * hw));
+    if (DUST) {
+        const float corner = spr ? spr[L] : p.sdb;
+        if (part) {
+            const DustbinPair d = dustbin_pair<NTHR>(p, part, corner, red);
+            uL = d.u; vL = d.v;
+        } else {
+            uL = xsp[L]; vL = vp[L];
+        }
+        if (seg == 0 && tid == 0) {
+            dust[2 * p.nseg] = uL; dust[2 * p.nseg + 1] = vL;
+            if (part) { p.u_fin[n * p.us + L] = uL; v_out[L] = vL; }
+        }
+    }
+    // v of a column from its sums; what the dustbin's row gets from it
+    auto finish_v = [&](int t, float v, float sum, float lb, float sp) {
+        if (DUST && !spc) sp = p.sdb;
+        if (part) {
+            if (DUST) sum += fast_exp2((sp + uL + v) * LOG2E);
+            v = t < Lc ? column_update(v, sum, lb) : 0.f;
+        }
+        if (t >= b0 * BM && t < min(bv * BM, L)) {
+            if (part) v_out[t] = v;
+            if (DUST) to_row += fast_exp2((sp + v + uL) * LOG2E);
+        }
+        return v;
+    };
     OwnerFrag<T, D> xf;
     dma(kseg, nwt, 0);
     xf.load(reinterpret_cast<const T *>(Xb), min((b0 * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
         const int i = tid + k * NTHR, t = 32 * kseg + i;
-        float v = win_v[k];
+        float sum = 0.f;
         if (part) {
             const ColumnSegments cg(p, min(max(t, 0), L - 1), nseg_valid);
-            float sum = 0.f;
 #pragma unroll
             for (int q = 0; q < NSUM; ++q) sum += q < cg.n ? win_sum[k][q] : 0.f;
-            v = t < Lc ? column_update(v, sum, win_lb[k]) : 0.f;
-            if (t >= b0 * BM && t < min(bv * BM, L)) p.v_out.p[n * p.v_out.stride + t] = v;
         }
-        if (i < 32 * nwt) stage_v(i, t, v);
+        if (i < 32 * nwt) stage_v(i, t, finish_v(t, win_v[k], sum, win_lb[k], win_sp[k]));   // (later columns: with their block)
     }
     if (tid < BM) us[tid] = u_first;
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
@@ -284,15 +351,12 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         const int c = lane & 31, h = lane >> 5;
         const int par = MARCH ? (b - b0) & 1 : 0, k0 = b * NF - hw, o_f = (b * NF + f) * 32, o = o_f + c;
         const bool more = MARCH && b + 1 < bv;
-        float spoke = 0.f, spoke_v = 0.f, la = 0.f;   // of this lane's row
-        if (a.dustbin) {
-            spoke = a.spoke_own.p ? a.spoke_own.p[n * a.spoke_own.stride + min(o, L - 1)] : a.sdb2 * LN2;
-            spoke_v = vp[L];
-        }
-        if (a.olog.p) la = a.olog.p[n * a.olog.stride + min(o, Le - 1)];
+        float spoke = 0.f, la = 0.f;   // of this lane's row
+        if (DUST) spoke = spr ? spr[min(o, L - 1)] : p.sdb;
+        if (lap) la = lap[min(o, Le - 1)];
         // what the next block adds (a thread below BM: one column, one row): requested now, stored after this block's last
         // use of the slots' old content
-        float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nlb = 0.f;
+        float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nlb = 0.f, nsp = 0.f;
         const int nt = 32 * (k0 + nwt) + tid, no = (b + 1) * BM + tid;
         const int nq = min(segment_of(p, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
         auto request_tiles = [&]() {
@@ -305,6 +369,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             nv = vp[tc];
             nu = xsp[min(no, Le - 1)];
             if (lbp) nlb = lbp[min(tc, max(Lc - 1, 0))];
+            nsp = (DUST && spc ? spc : vp)[tc];
             if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
                 const float *pp = part + (long)seg * (32 * (NF * M + 2 * hw)) + (tc - 32 * kseg);
 #pragma unroll
@@ -434,7 +499,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                         E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 3], y.w, E[s], 0, 0, 0);
                     }
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) E[s][r] = fast_exp2(fmaf(E[s][r], a.c2, ci[r] + vt));
+                    for (int r = 0; r < 16; ++r) E[s][r] = fast_exp2(fmaf(E[s][r], p.c2, ci[r] + vt));
                     if (!interior(s)) mask(E[s], 32 * (kw + s), true);
 #pragma unroll
                     for (int r = 0; r < 16; ++r) add_rows(E[s], r);
@@ -475,7 +540,8 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         float tot = 0.f;
 #pragma unroll
         for (int i = 0; i < G; ++i) tot += rs[(f * G + i) * 32 + c];
-        if (a.dustbin) tot += fast_exp2((spoke + spoke_v + u_old) * LOG2E);   // spoke edge (o, dustbin element of the other side)
+        const float edge = DUST ? fast_exp2((spoke + vL + u_old) * LOG2E) : 0.f;   // spoke (o, dustbin of the other side)
+        tot += edge;
         float u_new = 0.f, w = 0.f;
         if (o < Le) {
             if (u_old == -INFINITY) {
@@ -485,10 +551,11 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             } else {
                 u_new = u_old - LN2 * fast_log2(tot) + la;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
-                if (a.olog.p) w *= __expf(la);
+                if (lap) w *= __expf(la);
             }
         }
         if (h == 0) wsw[c] = w;
+        if (h == 0 && g == 0 && o < Le) to_col += edge * w;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         f32x16 wv;
 #pragma unroll
@@ -512,22 +579,28 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             const float y = halves_sum(x, x);
             if (h == 0) cpw[32 * (NTW - 1) + c] = y;
         }
-        float v_new = nv;
         if (more && tid < BM) {
-            if (part && nt < L) {
-                const float sum = np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f);
-                v_new = nt < Lc ? column_update(nv, sum, nlb) : 0.f;
-            }
+            const float v_new = finish_v(nt, nv, np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f), nlb, nsp);
             int sl = 32 * (base + nwt) + tid;
             if (sl >= 32 * RS) sl -= 32 * RS;
             stage_v(sl, nt, v_new);
             us[(par ^ 1) * BM + tid] = no < Le ? nu : -INFINITY;
         }
+        if (DUST && !more) {   // the segment's last block: every thread has added its share
+#pragma unroll
+            for (int s = 32; s >= 1; s >>= 1) { to_row += __shfl_xor(to_row, s); to_col += __shfl_xor(to_col, s); }
+            if (lane == 0) { red[wave] = to_row; red[16 + wave] = to_col; }
+        }
         __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
         __syncthreads();
-        // stores to memory only now: the wait above would wait for them as well
-        if (h == 0 && g == 0 && o < L) a.out_vec.p[n * a.out_vec.stride + o] = u_new;
-        if (more && part && tid < BM && nt >= b0 * BM && nt < min(bv * BM, L)) p.v_out.p[n * p.v_out.stride + nt] = v_new;
+        // rows' stores only now: the wait above would wait for them as well
+        if (h == 0 && g == 0 && o < L) u_out[o] = u_new;
+        if (DUST && !more && tid < 2) {
+            float s = 0.f;
+#pragma unroll
+            for (int i = 0; i < NF * G; ++i) s += red[16 * tid + i];
+            dust[tid * p.nseg + seg] = s;
+        }
         // the block's column sums onto the segment's; tiles that no later block of the segment meets are done
         float *po = p.part_out + n * p.part_stride + (long)seg * (32 * (NF * M + 2 * hw));
         if constexpr (!MARCH) {
@@ -565,35 +638,32 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     }
 }
 
-// v from the column sums of a step: the last step of a run, and every step with a dustbin, whose spokes need u of all
-// rows.  The arguments are those of the column half-step: yt = u', xs = v before the step (may be out_vec), lengths of the
-// columns first.  With a dustbin the leading workgroups compute its column's element.
+// v from the column sums of a step that no step follows (v_out may be p.v).
 __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
 {
-    const SweepArgs &a = p.s;
-    const int nprob = a.nb_total / a.nbp;
-    if ((int)blockIdx.x < a.lead) {
-        if ((int)blockIdx.x < nprob) dustbin_element<false, 8>(a, blockIdx.x);
-        return;
-    }
-    const int lb = (int)blockIdx.x - a.lead;
-    const int n = lb / a.nbp, t = (lb % a.nbp) * NTHREADS + threadIdx.x;
-    if (t >= a.L) return;
-    const Lens ln = problem_lens(a, n);   // own = columns: Le of them have an edge
-    SweepArgs r = a;                      // the rows' view, for the number of blocks that wrote sums
-    r.len_own = a.len_oth; r.len_oth = a.len_own;
-    const int rows = problem_lens(r, n).Le;
-    const float v = a.xs.p[n * a.xs.stride + t];
-    float out = 0.f;
-    if (t < ln.Le) {
-        float sum = column_sum(p, p.part_in + n * p.part_stride, t, (rows + 32 * p.NF * p.M - 1) / (32 * p.NF * p.M));
-        if (a.dustbin) {
-            const float sp2 = a.spoke_own.p ? a.spoke_own.p[n * a.spoke_own.stride + t] * LOG2E : a.sdb2;
-            sum += fast_exp2(sp2 + a.yt.p[n * a.yt.stride + a.L] * LOG2E + v * LOG2E);
+    __shared__ float red[32];
+    const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk, blk = blockIdx.x % nblk, t = blk * NTHREADS + threadIdx.x;
+    const float *part = p.part_in + n * p.part_stride, *spr = p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr;
+    float *v_out = p.v_out + n * p.us;
+    float uL = 0.f;
+    if (p.dustbin) {
+        const DustbinPair d = dustbin_pair<NTHREADS>(p, part, spr ? spr[p.L] : p.sdb, red);
+        uL = d.u;
+        if (blk == 0 && threadIdx.x == 0) {
+            p.u_fin[n * p.us + p.L] = d.u;
+            v_out[p.L] = d.v;
         }
-        out = column_update(v, sum, a.olog.p ? a.olog.p[n * a.olog.stride + t] : 0.f);
     }
-    a.out_vec.p[n * a.out_vec.stride + t] = out;
+    if (t >= p.L) return;
+    const StepLens ln = step_lens(p, n);
+    float out = 0.f;
+    if (t < ln.Lc) {
+        const float v = p.v[n * p.us + t];
+        float sum = column_sum(p, part, t, (ln.Le + 32 * p.NF * p.M - 1) / (32 * p.NF * p.M));
+        if (p.dustbin) sum += fast_exp2(((p.spoke_c ? p.spoke_c[(long)n * p.sstride + t] : p.sdb) + uL + v) * LOG2E);
+        out = column_update(v, sum, p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f);
+    }
+    v_out[t] = out;
 }
 
 }  // namespace
