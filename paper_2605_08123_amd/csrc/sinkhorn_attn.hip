@@ -449,14 +449,17 @@ template <typename T, int D> int sweep(Call &cx, int mode, const SweepArgs &a, i
 // Blocks of NF fragments of 32 rows, G wavefronts per fragment with NTW tiles each, M blocks per workgroup (a segment);
 // hw = ceil(W / 32).  NF = 0: the half-steps run one by one.
 struct StepShape { int NF, G, NTW, hw, M, kind; };
-constexpr int STEP_LDS = 159 * 1024;   // dynamic part; the dustbin element has a little of its own
+constexpr int STEP_LDS = 159 * 1024;
 // The instances, by the bytes of a 32-row tile (TB).
 #define SKA_STEP_SHAPES(X) \
-    X(TB <= 16384, 2, 2, 3, STEP_BLOCK) X(TB <= 16384, 4, 1, 5, STEP_BLOCK) X(TB <= 8192, 2, 2, 5, STEP_BLOCK) \
-    X(TB <= 8192, 8, 1, 9, STEP_BLOCK) X(TB <= 8192, 2, 4, 5, STEP_BLOCK) X(TB == 8192, 4, 1, 9, STEP_BLOCK) \
-    X(TB == 8192 && sizeof(T) == 4, 1, 4, 5, STEP_BLOCK) X(TB == 16384, 1, 2, 5, STEP_BLOCK) X(TB <= 4096, 4, 2, 9, STEP_BLOCK) \
-    X(TB <= 4096, 8, 1, 9, STEP_MARCH) X(TB <= 4096, 4, 2, 9, STEP_MARCH) X(TB == 8192, 2, 4, 5, STEP_TIGHT) \
-    X(TB <= 4096, 2, 4, 9, STEP_BLOCK)
+    X(TB <= 16384, 2, 2, 2, STEP_BLOCK) X(TB <= 16384, 2, 2, 3, STEP_BLOCK) X(TB <= 8192, 2, 2, 4, STEP_BLOCK) X(TB <= 8192, 2, 2, 5, STEP_BLOCK) \
+    X(TB <= 16384, 4, 1, 3, STEP_BLOCK) X(TB <= 16384, 4, 1, 5, STEP_BLOCK) X(TB == 8192, 4, 1, 7, STEP_BLOCK) X(TB == 8192, 4, 1, 9, STEP_BLOCK) \
+    X(TB == 16384, 1, 2, 5, STEP_BLOCK) X(TB == 8192 && sizeof(T) == 4, 1, 4, 5, STEP_BLOCK) \
+    X(TB <= 8192, 8, 1, 7, STEP_BLOCK) X(TB <= 8192, 8, 1, 9, STEP_BLOCK) X(TB <= 4096, 8, 1, 7, STEP_MARCH) X(TB <= 4096, 8, 1, 9, STEP_MARCH) \
+    X(TB <= 8192, 2, 4, 3, STEP_BLOCK) X(TB <= 8192, 2, 4, 4, STEP_BLOCK) X(TB <= 8192, 2, 4, 5, STEP_BLOCK) X(TB <= 4096, 2, 4, 9, STEP_BLOCK) \
+    X(TB == 8192, 2, 4, 3, STEP_TIGHT) X(TB == 8192, 2, 4, 4, STEP_TIGHT) X(TB == 8192, 2, 4, 5, STEP_TIGHT) \
+    X(TB <= 4096, 4, 2, 6, STEP_MARCH) X(TB <= 4096, 4, 2, 7, STEP_MARCH) X(TB <= 4096, 4, 2, 8, STEP_MARCH) X(TB <= 4096, 4, 2, 9, STEP_MARCH) \
+    X(TB <= 4096, 4, 2, 9, STEP_BLOCK) X(TB <= 4096, 4, 2, 7, STEP_BLOCK) X(TB <= 4096, 4, 2, 8, STEP_BLOCK)
 template <typename T, int D> constexpr int step_tile_bytes = StepTile<T, D>::BYTES;
 template <typename T, int D> int step_lds(const StepShape &sh)
 {
@@ -481,6 +484,11 @@ template <typename T, int D> int step_lds(const StepShape &sh)
 //   rows 2701 / 2253 / 3181; 5600 rows (1,4,5) 381 (2,4,5) 436
 //   fp32 d = 128 (16 KB tiles): W = 32 32768 rows (2,2,3) 393 (4,1,5) 329; W = 128 5600 rows 539, half-steps 989; 32768 rows
 //   1532 / 995
+//   NTW is the least that the band's tiles need (absent ones cost as much as others): d = 64, W = 32: 262144 rows (4,1,5) 413
+//   (4,1,3) 333; W = 96: (8,1,9) 576 (8,1,7) 507; W = 160: (4,2,9) 974 (4,2,6) 738, half-steps 974; W = 192: 933, (4,2,7) 794, 888;
+//   W = 224: (4,2,9) 917 (4,2,8) 853; 16384 rows, W = 160: (2,4,5) 168 (2,4,3) 146; 32768 rows (2,4,3) 177 (4,2,7) 185, W = 192:
+//   (2,4,4) 266 (4,2,7) 190.  d = 128, W = 160: 131072 rows (2,4,5) 850 (2,4,3) 715.  fp32 d = 64, 8000 rows, W = 160: (1,4,5) 324
+//   (2,4,3) 311, W = 192: 343, (2,4,4) 372.  d = 32, W = 160: 262144 rows (4,2,6) 620, 524288 rows 1137, half-steps 656 / 935
 //   W = 300 .. 480 (2,4,9): 16384 rows 244 .. 271, half-steps 469 .. 618; 32768 rows 414 .. 456 / 470 .. 619; beyond, the 36
 //   tiles that a block of 64 rows reads are what bounds it
 template <typename T, int D> StepShape step_shape(int N, int L, int W)
@@ -492,30 +500,31 @@ template <typename T, int D> StepShape step_shape(int N, int L, int W)
     auto take = [&](int NF, int G, int NTW) { sh.NF = NF; sh.G = G; sh.NTW = NTW; };
     bool march = false;
     if (hw <= 2) {
-        if (rows <= (TB <= 4096 ? 49152 : TB == 8192 ? 32768 : 16384)) take(2, 2, 3);
-        else take(4, 1, 5);
+        if (rows <= (TB <= 4096 ? 49152 : TB == 8192 ? 32768 : 16384)) take(2, 2, hw < 2 ? 2 : 3);
+        else take(4, 1, hw < 2 ? 3 : 5);
     } else if (hw <= 4) {
         if (TB == 16384) {
             if (rows <= 8192) take(1, 2, 5);
         } else if (rows <= (TB <= 4096 ? 49152 : 16384)) {
-            take(2, 2, 5);
+            take(2, 2, hw + 1);
         } else if (TB == 8192 && rows <= 32768) {
-            take(4, 1, 9);
+            take(4, 1, 2 * hw + 1);
         } else {
-            take(8, 1, 9);
+            take(8, 1, 2 * hw + 1);
             march = TB <= 4096;
         }
     } else if (hw <= 8) {
+        const int ntw = hw == 5 ? 3 : hw <= 7 ? 4 : 5;   // of four wavefronts
         if (TB <= 4096) {
-            if (rows <= 16384) {
-                take(2, 4, 5);
+            if (rows <= (hw == 5 ? 32768 : 16384)) {
+                take(2, 4, ntw);
             } else if (TB == 4096 || rows <= 196608) {
-                take(4, 2, 9);
+                take(4, 2, hw + 1);
                 march = true;
             }
         } else if (TB == 8192) {
-            if (sizeof(T) == 4 && rows <= 8192) take(1, 4, 5);
-            else take(2, 4, 5);
+            if (sizeof(T) == 4 && hw > 5 && rows <= 8192) take(1, 4, 5);
+            else take(2, 4, ntw);
             march = rows > 32768;
         }
     } else if (hw <= 15 && TB <= 4096 && rows <= 32768) {
@@ -540,18 +549,18 @@ inline long step_part_stride(const StepShape &sh, int L, bool dustbin)   // floa
     const long nseg = step_segments(sh, L);
     return nseg * 32 * (sh.NF * sh.M + 2 * sh.hw) + (dustbin ? 2 * nseg + 2 : 0);
 }
-template <typename T, int D, int NF, int G, int NTW, int KIND, bool DUST> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
+template <typename T, int D, int NF, int G, int NTW, int KIND, int DB> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
     p.nb_total = p.nseg * N;
     const int lds = StepLds<T, D, NF, G, NTW, KIND>(p.hw).total;
     static bool raised[MAX_DEVICES];
     if (!raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, DUST>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, DB>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, DUST>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
+    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, DB>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
 template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape &sh, int N, hipStream_t st, int dev)
@@ -559,8 +568,11 @@ template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape
     constexpr int TB = step_tile_bytes<T, D>;
 #define SKA_LAUNCH(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
-        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) \
-            return p.dustbin ? launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, true>(p, N, st, dev) : launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, false>(p, N, st, dev);
+        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) { \
+            constexpr bool ANY = KIND_ == STEP_BLOCK; \
+            if (!ANY && p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_DUSTBIN>(p, N, st, dev); \
+            return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_PLAIN>(p, N, st, dev); \
+        }
     SKA_STEP_SHAPES(SKA_LAUNCH)
 #undef SKA_LAUNCH
     return SKA_EUNSUPPORTED;

@@ -16,8 +16,8 @@ namespace {
 // of the 2 ceil(W / 32) + 1 tiles that its band meets.  The other side's rows that a block meets lie in LDS as
 // a whole (written by LDS-direct loads, 16-byte chunks swizzled on the way), so the evaluation runs without a barrier.
 // With MARCH a workgroup walks M blocks (a segment) on a ring of tiles: a block adds NF tiles, requested one block ahead.
-//   Column sums are summed over the fragments of a block and the blocks of a segment in LDS, and written per
-// segment; a column has those of at most ceil(2 ceil(W / 32) / (NF M)) + 1 segments, which the next launch adds up in a fixed
+//   Column sums are summed over the fragments of a block in LDS and over the blocks of a segment in registers (a thread keeps
+// its places of the ring), and written per segment; a column has those of at most ceil(2 ceil(W / 32) / (NF M)) + 1 segments, which the next launch adds up in a fixed
 // order where it needs v' (vfinal_kernel where no step follows).
 //   Every row and every column carries its own potential as stabiliser: after one step the row sums of a
 // column-normalised plan lie between 1 / (2 W + 1) and 2 W + 1 (unit targets), and likewise the column sums.
@@ -34,8 +34,9 @@ namespace {
 //   DUST: every segment also writes what the dustbin's row and its column get from it, and the next launch makes the dustbin's
 // two potentials of them (dustbin_pair), each workgroup for itself.  A launch between the steps (the column sums and
 // the dustbin's elements, one long workgroup each) took a fifth of the step: forward and backward of 8 problems of L = 16384,
-// W = 256, T = 20 1022 -> 863 us, 16 of 1501, W = 64 with learned tokens 396 -> 356.  A template parameter, since
-// its branches and registers cost calls without a dustbin 4 % (2 problems of 262144: 2730 -> 2650 us).
+// W = 256, T = 20 1022 -> 863 us, 8 of 5000, W = 128 with learned tokens 396 -> 357.  In segments a
+// template parameter (DB), since its branches and registers cost calls without a dustbin 4 % (2 problems of 262144: 2730 -> 2650
+// us); single blocks have registers to spare and read a flag.
 //   The arguments are a struct of their own, read as a whole at a kernel's start (take_args): fetched where they are first
 // used they cost a short launch one wait of some hundred cycles after another.
 struct StepArgs {
@@ -61,7 +62,7 @@ __device__ __forceinline__ void take_args(const StepArgs &p)
 {
     asm volatile("" ::"s"(p.X), "s"(p.Y), "s"(p.v), "s"(p.u), "s"(p.u_out), "s"(p.v_out), "s"(p.part_in), "s"(p.part_out),
                  "s"(p.log_a), "s"(p.log_b), "s"(p.len_q), "s"(p.len_k), "s"(p.spoke_c), "s"(p.us), "s"(p.part_stride), "s"(p.L),
-                 "s"(p.W), "s"(p.M), "s"(p.hw), "s"(p.nseg), "s"(p.rcp), "s"(p.nb_total), "s"(p.rev), "s"(p.lstride));
+                 "s"(p.W), "s"(p.M), "s"(p.hw), "s"(p.nseg), "s"(p.rcp), "s"(p.nb_total), "s"(p.rev), "s"(p.lstride), "s"(p.dustbin));
 }
 // Valid lengths of problem n: Lt columns, Le rows and Lc columns with at least one band edge.
 struct StepLens { int Lt, Le, Lc; };
@@ -173,30 +174,28 @@ template <typename T, int D> struct StepTile {
 // W = 256 1321 us block by block, 916 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
 // window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
 enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
+enum StepDustbin { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY };   // without, with a dustbin, as the arguments say
 template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds {   // offsets in bytes
     static constexpr int RSUM = 0;                              // [NF][G][32] row sums
     static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
     static constexpr int US = WS + NF * G * 128;                // [2][32 NF] potentials of the rows
     static constexpr bool MARCH = KIND != STEP_BLOCK;
-    static constexpr int TWO = MARCH ? 2 : 1;
     static_assert(KIND != STEP_TIGHT || G > 1, "the exchange of row sums says that the products are done");
-    static constexpr int CP = US + TWO * NF * 128;                // [2][NF][G NTW 32] column sums of a fragment
-    // two buffers where a wavefront can write its sums of the next block while others read these: with G > 1 the exchange
-    // of row sums lies in between
-    static constexpr int CP2 = MARCH && G == 1 ? 2 : 1;
-    static constexpr int Y = CP + CP2 * NF * G * NTW * 128;     // ring of the other side's tiles
+    // With G > 1 that exchange lies between a wavefront's reads and its next block's writes; without it there are two buffers.
+    static constexpr int TWO = MARCH && G == 1 ? 2 : 1;
+    static constexpr int CP = US + TWO * NF * 128;              // [TWO][NF][G NTW 32] column sums of a fragment
+    static constexpr int Y = CP + TWO * NF * G * NTW * 128;   // ring of the other side's tiles
     static constexpr int VB = sizeof(T) == 2 ? 8 : 4;           // bytes of a column's potential
-    int rs, vs, cs, total;
+    int rs, vs, total;
     __host__ __device__ StepLds(int hw)
     {
         rs = NF + 2 * hw + (KIND == STEP_MARCH ? NF : 0);   // ring slots: the window of a block (and the tiles the next one adds)
         vs = Y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
-        cs = vs + rs * 32 * VB;                // MARCH: [32 rs] column sums of the segment so far
-        total = cs + (MARCH ? rs * 128 : 0);
+        total = vs + rs * 32 * VB;
     }
 };
 
-template <typename T, int D, int NF, int G, int NTW, int KIND, bool DUST>
+template <typename T, int D, int NF, int G, int NTW, int KIND, int DB>
 __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 {
     using ST = StepTile<T, D>;
@@ -204,8 +203,8 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     constexpr bool MARCH = KIND != STEP_BLOCK, TIGHT = KIND == STEP_TIGHT;
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
+    const bool DUST = DB == STEP_ANY ? p.dustbin != 0 : DB == STEP_DUSTBIN;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ float red[32];
     take_args(p);
     const int chunk = (p.nb_total + 7) >> 3, bx = (int)blockIdx.x;
     const int lb = (bx & 7) * chunk + (p.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
@@ -224,7 +223,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 
     unsigned char *vs = smem + lds.vs;
     float *us = reinterpret_cast<float *>(smem + LD::US);
-    float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cs = reinterpret_cast<float *>(smem + lds.cs);
+    float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cp0 = reinterpret_cast<float *>(smem + LD::CP);
     float *wsw = reinterpret_cast<float *>(smem + LD::WS) + 32 * wave;
 
     const float *vp = p.v + n * p.us, *xsp = p.u + n * p.us;
@@ -300,7 +299,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     if (DUST) {
         const float corner = spr ? spr[L] : p.sdb;
         if (part) {
-            const DustbinPair d = dustbin_pair<NTHR>(p, part, corner, red);
+            const DustbinPair d = dustbin_pair<NTHR>(p, part, corner, rs);
             uL = d.u; vL = d.v;
         } else {
             uL = xsp[L]; vL = vp[L];
@@ -343,13 +342,15 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 
     const int j0 = g * NTW, klast = (Lt - 1) / TT;
     int base = 0;   // ring slot of the block's first tile
+    constexpr int NPOS = (32 * ((TIGHT ? 1 : 2) * NF + G * NTW) + NTHR - 1) / NTHR;   // ring positions of a thread, always the same ones
+    [[maybe_unused]] float acc[NPOS];   // MARCH: the segment's column sums there so far
     for (int b = b0; b < (MARCH ? bv : b0 + 1); ++b) {
         // what depends on the lane alone is computed again in every block: kept across the loop it would take the
         // registers that the plan entries need
         if constexpr (MARCH) asm volatile("" : "+v"(tid));
         lane = tid & 63;
         const int c = lane & 31, h = lane >> 5;
-        const int par = MARCH ? (b - b0) & 1 : 0, k0 = b * NF - hw, o_f = (b * NF + f) * 32, o = o_f + c;
+        const int par = LD::TWO == 2 ? (b - b0) & 1 : 0, k0 = b * NF - hw, o_f = (b * NF + f) * 32, o = o_f + c;
         const bool more = MARCH && b + 1 < bv;
         float spoke = 0.f, la = 0.f;   // of this lane's row
         if (DUST) spoke = spr ? spr[min(o, L - 1)] : p.sdb;
@@ -564,7 +565,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             wv[4 * q + 0] = v4.x; wv[4 * q + 1] = v4.y; wv[4 * q + 2] = v4.z; wv[4 * q + 3] = v4.w;
         }
         // column sums of the fragment
-        float *cp = reinterpret_cast<float *>(smem + LD::CP) + (LD::CP2 == 2 ? par : 0) * NF * G * NTW * 32;
+        float *cp = cp0 + par * NF * G * NTW * 32;
         float *cpw = cp + (f * G * NTW + j0) * 32;
         auto col = [&](const f32x16 &e) {
             float x = 0.f, y = 0.f;
@@ -584,12 +585,12 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             int sl = 32 * (base + nwt) + tid;
             if (sl >= 32 * RS) sl -= 32 * RS;
             stage_v(sl, nt, v_new);
-            us[(par ^ 1) * BM + tid] = no < Le ? nu : -INFINITY;
+            us[(LD::TWO == 2 ? par ^ 1 : 0) * BM + tid] = no < Le ? nu : -INFINITY;
         }
         if (DUST && !more) {   // the segment's last block: every thread has added its share
 #pragma unroll
             for (int s = 32; s >= 1; s >>= 1) { to_row += __shfl_xor(to_row, s); to_col += __shfl_xor(to_col, s); }
-            if (lane == 0) { red[wave] = to_row; red[16 + wave] = to_col; }
+            if (lane == 0) { wsw[0] = to_row; wsw[1] = to_col; }   // (its weights have been read)
         }
         __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
         __syncthreads();
@@ -598,7 +599,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         if (DUST && !more && tid < 2) {
             float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < NF * G; ++i) s += red[16 * tid + i];
+            for (int i = 0; i < NF * G; ++i) s += reinterpret_cast<const float *>(smem + LD::WS)[32 * i + tid];
             dust[tid * p.nseg + seg] = s;
         }
         // the block's column sums onto the segment's; tiles that no later block of the segment meets are done
@@ -617,21 +618,20 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             }
             return;
         }
-        constexpr int NPOS = (32 * (2 * NF + G * NTW) + NTHR - 1) / NTHR;   // ring positions of a thread, always the same ones
 #pragma unroll
         for (int k = 0; k < NPOS; ++k) {
             const int i = tid + k * NTHR;
             int wt = (i >> 5) - base;
             if (wt < 0) wt += RS;
             if (i >= 32 * RS || wt >= nwt) continue;
-            float x[NF], s = cs[i];
+            float s = b == b0 || wt >= nwt - NF ? 0.f : acc[k];
+            float x[NF];
 #pragma unroll
             for (int q = 0; q < NF; ++q) x[q] = cp[(q * G * NTW + min(max(wt - q, 0), NT - 1)) * 32 + (i & 31)];
-            if (b == b0 || wt >= nwt - NF) s = 0.f;
 #pragma unroll
             for (int q = 0; q < NF; ++q) s += (unsigned)(wt - q) < (unsigned)NT ? x[q] : 0.f;
             if (!more || wt < NF) po[32 * (k0 + wt - kseg) + (i & 31)] = s;
-            else cs[i] = s;
+            acc[k] = s;
         }
         base += NF;
         if (base >= RS) base -= RS;

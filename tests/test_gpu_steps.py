@@ -27,7 +27,10 @@ SHORT = [  # kind, dtype, d, N, L, W, T, R
     ("varlen", "bf16", 64, 4, 600, 50, 3, 2), ("varlen", "f32", 64, 4, 500, 100, 2, 2), ("varlen", "bf16", 64, 4, 900, 200, 3, 1),
     ("marginals", "bf16", 64, 2, 600, 100, 3, 2), ("marginals", "f32", 32, 2, 400, 20, 2, 2), ("masked", "bf16", 64, 2, 500, 31, 3, 2),
     ("masked", "f32", 64, 2, 700, 128, 3, 2), ("dustbin", "bf16", 64, 2, 701, 30, 3, 2), ("dustbin", "f32", 32, 2, 500, 100, 1, 2),
-    ("dustbin", "bf16", 128, 2, 600, 222, 2, 2), ("dustbin", "bf16", 64, 1, 9000, 256, 2, 1)]
+    ("dustbin", "bf16", 128, 2, 600, 222, 2, 2), ("dustbin", "bf16", 64, 1, 9000, 256, 2, 1),
+    ("plain", "bf16", 64, 1, 1000, 160, 3, 2), ("plain", "bf16", 64, 2, 777, 161, 3, 2), ("plain", "bf16", 32, 1, 900, 192, 3, 1),
+    ("plain", "bf16", 128, 1, 700, 150, 3, 2), ("dustbin", "bf16", 128, 1, 900, 180, 2, 1), ("plain", "f32", 64, 1, 700, 160, 3, 2),
+    ("plain", "f32", 64, 1, 700, 161, 2, 2), ("dustbin", "f32", 64, 2, 300, 90, 2, 2), ("plain", "f32", 128, 1, 300, 32, 3, 2)]
 LONG = [  # other block shapes; segments of several blocks, also ragged ones and ones that end inside a problem
     ("plain", "bf16", 64, 1, 50000, 20, 2, 1), ("plain", "bf16", 64, 1, 50001, 100, 2, 2), ("plain", "bf16", 64, 1, 66000, 97, 3, 1),
     ("plain", "bf16", 64, 3, 40001, 128, 2, 1), ("plain", "bf16", 64, 1, 17000, 130, 2, 1), ("plain", "bf16", 64, 1, 40000, 256, 3, 1),
@@ -38,7 +41,11 @@ LONG = [  # other block shapes; segments of several blocks, also ragged ones and
     ("plain", "bf16", 128, 600, 100, 130, 2, 1), ("plain", "f32", 32, 1, 60000, 100, 2, 1), ("plain", "f32", 32, 1, 60000, 256, 2, 1),
     ("plain", "f32", 64, 1, 40000, 128, 2, 1), ("plain", "f32", 128, 1, 20000, 64, 2, 1), ("varlen", "bf16", 64, 4, 40000, 256, 3, 1),
     ("varlen", "bf16", 64, 8, 20000, 70, 2, 1), ("marginals", "bf16", 64, 2, 70000, 128, 2, 1), ("masked", "bf16", 64, 2, 70000, 129, 2, 1),
-    ("dustbin", "bf16", 64, 1, 70000, 128, 2, 1), ("dustbin", "f32", 32, 1, 60000, 200, 2, 1)]
+    ("dustbin", "bf16", 64, 1, 70000, 128, 2, 1), ("dustbin", "f32", 32, 1, 60000, 200, 2, 1),
+    ("plain", "bf16", 64, 1, 17000, 170, 2, 1), ("plain", "bf16", 64, 1, 17001, 200, 2, 1), ("plain", "bf16", 64, 1, 40000, 150, 2, 2),
+    ("dustbin", "bf16", 64, 1, 40001, 190, 2, 1), ("plain", "bf16", 128, 1, 40001, 160, 2, 1), ("dustbin", "bf16", 128, 1, 20000, 90, 2, 1),
+    ("plain", "bf16", 128, 1, 40000, 70, 2, 1), ("plain", "bf16", 128, 1, 34000, 170, 2, 2), ("dustbin", "bf16", 64, 1, 70000, 96, 2, 1),
+    ("plain", "f32", 64, 1, 10000, 170, 2, 1), ("plain", "bf16", 128, 1, 40000, 16, 2, 1), ("dustbin", "bf16", 64, 1, 60000, 20, 2, 1)]
 
 
 @pytest.mark.parametrize("case", SHORT + LONG, ids=lambda c: "-".join(map(str, c)))
