@@ -17,26 +17,30 @@ namespace {
 // a whole (written by LDS-direct loads, 16-byte chunks swizzled on the way), so the evaluation runs without a barrier.
 // With MARCH a workgroup walks M blocks (a segment) on a ring of tiles: a block adds NF tiles, requested one block ahead.
 //   Column sums are summed over the fragments of a block in LDS and over the blocks of a segment in registers (a thread keeps
-// its places of the ring), and written per segment; a column has those of at most ceil(2 ceil(W / 32) / (NF M)) + 1 segments, which the next launch adds up in a fixed
-// order where it needs v' (vfinal_kernel where no step follows).
+// its places of the ring), and written per segment; a column has those of at most ceil(2 ceil(W / 32) / (NF M)) + 1
+// segments, which the next launch adds up in a fixed order where it needs v' (vfinal_kernel where no step follows).
 //   Every row and every column carries its own potential as stabiliser: after one step the row sums of a
 // column-normalised plan lie between 1 / (2 W + 1) and 2 W + 1 (unit targets), and likewise the column sums.
 //   What bounds it: the issue slots of the SIMDs.  Per tile and wavefront 16 exponentials, 16 adds, 16 multiply-adds, five
-// products at d = 64, five 16-byte LDS reads; 18 tiles of a SIMD take about 6000 cycles, what a block does around them (the
-// exchange of row sums, the column sums, staging) about 4000 more.  Small calls are bound by latency from start to end: a
-// launch of short blocks is 5 us, 2.3 of them until the first product.  Forward of T = 16, R = 2 steps, bf16, d = 64, us, by
-// half-steps -> by steps: 8 problems of L = 700, W = 64 210 -> 115; 16 of 3000, W = 128 312 -> 196; 32 of 4096, W = 128
-// 467 -> 340; 8 of 32768, W = 64 708 -> 427, W = 256 1094 -> 948; 2 of 262144, W = 256 1941 -> 1757.  fp32: 8 of 4096, W = 128
-// 607 -> 370 (matrix instructions: half as many).
-//   The potentials enter through the products (potential_row): as 16 adds per tile they took 6 % of a long call, and as
+// products at d = 64, five 16-byte LDS reads.  A block of a long call (two wavefronts of nine tiles per SIMD) takes 13200
+// cycles: 7700 for the evaluation, 5500 for the exchange of row sums, the column sums, the reduction and the two barriers,
+// which the SIMD's two wavefronts go through together.  A launch's start (arguments, the first window) is 9000 more.  Two
+// independent workgroups of half the size per CU would overlap these phases: W = 128 (4,1,9) 960 us instead of 990 at
+// 524288 rows, but 588 instead of 577 at 262144; at W = 256 two windows fit LDS only if the fragments' column sums
+// share their place by LDS atomics, which cost more than that (900 -> 1120).  Small calls are bound by latency from start to
+// end: a launch of short blocks is 5 us, 2.3 of them until the first product.
+//   Forward of T = 16, R = 2 steps, bf16, d = 64, us, by half-steps -> by steps: 8 problems of L = 700, W = 64 210 -> 117; 4 of
+// 3000, W = 128 266 -> 155; 32 of 4096, W = 128 460 -> 327; 4 of 65536, W = 64 702 -> 416, W = 256 1085 -> 900; 2 of 262144,
+// W = 256 1900 -> 1676.  fp32: 8 of 4096, W = 128 607 -> 370 (matrix instructions: half as many).
+//   The potentials enter through the products (potential_parts): as 16 adds per tile they took 6 % of a long call, and as
 // the products' initial accumulator 16 registers.  The products of a tile are issued among the exponentials of the tile
 // before it, in an order that scheduling barriers pin: left to itself the compiler puts all products first.
 //   DUST: every segment also writes what the dustbin's row and its column get from it, and the next launch makes the dustbin's
 // two potentials of them (dustbin_pair), each workgroup for itself.  A launch between the steps (the column sums and
 // the dustbin's elements, one long workgroup each) took a fifth of the step: forward and backward of 8 problems of L = 16384,
-// W = 256, T = 20 1022 -> 863 us, 8 of 5000, W = 128 with learned tokens 396 -> 357.  In segments a
-// template parameter (DB), since its branches and registers cost calls without a dustbin 4 % (2 problems of 262144: 2730 -> 2650
-// us); single blocks have registers to spare and read a flag.
+// W = 256, T = 20 1022 -> 863 us, 8 of 5000, W = 128 with learned tokens 396 -> 357.  In segments a template parameter (DB),
+// since its branches and registers cost calls without a dustbin 4 % (2 problems of 262144: 2730 -> 2650 us); single blocks
+// have registers to spare and read a flag.
 //   The arguments are a struct of their own, read as a whole at a kernel's start (take_args): fetched where they are first
 // used they cost a short launch one wait of some hundred cycles after another.
 struct StepArgs {
@@ -77,12 +81,20 @@ __device__ __forceinline__ StepLens step_lens(const StepArgs &p, int n)
 // x / SL (tiles per segment) as a multiplication: exact for x < 2^20 and SL <= 2^12, since x (SL - 1) < 2^32
 inline unsigned segment_reciprocal(int SL) { return SL == 1 ? 0u : (unsigned)((0x100000000ull + SL - 1) / SL); }
 __device__ __forceinline__ int segment_of(const StepArgs &p, int x) { return p.rcp ? (int)__umulhi((unsigned)x, p.rcp) : x; }
-// v' of a column from its old value and its column sum; the marks as in the half-steps' epilogue
-__device__ __forceinline__ float column_update(float v, float sum, float log_b)
+// What x in base 2 lost by rounding, as the evaluation takes it (x * LOG2E in fp32): a whole row's or column's entries are
+// off by it, and the update of its potential puts it right.  (Without: fp32 outputs 4 % further from their value.)
+__device__ __forceinline__ float base2_rest(float x)
+{
+    const float y = x * LOG2E;
+    return fmaf(x, LOG2E, -y) + x * 1.925963e-8f;   // (log2 e less its fp32 value)
+}
+// v' of a column from its old value and its column sum; the marks as in the half-steps' epilogue.  rest: base2_rest(v)
+// where the sum's entries were evaluated in base 2.
+__device__ __forceinline__ float column_update(float v, float sum, float log_b, float rest)
 {
     if (v == -INFINITY) return -INFINITY;                       // inactive token: stays so
     if (!(sum > 0.f && sum < INFINITY)) return __builtin_nanf("");
-    return v - LN2 * fast_log2(sum) + log_b;
+    return v + fmaf(-LN2, fast_log2(sum) + rest, log_b);
 }
 // where the sums of column t < L are: n segments from the first one that meets it
 struct ColumnSegments {
@@ -141,8 +153,8 @@ template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_pair(const St
     r = c = 0.f;
 #pragma unroll
     for (int i = 0; i < NTHR / 64; ++i) { r += red[i]; c += red[16 + i]; }
-    const float u = column_update(u0, r + fast_exp2((corner + v0 + u0) * LOG2E), 0.f);
-    return DustbinPair{u, column_update(v0, c + fast_exp2((corner + u + v0) * LOG2E), 0.f)};
+    const float u = column_update(u0, r + fast_exp2((corner + v0 + u0) * LOG2E), 0.f, 0.f);
+    return DustbinPair{u, column_update(v0, c + fast_exp2((corner + u + v0) * LOG2E), 0.f, 0.f)};
 }
 
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
@@ -171,7 +183,7 @@ template <typename T, int D> struct StepTile {
 // How a workgroup goes over its rows: one block; a segment of blocks on a ring of tiles, the next block's requested at a
 // block's start; the same on a ring that holds one block's window and no more (LDS): requested once a block's
 // products are done, into the slots that it leaves.  (8 KB tiles: a forward of eight problems of L = 16384, d = 128,
-// W = 256 1321 us block by block, 916 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
+// W = 256 1300 us block by block, 867 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
 // window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
 enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
 enum StepDustbin { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY };   // without, with a dustbin, as the arguments say
@@ -234,7 +246,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     // rows without an edge: zeros, and this segment's share of v there
     for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR) {
         u_out[t] = 0.f;
-        if (part) v_out[t] = t < Lc ? column_update(vp[t], column_sum(p, part, t, nseg_valid), lbp ? lbp[t] : 0.f) : 0.f;
+        if (part) v_out[t] = t < Lc ? column_update(vp[t], column_sum(p, part, t, nseg_valid), lbp ? lbp[t] : 0.f, base2_rest(vp[t])) : 0.f;
     }
     if (b0 >= bv) return;
     const long moff = (long)n * L * D;
@@ -314,7 +326,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         if (DUST && !spc) sp = p.sdb;
         if (part) {
             if (DUST) sum += fast_exp2((sp + uL + v) * LOG2E);
-            v = t < Lc ? column_update(v, sum, lb) : 0.f;
+            v = t < Lc ? column_update(v, sum, lb, base2_rest(v)) : 0.f;
         }
         if (t >= b0 * BM && t < min(bv * BM, L)) {
             if (part) v_out[t] = v;
@@ -366,21 +378,24 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             dma(k0 + nwt, NF, sl);
         };
         if (more) {
-            const int tc = min(nt, L - 1);
-            nv = vp[tc];
-            nu = xsp[min(no, Le - 1)];
-            if (lbp) nlb = lbp[min(tc, max(Lc - 1, 0))];
-            nsp = (DUST && spc ? spc : vp)[tc];
-            if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
-                const float *pp = part + (long)seg * (32 * (NF * M + 2 * hw)) + (tc - 32 * kseg);
+            if (64 * wave < BM) {   // (uniform: the other wavefronts have nothing to add)
+                const int tc = min(nt, L - 1);
+                nv = vp[tc];
+                nu = xsp[min(no, Le - 1)];
+                if (lbp) nlb = lbp[min(tc, max(Lc - 1, 0))];
+                if (DUST) nsp = (spc ? spc : vp)[tc];
+                if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
+                    const float *pp = part + (long)seg * (32 * (NF * M + 2 * hw)) + (tc - 32 * kseg);
 #pragma unroll
-                for (int i = 0; i < 3; ++i) np[i] = pp[(long)min(i, nq) * (64 * hw)];
+                    for (int i = 0; i < 3; ++i) np[i] = pp[(long)min(i, nq) * (64 * hw)];
+                }
             }
             if constexpr (!TIGHT) request_tiles();
         }
 
         [[maybe_unused]] f32x16 ci;   // fp32 storage: the rows' potentials
         if constexpr (!PRE) {
+#pragma clang fp contract(off)   // (rounded as base2_rest takes it)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float4 v4 = *reinterpret_cast<const float4 *>(us + par * BM + 32 * f + 8 * q + 4 * h);
@@ -550,9 +565,11 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             } else if (!(tot > 0.f && tot < INFINITY)) {
                 u_new = w = __builtin_nanf("");
             } else {
-                u_new = u_old - LN2 * fast_log2(tot) + la;
+                const float delta = fmaf(-LN2, fast_log2(tot) + base2_rest(u_old), la);
+                u_new = u_old + delta;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
                 if (lap) w *= __expf(la);
+                w = fmaf(w, (u_new - u_old) - delta, w);   // as u' was rounded, so that v' makes up for it
             }
         }
         if (h == 0) wsw[c] = w;
@@ -661,7 +678,7 @@ __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
         const float v = p.v[n * p.us + t];
         float sum = column_sum(p, part, t, (ln.Le + 32 * p.NF * p.M - 1) / (32 * p.NF * p.M));
         if (p.dustbin) sum += fast_exp2(((p.spoke_c ? p.spoke_c[(long)n * p.sstride + t] : p.sdb) + uL + v) * LOG2E);
-        out = column_update(v, sum, p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f);
+        out = column_update(v, sum, p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f, base2_rest(v));
     }
     v_out[t] = out;
 }
