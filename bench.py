@@ -33,6 +33,9 @@ MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}   # dense matrix peak of the s
 # 31.5 TFLOP/s at best.
 ALU_SLOTS_PER_S = 256 * 4 * 32 * 2.4e9
 ALU_PEAK_TFLOPS = ALU_SLOTS_PER_S * 2.0 / 5.0 / 1e12
+# A whole step in one launch (half-bands up to 256): per band edge one exp2, one add and one multiply-add, so a half-step's
+# share is again 2 flop, in 3 slots
+STEP_ALU_PEAK_TFLOPS = ALU_SLOTS_PER_S * 2.0 / 3.0 / 1e12
 
 
 def edges(w) -> float:
@@ -219,7 +222,10 @@ def main() -> int:
     ms_per_step = 1e3 * dt / args.steps
     tokens_per_s = w.B * w.L * args.steps / dt
     avg_s = 1e-3 * sweep_ms / max(launches, 1)
-    achieved = algorithmic_bytes_per_sweep(w) / avg_s / 1e9
+    # score evaluations (and operand reads) per half-step: one, or half of a whole step's one
+    whole = min(w.W, w.L) <= 256
+    per, alu_peak = (0.5, STEP_ALU_PEAK_TFLOPS) if whole else (1.0, ALU_PEAK_TFLOPS)
+    achieved = per * algorithmic_bytes_per_sweep(w) / avg_s / 1e9
     # HBM bytes per sweep beyond L2: not measurable from inside this process (rocprofv3 --pmc reads
     # FETCH_SIZE / WRITE_SIZE in runs of their own); the stored reading of those runs, with its source
     traffic, traffic_source = None, None
@@ -238,7 +244,7 @@ def main() -> int:
         if n == 0:
             continue
         t = 1e-3 * ms / n                      # seconds per launch
-        b, fl = model[name]
+        b, fl = (per * x for x in model[name]) if name == "scaling_sweeps" else model[name]
         phases[name] = {"launches": n, "avg_launch_us": 1e6 * t, "share_of_step": 1e-3 * ms / pdt,
                         "hbm_frac": b * w.L * w.N / t / 1e9 / HBM_PEAK_GBS,
                         "mfma_frac": fl * E / t / 1e12 / MFMA_PEAK_TFLOPS[dt_name]}
@@ -252,19 +258,19 @@ def main() -> int:
                    "R": w.R, "eps": w.eps, "dustbin": w.dustbin, "backward": args.backward,
                    "streams": args.streams, "calls_per_step": 2 if (args.separate_calls or variant) else 1,
                    "graph_replay": bool(args.graph), "fused_half_steps": args.fused},
-        # the scaling sweep against its three ceilings; the one that binds (the largest lower bound on
-        # a launch's time: 17.1 us ALU, 17.3 us HBM, 13.8 us MFMA at the paper workload) is the plain-ALU
-        # issue rate of one exp2 and one add per band edge
-        "roofline": {"kernel": "scaling sweep (row/column half-step, Eq. 1-2)", "bound": "alu",
-                     "achieved": alu_tflops, "peak": ALU_PEAK_TFLOPS, "unit": "TFLOP/s",
-                     "frac": alu_tflops / ALU_PEAK_TFLOPS, "traffic": traffic, "traffic_source": traffic_source,
-                     "flops": "one exp2 + one add per band edge; v_exp_f32 issues at quarter rate",
+        # the half-steps against three ceilings; the one that binds is the plain-ALU issue rate (run as whole steps, per
+        # band edge and step one exp2, one add and one multiply-add; else one exp2 and one add per half-step)
+        "roofline": {"kernel": "scaling (row and column half-steps, Eq. 1-2; times per half-step)", "bound": "alu",
+                     "achieved": alu_tflops, "peak": alu_peak, "unit": "TFLOP/s",
+                     "frac": alu_tflops / alu_peak, "traffic": traffic, "traffic_source": traffic_source,
+                     "flops": ("one exp2 + one add + one multiply-add per band edge and step" if whole else
+                               "one exp2 + one add per band edge") + "; v_exp_f32 issues at quarter rate",
                      "launches_timed": launches, "avg_launch_us": 1e6 * avg_s,
                      "hbm": {"achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                              "frac": achieved / HBM_PEAK_GBS,
-                             "algorithmic_bytes_per_launch": algorithmic_bytes_per_sweep(w)},
-                     "mfma": {"achieved": 2 * w.d * E / avg_s / 1e12, "peak": MFMA_PEAK_TFLOPS[dt_name],
-                              "unit": "TFLOP/s", "frac": 2 * w.d * E / avg_s / 1e12 / MFMA_PEAK_TFLOPS[dt_name]}},
+                             "algorithmic_bytes_per_launch": per * algorithmic_bytes_per_sweep(w)},
+                     "mfma": {"achieved": per * 2 * w.d * E / avg_s / 1e12, "peak": MFMA_PEAK_TFLOPS[dt_name],
+                              "unit": "TFLOP/s", "frac": per * 2 * w.d * E / avg_s / 1e12 / MFMA_PEAK_TFLOPS[dt_name]}},
         "phases": phases,
         # the same run in other units: per (token, head), per band edge and sweep (2(T+R) half-steps,
         # the output map and six backward sweeps), and the two directions apart
@@ -281,8 +287,8 @@ def main() -> int:
     issue_peak = simds * 1024.0 * 1.0 / tile_s["both"] if w.d == 64 and dt_name == "bf16" else None
     out["roofline"]["issue"] = {
         "probe_ns_per_tile_and_simd": {k: 1e9 * v for k, v in tile_s.items()},
-        "achieved": E / avg_s / 1e12, "peak": None if issue_peak is None else issue_peak / 1e12,
-        "unit": "T band edges/s", "frac": None if issue_peak is None else E / avg_s / issue_peak,
+        "achieved": per * E / avg_s / 1e12, "peak": None if issue_peak is None else issue_peak / 1e12,
+        "unit": "T band edges/s", "frac": None if issue_peak is None else per * E / avg_s / issue_peak,
         "note": "peak = SIMDs x 1024 edges per tile / measured time of one probe tile (d = 64 bf16 mix)"}
     if args.probe_issue:
         probe = {}

@@ -71,8 +71,8 @@ typedef enum {
 /*
  * Bytes of device scratch that sinkhorn_attn_bwd needs for these sizes; the
  * forward is content with the same buffer (it needs B*H*L*d*2 bytes for bf16
- * storage, none for fp32; with all of it, it can fuse half-steps, see
- * sinkhorn_attn_set_fused_half_steps).  Host-only, no GPU call.  Returns 0 on invalid sizes.
+ * storage, none for fp32; with all of it, it runs a Sinkhorn step as one launch or can fuse half-steps, see
+ * sinkhorn_attn_set_fused_half_steps; the potentials then agree with those of the smaller buffer to rounding).  Host-only, no GPU call.  Returns 0 on invalid sizes.
  */
 size_t sinkhorn_attn_workspace_bytes(int B, int H, int L, int d, int W, int T, int R, int dustbin,
                                      int dtype);
@@ -372,7 +372,9 @@ int sinkhorn_attn_set_streams(int n);
  * counter hand-over between neighbouring blocks through memory that all XCDs see; on MI355X the
  * two cost about the same (measured: a half-step takes 16 us fused against 13 us in launches of
  * its own at B*H*L = 131072, 60 us against 59 us at 524288 on one stream), so the default is 0.
- *   It applies to forward calls (and the forward half of sinkhorn_attn_step) without a dustbin and
+ *   Calls whose Sinkhorn steps run as one launch each (half-bands up to 256, short calls up to 480) have no half-steps to
+ * fuse: it does not affect them.
+ *   It applies to the other forward calls (and the forward half of sinkhorn_attn_step) without a dustbin and
  * without a continuation schedule, outside stream capture, whose workspace has
  * sinkhorn_attn_workspace_bytes() bytes (the counters live at its end); other calls run unfused.
  * The fused launch takes all problems on the caller's stream.  At most one call with fused
