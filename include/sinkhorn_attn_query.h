@@ -1,0 +1,37 @@
+/*
+ * sinkhorn_attn_query.h -- how the library would run a call: host-only, no GPU call, nothing of the operator.  For
+ * benchmarks, which price the kernels a call launches, and for tests.
+ */
+#ifndef SINKHORN_ATTN_QUERY_H
+#define SINKHORN_ATTN_QUERY_H
+
+#include <stddef.h>
+
+#ifdef __cplusplus
+extern "C" {
+#endif
+
+/*
+ * The Sinkhorn steps after the first one of a forward (one_call 0), or of the forward half of sinkhorn_attn_step
+ * (one_call 1), with a workspace of workspace_bytes.
+ */
+typedef struct {
+    int whole_steps;       /* 1: a step is one launch; 0: two half-steps (the fields below are 0 then)             */
+    int block_rows;        /* rows a workgroup owns at a time                                                    */
+    int segment_blocks;    /* blocks a workgroup walks one after the other                                       */
+    int segments;          /* workgroups per problem                                                             */
+    int sums_apart;        /* 1: no problem's column sums lie where another problem's backward writes (if not, a  */
+                           /* one-call step joins its two streams between the directions)                        */
+    size_t sums_offset[2]; /* the two buffers of column sums: bytes from the workspace's start ...                */
+    size_t sums_stride;    /* ... and between problems                                                           */
+    size_t sums_bytes;     /* used of that, per problem                                                          */
+} ska_step_plan;
+
+/* Returns SKA_OK, or the error that the call itself would return for these sizes. */
+int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int dtype, size_t workspace_bytes,
+                        int one_call, ska_step_plan *plan);
+
+#ifdef __cplusplus
+}
+#endif
+#endif /* SINKHORN_ATTN_QUERY_H */

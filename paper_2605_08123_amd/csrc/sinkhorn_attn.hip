@@ -35,6 +35,7 @@
 #include <type_traits>
 
 #include "sinkhorn_attn.h"
+#include "sinkhorn_attn_query.h"
 #include "ska_common.h"
 #include "ska_small_kernels.h"
 #include "ska_step.h"
@@ -549,6 +550,36 @@ inline long step_part_stride(const StepShape &sh, int L, bool dustbin)   // floa
     const long nseg = step_segments(sh, L);
     return nseg * 32 * (sh.NF * sh.M + 2 * sh.hw) + (dustbin ? 2 * nseg + 2 : 0);
 }
+// Where a call keeps its two buffers of column sums: byte offsets in the workspace, floats between problems (stride 0: the
+// workspace has no room for them, the half-steps run one by one).
+//   In the one-call step the backward's vectors and packs follow in the same workspace, and the two halves of a split call
+// run forward and backward without waiting for each other.  So a problem's sums lie where only the same problem's backward
+// writes: one buffer in its rows of each of the first two packs of bf16 columns (32 bytes per row).  Blocks that
+// read much more of the band than they own have more sums than that; those lie over the backward's vectors, and the
+// streams are joined between the two directions (apart = false).
+struct StepSums { size_t off[2]; long stride; bool apart; };
+inline StepSums step_sums(const Problem &p, const StepShape &sh, bool one_call)
+{
+    StepSums s{{0, 0}, 0, true};
+    if (!sh.NF) return s;
+    const size_t N = p.N(), row = N * p.ldw(), gu = row * sizeof(float), pack = row * 32;
+    const long used = step_part_stride(sh, p.L, p.dustbin), own = 32 / (long)sizeof(float) * p.ldw();
+    if (one_call && used <= own) {
+        s.off[0] = ws_vec_bytes(p) - 4 * pack;
+        s.off[1] = s.off[0] + pack;
+        s.stride = own;
+        return s;
+    }
+    // between g_u and the end of the vectors (the same bytes at every R)
+    const size_t buf = N * used * sizeof(float);
+    s.off[0] = (one_call ? 0 : ws_qs_bytes(p)) + gu;
+    s.off[1] = s.off[0] + buf;
+    if (2 * buf <= row * 168 && (one_call || p.ws_given >= s.off[1] + buf)) {
+        s.stride = used;
+        s.apart = !one_call;
+    }
+    return s;
+}
 template <typename T, int D, int NF, int G, int NTW, int KIND, int DB> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
     p.nb_total = p.nseg * N;
@@ -809,16 +840,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
     const StepShape shape = step_shape<T, D>(N, L, p.W);
     const int nseg = shape.NF ? (int)step_segments(shape, L) : 0;
-    const long pstride = step_part_stride(shape.NF ? shape : StepShape{1, 1, 1, 0, 1, 0}, L, p.dustbin);
+    const StepSums sums = step_sums(p, shape, fused);
+    const long pstride = sums.stride;
     float *part[2] = {nullptr, nullptr};
-    if (shape.NF) {   // room for two buffers of sums between g_u and the end of the vectors (the same bytes at every R)
-        const size_t gu = (size_t)N * p.ldw() * sizeof(float), need = 2 * (size_t)N * pstride * sizeof(float);
-        const size_t off = (fused ? 0 : ws_qs_bytes(p)) + gu;
-        if (need <= (size_t)N * p.ldw() * 168 && ws && (fused || p.ws_given >= off + need)) {
-            part[0] = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + off);
-            part[1] = part[0] + (size_t)N * pstride;
-        }
-    }
+    if (pstride && ws)
+        for (int i = 0; i < 2; ++i) part[i] = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + sums.off[i]);
     if (part[0]) chain_done = nullptr;   // a step is one launch already
     bool first = !p.resume_t, pend = false;
     int vcur = p.resume_t ? 2 * p.resume_t - 1 : 1, vhome = 0, pbuf = 0;
@@ -980,8 +1006,9 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     float *partial = tok ? tok + 4 * nldp : nullptr;
     const int nchunk = ws_chunks(p);
     // the kernels before the sweeps take all problems on st -- except the plain row dot of a fused
-    // step, which each stream does for its own half so that the two chains stay apart
-    const bool own_halves = fused && cx.side && !seed && !p.dustbin;
+    // step, which each stream does for its own half so that the two chains stay apart (not if one half's vectors
+    // lie over sums that the other half may still read)
+    const bool own_halves = fused && cx.side && !seed && !p.dustbin && step_sums(p, step_shape<T, D>(N, L, p.W), true).apart;
     if (fused && !own_halves) SKA_TRY(cx.join());
     if (p.token()) {
         SQ = Vec{tok, ldw};
@@ -1185,6 +1212,34 @@ size_t sinkhorn_attn_workspace_bytes(int B, int H, int L, int d, int W, int T, i
     Problem p{B, H, L, d, W, T, R, dustbin ? 1 : 0, dtype, 1.f, 0.f};
     if (check_common(p) != SKA_OK) return 0;
     return ws_bytes(p);
+}
+
+int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int dtype, size_t workspace_bytes,
+                        int one_call, ska_step_plan *plan)
+{
+    Problem p{B, H, L, d, W, T, R, dustbin ? 1 : 0, dtype, 1.f, 0.f};
+    if (!plan) return SKA_EINVAL;
+    const int rc = check_common(p);
+    if (rc != SKA_OK) return rc;
+    p.ws_given = workspace_bytes;
+    if (workspace_bytes < (one_call ? ws_bytes(p) : ws_qs_bytes(p))) return SKA_EWORKSPACE;
+    auto with = [&](auto elem, auto dim) {
+        const StepShape sh = step_shape<decltype(elem), decltype(dim)::value>(p.N(), L, W);
+        const StepSums s = step_sums(p, sh, one_call != 0);
+        *plan = ska_step_plan{};
+        plan->sums_apart = s.apart;
+        if (!s.stride) return SKA_OK;
+        plan->whole_steps = 1;
+        plan->block_rows = 32 * sh.NF; plan->segment_blocks = sh.M; plan->segments = (int)step_segments(sh, L);
+        plan->sums_offset[0] = s.off[0]; plan->sums_offset[1] = s.off[1];
+        plan->sums_stride = s.stride * sizeof(float); plan->sums_bytes = step_part_stride(sh, L, p.dustbin) * sizeof(float);
+        return SKA_OK;
+    };
+    using D32 = std::integral_constant<int, 32>;
+    using D64 = std::integral_constant<int, 64>;
+    using D128 = std::integral_constant<int, 128>;
+    if (dtype == SKA_F32) return d == 32 ? with(0.f, D32{}) : d == 64 ? with(0.f, D64{}) : with(0.f, D128{});
+    return d == 32 ? with(__bf16{}, D32{}) : d == 64 ? with(__bf16{}, D64{}) : with(__bf16{}, D128{});
 }
 
 static int fwd_call(const Problem &p_in, const void *Q, const void *K, const void *V, void *O, float *UV,

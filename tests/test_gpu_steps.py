@@ -112,3 +112,46 @@ def test_steps_take_spread_potentials():
     s = (Q.double() * K.double()).sum(-1)[0, 0] / 8.0
     # after a column step the column sums are one; scores from a bf16 copy of Q: 2^-9 of the terms' sizes
     assert float((u + v + s).abs().max()) <= 2.0 ** -9 * float((Q.double() * K.double()).abs().sum(-1).max() / 8.0) + 1e-4
+
+
+SPLIT = [  # dtype, d, N, L, W, R, lengths of the first and of the second half of the problems (0: a padded item without tokens)
+    ("bf16", 64, 5, 20000, 128, 2, 40, 20000), ("bf16", 64, 5, 20000, 128, 1, 20000, 0), ("bf16", 64, 2, 60001, 256, 2, 0, 60001),
+    ("bf16", 64, 3, 9000, 60, 3, 9000, 300), ("bf16", 128, 3, 17000, 256, 2, 17000, 1), ("f32", 64, 3, 5001, 100, 2, 5001, 17),
+    ("bf16", 64, 3, 4001, 400, 2, 33, 4001), ("bf16", 64, 5, 4001, 470, 1, 4001, 0)]   # (these two: sums over the backward's vectors)
+
+
+@pytest.mark.parametrize("case", SPLIT, ids=lambda c: "-".join(map(str, c)))
+def test_split_step_with_unequal_halves_equals_one_stream(case):
+    """Without a dustbin the two halves of a one-call step run forward and backward without waiting for each other: the
+    half that is done first must not write over what the other one still reads.  The same bits as on one stream."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    dtype, d, N, L, W, R, len0, len1 = case
+    print(f"\n[case] {case}", flush=True)
+    td, code = (torch.float32, 0) if dtype == "f32" else (torch.bfloat16, 1)
+    plan = binding.query_step_plan(N, 1, L, d, W, 6, R, False, code, one_call=True)
+    assert plan.whole_steps and bool(plan.sums_apart) == (W <= 256)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(23)
+    Q, K, V, G = (torch.randn((N, 1, L, d), generator=gen, device="cuda").to(td) for _ in range(4))
+    lens = torch.tensor([len0] * (N // 2) + [len1] * (N - N // 2), dtype=torch.int32, device="cuda")
+    ws = torch.empty(ska.sinkhorn_attn_workspace_bytes(N, 1, L, d, W, 6, R, False, code), device="cuda", dtype=torch.uint8)
+
+    def step(streams):
+        ska.sinkhorn_attn_set_streams(streams)
+        ws.fill_(255)   # (NaN wherever a float is read that was not written)
+        out = ska.sinkhorn_attn_step(Q, K, V, G, W, 6, R, 0.7, False, 0.0, None, None, lens, lens, workspace=ws)
+        torch.cuda.synchronize()
+        return out
+
+    try:
+        ska.sinkhorn_attn_set_split_min_edges(0.0)
+        one = step(1)
+        for _ in range(3):
+            for x, y in zip(step(2), one):
+                assert torch.isfinite(y.float()).all() and torch.equal(x, y)
+    finally:
+        ska.sinkhorn_attn_set_streams(2)
+        ska.sinkhorn_attn_set_split_min_edges(5e7)
