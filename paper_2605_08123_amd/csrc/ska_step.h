@@ -1,6 +1,7 @@
 // A whole Sinkhorn step (row half-step and column half-step) from one evaluation of the scores.
 #pragma once
 #include "ska_common.h"
+#include "ska_step_shape.h"
 
 namespace {
 
@@ -174,38 +175,6 @@ __device__ __forceinline__ float rows16_sum(float a, float b)
     const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
-
-template <typename T, int D> struct StepTile {
-    static constexpr int ROWB = D * (int)sizeof(T), CPR = ROWB / 16, BYTES = 32 * ROWB;
-    // position of a 16-byte chunk in its row: sixteen consecutive rows spread one chunk over all 64 banks
-    static __device__ __forceinline__ int swz(int row) { return CPR >= 16 ? (row & 15) : CPR == 8 ? ((row >> 1) & 7) : ((row >> 2) & 3); }
-};
-// How a workgroup goes over its rows: one block; a segment of blocks on a ring of tiles, the next block's requested at a
-// block's start; the same on a ring that holds one block's window and no more (LDS): requested once a block's
-// products are done, into the slots that it leaves.  (8 KB tiles: a forward of eight problems of L = 16384, d = 128,
-// W = 256 1300 us block by block, 867 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
-// window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
-enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
-enum StepDustbin { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY };   // without, with a dustbin, as the arguments say
-template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds {   // offsets in bytes
-    static constexpr int RSUM = 0;                              // [NF][G][32] row sums
-    static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
-    static constexpr int US = WS + NF * G * 128;                // [2][32 NF] potentials of the rows
-    static constexpr bool MARCH = KIND != STEP_BLOCK;
-    static_assert(KIND != STEP_TIGHT || G > 1, "the exchange of row sums says that the products are done");
-    // With G > 1 that exchange lies between a wavefront's reads and its next block's writes; without it there are two buffers.
-    static constexpr int TWO = MARCH && G == 1 ? 2 : 1;
-    static constexpr int CP = US + TWO * NF * 128;              // [TWO][NF][G NTW 32] column sums of a fragment
-    static constexpr int Y = CP + TWO * NF * G * NTW * 128;   // ring of the other side's tiles
-    static constexpr int VB = sizeof(T) == 2 ? 8 : 4;           // bytes of a column's potential
-    int rs, vs, total;
-    __host__ __device__ StepLds(int hw)
-    {
-        rs = NF + 2 * hw + (KIND == STEP_MARCH ? NF : 0);   // ring slots: the window of a block (and the tiles the next one adds)
-        vs = Y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
-        total = vs + rs * 32 * VB;
-    }
-};
 
 template <typename T, int D, int NF, int G, int NTW, int KIND, int DB>
 __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
