@@ -402,8 +402,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         const unsigned icnt = o_f + 32 <= Le ? max(ihi - ilo + 1, 0) : 0, pcnt = max(nj - sfirst, 0);
         auto interior = [&](int s) { return (unsigned)(s - ilo) < icnt; };   // (uniform: one compare)
         auto present = [&](int s) { return (unsigned)(s - sfirst) < pcnt; };
-        int slot = base + f + j0;
-        if (slot >= RS) slot -= RS;
+        int slot = lds.slot(base + f + j0);
         if constexpr (PRE) {
             // one wavefront's pipeline: the products of tile s + 1 are issued among the exponentials of tile s, and the
             // operand of tile s + 2 is requested as its registers come free
@@ -428,7 +427,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                 const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
                 yv = bf16x8{v3[0], v3[1], v3[2], v3[3], one, one, one, no};
             };
-            auto step_slot = [&]() { ++slot; if (MARCH && slot == RS) slot = 0; };
+            auto step_slot = [&]() { slot = lds.slot(slot + 1); };
             rdv();
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) rd(ks);
@@ -492,8 +491,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
                 }
-                ++slot;
-                if (MARCH && slot == RS) slot = 0;
+                slot = lds.slot(slot + 1);
             }
         }
 

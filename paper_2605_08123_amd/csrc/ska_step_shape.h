@@ -34,6 +34,9 @@ template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds { 
         vs = Y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
         total = vs + rs * 32 * VB;
     }
+    // Ring slot of the tile `at` slots on from the ring's first.  A wavefront evaluates NTW tiles also where its band ends before:
+    // of a single block, whose ring is its window, it takes the last slot for those (their entries are masked).
+    __host__ __device__ int slot(int at) const { return MARCH ? (at >= rs ? at - rs : at) : (at < rs ? at : rs - 1); }
 };
 
 // Blocks of NF fragments of 32 rows, G wavefronts per fragment with NTW tiles each, M blocks per workgroup (a segment);

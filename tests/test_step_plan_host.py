@@ -1,12 +1,17 @@
-"""Where a one-call step keeps the column sums of its Sinkhorn steps (host-only query, no GPU).  The two halves of a split call
+"""Block shapes of the whole Sinkhorn steps (compiled for the host), and where a one-call step keeps their column sums (host-only
+query); no GPU.  The two halves of a split call
 run forward and backward without waiting for each other, so a half's backward must not write where the other half's
 sums lie, nor the reverse, unless the streams are joined between the directions."""
 import itertools
+import os
+import subprocess
 
 import pytest
 
 from paper_2605_08123_amd import binding as b
 
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2605_08123_amd", "csrc")
 SIZES = [(1, 1), (31, 7), (65, 0), (100, 99), (300, 128), (333, 5000), (700, 160), (701, 64), (3001, 100), (4096, 128), (9000, 300),
          (16384, 256), (16500, 480), (33001, 256), (40000, 97), (65536, 256), (70001, 200), (262144, 256)]
 
@@ -61,3 +66,13 @@ def test_forward_alone_keeps_its_sums_inside_the_workspace():
             assert ends[0] <= p.sums_offset[1]
         small = b.query_step_plan(N, 1, L, 64, W, 16, R, dustbin, workspace_bytes=2 * N * L * 64)
         assert not small.whole_steps   # room for the prescaled operand alone
+
+
+def test_block_shapes(tmp_path):
+    """step_shapes.cpp over the shapes that the rule takes: no wavefront reads a tile outside its launch's LDS."""
+    exe = str(tmp_path / "step_shapes")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-D__host__=", "-D__device__=", "-I", CSRC, "-o", exe,
+                    os.path.join(HERE, "step_shapes.cpp")], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True)
+    print(run.stdout)
+    assert run.returncode == 0, run.stdout
