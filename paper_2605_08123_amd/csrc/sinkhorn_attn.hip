@@ -477,18 +477,18 @@ inline StepSums step_sums(const Problem &p, const StepShape &sh, bool one_call)
     }
     return s;
 }
-template <typename T, int D, int NF, int G, int NTW, int KIND, int DB> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
+template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
     p.nb_total = p.nseg * N;
-    const int lds = StepLds<T, D, NF, G, NTW, KIND>(p.hw).total;
+    const int lds = StepLds<T, D, NF, G, NTW, KIND, FORM>(p.hw).total;
     static bool raised[MAX_DEVICES];
     if (!raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, DB>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, FORM>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
     }
-    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, DB>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
+    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, FORM>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
 template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape &sh, int N, hipStream_t st, int dev)
@@ -498,6 +498,7 @@ template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape
     if constexpr (COND) \
         if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) { \
             constexpr bool ANY = KIND_ == STEP_BLOCK; \
+            if (p.log_a || p.log_b) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(p, N, st, dev); \
             if (!ANY && p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_DUSTBIN>(p, N, st, dev); \
             return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_PLAIN>(p, N, st, dev); \
         }

@@ -42,6 +42,12 @@ namespace {
 // W = 256, T = 20 1022 -> 863 us, 8 of 5000, W = 128 with learned tokens 396 -> 357.  In segments a template parameter (DB),
 // since its branches and registers cost calls without a dustbin 4 % (2 problems of 262144: 2730 -> 2650 us); single blocks
 // have registers to spare and read a flag.
+//   TARGETS: small marginal targets stay out of the exponents (ColumnTarget) and come in as weights of the two sums: one more
+// factor where rows are summed (a multiply-add instead of an add).  With a row's and a column's target in them, the entries
+// of a row of e^-80 next to ordinary ones lost all but the largest, and at e^-90 the row was empty; a mask of -100 or -1e4 on
+// every sixteenth row gave NaN everywhere.  The block's largest potential, as the half-steps take it, would carry those, but
+// not potentials that lie apart by their scores.  A template parameter as well: forward and backward of four problems of
+// L = 65536, W = 256 1388 -> 1445 us, a forward of eight of 701, W = 64 113 -> 115; by half-steps 1674 and 211.
 //   The arguments are a struct of their own, read as a whole at a kernel's start (take_args): fetched where they are first
 // used they cost a short launch one wait of some hundred cycles after another.
 struct StepArgs {
@@ -89,13 +95,48 @@ __device__ __forceinline__ float base2_rest(float x)
     const float y = x * LOG2E;
     return fmaf(x, LOG2E, -y) + x * 1.925963e-8f;   // (log2 e less its fp32 value)
 }
-// v' of a column from its old value and its column sum; the marks as in the half-steps' epilogue.  rest: base2_rest(v)
-// where the sum's entries were evaluated in base 2.
-__device__ __forceinline__ float column_update(float v, float sum, float log_b, float rest)
+// x in base 2 less `two`, and what that difference lost by rounding
+struct Base2 { float x, lost; };
+__device__ __forceinline__ Base2 base2_less(float x, float two)
+{
+#pragma clang fp contract(off)   // (the product rounded by itself, as base2_rest takes it)
+    const float y = x * LOG2E, z = y - two;
+    return Base2{z, (y - z) - two};
+}
+// A target's log split up so that a small target (below 2^-32) stays out of the exponents of its column's entries: exp2(score +
+// u + v) would go down with the target until the column is empty, next to ordinary ones that need nothing of the kind.
+// The entries are evaluated with the potential less `nat` (natural units), then less `two` (base 2); `rest` is what the
+// target's log has beside the two.  Where rows are summed, a column's entries get the target back as the factor `weight`:
+// a power of two, exact in bf16, or zero, which a target below 2^-126 is beside any other (and whose potential may be
+// so large that base 2 loses it: less `nat` it is not).
+struct ColumnTarget {
+    float two, nat, rest, weight;
+    __device__ __forceinline__ ColumnTarget(float log_t) : two(0.f), nat(0.f), rest(log_t), weight(1.f)
+    {
+        const float y = log_t * LOG2E;
+        if (y < -126.f) {
+            nat = log_t; rest = 0.f; weight = 0.f;
+        } else if (y < -32.f) {
+            two = rintf(y);
+            rest = fmaf(-LN2, two, log_t);
+            weight = __builtin_amdgcn_ldexpf(1.f, (int)two);
+        }
+    }
+};
+// The same of a row: its weight, which no product takes, need not be a power of two, so all of the target's log is left out.
+__device__ __forceinline__ float row_target_nat(float log_t) { return log_t * LOG2E < -32.f ? log_t : 0.f; }
+__device__ __forceinline__ float less_nat(float x, float nat) { return x == -INFINITY ? x : x - nat; }   // (a mark stays one)
+
+// v' of a column from its old value and its column sum; the marks as in the half-steps' epilogue.  BASE2: the sum's entries
+// were evaluated with v in base 2.
+template <bool BASE2> __device__ __forceinline__ float column_update(float v, float sum, const ColumnTarget &t)
 {
     if (v == -INFINITY) return -INFINITY;                       // inactive token: stays so
     if (!(sum > 0.f && sum < INFINITY)) return __builtin_nanf("");
-    return v + fmaf(-LN2, fast_log2(sum) + rest, log_b);
+    float x = v - t.nat, rest = BASE2 ? base2_rest(x) : 0.f;
+    if (BASE2 && t.two != 0.f) rest += base2_less(x, t.two).lost;
+    x += fmaf(-LN2, fast_log2(sum) + rest, t.rest);
+    return t.nat != 0.f ? t.nat + x : x;
 }
 // where the sums of column t < L are: n segments from the first one that meets it
 struct ColumnSegments {
@@ -154,8 +195,8 @@ template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_pair(const St
     r = c = 0.f;
 #pragma unroll
     for (int i = 0; i < NTHR / 64; ++i) { r += red[i]; c += red[16 + i]; }
-    const float u = column_update(u0, r + fast_exp2((corner + v0 + u0) * LOG2E), 0.f, 0.f);
-    return DustbinPair{u, column_update(v0, c + fast_exp2((corner + u + v0) * LOG2E), 0.f, 0.f)};
+    const float u = column_update<false>(u0, r + fast_exp2((corner + v0 + u0) * LOG2E), ColumnTarget(0.f));
+    return DustbinPair{u, column_update<false>(v0, c + fast_exp2((corner + u + v0) * LOG2E), ColumnTarget(0.f))};
 }
 
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
@@ -176,15 +217,16 @@ __device__ __forceinline__ float rows16_sum(float a, float b)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <typename T, int D, int NF, int G, int NTW, int KIND, int DB>
+template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM>
 __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 {
     using ST = StepTile<T, D>;
-    using LD = StepLds<T, D, NF, G, NTW, KIND>;
+    using LD = StepLds<T, D, NF, G, NTW, KIND, FORM>;
     constexpr bool MARCH = KIND != STEP_BLOCK, TIGHT = KIND == STEP_TIGHT;
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
-    const bool DUST = DB == STEP_ANY ? p.dustbin != 0 : DB == STEP_DUSTBIN;
+    constexpr bool TARGETS = FORM == STEP_TARGETS;
+    const bool DUST = FORM == STEP_ANY ? p.dustbin != 0 : FORM == STEP_DUSTBIN;
     extern __shared__ __align__(16) unsigned char smem[];
     take_args(p);
     const int chunk = (p.nb_total + 7) >> 3, bx = (int)blockIdx.x;
@@ -210,12 +252,13 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     const float *vp = p.v + n * p.us, *xsp = p.u + n * p.us;
     float *u_out = p.u_out + n * p.us, *v_out = p.v_out + n * p.us;
     const float *part = p.part_in ? p.part_in + n * p.part_stride : nullptr;
-    const float *lap = p.log_a ? p.log_a + (long)n * p.lstride : nullptr, *lbp = p.log_b ? p.log_b + (long)n * p.lstride : nullptr;
+    const float *lap = TARGETS && p.log_a ? p.log_a + (long)n * p.lstride : nullptr;
+    const float *lbp = TARGETS && p.log_b ? p.log_b + (long)n * p.lstride : nullptr;
     const float *spr = p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr, *spc = p.spoke_c ? p.spoke_c + (long)n * p.sstride : nullptr;
     // rows without an edge: zeros, and this segment's share of v there
     for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR) {
         u_out[t] = 0.f;
-        if (part) v_out[t] = t < Lc ? column_update(vp[t], column_sum(p, part, t, nseg_valid), lbp ? lbp[t] : 0.f, base2_rest(vp[t])) : 0.f;
+        if (part) v_out[t] = t < Lc ? column_update<true>(vp[t], column_sum(p, part, t, nseg_valid), ColumnTarget(lbp ? lbp[t] : 0.f)) : 0.f;
     }
     if (b0 >= bv) return;
     const long moff = (long)n * L * D;
@@ -250,16 +293,27 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             dma_rows(32L * (k + i / IPT) + (i % IPT) * RPI, LD::Y + sl * ST::BYTES + (i % IPT) * 1024, whole);
         }
     };
-    // v of a column into its place in LDS, as the evaluation takes it
-    auto stage_v = [&](int at, int t, float v) {
-        v = t >= 0 && t < Lt ? v * LOG2E : -INFINITY;
-        if constexpr (PRE) *reinterpret_cast<bf16x4 *>(vs + at * 8) = potential_parts(v);
-        else *reinterpret_cast<float *>(vs + at * 4) = v;
+    // v of a column (and with targets its weight) into its place in LDS, as the evaluation takes it
+    auto stage_v = [&](int at, int t, float v, float lb) {
+        const ColumnTarget tg(TARGETS ? lb : 0.f);
+        v = t >= 0 && t < Lt ? base2_less(less_nat(v, tg.nat), tg.two).x : -INFINITY;
+        if constexpr (PRE) {
+            bf16x4 parts = potential_parts(v);
+            if constexpr (TARGETS) parts[3] = (__bf16)tg.weight;
+            *reinterpret_cast<bf16x4 *>(vs + at * 8) = parts;
+        } else if constexpr (TARGETS) {
+            *reinterpret_cast<float2 *>(vs + at * 8) = make_float2(v, tg.weight);
+        } else {
+            *reinterpret_cast<float *>(vs + at * 4) = v;
+        }
     };
+    // u of a row with its target, as the evaluation takes it
+    auto row_u = [&](float u, float log_a) { return TARGETS ? less_nat(u, row_target_nat(log_a)) : u; };
     // Loads return in order: the vectors, which need work, are requested before the tiles and the owner rows.
     constexpr int NWIN = (32 * (NF + G * NTW) + NTHR - 1) / NTHR;   // columns of a window per thread
     constexpr int NSUM = MARCH ? 3 : (G * NTW - 1) / NF + 2;        // segments that a column can have sums from, at most
-    const float u_first = tid < BM && b0 * BM + tid < Le ? xsp[b0 * BM + tid] : -INFINITY;
+    float u_first = tid < BM && b0 * BM + tid < Le ? xsp[b0 * BM + tid] : -INFINITY;
+    if (lap) u_first = row_u(u_first, lap[min(b0 * BM + min(tid, BM - 1), Le - 1)]);
     float win_v[NWIN], win_sum[NWIN][NSUM], win_lb[NWIN], win_sp[NWIN];
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
@@ -295,7 +349,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         if (DUST && !spc) sp = p.sdb;
         if (part) {
             if (DUST) sum += fast_exp2((sp + uL + v) * LOG2E);
-            v = t < Lc ? column_update(v, sum, lb, base2_rest(v)) : 0.f;
+            v = t < Lc ? column_update<true>(v, sum, ColumnTarget(TARGETS ? lb : 0.f)) : 0.f;
         }
         if (t >= b0 * BM && t < min(bv * BM, L)) {
             if (part) v_out[t] = v;
@@ -315,7 +369,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 #pragma unroll
             for (int q = 0; q < NSUM; ++q) sum += q < cg.n ? win_sum[k][q] : 0.f;
         }
-        if (i < 32 * nwt) stage_v(i, t, finish_v(t, win_v[k], sum, win_lb[k], win_sp[k]));   // (later columns: with their block)
+        if (i < 32 * nwt) stage_v(i, t, finish_v(t, win_v[k], sum, win_lb[k], win_sp[k]), win_lb[k]);   // (later columns: with their block)
     }
     if (tid < BM) us[tid] = u_first;
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
@@ -338,7 +392,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         if (lap) la = lap[min(o, Le - 1)];
         // what the next block adds (a thread below BM: one column, one row): requested now, stored after this block's last
         // use of the slots' old content
-        float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nlb = 0.f, nsp = 0.f;
+        float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nla = 0.f, nlb = 0.f, nsp = 0.f;
         const int nt = 32 * (k0 + nwt) + tid, no = (b + 1) * BM + tid;
         const int nq = min(segment_of(p, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
         auto request_tiles = [&]() {
@@ -351,6 +405,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                 const int tc = min(nt, L - 1);
                 nv = vp[tc];
                 nu = xsp[min(no, Le - 1)];
+                if (lap) nla = lap[min(no, Le - 1)];
                 if (lbp) nlb = lbp[min(tc, max(Lc - 1, 0))];
                 if (DUST) nsp = (spc ? spc : vp)[tc];
                 if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
@@ -371,13 +426,17 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                 ci[4 * q + 0] = v4.x * LOG2E; ci[4 * q + 1] = v4.y * LOG2E; ci[4 * q + 2] = v4.z * LOG2E; ci[4 * q + 3] = v4.w * LOG2E;
             }
         }
-        const float u_old = us[par * BM + 32 * f + c];
+        const float u_old = us[par * BM + 32 * f + c];   // (TARGETS: less nat)
 
         f32x16 E[NTW];
         float rsum[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) rsum[r] = 0.f;
-        auto add_rows = [&](const f32x16 &e, int r) { rsum[r] += e[r]; };
+        [[maybe_unused]] float bt[NTW];   // TARGETS: weight of this lane's column of each tile
+        auto add_rows = [&](const f32x16 &e, int s, int r) {
+            if constexpr (TARGETS) rsum[r] = fmaf(e[r], bt[s], rsum[r]);
+            else rsum[r] += e[r];
+        };
         // entries of an edge tile outside the band or the matrix become zero (whatever they are): with o = o_f + 4 h +
         // off_r and t = t0 + c, |t - o| <= W keeps lo <= off_r <= lo + 2 W.  As a bit per offset: two instructions an
         // entry, the first ones of eight entries together (one after the other they wait for each other).
@@ -422,18 +481,20 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             auto rd = [&](int ks) {
                 y[ks] = *reinterpret_cast<const bf16x8 *>(ybase + slot * ST::BYTES + (((2 * ks + h) ^ ST::swz(c)) << 4));
             };
-            auto rdv = [&]() {
+            auto rdv = [&](int s) {   // (tile s)
                 const bf16x4 v3 = *reinterpret_cast<const bf16x4 *>(vs + (32 * slot + c) * 8);
+                // (a zero of the row's operand meets it; an absent tile's slot may hold anything, and its zero entries stay zero)
+                if constexpr (TARGETS) bt[s] = present(s) ? (float)v3[3] : 0.f;
                 const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
                 yv = bf16x8{v3[0], v3[1], v3[2], v3[3], one, one, one, no};
             };
             auto step_slot = [&]() { slot = lds.slot(slot + 1); };
-            rdv();
+            rdv(0);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) rd(ks);
             step_slot();
             E[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
-            if (NTW > 1) rdv();
+            if (NTW > 1) rdv(1);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 E[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks], y[ks], E[0], 0, 0, 0);
@@ -450,14 +511,14 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                         else E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks - 1], y[ks - 1], E[s + 1], 0, 0, 0);
                         __builtin_amdgcn_sched_barrier(0);
                         if (s + 2 < NTW) {
-                            if (ks == 0) rdv();
+                            if (ks == 0) rdv(s + 2);
                             else rd(ks - 1);
                         }
                     }
 #pragma unroll
                     for (int r = ks * RPS; r < 16 && r < (ks + 1) * RPS; ++r) {
                         E[s][r] = fast_exp2(E[s][r]);
-                        if (s > 0) add_rows(E[s - 1], r);
+                        if (s > 0) add_rows(E[s - 1], s - 1, r);
                         asm volatile("" : "+v"(rsum[r]));   // the sums here, among the products, not for all tiles at the end
                     }
                     __builtin_amdgcn_sched_barrier(0);
@@ -465,13 +526,14 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                 if (!interior(s)) mask(E[s], 32 * (kw + s), present(s));
             }
 #pragma unroll
-            for (int r = 0; r < 16; ++r) add_rows(E[NTW - 1], r);
+            for (int r = 0; r < 16; ++r) add_rows(E[NTW - 1], NTW - 1, r);
         } else {
 #pragma unroll
             for (int s = 0; s < NTW; ++s) {
                 if (present(s)) {   // (uniform)
                     const unsigned char *yr = smem + LD::Y + slot * ST::BYTES + c * ST::ROWB;
-                    const float vt = *reinterpret_cast<const float *>(vs + (32 * slot + c) * 4);
+                    const float vt = *reinterpret_cast<const float *>(vs + (32 * slot + c) * LD::VB);
+                    if constexpr (TARGETS) bt[s] = *reinterpret_cast<const float *>(vs + (32 * slot + c) * LD::VB + 4);
 #pragma unroll
                     for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
 #pragma unroll
@@ -486,7 +548,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                     for (int r = 0; r < 16; ++r) E[s][r] = fast_exp2(fmaf(E[s][r], p.c2, ci[r] + vt));
                     if (!interior(s)) mask(E[s], 32 * (kw + s), true);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) add_rows(E[s], r);
+                    for (int r = 0; r < 16; ++r) add_rows(E[s], s, r);
                 } else {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
@@ -526,18 +588,36 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         const float edge = DUST ? fast_exp2((spoke + vL + u_old) * LOG2E) : 0.f;   // spoke (o, dustbin of the other side)
         tot += edge;
         float u_new = 0.f, w = 0.f;
+        [[maybe_unused]] int wexp = 0;   // TARGETS: exponent that the fragment's weights are taken less of
         if (o < Le) {
             if (u_old == -INFINITY) {
                 u_new = -INFINITY;   // inactive token: stays so
             } else if (!(tot > 0.f && tot < INFINITY)) {
                 u_new = w = __builtin_nanf("");
-            } else {
-                const float delta = fmaf(-LN2, fast_log2(tot) + base2_rest(u_old), la);
+            } else if constexpr (!TARGETS) {
+                const float delta = fmaf(-LN2, fast_log2(tot) + base2_rest(u_old), 0.f);
                 u_new = u_old + delta;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
-                if (lap) w *= __expf(la);
                 w = fmaf(w, (u_new - u_old) - delta, w);   // as u' was rounded, so that v' makes up for it
+            } else {
+                const float nat = row_target_nat(la), delta = fmaf(-LN2, fast_log2(tot) + base2_rest(u_old), la - nat), x = u_old + delta;
+                u_new = nat + x;
+                w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
+                w = fmaf(w, ((u_new - nat) - x) + ((x - u_old) - delta), w);
             }
+        }
+        if constexpr (TARGETS) {
+            // the weight is target / sum.  Where a fragment's rows all weigh little (small targets over columns of ordinary ones),
+            // their entries are as large as the weights are small: a common exponent is left out until the column sums are done
+            const float lac = fmaxf(la, -1e5f), la2 = lac * LOG2E, q = rintf(la2);   // (a target below that weighs nothing either way)
+            w *= fast_exp2((la2 - q) + base2_rest(lac));
+            float top = w > 0.f ? q + fast_log2(w) : -INFINITY;
+            if (!__any(top >= -40.f)) {
+#pragma unroll
+                for (int s = 16; s >= 1; s >>= 1) top = fmaxf(top, __shfl_xor(top, s));
+                if (top > -INFINITY) wexp = (int)top;
+            }
+            w = __builtin_amdgcn_ldexpf(w, (int)q - wexp);
         }
         if (h == 0) wsw[c] = w;
         if (h == 0 && g == 0 && o < Le) to_col += edge * w;
@@ -555,7 +635,8 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             float x = 0.f, y = 0.f;
 #pragma unroll
             for (int r = 0; r < 16; r += 2) { x = fmaf(e[r], wv[r], x); y = fmaf(e[r + 1], wv[r + 1], y); }
-            return x + y;
+            if constexpr (TARGETS) return __builtin_amdgcn_ldexpf(x + y, wexp);
+            else return x + y;
         };
 #pragma unroll
         for (int s = 0; s + 1 < NTW; s += 2) cpw[32 * s + lane] = halves_sum(col(E[s]), col(E[s + 1]));
@@ -568,8 +649,8 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             const float v_new = finish_v(nt, nv, np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f), nlb, nsp);
             int sl = 32 * (base + nwt) + tid;
             if (sl >= 32 * RS) sl -= 32 * RS;
-            stage_v(sl, nt, v_new);
-            us[(LD::TWO == 2 ? par ^ 1 : 0) * BM + tid] = no < Le ? nu : -INFINITY;
+            stage_v(sl, nt, v_new, nlb);
+            us[(LD::TWO == 2 ? par ^ 1 : 0) * BM + tid] = no < Le ? row_u(nu, nla) : -INFINITY;
         }
         if (DUST && !more) {   // the segment's last block: every thread has added its share
 #pragma unroll
@@ -645,7 +726,7 @@ __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
         const float v = p.v[n * p.us + t];
         float sum = column_sum(p, part, t, (ln.Le + 32 * p.NF * p.M - 1) / (32 * p.NF * p.M));
         if (p.dustbin) sum += fast_exp2(((p.spoke_c ? p.spoke_c[(long)n * p.sstride + t] : p.sdb) + uL + v) * LOG2E);
-        out = column_update(v, sum, p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f, base2_rest(v));
+        out = column_update<true>(v, sum, ColumnTarget(p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f));
     }
     v_out[t] = out;
 }

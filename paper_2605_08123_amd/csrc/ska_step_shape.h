@@ -15,8 +15,10 @@ template <typename T, int D> struct StepTile {
 // W = 256 1300 us block by block, 867 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
 // window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
 enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
-enum StepDustbin { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY };   // without, with a dustbin, as the arguments say
-template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds {   // offsets in bytes
+// What a call's steps add to the plain ones: nothing, a dustbin, a dustbin if the arguments say so, targets of rows or columns
+// (which go with no dustbin).
+enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS };
+template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> struct StepLds {   // offsets in bytes
     static constexpr int RSUM = 0;                              // [NF][G][32] row sums
     static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
     static constexpr int US = WS + NF * G * 128;                // [2][32 NF] potentials of the rows
@@ -26,7 +28,7 @@ template <typename T, int D, int NF, int G, int NTW, int KIND> struct StepLds { 
     static constexpr int TWO = MARCH && G == 1 ? 2 : 1;
     static constexpr int CP = US + TWO * NF * 128;              // [TWO][NF][G NTW 32] column sums of a fragment
     static constexpr int Y = CP + TWO * NF * G * NTW * 128;   // ring of the other side's tiles
-    static constexpr int VB = sizeof(T) == 2 ? 8 : 4;           // bytes of a column's potential
+    static constexpr int VB = sizeof(T) == 2 || FORM == STEP_TARGETS ? 8 : 4;   // bytes of a column's potential (and weight)
     int rs, vs, total;
     __host__ __device__ StepLds(int hw)
     {
@@ -54,12 +56,12 @@ constexpr int STEP_LDS = 159 * 1024;
     X(TB <= 4096, 4, 2, 6, STEP_MARCH) X(TB <= 4096, 4, 2, 7, STEP_MARCH) X(TB <= 4096, 4, 2, 8, STEP_MARCH) X(TB <= 4096, 4, 2, 9, STEP_MARCH) \
     X(TB <= 4096, 4, 2, 9, STEP_BLOCK) X(TB <= 4096, 4, 2, 7, STEP_BLOCK) X(TB <= 4096, 4, 2, 8, STEP_BLOCK)
 template <typename T, int D> constexpr int step_tile_bytes = StepTile<T, D>::BYTES;
-template <typename T, int D> int step_lds(const StepShape &sh)
+template <typename T, int D> int step_lds(const StepShape &sh)   // (of the form that takes most)
 {
     constexpr int TB = step_tile_bytes<T, D>;
 #define SKA_LDS(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
-        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) return StepLds<T, D, NF_, G_, NTW_, KIND_>(sh.hw).total;
+        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) return StepLds<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(sh.hw).total;
     SKA_STEP_SHAPES(SKA_LDS)
 #undef SKA_LDS
     return STEP_LDS + 1;

@@ -11,7 +11,7 @@ long shapes = 0, clamped = 0;
 // the slots that the kernel's wavefronts go through in a block whose first tile lies in slot `base`
 template <typename T, int D, int NF, int G, int NTW, int KIND> bool reads_inside(const StepShape &sh)
 {
-    const StepLds<T, D, NF, G, NTW, KIND> lds(sh.hw);
+    const StepLds<T, D, NF, G, NTW, KIND, STEP_TARGETS> lds(sh.hw);   // (the form that takes most)
     const int window = NF + 2 * sh.hw, NT = 2 * sh.hw + 1;
     if (G * NTW < NT || lds.total > STEP_LDS || lds.rs < window) return false;
     for (int base = 0; base < (KIND == STEP_BLOCK ? 1 : lds.rs); ++base)

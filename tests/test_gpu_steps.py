@@ -114,6 +114,59 @@ def test_steps_take_spread_potentials():
     assert float((u + v + s).abs().max()) <= 2.0 ** -9 * float((Q.double() * K.double()).abs().sum(-1).max() / 8.0) + 1e-4
 
 
+LOWEST = -3.4028234663852886e38
+TARGETS = [  # dtype, d, L, W, which tokens have the target e^x, x
+    *[("bf16", 64, 1000, 64, k, x) for k in ("rows", "columns", "both") for x in (-80.0, -100.0, -1e4, LOWEST, float("-inf"))],
+    *[("f32", 64, 1000, 64, k, x) for k in ("rows", "columns", "both") for x in (-30.0, -84.0, -1e4)],
+    ("bf16", 64, 70000, 128, "both", -100.0), ("bf16", 64, 40000, 256, "both", -90.0), ("bf16", 64, 17000, 200, "both", -1e4),   # segments, blocks
+    ("bf16", 128, 33000, 200, "both", -100.0), ("bf16", 128, 33000, 100, "both", -90.0), ("f32", 64, 40000, 256, "both", -100.0),
+    ("f32", 32, 60000, 100, "both", -90.0), ("bf16", 64, 1000, 400, "both", -100.0),
+    ("bf16", 64, 1000, 64, "all", -60.0), ("f32", 64, 1000, 100, "all", -60.0), ("bf16", 64, 1000, 64, "end", -60.0)]
+
+
+@pytest.mark.parametrize("case", TARGETS, ids=lambda c: "-".join(map(str, c)))
+def test_steps_take_small_targets(case):
+    """Targets of e^x among unit ones: every sixteenth row and / or column, all of them, or rows and columns from some token on.
+    Against the half-steps, which take the largest potential of a block as stabiliser; token by token, since a
+    potential near x is known to its own rounding and the others as without small targets."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    dtype, d, L, W, which, x = case
+    print(f"\n[case] {case}", flush=True)
+    td, code = (torch.float32, 0) if dtype == "f32" else (torch.bfloat16, 1)
+    T, R, eps = 3, 2, 1.0
+    assert binding.query_step_plan(1, 1, L, d, W, T, R, False, code).whole_steps
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(29)
+    Q, K, V = (torch.randn((1, 1, L, d), generator=gen, device="cuda").to(td) for _ in range(3))
+    i = torch.arange(L, device="cuda")
+    hit = {"all": i >= 0, "end": i >= 700}.get(which)
+    la, lb = torch.zeros((2, 1, 1, L), device="cuda")
+    la[..., hit if hit is not None else i % 16 == 0] = x if which != "columns" else 0.0
+    lb[..., hit if hit is not None else i % 16 == 5] = x if which != "rows" else 0.0
+
+    def forward(nbytes):
+        ws = None if nbytes is None else torch.empty(nbytes, device="cuda", dtype=torch.uint8)
+        return ska.sinkhorn_attn_fwd_marginals(Q, K, V, la, lb, W, T, R, eps, workspace=ws)
+
+    O, UV = forward(None)
+    O0, UV0 = forward(max(16, Q.numel() * 2 if dtype == "bf16" else 16))   # half-steps
+    assert torch.equal(torch.isneginf(UV), torch.isneginf(UV0))
+    a, b = (torch.where(torch.isneginf(z), 0.0, z.double()) for z in (UV, UV0))
+    assert torch.isfinite(a).all() and torch.isfinite(b).all() and torch.isfinite(O.float()).all()
+    score = float((Q.double().norm(dim=-1).max() * K.double().norm(dim=-1).max()) / (eps * d ** 0.5))
+    M = 1.4427 * torch.clamp(b.abs(), min=score + (abs(x) if which in ("all", "end") else 0.0))
+    # (the bound of test_steps_equal_half_steps; a potential as large as its target has one rounding of its own per update more)
+    bound = 2 * 2 * (T + R) * (2 * W + 1 + 20 + 4 * M) * 2.0 ** -24
+    worst = float(((a - b).abs() / bound).max())
+    print(f"   |UV - UV0| at most {worst:.2f} of the bound", flush=True)
+    assert worst <= 1.0
+    rel = float((O.double() - O0.double()).norm() / O0.double().norm())
+    assert rel <= 2 * 2 * 2 * (T + R) * (2 * W + 21 + 4 * 1.4427 * (score + 64)) * 2.0 ** -24 + (2.0 ** -8 if dtype == "bf16" else 0.0), rel
+
+
 SPLIT = [  # dtype, d, N, L, W, R, lengths of the first and of the second half of the problems (0: a padded item without tokens)
     ("bf16", 64, 5, 20000, 128, 2, 40, 20000), ("bf16", 64, 5, 20000, 128, 1, 20000, 0), ("bf16", 64, 2, 60001, 256, 2, 0, 60001),
     ("bf16", 64, 3, 9000, 60, 3, 9000, 300), ("bf16", 128, 3, 17000, 256, 2, 17000, 1), ("f32", 64, 3, 5001, 100, 2, 5001, 17),
