@@ -732,7 +732,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         }
         return SKA_OK;
     };
-    // Whole steps (vstep_kernel) after the first one.  `pend`: the last step's column sums have not been taken into v
+    // Whole steps (vstep_kernel) after the first one of a stage, which normalises the columns.  `pend`: the last step's column sums have not been taken into v
     // yet; the next step's launch does so on the way, and a launch of its own (flush) where v is needed by itself.  The
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
@@ -813,6 +813,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
                 if (hipGetLastError() != hipSuccess) return SKA_EHIP;
                 SKA_TRY((make_scores_operand<T>(p, es, Qin, ws, &Q, &stage_c2, st)));
                 SKA_TRY(cx.fork());
+                first = true;   // the plan to the power of the ratio: its row sums are bounded by nothing (as before the first step)
             }
             stage_sdb2 = p.sdb * (p.eps / es) * LOG2E;
             for (int t = 0; t < Ts; ++t) SKA_TRY(full(0, 0, 1, sidx + 1 < nst ? 0 : Ts - 1 - t));

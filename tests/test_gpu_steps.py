@@ -114,6 +114,35 @@ def test_steps_take_spread_potentials():
     assert float((u + v + s).abs().max()) <= 2.0 ** -9 * float((Q.double() * K.double()).abs().sum(-1).max() / 8.0) + 1e-4
 
 
+@pytest.mark.parametrize("dtype,L", [("bf16", 1024), ("f32", 1000), ("bf16", 70000)])
+def test_first_step_of_a_continuation_stage_takes_the_half_steps_range(dtype, L):
+    """A stage raises the plan to the ratio of the two eps.  Every second row here spreads evenly over its 257 partners, so
+    that at a ratio of 20 its entries go down to e^-111 and its sum to e^-105; the other rows match one partner each and have
+    potentials e^100 larger, which the half-steps' common stabiliser takes.  Finite, and the same as by half-steps."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    W, d, R, eps_s = 128, 64, 2, [10.0, 0.5, 0.5]
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    r = torch.randn((L, d), generator=gen, device="cuda")
+    r[:, 0] = 0
+    r /= r.norm(dim=-1, keepdim=True)
+    e0 = torch.zeros(d, device="cuda")
+    e0[0] = 1
+    even = (torch.arange(L, device="cuda") % 2 == 0)[:, None]
+    Q, K, V = (x.view(1, 1, L, d).to(td).contiguous() for x in (torch.where(even, 30.5 * e0, 31 * r), 30 * e0 + 31 * r, r))
+    for T_stage in ([3, 0, 2], [3, 0, 0], [3, 2, 1]):
+        O, UV = ska.sinkhorn_attn_fwd_eps_schedule(Q, K, V, W, eps_s, T_stage, R, 0.5)
+        ws = torch.empty(max(16, Q.numel() * 2 if dtype == "bf16" else 16), device="cuda", dtype=torch.uint8)
+        O0, UV0 = ska.sinkhorn_attn_fwd_eps_schedule(Q, K, V, W, eps_s, T_stage, R, 0.5, workspace=ws)
+        assert torch.isfinite(UV0).all() and torch.isfinite(UV).all(), T_stage
+        M = 1.4427 * max(31.0 * 31.0 * 1.1 / (0.5 * d ** 0.5), float(UV0.abs().max()))
+        bound = 2 * 2 * (sum(T_stage) + R) * (2 * W + 21 + 4 * M) * 2.0 ** -24
+        assert float((UV - UV0).abs().max()) <= bound, T_stage
+
+
 LOWEST = -3.4028234663852886e38
 TARGETS = [  # dtype, d, L, W, which tokens have the target e^x, x
     *[("bf16", 64, 1000, 64, k, x) for k in ("rows", "columns", "both") for x in (-80.0, -100.0, -1e4, LOWEST, float("-inf"))],
