@@ -56,7 +56,7 @@ constexpr int STEP_LDS = 159 * 1024;
     X(TB <= 4096, 4, 2, 6, STEP_MARCH) X(TB <= 4096, 4, 2, 7, STEP_MARCH) X(TB <= 4096, 4, 2, 8, STEP_MARCH) X(TB <= 4096, 4, 2, 9, STEP_MARCH) \
     X(TB <= 4096, 4, 2, 9, STEP_BLOCK) X(TB <= 4096, 4, 2, 7, STEP_BLOCK) X(TB <= 4096, 4, 2, 8, STEP_BLOCK)
 template <typename T, int D> constexpr int step_tile_bytes = StepTile<T, D>::BYTES;
-template <typename T, int D> int step_lds(const StepShape &sh)   // (of the form that takes most)
+template <typename T, int D> int step_lds(const StepShape &sh)   // bytes (of the form that takes most); -1: no such instance
 {
     constexpr int TB = step_tile_bytes<T, D>;
 #define SKA_LDS(COND, NF_, G_, NTW_, KIND_) \
@@ -64,7 +64,7 @@ template <typename T, int D> int step_lds(const StepShape &sh)   // (of the form
         if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) return StepLds<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(sh.hw).total;
     SKA_STEP_SHAPES(SKA_LDS)
 #undef SKA_LDS
-    return STEP_LDS + 1;
+    return -1;
 }
 // Which shape a call takes, from the rows of the whole call (not of a launch: results do not depend on how a call is cut).
 // Short blocks while they leave CUs idle or barely fill them, large ones (less of the band read twice) beyond, one segment per
@@ -86,7 +86,7 @@ template <typename T, int D> int step_lds(const StepShape &sh)   // (of the form
 //   (2,4,3) 311, W = 192: 343, (2,4,4) 372.  d = 32, W = 160: 262144 rows (4,2,6) 620, 524288 rows 1137, half-steps 656 / 935
 //   W = 300 .. 480 (2,4,9): 16384 rows 244 .. 271, half-steps 469 .. 618; 32768 rows 414 .. 456 / 470 .. 619; beyond, the 36
 //   tiles that a block of 64 rows reads are what bounds it
-template <typename T, int D> StepShape step_shape(int N, int L, int W)
+template <typename T, int D> StepShape step_choice(int N, int L, int W)
 {
     constexpr int TB = step_tile_bytes<T, D>;
     const int hw = ((W < L ? W : L) + 31) / 32;
@@ -135,7 +135,15 @@ template <typename T, int D> StepShape step_shape(int N, int L, int W)
         sh.M = M;
         if (M > 1) sh.kind = TB <= 4096 ? STEP_MARCH : STEP_TIGHT;
     }
-    if (step_lds<T, D>(sh) > STEP_LDS) sh.NF = 0;
+    return sh;
+}
+// Every choice has an instance that fits LDS (a test goes over them).  (4,2,6) needs none for single blocks: beyond 32768 rows
+// there are more blocks of 128 than segments, so that a segment has at least two.
+template <typename T, int D> StepShape step_shape(int N, int L, int W)
+{
+    StepShape sh = step_choice<T, D>(N, L, W);
+    const int lds = sh.NF ? step_lds<T, D>(sh) : 0;
+    if (lds < 0 || lds > STEP_LDS) sh.NF = 0;
     return sh;
 }
 inline long step_segments(const StepShape &sh, int L) { return (L + 32L * sh.NF * sh.M - 1) / (32L * sh.NF * sh.M); }

@@ -1,5 +1,5 @@
-// Block shapes of the step kernel over sizes and types, on the host: every tile that a wavefront reads lies inside the
-// launch's ring.  Prints the first violation and returns 1.
+// Block shapes of the step kernel over sizes and types, on the host: every shape that the rule takes has an instance and fits
+// LDS, and every tile that a wavefront reads lies inside the launch's ring.  Prints the first violation and returns 1.
 #include "ska_step_shape.h"
 
 #include <cstdio>
@@ -29,19 +29,21 @@ template <typename T, int D, int NF, int G, int NTW, int KIND> bool reads_inside
 }
 template <typename T, int D> bool check(int N, int L, int W)
 {
-    const StepShape sh = step_shape<T, D>(N, L, W);
+    const StepShape sh = step_choice<T, D>(N, L, W);
     if (!sh.NF) return true;
+    const int lds = step_lds<T, D>(sh);
     constexpr int TB = step_tile_bytes<T, D>;
-    bool ok = false;
+    bool ok = lds >= 0 && lds <= STEP_LDS && step_shape<T, D>(N, L, W).NF == sh.NF, instance = false;
 #define CHECK(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
-        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) ok = reads_inside<T, D, NF_, G_, NTW_, KIND_>(sh);
+        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) instance = reads_inside<T, D, NF_, G_, NTW_, KIND_>(sh);
     SKA_STEP_SHAPES(CHECK)
 #undef CHECK
     ++shapes;
-    if (!ok) std::printf("%d-byte d = %d, N = %d, L = %d, W = %d: (%d, %d, %d) kind %d, %d blocks\n", (int)sizeof(T), D, N, L, W, sh.NF, sh.G,
-                         sh.NTW, sh.kind, sh.M);
-    return ok;
+    if (ok && instance) return true;
+    std::printf("%d-byte d = %d, N = %d, L = %d, W = %d: (%d, %d, %d) kind %d, %d blocks, %d bytes of LDS\n", (int)sizeof(T), D, N, L, W,
+                sh.NF, sh.G, sh.NTW, sh.kind, sh.M, lds);
+    return false;
 }
 }  // namespace
 

@@ -69,7 +69,8 @@ def test_forward_alone_keeps_its_sums_inside_the_workspace():
 
 
 def test_block_shapes(tmp_path):
-    """step_shapes.cpp over the shapes that the rule takes: no wavefront reads a tile outside its launch's LDS."""
+    """step_shapes.cpp over the shapes that the rule takes: each has an instance that fits LDS, and no wavefront reads a tile
+    outside it."""
     exe = str(tmp_path / "step_shapes")
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-D__host__=", "-D__device__=", "-I", CSRC, "-o", exe,
                     os.path.join(HERE, "step_shapes.cpp")], check=True)
