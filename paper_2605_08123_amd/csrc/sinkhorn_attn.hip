@@ -756,6 +756,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     step.L = L; step.W = base.W; step.NF = shape.NF; step.M = shape.M; step.hw = shape.hw; step.nseg = nseg;
     step.rcp = shape.NF ? segment_reciprocal(shape.NF * shape.M) : 0;
     step.nh = p.H; step.dustbin = p.dustbin;
+    if (sizeof(T) == 4) step.up = (float)ilogbf((float)(2 * base.W + 1));
     auto flush = [&]() -> int {
         if (!pend) return SKA_OK;
         StepArgs f = step;

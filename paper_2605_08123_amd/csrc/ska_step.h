@@ -68,6 +68,12 @@ struct StepArgs {
     unsigned rcp;                  // segment_reciprocal(NF M)
     int nb_total, rev, nh, n0, dustbin;   // (as in SweepArgs)
     float c2, sdb;                 // score scale in base 2 (fp32 storage); scalar dustbin score
+    // fp32 storage: entries are evaluated 2^up times too large, about 2 W + 1, which their row's sum and weight take out again:
+    // their exponents are then near zero, where fp32 is finest.  It goes into the rows' potentials, whose rounding a row's own
+    // sum sees as a whole (in the columns' the row sums would be off by it).  Distance of O from 64 bits, rms over 40 problems
+    // of L = 256, d = 32, W = 16: half-steps 2.61e-7, without 2.70e-7, with 2.52e-7; 16 of L = 4096, d = 64, W = 128: 5.44, 5.36,
+    // 4.99e-7.
+    float up;
 };
 __device__ __forceinline__ void take_args(const StepArgs &p)
 {
@@ -302,7 +308,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             if constexpr (TARGETS) parts[3] = (__bf16)tg.weight;
             *reinterpret_cast<bf16x4 *>(vs + at * 8) = parts;
         } else if constexpr (TARGETS) {
-            *reinterpret_cast<float2 *>(vs + at * 8) = make_float2(v, tg.weight);
+            *reinterpret_cast<float2 *>(vs + at * 8) = make_float2(v, __builtin_amdgcn_ldexpf(tg.weight, -(int)p.up));
         } else {
             *reinterpret_cast<float *>(vs + at * 4) = v;
         }
@@ -423,10 +429,12 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float4 v4 = *reinterpret_cast<const float4 *>(us + par * BM + 32 * f + 8 * q + 4 * h);
-                ci[4 * q + 0] = v4.x * LOG2E; ci[4 * q + 1] = v4.y * LOG2E; ci[4 * q + 2] = v4.z * LOG2E; ci[4 * q + 3] = v4.w * LOG2E;
+                ci[4 * q + 0] = base2_less(v4.x, -p.up).x; ci[4 * q + 1] = base2_less(v4.y, -p.up).x;
+                ci[4 * q + 2] = base2_less(v4.z, -p.up).x; ci[4 * q + 3] = base2_less(v4.w, -p.up).x;
             }
         }
         const float u_old = us[par * BM + 32 * f + c];   // (TARGETS: less nat)
+        const float u_rest = PRE ? base2_rest(u_old) : base2_rest(u_old) + base2_less(u_old, -p.up).lost;
 
         f32x16 E[NTW];
         float rsum[16];
@@ -585,6 +593,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         float tot = 0.f;
 #pragma unroll
         for (int i = 0; i < G; ++i) tot += rs[(f * G + i) * 32 + c];
+        if constexpr (!PRE && !TARGETS) tot = __builtin_amdgcn_ldexpf(tot, -(int)p.up);   // (TARGETS: in the columns' weights)
         const float edge = DUST ? fast_exp2((spoke + vL + u_old) * LOG2E) : 0.f;   // spoke (o, dustbin of the other side)
         tot += edge;
         float u_new = 0.f, w = 0.f;
@@ -595,12 +604,12 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             } else if (!(tot > 0.f && tot < INFINITY)) {
                 u_new = w = __builtin_nanf("");
             } else if constexpr (!TARGETS) {
-                const float delta = fmaf(-LN2, fast_log2(tot) + base2_rest(u_old), 0.f);
+                const float delta = fmaf(-LN2, fast_log2(tot) + u_rest, 0.f);
                 u_new = u_old + delta;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
                 w = fmaf(w, (u_new - u_old) - delta, w);   // as u' was rounded, so that v' makes up for it
             } else {
-                const float nat = row_target_nat(la), delta = fmaf(-LN2, fast_log2(tot) + base2_rest(u_old), la - nat), x = u_old + delta;
+                const float nat = row_target_nat(la), delta = fmaf(-LN2, fast_log2(tot) + u_rest, la - nat), x = u_old + delta;
                 u_new = nat + x;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
                 w = fmaf(w, ((u_new - nat) - x) + ((x - u_old) - delta), w);
@@ -619,7 +628,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             }
             w = __builtin_amdgcn_ldexpf(w, (int)q - wexp);
         }
-        if (h == 0) wsw[c] = w;
+        if (h == 0) wsw[c] = PRE ? w : __builtin_amdgcn_ldexpf(w, -(int)p.up);
         if (h == 0 && g == 0 && o < Le) to_col += edge * w;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         f32x16 wv;

@@ -143,6 +143,26 @@ def test_first_step_of_a_continuation_stage_takes_the_half_steps_range(dtype, L)
         assert float((UV - UV0).abs().max()) <= bound, T_stage
 
 
+@pytest.mark.parametrize("L,W,d", [(256, 16, 32), (256, 32, 32), (700, 30, 128)])
+def test_fp32_steps_are_no_further_from_64_bits_than_half_steps(L, W, d):
+    """The same 24 problems both ways against the oracle: the rms distance of O."""
+    import torch
+
+    import oracle
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd.workloads import Workload, make_inputs
+    w = Workload("fp32", 41, 1, 24, L, d, W, 8, 2, 1.0, "f32")
+    arrays = make_inputs(w, 41)
+    ref = oracle.band_batched(*arrays, w.W, w.T, w.R, w.eps)["O"]
+    Q, K, V = (torch.from_numpy(x).cuda() for x in arrays[:3])
+    err = []
+    for ws in (None, torch.empty(16, device="cuda", dtype=torch.uint8)):
+        O, _ = ska.sinkhorn_attn_fwd(Q, K, V, w.W, w.T, w.R, w.eps, workspace=ws)
+        err.append(float(np.sqrt(np.mean((O.cpu().numpy().astype(np.float64) - ref) ** 2))))
+    print(f"\n   steps {err[0]:.3e}, half-steps {err[1]:.3e}", flush=True)
+    assert err[0] <= err[1]
+
+
 LOWEST = -3.4028234663852886e38
 TARGETS = [  # dtype, d, L, W, which tokens have the target e^x, x
     *[("bf16", 64, 1000, 64, k, x) for k in ("rows", "columns", "both") for x in (-80.0, -100.0, -1e4, LOWEST, float("-inf"))],
