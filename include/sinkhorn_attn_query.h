@@ -16,7 +16,10 @@ extern "C" {
  * (one_call 1), with a workspace of workspace_bytes.
  */
 typedef struct {
-    int whole_steps;       /* 1: a step is one launch; 0: two half-steps (the fields below are 0 then)             */
+    int whole_steps;       /* 1: a step is one launch; 0: two half-steps                                           */
+    int half_steps_fuse;   /* 1: sinkhorn_attn_set_fused_half_steps applies (outside capture, without a continuation */
+                           /* schedule, on a device that holds the launch); 0 where steps are whole                 */
+                           /* the rest is about whole steps, 0 otherwise:                                          */
     int block_rows;        /* rows a workgroup owns at a time                                                    */
     int segment_blocks;    /* blocks a workgroup walks one after the other                                       */
     int segments;          /* workgroups per problem                                                             */

@@ -98,7 +98,7 @@ def load():
 
 class StepPlan(ctypes.Structure):
     """How a call runs its Sinkhorn steps (ska_step_plan, include/sinkhorn_attn_query.h)."""
-    _fields_ = [(n, ctypes.c_int) for n in ("whole_steps", "block_rows", "segment_blocks", "segments", "sums_apart")] + [
+    _fields_ = [(n, ctypes.c_int) for n in ("whole_steps", "half_steps_fuse", "block_rows", "segment_blocks", "segments", "sums_apart")] + [
         ("sums_offset", ctypes.c_size_t * 2), ("sums_stride", ctypes.c_size_t), ("sums_bytes", ctypes.c_size_t)]
 
 

@@ -95,6 +95,12 @@ size_t ws_tok_bytes(const Problem &p)
 size_t ws_chain_bytes(const Problem &p) { return ((size_t)p.N() * ((p.L + 127) / 128) * sizeof(int) + 255) / 256 * 256; }
 size_t ws_core_bytes(const Problem &p) { return (ws_vec_bytes(p) + ws_qs_bytes(p) + ws_tok_bytes(p) + 255) / 256 * 256; }
 size_t ws_bytes(const Problem &p) { return ws_core_bytes(p) + ws_chain_bytes(p); }
+// whether a call's half-steps can be fused (see fwd_impl) and its workspace has room for the counters; where they lie
+bool chain_room(const Problem &p, bool one_call, size_t *off)
+{
+    *off = one_call ? ws_core_bytes(p) : (ws_qs_bytes(p) + 255) / 256 * 256;
+    return !p.dustbin && !p.n_stages && p.ws_given >= *off + ws_chain_bytes(p);
+}
 inline float *ws_tok(const Problem &p, void *ws)
 {
     return reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + ws_vec_bytes(p) + ws_qs_bytes(p));
@@ -657,8 +663,8 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
-        const size_t off = fused ? ws_core_bytes(p) : (ws_qs_bytes(p) + 255) / 256 * 256;
-        if (g_fuse && !cx.noalloc && !capturing && !p.dustbin && !p.n_stages && ws && p.ws_given >= off + ws_chain_bytes(p))
+        size_t off;
+        if (g_fuse && !cx.noalloc && !capturing && ws && chain_room(p, fused, &off))
             chain_done = reinterpret_cast<int *>(reinterpret_cast<unsigned char *>(ws) + off);
     }
     // the stabiliser of the separate launches (stab_rows) is taken per dispatch; the chain is one launch, so it
@@ -1128,7 +1134,11 @@ int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dus
         const StepSums s = step_sums(p, sh, one_call != 0);
         *plan = ska_step_plan{};
         plan->sums_apart = s.apart;
-        if (!s.stride) return SKA_OK;
+        if (!s.stride) {
+            size_t off;
+            plan->half_steps_fuse = chain_room(p, one_call != 0, &off);
+            return SKA_OK;
+        }
         plan->whole_steps = 1;
         plan->block_rows = 32 * sh.NF; plan->segment_blocks = sh.M; plan->segments = (int)step_segments(sh, L);
         plan->sums_offset[0] = s.off[0]; plan->sums_offset[1] = s.off[1];

@@ -13,20 +13,27 @@ from tests.measures import assert_per_tensor, floors
 
 pytestmark = pytest.mark.gpu
 
-CASES = [
+CASES = [   # (half-bands and sizes whose steps are two half-steps: whole steps have nothing to fuse)
     # name, B, H, L, d, W, T, R, eps, dtype, kind
-    ("f32_tiny", 1, 1, 256, 32, 16, 8, 2, 1.0, "f32", "plain"),
-    ("bf16_many", 2, 3, 3000, 64, 70, 6, 2, 0.5, "bf16", "plain"),
-    ("bf16_big_blocks", 1, 2, 120000, 64, 256, 3, 2, 0.5, "bf16", "plain"),   # 256-row blocks, two per workgroup
+    ("f32_tiny", 1, 1, 700, 32, 500, 8, 2, 1.0, "f32", "plain"),
+    ("bf16_many", 2, 3, 3000, 64, 490, 6, 2, 0.5, "bf16", "plain"),
+    ("bf16_big_blocks", 1, 2, 120000, 64, 300, 3, 2, 0.5, "bf16", "plain"),   # 256-row blocks, two per workgroup
     ("bf16_dense", 1, 2, 700, 64, 5000, 4, 2, 0.8, "bf16", "plain"),
-    ("f32_ragged_R3", 1, 2, 1001, 64, 33, 0, 3, 1.0, "f32", "plain"),
-    ("bf16_lengths", 2, 2, 2000, 64, 100, 4, 2, 0.7, "bf16", "varlen"),
-    ("f32_marginals", 1, 2, 900, 32, 40, 5, 2, 1.0, "f32", "marginals"),
-    ("bf16_masks", 2, 1, 1500, 64, 31, 4, 2, 0.6, "bf16", "masked"),
-    ("bf16_d128", 1, 1, 1300, 128, 64, 3, 1, 0.5, "bf16", "plain"),
-    ("bf16_d128_more_blocks_than_fit", 1, 2, 40000, 128, 40, 3, 1, 0.5, "bf16", "plain"),   # 626 blocks, 512 at once (d = 64: 1024)
-    ("bf16_d128_256_rows", 1, 1, 100000, 128, 200, 3, 1, 0.5, "bf16", "plain"),
+    ("f32_ragged_R3", 1, 1, 1001, 64, 300, 0, 3, 1.0, "f32", "plain"),
+    ("bf16_lengths", 2, 2, 2000, 64, 500, 4, 2, 0.7, "bf16", "varlen"),
+    ("f32_marginals", 1, 2, 900, 32, 500, 5, 2, 1.0, "f32", "marginals"),
+    ("bf16_masks", 2, 1, 1500, 64, 490, 4, 2, 0.6, "bf16", "masked"),
+    ("bf16_d128", 1, 1, 1300, 128, 300, 3, 1, 0.5, "bf16", "plain"),
+    ("bf16_d128_more_blocks_than_fit", 1, 2, 40000, 128, 260, 3, 1, 0.5, "bf16", "plain"),   # 626 blocks, 512 at once (d = 64: 1024)
+    ("bf16_d128_256_rows", 1, 1, 100000, 128, 300, 3, 1, 0.5, "bf16", "plain"),
 ]
+
+
+def _assert_half_steps(w):
+    from paper_2605_08123_amd import binding
+    for one_call in (False, True):
+        p = binding.query_step_plan(w.B, w.H, w.L, w.d, w.W, w.T, w.R, False, 0 if w.dtype == "f32" else 1, one_call=one_call)
+        assert not p.whole_steps and p.half_steps_fuse, "nothing to fuse: the modes would be one path compared with itself"
 
 
 def _forward(ska, torch, w, kind, Q, K, V, extra):
@@ -47,6 +54,7 @@ def test_fused_half_steps_equal_separate_launches(case):
     name, B, H, L, d, W, T, R, eps, dtype, kind = case
     w = Workload(name, 31, B, H, L, d, W, T, R, eps, dtype)
     print(f"\n[case] {w} ({kind})", flush=True)
+    _assert_half_steps(w)
     dev = torch.device("cuda:0")
     td = torch.float32 if dtype == "f32" else torch.bfloat16
     arrays = make_inputs(w, 310 + len(name))
@@ -96,7 +104,8 @@ def test_a_wait_that_runs_out_ends_the_launch():
     import torch
 
     import paper_2605_08123_amd as ska
-    w = Workload("giveup", 32, 1, 2, 20000, 64, 256, 6, 2, 0.5, "bf16")
+    w = Workload("giveup", 32, 1, 2, 20000, 64, 300, 6, 2, 0.5, "bf16")
+    _assert_half_steps(w)
     print(f"\n[case] {w} poll limit 1", flush=True)
     dev = torch.device("cuda:0")
     Q, K, V, G = (torch.from_numpy(x).to(dev).to(torch.bfloat16) for x in make_inputs(w, 3))
