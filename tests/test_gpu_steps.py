@@ -48,13 +48,19 @@ LONG = [  # other block shapes; segments of several blocks, also ragged ones and
     ("plain", "f32", 64, 1, 10000, 170, 2, 1), ("plain", "bf16", 128, 1, 40000, 16, 2, 1), ("dustbin", "bf16", 64, 1, 60000, 20, 2, 1)]
 
 
+HALF_STEPS = [("plain", "bf16", 64, 1, 1500, 481, 2, 1)]   # the others run whole steps
+
+
 @pytest.mark.parametrize("case", SHORT + LONG, ids=lambda c: "-".join(map(str, c)))
 def test_steps_equal_half_steps(case):
     import torch
 
     import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
     kind, dtype, d, N, L, W, T, R = case
     print(f"\n[case] {case}", flush=True)
+    whole = binding.query_step_plan(N, 1, L, d, W, T, R, kind == "dustbin", 0 if dtype == "f32" else 1).whole_steps
+    assert bool(whole) == (case not in HALF_STEPS)   # (both sides of the rule's lines)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(17)
     td = torch.float32 if dtype == "f32" else torch.bfloat16
@@ -85,7 +91,10 @@ def test_steps_equal_half_steps(case):
     assert torch.isfinite(x).all() and torch.isfinite(y).all()
     score = float((Q.double().norm(dim=-1).max() * K.double().norm(dim=-1).max()) / (eps * d ** 0.5))
     M = 1.4427 * max(score, float(y.abs().max()))
-    terms = 2 * min(W, L) + 1 + (L if db else 0)
+    # a dustbin's row and column are sums over all tokens, taken in a tree: a thread's own terms (one per block of its segment,
+    # L / 256 in a half-step's element), its wavefront's, its workgroup's, the segments'.  (A segment left out of
+    # ("dustbin", L = 70000, W = 128) would move the dustbin's potentials by 1 / 137, more than ten times the bound.)
+    terms = 2 * min(W, L) + 1 + (L // 256 + 64 if db else 0)
     bound = 2 * 2 * (T + R) * (terms + 20 + 4 * M) * 2.0 ** -24
     err = float((x - y).abs().max())
     print(f"   |UV - UV0| {err:.1e} (bound {bound:.1e}), M {M:.0f}", flush=True)
