@@ -67,6 +67,13 @@ def algorithmic_bytes_per_sweep(w) -> float:
     return phase_model(w)["scaling_sweeps"][0] * w.L * w.N
 
 
+def whole_steps(w, one_call=True) -> bool:
+    """Whether the library runs a Sinkhorn step of this workload as one launch (its own answer)."""
+    from paper_2605_08123_amd import binding
+    return bool(binding.query_step_plan(w.B, w.H, w.L, w.d, w.W, w.T, w.R, w.dustbin, 0 if w.dtype == "f32" else 1,
+                                        one_call=one_call).whole_steps)
+
+
 def cpu_baseline(w, budget_tokens: int):
     """Oracle as it stands on a slice of head 0 (first `budget_tokens` tokens)."""
     import oracle
@@ -223,7 +230,7 @@ def main() -> int:
     tokens_per_s = w.B * w.L * args.steps / dt
     avg_s = 1e-3 * sweep_ms / max(launches, 1)
     # score evaluations (and operand reads) per half-step: one, or half of a whole step's one
-    whole = min(w.W, w.L) <= 256
+    whole = whole_steps(w, one_call=not (args.separate_calls or variant))
     per, alu_peak = (0.5, STEP_ALU_PEAK_TFLOPS) if whole else (1.0, ALU_PEAK_TFLOPS)
     achieved = per * algorithmic_bytes_per_sweep(w) / avg_s / 1e9
     # HBM bytes per sweep beyond L2: not measurable from inside this process (rocprofv3 --pmc reads

@@ -372,8 +372,9 @@ int sinkhorn_attn_set_streams(int n);
  * counter hand-over between neighbouring blocks through memory that all XCDs see; on MI355X the
  * two cost about the same (measured: a half-step takes 16 us fused against 13 us in launches of
  * its own at B*H*L = 131072, 60 us against 59 us at 524288 on one stream), so the default is 0.
- *   Calls whose Sinkhorn steps run as one launch each (half-bands up to 256, short calls up to 480) have no half-steps to
- * fuse: it does not affect them.
+ *   Calls whose Sinkhorn steps run as one launch each have no half-steps to fuse: it does not affect them.  Which these are
+ * depends on rows, half-band, d, type and workspace: ska_query_step_plan (sinkhorn_attn_query.h) says it; roughly half-bands
+ * up to 256, short bf16 calls (d <= 64; fp32 d = 32) up to 480, but not long calls at fp32 d = 128 (W > 64) or bf16 d = 32 (W > 128).
  *   It applies to the other forward calls (and the forward half of sinkhorn_attn_step) without a dustbin and
  * without a continuation schedule, outside stream capture, whose workspace has
  * sinkhorn_attn_workspace_bytes() bytes (the counters live at its end); other calls run unfused.

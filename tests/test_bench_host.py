@@ -57,6 +57,16 @@ def test_alu_ceiling():
     assert bench.HBM_PEAK_GBS == 8000.0 and bench.MFMA_PEAK_TFLOPS == {"bf16": 2500.0, "f32": 157.3}
 
 
+def test_ceilings_follow_the_library_on_whole_steps():
+    """Half an evaluation per half-step where a step is one launch: the library decides by rows, d and type as well, not by
+    the half-band alone."""
+    assert bench.whole_steps(CONFIGS["paper"]) and bench.whole_steps(CONFIGS["mid"], one_call=False)
+    for (N, L, d, W, dtype), whole in (((1, 262144, 64, 1024, "bf16"), False), ((1, 16384, 64, 400, "bf16"), True),
+                                       ((1, 65536, 64, 400, "bf16"), False), ((8, 65536, 32, 200, "bf16"), False),
+                                       ((1, 65536, 128, 128, "f32"), False), ((1, 4096, 128, 128, "f32"), True)):
+        assert bench.whole_steps(Workload("x", 0, 1, N, L, d, W, 1, 2, 1.0, dtype)) == whole, (N, L, d, W, dtype)
+
+
 def test_more_than_one_gpu_is_refused_before_anything_runs():
     env = dict(os.environ)
     env.pop("WORLD_SIZE", None)
