@@ -13,7 +13,7 @@ extern "C" {
 
 /*
  * The Sinkhorn steps after the first one of a forward (one_call 0), or of the forward half of sinkhorn_attn_step
- * (one_call 1), with a workspace of workspace_bytes.
+ * (one_call 1), with a workspace of workspace_bytes; lengths: 1 if the call gives any.
  */
 typedef struct {
     int whole_steps;       /* 1: a step is one launch; 0: two half-steps                                           */
@@ -21,7 +21,7 @@ typedef struct {
                            /* schedule, on a device that holds the launch); 0 where steps are whole                 */
                            /* the rest is about whole steps, 0 otherwise:                                          */
     int block_rows;        /* rows a workgroup owns at a time                                                    */
-    int segment_blocks;    /* blocks a workgroup walks one after the other                                       */
+    int segment_blocks;    /* blocks a workgroup walks one after the other, at most                              */
     int segments;          /* workgroups per problem                                                             */
     int sums_apart;        /* 1: no problem's column sums lie where another problem's backward writes (if not, a  */
                            /* one-call step joins its two streams between the directions)                        */
@@ -31,8 +31,8 @@ typedef struct {
 } ska_step_plan;
 
 /* Returns SKA_OK, or the error that the call itself would return for these sizes. */
-int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int dtype, size_t workspace_bytes,
-                        int one_call, ska_step_plan *plan);
+int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int lengths, int dtype,
+                        size_t workspace_bytes, int one_call, ska_step_plan *plan);
 
 #ifdef __cplusplus
 }

@@ -89,7 +89,7 @@ def load():
         lib.sinkhorn_attn_profile_read_phases.argtypes = [ctypes.POINTER(ctypes.c_double),
                                                           ctypes.POINTER(ctypes.c_long)]
         lib.ska_query_step_plan.restype = i
-        lib.ska_query_step_plan.argtypes = [i] * 9 + [sz, i, ctypes.POINTER(StepPlan)]
+        lib.ska_query_step_plan.argtypes = [i] * 10 + [sz, i, ctypes.POINTER(StepPlan)]
         lib.sinkhorn_attn_strerror.restype = ctypes.c_char_p
         lib.sinkhorn_attn_strerror.argtypes = [i]
         _lib = lib
@@ -102,13 +102,15 @@ class StepPlan(ctypes.Structure):
         ("sums_offset", ctypes.c_size_t * 2), ("sums_stride", ctypes.c_size_t), ("sums_bytes", ctypes.c_size_t)]
 
 
-def query_step_plan(B, H, L, d, W, T, R=2, dustbin=False, dtype=SKA_BF16, workspace_bytes=None, one_call=False) -> StepPlan:
+def query_step_plan(B, H, L, d, W, T, R=2, dustbin=False, dtype=SKA_BF16, workspace_bytes=None, one_call=False,
+                    lengths=False) -> StepPlan:
     """How a forward (one_call: sinkhorn_attn_step) of these sizes runs its Sinkhorn steps; host only.  workspace_bytes:
     those of sinkhorn_attn_workspace_bytes, as the binding allocates them, unless given."""
     if workspace_bytes is None:
         workspace_bytes = sinkhorn_attn_workspace_bytes(B, H, L, d, W, T, R, dustbin, dtype)
     plan = StepPlan()
-    rc = load().ska_query_step_plan(B, H, L, d, W, T, R, int(bool(dustbin)), int(dtype), workspace_bytes, int(bool(one_call)), plan)
+    rc = load().ska_query_step_plan(B, H, L, d, W, T, R, int(bool(dustbin)), int(bool(lengths)), int(dtype), workspace_bytes,
+                                    int(bool(one_call)), plan)
     if rc != SKA_OK:
         raise SinkhornAttnError(rc)
     return plan

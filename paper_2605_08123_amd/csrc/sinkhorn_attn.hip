@@ -57,6 +57,7 @@ struct Problem {
     const float *q_db = nullptr, *k_db = nullptr, *v_db = nullptr;   // learned dustbin tokens [N][d] fp32, or null
     float *dq_db = nullptr, *dk_db = nullptr, *dv_db = nullptr;      //   and their gradients (backward)
     bool token() const { return q_db != nullptr; }
+    bool lengths() const { return len_q || len_k; }
     long uv_us = 0;                                   // floats between the UV blocks of consecutive problems (0: dense, 2(R+1) Lp)
     int resume_t = 0;                                 // forward: UV holds the iterates up to tail step resume_t - 1; run that
                                                       //   tail step and the output map only (the depth selector's increments)
@@ -742,7 +743,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // yet; the next step's launch does so on the way, and a launch of its own (flush) where v is needed by itself.  The
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
-    const StepShape shape = step_shape<T, D>(N, L, p.W);
+    const StepShape shape = step_shape<T, D>(N, L, p.W, p.lengths());
     const int nseg = shape.NF ? (int)step_segments(shape, L) : 0;
     const StepSums sums = step_sums(p, shape, fused);
     const long pstride = sums.stride;
@@ -761,6 +762,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     step.us = us; step.part_stride = pstride;
     step.L = L; step.W = base.W; step.NF = shape.NF; step.M = shape.M; step.hw = shape.hw; step.nseg = nseg;
     step.rcp = shape.NF ? segment_reciprocal(shape.NF * shape.M) : 0;
+    if (p.lengths() && shape.M > 1) {
+        const int least = (shape.hw + shape.NF - 1) / shape.NF;
+        if (least < shape.M) step.least = least > 1 ? least : 1;
+        step.rseg = segment_reciprocal(shape.NF * nseg);
+    }
     step.nh = p.H; step.dustbin = p.dustbin;
     if (sizeof(T) == 4) step.up = (float)ilogbf((float)(2 * base.W + 1));
     auto flush = [&]() -> int {
@@ -914,7 +920,7 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // the kernels before the sweeps take all problems on st -- except the plain row dot of a fused
     // step, which each stream does for its own half so that the two chains stay apart (not if one half's vectors
     // lie over sums that the other half may still read)
-    const bool own_halves = fused && cx.side && !seed && !p.dustbin && step_sums(p, step_shape<T, D>(N, L, p.W), true).apart;
+    const bool own_halves = fused && cx.side && !seed && !p.dustbin && step_sums(p, step_shape<T, D>(N, L, p.W, p.lengths()), true).apart;
     if (fused && !own_halves) SKA_TRY(cx.join());
     if (p.token()) {
         SQ = Vec{tok, ldw};
@@ -1120,17 +1126,18 @@ size_t sinkhorn_attn_workspace_bytes(int B, int H, int L, int d, int W, int T, i
     return ws_bytes(p);
 }
 
-int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int dtype, size_t workspace_bytes,
-                        int one_call, ska_step_plan *plan)
+int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int lengths, int dtype,
+                        size_t workspace_bytes, int one_call, ska_step_plan *plan)
 {
     Problem p{B, H, L, d, W, T, R, dustbin ? 1 : 0, dtype, 1.f, 0.f};
     if (!plan) return SKA_EINVAL;
+    if (lengths && dustbin) return SKA_EUNSUPPORTED;
     const int rc = check_common(p);
     if (rc != SKA_OK) return rc;
     p.ws_given = workspace_bytes;
     if (workspace_bytes < (one_call ? ws_bytes(p) : ws_qs_bytes(p))) return SKA_EWORKSPACE;
     auto with = [&](auto elem, auto dim) {
-        const StepShape sh = step_shape<decltype(elem), decltype(dim)::value>(p.N(), L, W);
+        const StepShape sh = step_shape<decltype(elem), decltype(dim)::value>(p.N(), L, W, lengths != 0);
         const StepSums s = step_sums(p, sh, one_call != 0);
         *plan = ska_step_plan{};
         plan->sums_apart = s.apart;

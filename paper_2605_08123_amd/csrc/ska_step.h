@@ -66,6 +66,8 @@ struct StepArgs {
     int lstride, sstride;          // ... targets, spokes
     int L, W, NF, M, hw, nseg;     // fragments per block, blocks per segment, ceil(W / 32), segments per problem
     unsigned rcp;                  // segment_reciprocal(NF M)
+    int least;                     // blocks that a segment cut by lengths has at least (0: M blocks always)
+    unsigned rseg;                 // segment_reciprocal(NF nseg)
     int nb_total, rev, nh, n0, dustbin;   // (as in SweepArgs)
     float c2, sdb;                 // score scale in base 2 (fp32 storage); scalar dustbin score
     // fp32 storage: entries are evaluated 2^up times too large, about 2 W + 1, which their row's sum and weight take out again:
@@ -93,7 +95,20 @@ __device__ __forceinline__ StepLens step_lens(const StepArgs &p, int n)
 
 // x / SL (tiles per segment) as a multiplication: exact for x < 2^20 and SL <= 2^12, since x (SL - 1) < 2^32
 inline unsigned segment_reciprocal(int SL) { return SL == 1 ? 0u : (unsigned)((0x100000000ull + SL - 1) / SL); }
-__device__ __forceinline__ int segment_of(const StepArgs &p, int x) { return p.rcp ? (int)__umulhi((unsigned)x, p.rcp) : x; }
+// How a problem is cut into segments: SL tiles each, and 1 / SL as above.  With lengths the segments share the valid rows (each at
+// least hw tiles long): cut for all L rows, most of them had nothing to do where a padded batch is short.  A forward of
+// eight problems of L = 32768, W = 256, all of a tenth of that: 810 -> 361 us, half-steps 450.
+struct StepCut { int SL; unsigned rcp; };
+__device__ __forceinline__ StepCut step_cut(const StepArgs &p, int Le)
+{
+    StepCut cut{p.NF * p.M, p.rcp};
+    if (!p.least) return cut;
+    const unsigned tiles = ((unsigned)Le + 31) / 32 + p.nseg * p.NF - 1;   // ceil(tiles / (NF nseg)) blocks
+    const int SL = p.NF * max((int)(p.rseg ? __umulhi(tiles, p.rseg) : tiles), p.least);
+    if (SL != cut.SL) cut = StepCut{SL, SL == 1 ? 0u : 0xffffffffu / (unsigned)SL + 1u};   // (a division; mostly nothing changes)
+    return cut;
+}
+__device__ __forceinline__ int segment_of(const StepCut &cut, int x) { return cut.rcp ? (int)__umulhi((unsigned)x, cut.rcp) : x; }
 // What x in base 2 lost by rounding, as the evaluation takes it (x * LOG2E in fp32): a whole row's or column's entries are
 // off by it, and the update of its potential puts it right.  (Without: fp32 outputs 4 % further from their value.)
 __device__ __forceinline__ float base2_rest(float x)
@@ -148,10 +163,10 @@ template <bool BASE2> __device__ __forceinline__ float column_update(float v, fl
 struct ColumnSegments {
     int n, step;
     long first;
-    __device__ __forceinline__ ColumnSegments(const StepArgs &p, int t, int nseg_valid)
+    __device__ __forceinline__ ColumnSegments(const StepArgs &p, const StepCut &cut, int t, int nseg_valid)
     {
-        const int tile = t >> 5, SL = p.NF * p.M;
-        const int lo = min(segment_of(p, max(tile - p.hw, 0)), nseg_valid - 1), hi = min(segment_of(p, tile + p.hw), nseg_valid - 1);
+        const int tile = t >> 5, SL = cut.SL;
+        const int lo = min(segment_of(cut, max(tile - p.hw, 0)), nseg_valid - 1), hi = min(segment_of(cut, tile + p.hw), nseg_valid - 1);
         n = hi - lo + 1;
         step = 64 * p.hw;   // (segments overlap by 2 hw tiles)
         first = (long)lo * (32 * (SL + 2 * p.hw)) + (t - 32 * (lo * SL - p.hw));
@@ -160,9 +175,9 @@ struct ColumnSegments {
     __device__ __forceinline__ long at(int i) const { return first + (long)min(i, n - 1) * step; }
 };
 // their sum, in the order of the segments
-__device__ __forceinline__ float column_sum(const StepArgs &p, const float *part, int t, int nseg_valid)
+__device__ __forceinline__ float column_sum(const StepArgs &p, const StepCut &cut, const float *part, int t, int nseg_valid)
 {
-    const ColumnSegments cg(p, t, nseg_valid);
+    const ColumnSegments cg(p, cut, t, nseg_valid);
     float c = 0.f;
     for (int i0 = 0; i0 < cg.n; i0 += 4) {
         float x[4];
@@ -238,7 +253,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     const int chunk = (p.nb_total + 7) >> 3, bx = (int)blockIdx.x;
     const int lb = (bx & 7) * chunk + (p.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
     if (lb >= p.nb_total) return;
-    const int hw = p.hw, M = MARCH ? p.M : 1, NT = 2 * hw + 1, nwt = NF + 2 * hw;
+    const int hw = p.hw, NT = 2 * hw + 1, nwt = NF + 2 * hw;
     const LD lds(hw);
     const int RS = lds.rs;
     const int n = lb / p.nseg, seg = lb % p.nseg;
@@ -247,8 +262,11 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     const int f = wave / G, g = wave % G;
     const int L = p.L, W = p.W;
     const StepLens ln = step_lens(p, n);
-    const int Lt = ln.Lt, Le = ln.Le, Lc = ln.Lc, nseg_valid = (Le + BM * M - 1) / (BM * M);
-    const int b0 = seg * M, b1 = min(b0 + M, (L + BM - 1) / BM), bv = min(b1, (Le + BM - 1) / BM);   // blocks; those with valid rows
+    const int Lt = ln.Lt, Le = ln.Le, Lc = ln.Lc;
+    const StepCut cut = MARCH ? step_cut(p, Le) : StepCut{NF, p.rcp};
+    const int M = MARCH ? cut.SL / NF : 1, nseg_valid = (Le + BM * M - 1) / (BM * M), nblk = (L + BM - 1) / BM;
+    // blocks (the last segment's go on to the end: the rows past the valid ones are its to clear); those with valid rows
+    const int b0 = min(seg * M, nblk), b1 = seg + 1 == p.nseg ? nblk : min(b0 + M, nblk), bv = min(b1, (Le + BM - 1) / BM);
 
     unsigned char *vs = smem + lds.vs;
     float *us = reinterpret_cast<float *>(smem + LD::US);
@@ -264,7 +282,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     // rows without an edge: zeros, and this segment's share of v there
     for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR) {
         u_out[t] = 0.f;
-        if (part) v_out[t] = t < Lc ? column_update<true>(vp[t], column_sum(p, part, t, nseg_valid), ColumnTarget(lbp ? lbp[t] : 0.f)) : 0.f;
+        if (part) v_out[t] = t < Lc ? column_update<true>(vp[t], column_sum(p, cut, part, t, nseg_valid), ColumnTarget(lbp ? lbp[t] : 0.f)) : 0.f;
     }
     if (b0 >= bv) return;
     const long moff = (long)n * L * D;
@@ -329,7 +347,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         win_sp[k] = (DUST && spc ? spc : vp)[t];   // (v, which is requested anyway, where nobody asks)
         if (lbp) win_lb[k] = lbp[min(t, max(Lc - 1, 0))];
         if (part) {
-            const ColumnSegments cg(p, t, nseg_valid);
+            const ColumnSegments cg(p, cut, t, nseg_valid);
 #pragma unroll
             for (int i = 0; i < NSUM; ++i) win_sum[k][i] = part[cg.at(i)];
         }
@@ -371,7 +389,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         const int i = tid + k * NTHR, t = 32 * kseg + i;
         float sum = 0.f;
         if (part) {
-            const ColumnSegments cg(p, min(max(t, 0), L - 1), nseg_valid);
+            const ColumnSegments cg(p, cut, min(max(t, 0), L - 1), nseg_valid);
 #pragma unroll
             for (int q = 0; q < NSUM; ++q) sum += q < cg.n ? win_sum[k][q] : 0.f;
         }
@@ -400,7 +418,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         // use of the slots' old content
         float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nla = 0.f, nlb = 0.f, nsp = 0.f;
         const int nt = 32 * (k0 + nwt) + tid, no = (b + 1) * BM + tid;
-        const int nq = min(segment_of(p, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
+        const int nq = min(segment_of(cut, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
         auto request_tiles = [&]() {
             int sl = base + nwt;
             if (sl >= RS) sl -= RS;
@@ -733,7 +751,8 @@ __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
     float out = 0.f;
     if (t < ln.Lc) {
         const float v = p.v[n * p.us + t];
-        float sum = column_sum(p, part, t, (ln.Le + 32 * p.NF * p.M - 1) / (32 * p.NF * p.M));
+        const StepCut cut = step_cut(p, ln.Le);
+        float sum = column_sum(p, cut, part, t, (ln.Le + 32 * cut.SL - 1) / (32 * cut.SL));
         if (p.dustbin) sum += fast_exp2(((p.spoke_c ? p.spoke_c[(long)n * p.sstride + t] : p.sdb) + uL + v) * LOG2E);
         out = column_update<true>(v, sum, ColumnTarget(p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f));
     }

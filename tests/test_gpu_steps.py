@@ -45,10 +45,15 @@ LONG = [  # other block shapes; segments of several blocks, also ragged ones and
     ("plain", "bf16", 64, 1, 17000, 170, 2, 1), ("plain", "bf16", 64, 1, 17001, 200, 2, 1), ("plain", "bf16", 64, 1, 40000, 150, 2, 2),
     ("dustbin", "bf16", 64, 1, 40001, 190, 2, 1), ("plain", "bf16", 128, 1, 40001, 160, 2, 1), ("dustbin", "bf16", 128, 1, 20000, 90, 2, 1),
     ("plain", "bf16", 128, 1, 40000, 70, 2, 1), ("plain", "bf16", 128, 1, 34000, 170, 2, 2), ("dustbin", "bf16", 64, 1, 70000, 96, 2, 1),
-    ("plain", "f32", 64, 1, 10000, 170, 2, 1), ("plain", "bf16", 128, 1, 40000, 16, 2, 1), ("dustbin", "bf16", 64, 1, 60000, 20, 2, 1)]
+    ("plain", "f32", 64, 1, 10000, 170, 2, 1), ("plain", "bf16", 128, 1, 40000, 16, 2, 1), ("dustbin", "bf16", 64, 1, 60000, 20, 2, 1),
+    # padded batches whose items are all short (the segments share the valid rows), with targets as well; above the line for lengths
+    ("short", "bf16", 64, 4, 20000, 256, 3, 1), ("short", "bf16", 64, 8, 16001, 128, 2, 2), ("short", "bf16", 128, 4, 20000, 200, 2, 1),
+    ("short", "f32", 64, 3, 30000, 250, 2, 1), ("short", "f32", 32, 4, 20001, 100, 2, 1), ("short", "bf16", 32, 5, 20001, 256, 2, 1),
+    ("short targets", "bf16", 64, 4, 20000, 200, 3, 1), ("short targets", "f32", 64, 3, 30000, 250, 2, 1),
+    ("short", "bf16", 64, 8, 30000, 200, 2, 1), ("short", "bf16", 64, 14, 30000, 200, 2, 1), ("short", "bf16", 64, 300, 700, 256, 2, 1)]
 
 
-HALF_STEPS = [("plain", "bf16", 64, 1, 1500, 481, 2, 1)]   # the others run whole steps
+HALF_STEPS = [("plain", "bf16", 64, 1, 1500, 481, 2, 1), ("short", "bf16", 64, 14, 30000, 200, 2, 1)]   # the others run whole steps
 
 
 @pytest.mark.parametrize("case", SHORT + LONG, ids=lambda c: "-".join(map(str, c)))
@@ -59,7 +64,8 @@ def test_steps_equal_half_steps(case):
     from paper_2605_08123_amd import binding
     kind, dtype, d, N, L, W, T, R = case
     print(f"\n[case] {case}", flush=True)
-    whole = binding.query_step_plan(N, 1, L, d, W, T, R, kind == "dustbin", 0 if dtype == "f32" else 1).whole_steps
+    whole = binding.query_step_plan(N, 1, L, d, W, T, R, kind == "dustbin", 0 if dtype == "f32" else 1,
+                                    lengths=kind[:5] in ("varle", "short")).whole_steps
     assert bool(whole) == (case not in HALF_STEPS)   # (both sides of the rule's lines)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(17)
@@ -71,7 +77,10 @@ def test_steps_equal_half_steps(case):
         lq, lk = (torch.randint(1, L + 1, (N,), generator=gen, device="cuda").int() for _ in range(2))
         lq[0], lk[1] = 0, 1
         lq[2], lk[2] = L // 3, L   # rows end well before the columns do
-    if kind == "marginals":
+    if kind.startswith("short"):
+        lq, lk = (torch.randint(L // 12, L // 8, (N,), generator=gen, device="cuda").int() for _ in range(2))
+        lk[-1] = 3   # (less than a block, and queries far beyond it)
+    if kind in ("marginals", "short targets"):
         a, b = (torch.rand((N, 1, L), generator=gen, device="cuda") + 0.5 for _ in range(2))
         la, lb = a.log(), (b * a.sum(-1, keepdim=True) / b.sum(-1, keepdim=True)).log()
     if kind == "masked":
@@ -242,7 +251,7 @@ def test_split_step_with_unequal_halves_equals_one_stream(case):
     dtype, d, N, L, W, R, len0, len1 = case
     print(f"\n[case] {case}", flush=True)
     td, code = (torch.float32, 0) if dtype == "f32" else (torch.bfloat16, 1)
-    plan = binding.query_step_plan(N, 1, L, d, W, 6, R, False, code, one_call=True)
+    plan = binding.query_step_plan(N, 1, L, d, W, 6, R, False, code, one_call=True, lengths=True)
     assert plan.whole_steps and bool(plan.sums_apart) == (W <= 256)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(23)
