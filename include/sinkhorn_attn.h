@@ -157,8 +157,10 @@ int sinkhorn_attn_step_static(const void *Q, const void *K, const void *V, const
  * exp(S_ij + u_i); in the backward every ubar is divided by a and every vbar by b where it
  * multiplies a plan, per the general-marginal half-step Jacobians and finite-tail VJP there).
  *   log_a, log_b: [B,H,L] fp32 device arrays, logarithms of the positive row / column
- *   targets; the caller makes them compatible (equal totals per problem).  NULL = unit
- *   targets (both NULL: exactly the calls above).  eta0, when requested, is the raw base
+ *   targets; the caller makes them compatible (equal totals per problem).  A target may be as small as
+ *   it likes (-100, -1e4, -inf: as a soft mask) where every token's window holds ordinary ones too; over a
+ *   whole window targets carry from about e^-75 to e^80, and so far may rows and columns be out of balance.
+ *   NULL = unit targets (both NULL: exactly the calls above).  eta0, when requested, is the raw base
  *   cotangent vbar^(0) (not divided by b).  Not combined with the dustbin, whose targets are
  *   all one: SKA_EUNSUPPORTED.
  */

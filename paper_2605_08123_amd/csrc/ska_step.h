@@ -331,13 +331,17 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             *reinterpret_cast<float *>(vs + at * 4) = v;
         }
     };
-    // u of a row with its target, as the evaluation takes it
-    auto row_u = [&](float u, float log_a) { return TARGETS ? less_nat(u, row_target_nat(log_a)) : u; };
+    // u of a row of a block, less its target, into its place in LDS
+    auto stage_u = [&](int at, float u, float log_a) {
+        if constexpr (TARGETS) u = less_nat(u, row_target_nat(log_a));
+        us[at] = u;
+        if constexpr (!PRE) us[(LD::UE - LD::US) / 4 + at] = base2_less(u, -p.up).x;
+    };
     // Loads return in order: the vectors, which need work, are requested before the tiles and the owner rows.
     constexpr int NWIN = (32 * (NF + G * NTW) + NTHR - 1) / NTHR;   // columns of a window per thread
     constexpr int NSUM = MARCH ? 3 : (G * NTW - 1) / NF + 2;        // segments that a column can have sums from, at most
-    float u_first = tid < BM && b0 * BM + tid < Le ? xsp[b0 * BM + tid] : -INFINITY;
-    if (lap) u_first = row_u(u_first, lap[min(b0 * BM + min(tid, BM - 1), Le - 1)]);
+    const float u_first = tid < BM && b0 * BM + tid < Le ? xsp[b0 * BM + tid] : -INFINITY;
+    const float la_first = lap ? lap[min(b0 * BM + min(tid, BM - 1), Le - 1)] : 0.f;
     float win_v[NWIN], win_sum[NWIN][NSUM], win_lb[NWIN], win_sp[NWIN];
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
@@ -395,7 +399,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         }
         if (i < 32 * nwt) stage_v(i, t, finish_v(t, win_v[k], sum, win_lb[k], win_sp[k]), win_lb[k]);   // (later columns: with their block)
     }
-    if (tid < BM) us[tid] = u_first;
+    if (tid < BM) stage_u(tid, u_first, la_first);
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
     __syncthreads();
 
@@ -443,12 +447,10 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 
         [[maybe_unused]] f32x16 ci;   // fp32 storage: the rows' potentials
         if constexpr (!PRE) {
-#pragma clang fp contract(off)   // (rounded as base2_rest takes it)
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 v4 = *reinterpret_cast<const float4 *>(us + par * BM + 32 * f + 8 * q + 4 * h);
-                ci[4 * q + 0] = base2_less(v4.x, -p.up).x; ci[4 * q + 1] = base2_less(v4.y, -p.up).x;
-                ci[4 * q + 2] = base2_less(v4.z, -p.up).x; ci[4 * q + 3] = base2_less(v4.w, -p.up).x;
+                const float4 v4 = *reinterpret_cast<const float4 *>(us + (LD::UE - LD::US) / 4 + par * BM + 32 * f + 8 * q + 4 * h);
+                ci[4 * q + 0] = v4.x; ci[4 * q + 1] = v4.y; ci[4 * q + 2] = v4.z; ci[4 * q + 3] = v4.w;
             }
         }
         const float u_old = us[par * BM + 32 * f + c];   // (TARGETS: less nat)
@@ -677,7 +679,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             int sl = 32 * (base + nwt) + tid;
             if (sl >= 32 * RS) sl -= 32 * RS;
             stage_v(sl, nt, v_new, nlb);
-            us[(LD::TWO == 2 ? par ^ 1 : 0) * BM + tid] = no < Le ? row_u(nu, nla) : -INFINITY;
+            stage_u((LD::TWO == 2 ? par ^ 1 : 0) * BM + tid, no < Le ? nu : -INFINITY, nla);
         }
         if (DUST && !more) {   // the segment's last block: every thread has added its share
 #pragma unroll
