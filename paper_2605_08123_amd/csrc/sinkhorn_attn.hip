@@ -462,12 +462,23 @@ template <typename T, int D> int sweep(Call &cx, int mode, const SweepArgs &a, i
 // read much more of the band than they own have more sums than that; those lie over the backward's vectors, and the
 // streams are joined between the two directions (apart = false).
 struct StepSums { size_t off[2]; long stride; bool apart; };
+// whether a call with lengths cuts its segments from the valid rows: in the place of the fused half-steps' counters, if that
+// has room.  Not for segments of four blocks and less, where finding its place costs a workgroup more than there is to gain at
+// ordinary lengths (L/2 .. L: eight problems of L = 16384, W = 256 502 -> 527 us, 128 of L = 600, W = 200 536 -> 551; five blocks, eight
+// of 17401, d = 32, W = 184: 475 -> 439).
+inline bool step_is_cut(const Problem &p, const StepShape &sh)
+{
+    if (!p.lengths() || !sh.NF || sh.M <= 4 || sh.M <= step_least(sh) || p.B > CUT_ITEMS) return false;
+    const long nseg = step_segments(sh, p.L);   // (M blocks each must be within the cut's bounds)
+    return nseg * p.N() <= CUT_SEGS && (p.N() == 1 || nseg * ((p.N() + 1) / 2) <= CUT_HALF) && p.ws_given >= ws_bytes(p) &&
+           ws_chain_bytes(p) >= (size_t)(CUT_HEAD + p.B + 1) * sizeof(int);
+}
 inline StepSums step_sums(const Problem &p, const StepShape &sh, bool one_call)
 {
     StepSums s{{0, 0}, 0, true};
     if (!sh.NF) return s;
     const size_t N = p.N(), row = N * p.ldw(), gu = row * sizeof(float), pack = row * 32;
-    const long used = step_part_stride(sh, p.L, p.dustbin), own = 32 / (long)sizeof(float) * p.ldw();
+    const long used = step_part_stride(sh, p.L, p.dustbin, step_is_cut(p, sh)), own = 32 / (long)sizeof(float) * p.ldw();
     if (one_call && used <= own) {
         s.off[0] = ws_vec_bytes(p) - 4 * pack;
         s.off[1] = s.off[0] + pack;
@@ -486,7 +497,7 @@ inline StepSums step_sums(const Problem &p, const StepShape &sh, bool one_call)
 }
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
-    p.nb_total = p.nseg * N;
+    p.nb_total = p.cut ? (N < p.items * p.nh ? CUT_HALF : CUT_SEGS) : p.nseg * N;
     const int lds = StepLds<T, D, NF, G, NTW, KIND, FORM>(p.hw).total;
     static bool raised[MAX_DEVICES];
     if (!raised[dev]) {
@@ -506,6 +517,8 @@ template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape
         if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) { \
             constexpr bool ANY = KIND_ == STEP_BLOCK; \
             if (p.log_a || p.log_b) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(p, N, st, dev); \
+            if constexpr (!ANY) \
+                if (p.cut) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_CUT>(p, N, st, dev); \
             if (!ANY && p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_DUSTBIN>(p, N, st, dev); \
             return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_PLAIN>(p, N, st, dev); \
         }
@@ -526,9 +539,12 @@ template <typename T, int D> int step_sweep(Call &cx, const StepArgs &p, const S
     };
     if (!cx.side || N < 2) return launch(p, N, cx.st);
     const int n0 = N / 2;
-    SKA_TRY(launch(p, n0, cx.st));
+    StepArgs a = p;
+    a.np = n0;
+    SKA_TRY(launch(a, n0, cx.st));
     cx.busy = true;
     StepArgs b = p;
+    b.np = N - n0;
     auto mat = [&](const void *q) -> const void * {
         return q ? reinterpret_cast<const unsigned char *>(q) + (long)n0 * p.L * D * (long)sizeof(T) : nullptr;
     };
@@ -743,7 +759,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // yet; the next step's launch does so on the way, and a launch of its own (flush) where v is needed by itself.  The
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
-    const StepShape shape = step_shape<T, D>(N, L, p.W, p.lengths());
+    const StepShape shape = step_shape<T, D>(N, L, p.W);
     const int nseg = shape.NF ? (int)step_segments(shape, L) : 0;
     const StepSums sums = step_sums(p, shape, fused);
     const long pstride = sums.stride;
@@ -762,10 +778,13 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     step.us = us; step.part_stride = pstride;
     step.L = L; step.W = base.W; step.NF = shape.NF; step.M = shape.M; step.hw = shape.hw; step.nseg = nseg;
     step.rcp = shape.NF ? segment_reciprocal(shape.NF * shape.M) : 0;
-    if (p.lengths() && shape.M > 1) {
-        const int least = (shape.hw + shape.NF - 1) / shape.NF;
-        if (least < shape.M) step.least = least > 1 ? least : 1;
-        step.rseg = segment_reciprocal(shape.NF * nseg);
+    step.items = p.B; step.np = N;
+    if (part[0] && step_is_cut(p, shape)) {
+        int *cut = reinterpret_cast<int *>(reinterpret_cast<unsigned char *>(ws) + ws_core_bytes(p));
+        hipLaunchKernelGGL(step_cut_kernel, dim3(1), dim3(NTHREADS), 0, st,
+                           CutArgs{p.len_q, p.len_k, cut, p.B, p.H, L, base.W, shape.NF, shape.M, step_least(shape)});
+        if (hipGetLastError() != hipSuccess) return SKA_EHIP;
+        step.cut = cut;
     }
     step.nh = p.H; step.dustbin = p.dustbin;
     if (sizeof(T) == 4) step.up = (float)ilogbf((float)(2 * base.W + 1));
@@ -920,7 +939,7 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // the kernels before the sweeps take all problems on st -- except the plain row dot of a fused
     // step, which each stream does for its own half so that the two chains stay apart (not if one half's vectors
     // lie over sums that the other half may still read)
-    const bool own_halves = fused && cx.side && !seed && !p.dustbin && step_sums(p, step_shape<T, D>(N, L, p.W, p.lengths()), true).apart;
+    const bool own_halves = fused && cx.side && !seed && !p.dustbin && step_sums(p, step_shape<T, D>(N, L, p.W), true).apart;
     if (fused && !own_halves) SKA_TRY(cx.join());
     if (p.token()) {
         SQ = Vec{tok, ldw};
@@ -1129,7 +1148,8 @@ size_t sinkhorn_attn_workspace_bytes(int B, int H, int L, int d, int W, int T, i
 int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int lengths, int dtype,
                         size_t workspace_bytes, int one_call, ska_step_plan *plan)
 {
-    Problem p{B, H, L, d, W, T, R, dustbin ? 1 : 0, dtype, 1.f, 0.f};
+    static const int some = 0;   // (a length is asked about, never read)
+    Problem p{B, H, L, d, W, T, R, dustbin ? 1 : 0, dtype, 1.f, 0.f, nullptr, nullptr, lengths ? &some : nullptr};
     if (!plan) return SKA_EINVAL;
     if (lengths && dustbin) return SKA_EUNSUPPORTED;
     const int rc = check_common(p);
@@ -1137,7 +1157,7 @@ int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dus
     p.ws_given = workspace_bytes;
     if (workspace_bytes < (one_call ? ws_bytes(p) : ws_qs_bytes(p))) return SKA_EWORKSPACE;
     auto with = [&](auto elem, auto dim) {
-        const StepShape sh = step_shape<decltype(elem), decltype(dim)::value>(p.N(), L, W, lengths != 0);
+        const StepShape sh = step_shape<decltype(elem), decltype(dim)::value>(p.N(), L, W);
         const StepSums s = step_sums(p, sh, one_call != 0);
         *plan = ska_step_plan{};
         plan->sums_apart = s.apart;
@@ -1149,7 +1169,7 @@ int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dus
         plan->whole_steps = 1;
         plan->block_rows = 32 * sh.NF; plan->segment_blocks = sh.M; plan->segments = (int)step_segments(sh, L);
         plan->sums_offset[0] = s.off[0]; plan->sums_offset[1] = s.off[1];
-        plan->sums_stride = s.stride * sizeof(float); plan->sums_bytes = step_part_stride(sh, L, p.dustbin) * sizeof(float);
+        plan->sums_stride = s.stride * sizeof(float); plan->sums_bytes = step_part_stride(sh, L, p.dustbin, step_is_cut(p, sh)) * sizeof(float);
         return SKA_OK;
     };
     using D32 = std::integral_constant<int, 32>;
@@ -1405,6 +1425,7 @@ int sinkhorn_attn_step_static(const void *Q, const void *K, const void *V, const
     int rc = check_common(p);
     if (rc != SKA_OK) return rc;
     if (ws_bytes(p) > (size_t)SKA_STATIC_SCRATCH_BYTES) return SKA_ESTATIC;
+    p.ws_given = ws_bytes(p);
     // everything on the caller's stream: no helper stream, no events, nothing created
     Call cx(stream, p.N(), p.L, p.W, false);
     if (cx.rc != SKA_OK) return cx.rc;

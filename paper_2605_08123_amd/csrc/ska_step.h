@@ -66,8 +66,8 @@ struct StepArgs {
     int lstride, sstride;          // ... targets, spokes
     int L, W, NF, M, hw, nseg;     // fragments per block, blocks per segment, ceil(W / 32), segments per problem
     unsigned rcp;                  // segment_reciprocal(NF M)
-    int least;                     // blocks that a segment cut by lengths has at least (0: M blocks always)
-    unsigned rseg;                 // segment_reciprocal(NF nseg)
+    const int *cut;                // with lengths: how the problems are cut into segments (null: M blocks each, nseg of them)
+    int items, np;                 // batch items of the call, problems of the launch
     int nb_total, rev, nh, n0, dustbin;   // (as in SweepArgs)
     float c2, sdb;                 // score scale in base 2 (fp32 storage); scalar dustbin score
     // fp32 storage: entries are evaluated 2^up times too large, about 2 W + 1, which their row's sum and weight take out again:
@@ -95,18 +95,43 @@ __device__ __forceinline__ StepLens step_lens(const StepArgs &p, int n)
 
 // x / SL (tiles per segment) as a multiplication: exact for x < 2^20 and SL <= 2^12, since x (SL - 1) < 2^32
 inline unsigned segment_reciprocal(int SL) { return SL == 1 ? 0u : (unsigned)((0x100000000ull + SL - 1) / SL); }
-// How a problem is cut into segments: SL tiles each, and 1 / SL as above.  With lengths the segments share the valid rows (each at
-// least hw tiles long): cut for all L rows, most of them had nothing to do where a padded batch is short.  A forward of
-// eight problems of L = 32768, W = 256, all of a tenth of that: 810 -> 361 us, half-steps 450.
+// How a problem is cut into segments: SL tiles each, and 1 / SL as above.
 struct StepCut { int SL; unsigned rcp; };
-__device__ __forceinline__ StepCut step_cut(const StepArgs &p, int Le)
+// With lengths the segments are cut from the valid rows of all problems (step_cut_kernel, once per call): as long as it takes to
+// have one per CU, each problem as many as its rows need.  Cut for all L rows, most of them have nothing to do where a padded
+// batch is short, and the longest item alone sets the time of a launch.  Forward of 32 problems of L = 16384, W = 200, us, cut for
+// all rows / so / half-steps: lengths of L/2 .. L 1527 / 1401 / 1416, L/8 .. L 1518 / 1080 / 1239, one item of eight of L and the
+// others L/10 1472 / 583 / 1129, all L/10 1220 / 385 / 734; all L the same 1605 / 1746.  In memory: CUT_HEAD words (tiles and blocks per
+// segment, 1 / tiles, segments of the problems before the second half and of all), then the segments of the problems before each item.
+constexpr int CUT_HEAD = 5, CUT_ITEMS = 128, CUT_SEGS = 256, CUT_HALF = 176;   // (at most so many segments in all, in either half)
+struct CutArgs {
+    const int *len_q, *len_k;
+    int *cut;
+    int items, nh, L, W, NF, M, least;   // M blocks per segment at most, at least `least`
+};
+__device__ __forceinline__ StepCut step_cut(const StepArgs &p)
 {
-    StepCut cut{p.NF * p.M, p.rcp};
-    if (!p.least) return cut;
-    const unsigned tiles = ((unsigned)Le + 31) / 32 + p.nseg * p.NF - 1;   // ceil(tiles / (NF nseg)) blocks
-    const int SL = p.NF * max((int)(p.rseg ? __umulhi(tiles, p.rseg) : tiles), p.least);
-    if (SL != cut.SL) cut = StepCut{SL, SL == 1 ? 0u : 0xffffffffu / (unsigned)SL + 1u};   // (a division; mostly nothing changes)
-    return cut;
+    if (!p.cut) return StepCut{p.NF * p.M, p.rcp};
+    return StepCut{p.cut[0], (unsigned)p.cut[2]};
+}
+// problem and segment of the launch's lb-th one (n < 0: there are no more); the problem's segments
+struct CutPlace { int n, seg, nseg; };
+__device__ __forceinline__ CutPlace cut_place(const StepArgs &p, int bx)
+{
+    const int lane = threadIdx.x & 63, half = p.cut[3], all = p.cut[4];
+    // the launch's problems are all of the call's, or its first or second half
+    const int first = p.n0 ? half : 0, count = (p.n0 ? all : p.np < p.items * p.nh ? half : all) - first;
+    const int chunk = (count + 7) >> 3, k = bx >> 3, lb = (bx & 7) * chunk + (p.rev ? chunk - 1 - k : k);
+    if (k >= chunk || lb >= count) return CutPlace{-1, 0, 0};
+    const int g = first + lb;
+    int item = -1;
+#pragma unroll
+    for (int q = 0; q < CUT_ITEMS / 64; ++q) {
+        const int i = 64 * q + lane;
+        item += __popcll(__ballot(i < p.items && p.cut[CUT_HEAD + min(i, p.items)] <= g));
+    }
+    const int before = p.cut[CUT_HEAD + item], nseg = (p.cut[CUT_HEAD + item + 1] - before) / p.nh, r = g - before;
+    return CutPlace{item * p.nh + r / nseg - p.n0, r % nseg, nseg};
 }
 __device__ __forceinline__ int segment_of(const StepCut &cut, int x) { return cut.rcp ? (int)__umulhi((unsigned)x, cut.rcp) : x; }
 // What x in base 2 lost by rounding, as the evaluation takes it (x * LOG2E in fp32): a whole row's or column's entries are
@@ -246,27 +271,34 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     constexpr bool MARCH = KIND != STEP_BLOCK, TIGHT = KIND == STEP_TIGHT;
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
-    constexpr bool TARGETS = FORM == STEP_TARGETS;
+    constexpr bool TARGETS = FORM == STEP_TARGETS, MAY_CUT = MARCH && (TARGETS || FORM == STEP_CUT);
     const bool DUST = FORM == STEP_ANY ? p.dustbin != 0 : FORM == STEP_DUSTBIN;
     extern __shared__ __align__(16) unsigned char smem[];
     take_args(p);
-    const int chunk = (p.nb_total + 7) >> 3, bx = (int)blockIdx.x;
-    const int lb = (bx & 7) * chunk + (p.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
-    if (lb >= p.nb_total) return;
+    const int bx = (int)blockIdx.x;
+    int n, seg, nseg = p.nseg;
+    if (MAY_CUT && p.cut) {
+        const CutPlace at = cut_place(p, bx);
+        if (at.n < 0) return;
+        n = __builtin_amdgcn_readfirstlane(at.n); seg = __builtin_amdgcn_readfirstlane(at.seg); nseg = __builtin_amdgcn_readfirstlane(at.nseg);
+    } else {
+        const int chunk = (p.nb_total + 7) >> 3, lb = (bx & 7) * chunk + (p.rev ? chunk - 1 - (bx >> 3) : (bx >> 3));
+        if (lb >= p.nb_total) return;
+        n = lb / nseg; seg = lb % nseg;
+    }
     const int hw = p.hw, NT = 2 * hw + 1, nwt = NF + 2 * hw;
     const LD lds(hw);
     const int RS = lds.rs;
-    const int n = lb / p.nseg, seg = lb % p.nseg;
     int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int f = wave / G, g = wave % G;
     const int L = p.L, W = p.W;
     const StepLens ln = step_lens(p, n);
     const int Lt = ln.Lt, Le = ln.Le, Lc = ln.Lc;
-    const StepCut cut = MARCH ? step_cut(p, Le) : StepCut{NF, p.rcp};
-    const int M = MARCH ? cut.SL / NF : 1, nseg_valid = (Le + BM * M - 1) / (BM * M), nblk = (L + BM - 1) / BM;
+    const StepCut cut = MAY_CUT ? step_cut(p) : StepCut{MARCH ? NF * p.M : NF, p.rcp};
+    const int M = MAY_CUT ? cut.SL / NF : MARCH ? p.M : 1, nseg_valid = (Le + BM * M - 1) / (BM * M), nblk = (L + BM - 1) / BM;
     // blocks (the last segment's go on to the end: the rows past the valid ones are its to clear); those with valid rows
-    const int b0 = min(seg * M, nblk), b1 = seg + 1 == p.nseg ? nblk : min(b0 + M, nblk), bv = min(b1, (Le + BM - 1) / BM);
+    const int b0 = min(seg * M, nblk), b1 = seg + 1 == nseg ? nblk : min(b0 + M, nblk), bv = min(b1, (Le + BM - 1) / BM);
 
     unsigned char *vs = smem + lds.vs;
     float *us = reinterpret_cast<float *>(smem + LD::US);
@@ -732,6 +764,53 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     }
 }
 
+// The cut of a call with lengths: the shortest segments of which there are at most CUT_SEGS in all and CUT_HALF in either half of
+// the problems (M blocks, the segments of a call without lengths, always do).  One workgroup; thread i tries the i-th length.
+__global__ __launch_bounds__(NTHREADS) void step_cut_kernel(const CutArgs a)
+{
+    __shared__ int nb[CUT_ITEMS], total, best;
+    const int tid = threadIdx.x, n0 = a.items * a.nh / 2;
+    if (tid == 0) { total = 0; best = a.M; }
+    __syncthreads();
+    if (tid < a.items) {
+        int Lq = a.L, Lk = a.L;
+        if (a.len_q) Lq = min(max(a.len_q[tid], 0), a.L);
+        if (a.len_k) Lk = min(max(a.len_k[tid], 0), a.L);
+        nb[tid] = ((Lk > 0 ? min(Lq, Lk + a.W) : 0) + 32 * a.NF - 1) / (32 * a.NF);
+        atomicAdd(&total, nb[tid] * a.nh);
+    }
+    __syncthreads();
+    auto segments = [&](int b, int M) { return max((nb[b] + M - 1) / M, 1); };
+    const int M = max((total + CUT_SEGS - 1) / CUT_SEGS, a.least) + tid;
+    if (M < a.M) {
+        int lo = 0, hi = 0;
+        for (int b = 0; b < a.items; ++b) {
+            const int s = segments(b, M), in_lo = min(max(n0 - b * a.nh, 0), a.nh);
+            lo += s * in_lo;
+            hi += s * (a.nh - in_lo);
+        }
+        // (a split call's halves share the CUs of each XCD; uneven ones that fill all 32 of them get in each other's way: 104 + 148
+        // segments 1653 us, 112 + 144 longer ones 1424)
+        const int xlo = (lo + 7) / 8, xhi = (hi + 7) / 8;
+        const bool halves = lo <= CUT_HALF && hi <= CUT_HALF && (xlo == xhi || xlo + xhi < CUT_SEGS / 8);
+        if (lo + hi <= CUT_SEGS && (n0 == 0 || halves)) atomicMin(&best, M);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const int SL = a.NF * best;
+        a.cut[0] = SL; a.cut[1] = best;
+        a.cut[2] = SL == 1 ? 0 : (int)(0xffffffffu / (unsigned)SL + 1u);
+        int at = 0;
+        for (int b = 0; b < a.items; ++b) {
+            const int s = segments(b, best);
+            a.cut[CUT_HEAD + b] = at;
+            if (n0 >= b * a.nh && n0 < (b + 1) * a.nh) a.cut[3] = at + s * (n0 - b * a.nh);
+            at += s * a.nh;
+        }
+        a.cut[CUT_HEAD + a.items] = a.cut[4] = at;
+    }
+}
+
 // v from the column sums of a step that no step follows (v_out may be p.v).
 __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
 {
@@ -753,7 +832,7 @@ __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
     float out = 0.f;
     if (t < ln.Lc) {
         const float v = p.v[n * p.us + t];
-        const StepCut cut = step_cut(p, ln.Le);
+        const StepCut cut = step_cut(p);
         float sum = column_sum(p, cut, part, t, (ln.Le + 32 * cut.SL - 1) / (32 * cut.SL));
         if (p.dustbin) sum += fast_exp2(((p.spoke_c ? p.spoke_c[(long)n * p.sstride + t] : p.sdb) + uL + v) * LOG2E);
         out = column_update<true>(v, sum, ColumnTarget(p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f));

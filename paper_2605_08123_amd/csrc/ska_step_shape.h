@@ -16,8 +16,8 @@ template <typename T, int D> struct StepTile {
 // window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
 enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
 // What a call's steps add to the plain ones: nothing, a dustbin, a dustbin if the arguments say so, targets of rows or columns
-// (which go with no dustbin).
-enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS };
+// (which go with no dustbin; a cut or none), segments cut from valid rows.
+enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS, STEP_CUT };
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> struct StepLds {   // offsets in bytes
     static constexpr int RSUM = 0;                              // [NF][G][32] row sums
     static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
@@ -87,12 +87,7 @@ template <typename T, int D> int step_lds(const StepShape &sh)   // bytes (of th
 //   (2,4,3) 311, W = 192: 343, (2,4,4) 372.  d = 32, W = 160: 262144 rows (4,2,6) 620, 524288 rows 1137, half-steps 656 / 935
 //   W = 300 .. 480 (2,4,9): 16384 rows 244 .. 271, half-steps 469 .. 618; 32768 rows 414 .. 456 / 470 .. 619; beyond, the 36
 //   tiles that a block of 64 rows reads are what bounds it
-//   With lengths the longest problem sets a launch's time, while half-steps take time by valid rows.  Steps over half-steps with
-// full problems / lengths of L/2 .. L / L/8 .. L / one of eight of L, the others L/10: 131072 rows, W = 256 1.21 1.29 1.28 1.21;
-// 262144 1.13 1.10 0.98 0.85, W = 140 1.30 1.21 1.20 1.19; 393216, W = 200 1.15 1.03 0.93 0.85; 524288, W = 128 1.23 1.12 1.04 0.92,
-// W = 200 1.08 0.95 0.82 0.75, W = 140 1.05 0.93 0.83 0.74; d = 128, W = 256: 262144 1.15 1.03 0.91 0.87, 524288 1.18 1.08 1.02 0.82.
-// So half-steps where those win at L/2 .. L already.
-template <typename T, int D> StepShape step_choice(int N, int L, int W, bool lengths)
+template <typename T, int D> StepShape step_choice(int N, int L, int W)
 {
     constexpr int TB = step_tile_bytes<T, D>;
     const int hw = ((W < L ? W : L) + 31) / 32;
@@ -132,8 +127,7 @@ template <typename T, int D> StepShape step_choice(int N, int L, int W, bool len
         take(2, 4, 9);
     }
     if (!sh.NF) return sh;
-    if (march && lengths && TB <= 4096 && hw > 4 && rows > 393216) sh.NF = 0;
-    if (march && sh.NF) {   // one segment per CU, of equal lengths and at least hw tiles
+    if (march) {   // one segment per CU, of equal lengths and at least hw tiles
         const int nblk = (L + 32 * sh.NF - 1) / (32 * sh.NF);
         const long per = 256 / N > 1 ? 256 / N : 1;   // segments per problem
         int M = (int)((nblk + per - 1) / per);
@@ -146,17 +140,24 @@ template <typename T, int D> StepShape step_choice(int N, int L, int W, bool len
 }
 // Every choice has an instance that fits LDS (a test goes over them).  (4,2,6) needs none for single blocks: beyond 32768 rows
 // there are more blocks of 128 than segments, so that a segment has at least two.
-template <typename T, int D> StepShape step_shape(int N, int L, int W, bool lengths)
+template <typename T, int D> StepShape step_shape(int N, int L, int W)
 {
-    StepShape sh = step_choice<T, D>(N, L, W, lengths);
+    StepShape sh = step_choice<T, D>(N, L, W);
     const int lds = sh.NF ? step_lds<T, D>(sh) : 0;
     if (lds < 0 || lds > STEP_LDS) sh.NF = 0;
     return sh;
 }
 inline long step_segments(const StepShape &sh, int L) { return (L + 32L * sh.NF * sh.M - 1) / (32L * sh.NF * sh.M); }
-inline long step_part_stride(const StepShape &sh, int L, bool dustbin)   // floats of column sums per problem
+inline int step_least(const StepShape &sh) { return sh.hw > sh.NF ? (sh.hw + sh.NF - 1) / sh.NF : 1; }   // blocks of a segment, at least
+// floats of column sums per problem; cut: segments of any length from step_least to M blocks
+inline long step_part_stride(const StepShape &sh, int L, bool dustbin, bool cut)
 {
     const long nseg = step_segments(sh, L);
+    if (cut) {   // (blocks / m + 1) (NF m + 2 hw) tiles with m blocks each: convex in m
+        const long nblk = (L + 32L * sh.NF - 1) / (32L * sh.NF), least = step_least(sh);
+        const long a = sh.NF * least + 2 * sh.hw * (nblk / least + 1), b = sh.NF * sh.M + 2 * sh.hw * (nblk / sh.M + 1);
+        return 32 * (sh.NF * nblk + 2 * sh.hw + (a > b ? a : b));
+    }
     return nseg * 32 * (sh.NF * sh.M + 2 * sh.hw) + (dustbin ? 2 * nseg + 2 : 0);
 }
 

@@ -27,13 +27,13 @@ template <typename T, int D, int NF, int G, int NTW, int KIND> bool reads_inside
             }
     return true;
 }
-template <typename T, int D> bool check(int N, int L, int W, bool lengths)
+template <typename T, int D> bool check(int N, int L, int W)
 {
-    const StepShape sh = step_choice<T, D>(N, L, W, lengths);
+    const StepShape sh = step_choice<T, D>(N, L, W);
     if (!sh.NF) return true;
     const int lds = step_lds<T, D>(sh);
     constexpr int TB = step_tile_bytes<T, D>;
-    bool ok = lds >= 0 && lds <= STEP_LDS && step_shape<T, D>(N, L, W, lengths).NF == sh.NF, instance = false;
+    bool ok = lds >= 0 && lds <= STEP_LDS && step_shape<T, D>(N, L, W).NF == sh.NF, instance = false;
 #define CHECK(COND, NF_, G_, NTW_, KIND_) \
     if constexpr (COND) \
         if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) instance = reads_inside<T, D, NF_, G_, NTW_, KIND_>(sh);
@@ -53,11 +53,10 @@ int main()
     for (int N : Ns)
         for (int L : Ls)
             for (int W = 0; W <= 520; W += W < 40 || W % 32 > 28 || W % 32 < 2 ? 1 : 9)
-                for (int ln = 0; ln < 2; ++ln)
-                    if ((long)N * L <= 1L << 22 &&
-                        !(check<half_word, 32>(N, L, W, ln) && check<half_word, 64>(N, L, W, ln) && check<half_word, 128>(N, L, W, ln) &&
-                          check<float, 32>(N, L, W, ln) && check<float, 64>(N, L, W, ln) && check<float, 128>(N, L, W, ln)))
-                        return 1;
+                if ((long)N * L <= 1L << 22 &&
+                    !(check<half_word, 32>(N, L, W) && check<half_word, 64>(N, L, W) && check<half_word, 128>(N, L, W) &&
+                      check<float, 32>(N, L, W) && check<float, 64>(N, L, W) && check<float, 128>(N, L, W)))
+                    return 1;
     std::printf("%ld shapes, %ld tiles beyond a window\n", shapes, clamped);
     return shapes > 1000 && clamped > 0 ? 0 : 1;
 }

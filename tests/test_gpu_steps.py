@@ -46,14 +46,18 @@ LONG = [  # other block shapes; segments of several blocks, also ragged ones and
     ("dustbin", "bf16", 64, 1, 40001, 190, 2, 1), ("plain", "bf16", 128, 1, 40001, 160, 2, 1), ("dustbin", "bf16", 128, 1, 20000, 90, 2, 1),
     ("plain", "bf16", 128, 1, 40000, 70, 2, 1), ("plain", "bf16", 128, 1, 34000, 170, 2, 2), ("dustbin", "bf16", 64, 1, 70000, 96, 2, 1),
     ("plain", "f32", 64, 1, 10000, 170, 2, 1), ("plain", "bf16", 128, 1, 40000, 16, 2, 1), ("dustbin", "bf16", 64, 1, 60000, 20, 2, 1),
-    # padded batches whose items are all short (the segments share the valid rows), with targets as well; above the line for lengths
+    # padded batches whose items are all short, or one long among short ones (the segments are cut from the valid rows), with
+    # targets as well
     ("short", "bf16", 64, 4, 20000, 256, 3, 1), ("short", "bf16", 64, 8, 16001, 128, 2, 2), ("short", "bf16", 128, 4, 20000, 200, 2, 1),
     ("short", "f32", 64, 3, 30000, 250, 2, 1), ("short", "f32", 32, 4, 20001, 100, 2, 1), ("short", "bf16", 32, 5, 20001, 256, 2, 1),
     ("short targets", "bf16", 64, 4, 20000, 200, 3, 1), ("short targets", "f32", 64, 3, 30000, 250, 2, 1),
-    ("short", "bf16", 64, 8, 30000, 200, 2, 1), ("short", "bf16", 64, 14, 30000, 200, 2, 1), ("short", "bf16", 64, 300, 700, 256, 2, 1)]
+    ("short", "bf16", 64, 8, 30000, 200, 2, 1), ("short", "bf16", 64, 14, 30000, 200, 2, 1), ("short", "bf16", 64, 300, 700, 256, 2, 1),
+    ("uneven", "bf16", 64, 8, 30000, 200, 2, 1), ("uneven", "bf16", 64, 1, 200000, 256, 2, 1), ("uneven", "bf16", 128, 5, 30000, 150, 2, 1),
+    ("uneven", "bf16", 64, 33, 12000, 256, 2, 1), ("uneven", "bf16", 64, 7, 60000, 128, 2, 1), ("uneven", "f32", 64, 5, 30000, 250, 2, 1),
+    ("uneven", "bf16", 64, 16, 30000, 130, 2, 1)]
 
 
-HALF_STEPS = [("plain", "bf16", 64, 1, 1500, 481, 2, 1), ("short", "bf16", 64, 14, 30000, 200, 2, 1)]   # the others run whole steps
+HALF_STEPS = [("plain", "bf16", 64, 1, 1500, 481, 2, 1)]   # the others run whole steps
 
 
 @pytest.mark.parametrize("case", SHORT + LONG, ids=lambda c: "-".join(map(str, c)))
@@ -65,7 +69,7 @@ def test_steps_equal_half_steps(case):
     kind, dtype, d, N, L, W, T, R = case
     print(f"\n[case] {case}", flush=True)
     whole = binding.query_step_plan(N, 1, L, d, W, T, R, kind == "dustbin", 0 if dtype == "f32" else 1,
-                                    lengths=kind[:5] in ("varle", "short")).whole_steps
+                                    lengths=kind[:5] in ("varle", "short", "uneve")).whole_steps
     assert bool(whole) == (case not in HALF_STEPS)   # (both sides of the rule's lines)
     gen = torch.Generator(device="cuda")
     gen.manual_seed(17)
@@ -80,6 +84,10 @@ def test_steps_equal_half_steps(case):
     if kind.startswith("short"):
         lq, lk = (torch.randint(L // 12, L // 8, (N,), generator=gen, device="cuda").int() for _ in range(2))
         lk[-1] = 3   # (less than a block, and queries far beyond it)
+    if kind == "uneven":   # half of them empty or nearly so, at both ends one of all rows
+        lq, lk = (torch.randint(0, 40, (N,), generator=gen, device="cuda").int() for _ in range(2))
+        lq[::3], lk[::3] = L - 5, L
+        lq[N // 2:N // 2 + 2] = lk[N // 2:N // 2 + 2] = L // 2
     if kind in ("marginals", "short targets"):
         a, b = (torch.rand((N, 1, L), generator=gen, device="cuda") + 0.5 for _ in range(2))
         la, lb = a.log(), (b * a.sum(-1, keepdim=True) / b.sum(-1, keepdim=True)).log()

@@ -37,8 +37,8 @@ def written_by_backward(N, L, R, dtype):
 @pytest.mark.parametrize("dtype,d", itertools.product((b.SKA_F32, b.SKA_BF16), (32, 64, 128)))
 def test_sums_of_a_split_step_lie_apart_from_the_other_half(dtype, d):
     apart = 0
-    for (L, W), N, R in itertools.product(SIZES, (2, 3, 5, 8), (1, 2, 3, 7)):
-        p = b.query_step_plan(N, 1, L, d, W, 16, R, False, dtype, one_call=True)
+    for (L, W), N, R, lengths in itertools.product(SIZES, (2, 3, 5, 8), (1, 2, 3, 7), (False, True)):
+        p = b.query_step_plan(N, 1, L, d, W, 16, R, False, dtype, one_call=True, lengths=lengths)
         if not p.whole_steps:
             continue
         written, end = written_by_backward(N, L, R, dtype)
@@ -57,9 +57,9 @@ def test_sums_of_a_split_step_lie_apart_from_the_other_half(dtype, d):
 
 
 def test_forward_alone_keeps_its_sums_inside_the_workspace():
-    for (L, W), N, R, dustbin in itertools.product(SIZES, (1, 3), (1, 2, 5), (False, True)):
+    for (L, W), N, R, (dustbin, lengths) in itertools.product(SIZES, (1, 3), (1, 2, 5), ((False, False), (True, False), (False, True))):
         total = b.sinkhorn_attn_workspace_bytes(N, 1, L, 64, W, 16, R, dustbin)
-        p = b.query_step_plan(N, 1, L, 64, W, 16, R, dustbin)
+        p = b.query_step_plan(N, 1, L, 64, W, 16, R, dustbin, lengths=lengths)
         if p.whole_steps:
             ends = [off + (N - 1) * p.sums_stride + p.sums_bytes for off in p.sums_offset]
             assert min(p.sums_offset) >= 2 * N * L * 64 and max(ends) <= total   # behind the prescaled operand
