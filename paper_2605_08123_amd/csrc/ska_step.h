@@ -22,11 +22,16 @@ namespace {
 // segments, which the next launch adds up in a fixed order where it needs v' (vfinal_kernel where no step follows).
 //   Every row and every column carries its own potential as stabiliser: after one step the row sums of a
 // column-normalised plan lie between 1 / (2 W + 1) and 2 W + 1 (unit targets), and likewise the column sums.
-//   What bounds it: the issue slots of the SIMDs.  Per tile and wavefront 16 exponentials, 16 adds, 16 multiply-adds, five
-// products at d = 64, five 16-byte LDS reads.  A block of a long call (two wavefronts of nine tiles per SIMD) takes 13200
-// cycles: 7700 for the evaluation, 5500 for the exchange of row sums, the column sums, the reduction and the two barriers,
-// which the SIMD's two wavefronts go through together.  A launch's start (arguments, the first window) is 9000 more.  Two
-// independent workgroups of half the size per CU would overlap these phases: W = 128 (4,1,9) 960 us instead of 990 at
+//   What bounds it: the instructions of a SIMD's two wavefronts, which get little from each other's gaps.  A step of two problems of
+// L = 262144, W = 256 takes 88 us (256 segments of 16 blocks, one per CU); of these, measured by leaving it out, the exponentials
+// are 20, the products of the scores 13, the request of the next block's tiles 7, the segment's column sums 7, the adds of the row
+// sums 6, the masks 6, the exchange of row sums 4, the column sums 4, the LDS reads of the operands 2.  So what is not a product, an
+// exponential or one of the two sums is kept short: LDS addresses advance by the instructions' offsets, the tiles that are not there are
+// not evaluated and lie on all SIMDs evenly, fragments' column sums lie by column with zeros around, the reduction of row sums halves
+// its registers on the way, and the column sums of a block are added up among the products of the next one: 91.4 -> 83.2 us, the
+// one-call step of the same problems 2583 -> 2424, of four of 65536 1408 -> 1308.  Taking the column sums themselves from
+// the registers while the next block is evaluated into them, with one barrier a block instead of two: 91.8 -> 95.7.
+// Two independent workgroups of half the size per CU: W = 128 (4,1,9) 960 us instead of 990 at
 // 524288 rows, but 588 instead of 577 at 262144; at W = 256 two windows fit LDS only if the fragments' column sums
 // share their place by LDS atomics, which cost more than that (900 -> 1120).  Small calls are bound by latency from start to
 // end: a launch of short blocks is 5 us, 2.3 of them until the first product.
@@ -249,6 +254,23 @@ template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
 {
     return x + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
 }
+// a: in the lanes of the banks BANKS (quarters of a row of 16 lanes) the sum of b over a lane and its neighbour by CTRL, in the
+// others that of a.  (Written out: the compiler makes a move and an add of it.  A DPP source needs the s_nop after a VALU write, here and after it.)
+template <int CTRL, int BANKS> __device__ __forceinline__ void merge_add(float &a0, float &a1, float b0, float b1)
+{
+    a0 = dpp_add<CTRL>(a0); a1 = dpp_add<CTRL>(a1);
+    if constexpr (CTRL == 0x128)
+        asm("s_nop 1\n\tv_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:%4\n\tv_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:%4\n\ts_nop 1"
+            : "+v"(a0), "+v"(a1) : "v"(b0), "v"(b1), "n"(BANKS));
+    else
+        asm("s_nop 1\n\tv_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:%4\n\tv_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:%4\n\ts_nop 1"
+            : "+v"(a0), "+v"(a1) : "v"(b0), "v"(b1), "n"(BANKS));
+}
+template <int CTRL, int BANKS> __device__ __forceinline__ void merge_add(float &a0, float &a1, float &a2, float &a3, float b0, float b1, float b2, float b3)
+{
+    merge_add<CTRL, BANKS>(a0, a1, b0, b1);
+    merge_add<CTRL, BANKS>(a2, a3, b2, b3);
+}
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 // lanes 0 .. 31: a over both halves of the wavefront; lanes 32 .. 63: b
 __device__ __forceinline__ float halves_sum(float a, float b)
@@ -301,8 +323,10 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     const int b0 = min(seg * M, nblk), b1 = seg + 1 == nseg ? nblk : min(b0 + M, nblk), bv = min(b1, (Le + BM - 1) / BM);
 
     unsigned char *vs = smem + lds.vs;
+    // column sums of a fragment, by column of the block's window: zeros where its band does not reach
+    const int cps = lds.cps;
     float *us = reinterpret_cast<float *>(smem + LD::US);
-    float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cp0 = reinterpret_cast<float *>(smem + LD::CP);
+    float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cp0 = reinterpret_cast<float *>(smem + lds.cp);
     float *wsw = reinterpret_cast<float *>(smem + LD::WS) + 32 * wave;
 
     const float *vp = p.v + n * p.us, *xsp = p.u + n * p.us;
@@ -326,7 +350,13 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     // matrix repeat its first or last valid one; they are masked where they are used.
     constexpr int RPI = 64 / ST::CPR, IPT = 32 / RPI;
     const unsigned smem_at = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    auto dma_rows = [&](long t, int lds_at, bool whole) {   // rows t ... t + RPI - 1 (t uniform)
+    auto dma_at = [&](long t, int lds_at, unsigned o) {   // (t uniform)
+        // (written out, because the compiler takes every later LDS read for one of these bytes and waits at once; the
+        // kernel waits where it needs them.  No register is written.)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(smem_at + lds_at), "v"(o), "s"(Yb + t * ST::ROWB)
+                     : "memory", "m0");
+    };
+    auto dma_rows = [&](long t, int lds_at, bool whole) {   // rows t ... t + RPI - 1
         const int lrow = lane / ST::CPR;
         const unsigned col = ((lane % ST::CPR) ^ ST::swz((int)(t & 31) + lrow)) * 16;
         unsigned o = lrow * ST::ROWB + col;
@@ -335,10 +365,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             o = (unsigned)(min(max(t + lrow, 0L), last) - tb) * ST::ROWB + col;
             t = tb;
         }
-        // (written out, because the compiler takes every later LDS read for one of these bytes and waits at once; the
-        // kernel waits where it needs them.  No register is written.)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(smem_at + lds_at), "v"(o), "s"(Yb + t * ST::ROWB)
-                     : "memory", "m0");
+        dma_at(t, lds_at, o);
     };
     // `count` tiles from tile k on into the ring from `slot` on, by the whole workgroup
     auto dma = [&](int k, int count, int slot) {
@@ -346,7 +373,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         for (int i = wave; i < count * IPT; i += NF * G) {
             int sl = slot + i / IPT;
             if (sl >= RS) sl -= RS;
-            dma_rows(32L * (k + i / IPT) + (i % IPT) * RPI, LD::Y + sl * ST::BYTES + (i % IPT) * 1024, whole);
+            dma_rows(32L * (k + i / IPT) + (i % IPT) * RPI, lds.y + sl * ST::BYTES + (i % IPT) * 1024, whole);
         }
     };
     // v of a column (and with targets its weight) into its place in LDS, as the evaluation takes it
@@ -420,6 +447,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     OwnerFrag<T, D> xf;
     dma(kseg, nwt, 0);
     xf.load(reinterpret_cast<const T *>(Xb), min((b0 * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
+    for (int i = tid; i < LD::TWO * NF * cps; i += NTHR) cp0[i] = 0.f;   // (while the loads are on their way)
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
         const int i = tid + k * NTHR, t = 32 * kseg + i;
@@ -435,61 +463,98 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
     __syncthreads();
 
-    const int j0 = g * NTW, klast = (Lt - 1) / TT;
-    int base = 0;   // ring slot of the block's first tile
-    constexpr int NPOS = (32 * ((TIGHT ? 1 : 2) * NF + G * NTW) + NTHR - 1) / NTHR;   // ring positions of a thread, always the same ones
-    [[maybe_unused]] float acc[NPOS];   // MARCH: the segment's column sums there so far
-    for (int b = b0; b < (MARCH ? bv : b0 + 1); ++b) {
-        // what depends on the lane alone is computed again in every block: kept across the loop it would take the
-        // registers that the plan entries need
-        if constexpr (MARCH) asm volatile("" : "+v"(tid));
-        lane = tid & 63;
-        const int c = lane & 31, h = lane >> 5;
-        const int par = LD::TWO == 2 ? (b - b0) & 1 : 0, k0 = b * NF - hw, o_f = (b * NF + f) * 32, o = o_f + c;
-        const bool more = MARCH && b + 1 < bv;
-        float spoke = 0.f, la = 0.f;   // of this lane's row
-        if (DUST) spoke = spr ? spr[min(o, L - 1)] : p.sdb;
-        if (lap) la = lap[min(o, Le - 1)];
-        // what the next block adds (a thread below BM: one column, one row): requested now, stored after this block's last
-        // use of the slots' old content
-        float nv = 0.f, nu = 0.f, np[3] = {0.f, 0.f, 0.f}, nla = 0.f, nlb = 0.f, nsp = 0.f;
-        const int nt = 32 * (k0 + nwt) + tid, no = (b + 1) * BM + tid;
-        const int nq = min(segment_of(cut, (nt >> 5) + hw), nseg_valid - 1) - seg;   // segments after this one that have summed column nt
-        auto request_tiles = [&]() {
-            int sl = base + nwt;
-            if (sl >= RS) sl -= RS;
-            dma(k0 + nwt, NF, sl);
-        };
-        if (more) {
-            if (64 * wave < BM) {   // (uniform: the other wavefronts have nothing to add)
-                const int tc = min(nt, L - 1);
-                nv = vp[tc];
-                nu = xsp[min(no, Le - 1)];
-                if (lap) nla = lap[min(no, Le - 1)];
-                if (lbp) nlb = lbp[min(tc, max(Lc - 1, 0))];
-                if (DUST) nsp = (spc ? spc : vp)[tc];
-                if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
-                    const float *pp = part + (long)seg * (32 * (NF * M + 2 * hw)) + (tc - 32 * kseg);
+    const int klast = (Lt - 1) / TT;
+    // This wavefront's tiles of the 2 hw + 1: j0 on, cnt of them.  Groups of a fragment that have one more than others are other
+    // groups in its neighbour on the same SIMD, which has the wavefronts w and w + 4: a tile that is not there is not evaluated.
+    const int turn = G == 4 ? f : f >> 1;
+    int j0 = g * (NT / G), cnt = NT / G;
 #pragma unroll
-                    for (int i = 0; i < 3; ++i) np[i] = pp[(long)min(i, nq) * (64 * hw)];
-                }
-            }
-            if constexpr (!TIGHT) request_tiles();
+    for (int i = 0; i < G; ++i)
+        if ((i + turn) % G < NT % G) {
+            if (i < g) ++j0;
+            if (i == g) ++cnt;
         }
+    int base = 0;   // ring slot of the block's first tile
+    float *po = p.part_out + n * p.part_stride + (long)seg * (32 * (NF * M + 2 * hw));   // the segment's column sums
 
+    // what block b + 1 adds (a thread below BM: one column, one row): requested while block b is worked on, stored after the
+    // last use of the slots' old content
+    struct Added { float v, u, sum[3], la, lb, spoke; };
+    auto added_column = [&](int b) { return 32 * (b * NF - hw + nwt) + tid; };
+    auto later_segments = [&](int t) { return min(segment_of(cut, (t >> 5) + hw), nseg_valid - 1) - seg; };   // that have summed column t too
+    auto request = [&](int b) {
+        Added a{0.f, 0.f, {0.f, 0.f, 0.f}, 0.f, 0.f, 0.f};
+        if (64 * wave < BM) {   // (uniform: the other wavefronts have nothing to add)
+            const int nt = added_column(b), tc = min(nt, L - 1), o = min((b + 1) * BM + tid, Le - 1);
+            a.v = vp[tc];
+            a.u = xsp[o];
+            if (lap) a.la = lap[o];
+            if (lbp) a.lb = lbp[min(tc, max(Lc - 1, 0))];
+            if (DUST) a.spoke = (spc ? spc : vp)[tc];
+            if (part) {   // the first segment is this one, and there are at most three: a segment is at least hw tiles long
+                const float *pp = part + (long)seg * (32 * (NF * M + 2 * hw)) + (tc - 32 * kseg);
+                const int nq = later_segments(nt);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) a.sum[i] = pp[(long)min(i, nq) * (64 * hw)];
+            }
+        }
+        return a;
+    };
+    auto request_tiles = [&](int b) {
+        const int k = b * NF - hw + nwt;
+        int sl = base + nwt;
+        if (sl >= RS) sl -= RS;
+        if constexpr (MARCH) {   // (its address work is most of this: a wavefront loads the same piece of every few tiles)
+            static_assert(NF * G % IPT == 0 && NF * IPT % (NF * G) == 0, "whole tiles by all wavefronts");
+            constexpr int STEP = NF * G / IPT;
+            const int piece = wave % IPT, lrow = lane / ST::CPR;
+            const bool whole = 32 * (k + NF) <= Lt;
+            const unsigned o = lrow * ST::ROWB + ((lane % ST::CPR) ^ ST::swz(piece * RPI + lrow)) * 16;
+#pragma unroll
+            for (int i = 0; i < IPT / G; ++i) {
+                const int tile = wave / IPT + i * STEP;
+                int at = sl + tile;
+                if (at >= RS) at -= RS;
+                if (whole) dma_at(32L * (k + tile) + piece * RPI, lds.y + at * ST::BYTES + piece * 1024, o);
+                else dma_rows(32L * (k + tile) + piece * RPI, lds.y + at * ST::BYTES + piece * 1024, false);
+            }
+        }
+    };
+    auto stage_added_v = [&](const Added &a, int b) {
+        if (tid >= BM) return;
+        const int nt = added_column(b), nq = later_segments(nt);
+        const float v = finish_v(nt, a.v, a.sum[0] + (nq >= 1 ? a.sum[1] : 0.f) + (nq >= 2 ? a.sum[2] : 0.f), a.lb, a.spoke);
+        int sl = 32 * (base + nwt) + tid;
+        if (sl >= 32 * RS) sl -= 32 * RS;
+        stage_v(sl, nt, v, a.lb);
+    };
+    auto stage_added_u = [&](const Added &a, int b, int us_buf) {
+        if (tid < BM) stage_u(us_buf * BM + tid, (b + 1) * BM + tid < Le ? a.u : -INFINITY, a.la);
+    };
+    // a row of block b, this lane's: its potential (TARGETS: less nat), the score of its spoke, its target
+    struct Row { float u, rest, spoke, la; };
+    auto row_of = [&](int b, int us_buf) {
+        const int c = lane & 31, o = (b * NF + f) * 32 + c;
+        Row r;
+        r.spoke = r.la = 0.f;
+        if (DUST) r.spoke = spr ? spr[min(o, L - 1)] : p.sdb;
+        if (lap) r.la = lap[min(o, Le - 1)];
+        r.u = us[us_buf * BM + 32 * f + c];
+        r.rest = PRE ? base2_rest(r.u) : base2_rest(r.u) + base2_less(r.u, -p.up).lost;
+        return r;
+    };
+
+    f32x16 E[NTW];   // plan entries of a block: this wavefront's
+    auto evaluate = [&](int b, int us_buf, float u_own, float (&rsum)[16], auto &&late) {
+        const int c = lane & 31, h = lane >> 5, k0 = b * NF - hw, o_f = (b * NF + f) * 32;
         [[maybe_unused]] f32x16 ci;   // fp32 storage: the rows' potentials
         if constexpr (!PRE) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 v4 = *reinterpret_cast<const float4 *>(us + (LD::UE - LD::US) / 4 + par * BM + 32 * f + 8 * q + 4 * h);
+                const float4 v4 = *reinterpret_cast<const float4 *>(us + (LD::UE - LD::US) / 4 + us_buf * BM + 32 * f + 8 * q + 4 * h);
                 ci[4 * q + 0] = v4.x; ci[4 * q + 1] = v4.y; ci[4 * q + 2] = v4.z; ci[4 * q + 3] = v4.w;
             }
         }
-        const float u_old = us[par * BM + 32 * f + c];   // (TARGETS: less nat)
-        const float u_rest = PRE ? base2_rest(u_old) : base2_rest(u_old) + base2_less(u_old, -p.up).lost;
-
-        f32x16 E[NTW];
-        float rsum[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) rsum[r] = 0.f;
         [[maybe_unused]] float bt[NTW];   // TARGETS: weight of this lane's column of each tile
@@ -514,12 +579,13 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             }
         };
         const int kw = k0 + f + j0;   // this wavefront's first tile
-        const int nj = min(min(NT - j0, NTW), klast + 1 - kw), sfirst = max(0, -kw);   // tiles [sfirst, nj) are there
+        const int nj = min(cnt, klast + 1 - kw), sfirst = max(0, -kw);   // tiles [sfirst, nj) are there
         // [ilo, ilo + icnt): tiles wholly inside the matrix and, for all 32 rows, inside the band
         const int d0 = 32 * kw - o_f;
         const int ilo = max(sfirst, (62 - W - d0) >> 5), ihi = min(min((W - 31 - d0) >> 5, Lt / 32 - 1 - kw), nj - 1);
         const unsigned icnt = o_f + 32 <= Le ? max(ihi - ilo + 1, 0) : 0, pcnt = max(nj - sfirst, 0);
-        auto interior = [&](int s) { return (unsigned)(s - ilo) < icnt; };   // (uniform: one compare)
+        const unsigned whole = icnt ? (2u << (ilo + icnt - 1)) - (1u << ilo) : 0u;   // (ilo + icnt <= NTW)
+        auto interior = [&](int s) { return whole >> s & 1; };
         auto present = [&](int s) { return (unsigned)(s - sfirst) < pcnt; };
         int slot = lds.slot(base + f + j0);
         if constexpr (PRE) {
@@ -528,7 +594,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             constexpr int KS = D / 16;
             bf16x8 y[KS], yv, xv;
             {   // the rows' potentials, in the lanes that hold the first eight of the sixteen
-                const bf16x4 u3 = potential_parts(u_old * LOG2E);
+                const bf16x4 u3 = potential_parts(u_own * LOG2E);
                 const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
                 xv = bf16x8{one, one, one, no, u3[0], u3[1], u3[2], no};
 #pragma unroll
@@ -537,43 +603,48 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             f32x16 zero;
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-            const unsigned char *ybase = smem + LD::Y + c * ST::ROWB;
-            auto rd = [&](int ks) {
-                y[ks] = *reinterpret_cast<const bf16x8 *>(ybase + slot * ST::BYTES + (((2 * ks + h) ^ ST::swz(c)) << 4));
-            };
-            auto rdv = [&](int s) {   // (tile s)
-                const bf16x4 v3 = *reinterpret_cast<const bf16x4 *>(vs + (32 * slot + c) * 8);
+            // LDS addresses of tile s less s tiles: the instructions add those.  Where the ring ends (of a single block: where its
+            // window does) they go back by as much.
+            typedef __attribute__((address_space(3))) const unsigned char *lds_ptr;
+            unsigned ya[KS], va;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) ya[ks] = smem_at + lds.y + slot * ST::BYTES + c * ST::ROWB + (((2 * ks + h) ^ ST::swz(c)) << 4);
+            va = smem_at + lds.vs + (32 * slot + c) * 8;
+            auto rd = [&](int s, int ks) { y[ks] = *reinterpret_cast<__attribute__((address_space(3))) const bf16x8 *>((lds_ptr)(ya[ks] + 0u) + s * ST::BYTES); };
+            auto rdv = [&](int s) {   // (the first read of tile s)
+                if (s > 0 && (MARCH ? slot + s == RS : slot + s >= RS)) {
+                    const int back = MARCH ? RS : 1;
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) ya[ks] -= back * ST::BYTES;
+                    va -= back * 256;
+                }
+                const bf16x4 v3 = *reinterpret_cast<__attribute__((address_space(3))) const bf16x4 *>((lds_ptr)(va + 0u) + s * 256);
                 // (a zero of the row's operand meets it; an absent tile's slot may hold anything, and its zero entries stay zero)
                 if constexpr (TARGETS) bt[s] = present(s) ? (float)v3[3] : 0.f;
                 const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
                 yv = bf16x8{v3[0], v3[1], v3[2], v3[3], one, one, one, no};
             };
-            auto step_slot = [&]() { slot = lds.slot(slot + 1); };
             rdv(0);
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) rd(ks);
-            step_slot();
+            for (int ks = 0; ks < KS; ++ks) rd(0, ks);
             E[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
             if (NTW > 1) rdv(1);
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 E[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks], y[ks], E[0], 0, 0, 0);
-                if (NTW > 1) rd(ks);
+                if (NTW > 1) rd(1, ks);
             }
             constexpr int RPS = 16 / (KS + 1) + 1;   // entries per product: KS + 1 products and sixteen entries
 #pragma unroll
-            for (int s = 0; s < NTW; ++s) {
-                step_slot();
+            for (int s = 0; s + 1 < NTW; ++s) {
 #pragma unroll
                 for (int ks = 0; ks <= KS; ++ks) {
-                    if (s + 1 < NTW) {
-                        if (ks == 0) E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
-                        else E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks - 1], y[ks - 1], E[s + 1], 0, 0, 0);
-                        __builtin_amdgcn_sched_barrier(0);
-                        if (s + 2 < NTW) {
-                            if (ks == 0) rdv(s + 2);
-                            else rd(ks - 1);
-                        }
+                    if (ks == 0) E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
+                    else E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks - 1], y[ks - 1], E[s + 1], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (s + 2 < NTW) {
+                        if (ks == 0) rdv(s + 2);
+                        else rd(s + 2, ks - 1);
                     }
 #pragma unroll
                     for (int r = ks * RPS; r < 16 && r < (ks + 1) * RPS; ++r) {
@@ -584,14 +655,28 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (!interior(s)) mask(E[s], 32 * (kw + s), present(s));
+                if (s == (NTW > 4 ? 3 : NTW - 2)) late();
+            }
+            if (NTW > 1) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) add_rows(E[NTW - 2], NTW - 2, r);
+            }
+            if (NTW - 1 < cnt) {   // (uniform)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) E[NTW - 1][r] = fast_exp2(E[NTW - 1][r]);
+                if (!interior(NTW - 1)) mask(E[NTW - 1], 32 * (kw + NTW - 1), present(NTW - 1));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) E[NTW - 1][r] = 0.f;
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) add_rows(E[NTW - 1], NTW - 1, r);
         } else {
 #pragma unroll
             for (int s = 0; s < NTW; ++s) {
+                if (s == NTW / 2) late();
                 if (present(s)) {   // (uniform)
-                    const unsigned char *yr = smem + LD::Y + slot * ST::BYTES + c * ST::ROWB;
+                    const unsigned char *yr = smem + lds.y + slot * ST::BYTES + c * ST::ROWB;
                     const float vt = *reinterpret_cast<const float *>(vs + (32 * slot + c) * LD::VB);
                     if constexpr (TARGETS) bt[s] = *reinterpret_cast<const float *>(vs + (32 * slot + c) * LD::VB + 4);
 #pragma unroll
@@ -616,61 +701,59 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                 slot = lds.slot(slot + 1);
             }
         }
-
-        if (more) xf.load(reinterpret_cast<const T *>(Xb), min(((b + 1) * NF + f) * 32 + c, Le - 1), Le, h);
-
-        // row sums over the 32 columns of a lane half: registers r, r + 8 to the two rows of 16 lanes, then within those
-        {
-            float t8[8];
+    };
+    // row sums over the 32 columns of a lane half: registers r, r + 8 to the two rows of 16 lanes, then within those
+    auto write_row_sums = [&](const float (&rsum)[16], float *d) {
+        float t[8];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) t8[r] = rows16_sum(rsum[r], rsum[r + 8]);
+        for (int r = 0; r < 8; ++r) t[r] = rows16_sum(rsum[r], rsum[r + 8]);
+        // two registers into one each time: one in the first half of a row of lanes and one in the second, then by quarters
+        merge_add<0x128, 0xc>(t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7]);   // row_ror:8
+        merge_add<0x141, 0xa>(t[0], t[1], t[2], t[3]);                           // row_half_mirror
 #pragma unroll
-            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x128>(t8[r]);   // row_ror:8, 4, 2, 1
-#pragma unroll
-            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x124>(t8[r]);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x122>(t8[r]);
-#pragma unroll
-            for (int r = 0; r < 8; ++r) t8[r] = dpp_add<0x121>(t8[r]);
-            if ((lane & 15) == 0) {   // register r of the second row of lanes is r + 8: rows 16 further
-                float *d = rs + (f * G + g) * 32 + 16 * ((lane >> 4) & 1) + 4 * h;
-                *reinterpret_cast<float4 *>(d) = make_float4(t8[0], t8[1], t8[2], t8[3]);
-                *reinterpret_cast<float4 *>(d + 8) = make_float4(t8[4], t8[5], t8[6], t8[7]);
-            }
+        for (int r = 0; r < 2; ++r) t[r] = dpp_add<0xb1>(dpp_add<0x4e>(t[r]));   // quad_perm:[2,3,0,1], [1,0,3,2]
+        // register r of quarter q of a row of lanes is the r + 2 (q & 1) + 4 (q >> 1)-th of eight, the second row's 8 further; the
+        // i-th of sixteen is row 8 (i >> 2) + (i & 3) (+ 4 in the second half)
+        if ((lane & 3) == 0) {
+            const int q = lane >> 2;
+            d += (f * G + g) * 32 + 16 * ((q >> 2) & 1) + 8 * ((q >> 1) & 1) + 4 * (lane >> 5) + 2 * (q & 1);
+            *reinterpret_cast<float2 *>(d) = make_float2(t[0], t[1]);
         }
-        if constexpr (G > 1) __syncthreads();
-        else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if constexpr (TIGHT)
-            if (more) request_tiles();   // (every wavefront is done with this block's)
+    };
+    // From the row sums of block b: u' of this lane's row, and the weights of the fragment's rows as the column sums take them.
+    // exp: TARGETS, exponent that the weights are taken less of.
+    struct Weights { f32x16 w; float u_new; int exp; };
+    auto weights = [&](int b, const Row &row, const float *sums) {
+        const int c = lane & 31, h = lane >> 5, o = (b * NF + f) * 32 + c;
         float tot = 0.f;
 #pragma unroll
-        for (int i = 0; i < G; ++i) tot += rs[(f * G + i) * 32 + c];
+        for (int i = 0; i < G; ++i) tot += sums[(f * G + i) * 32 + c];
         if constexpr (!PRE && !TARGETS) tot = __builtin_amdgcn_ldexpf(tot, -(int)p.up);   // (TARGETS: in the columns' weights)
-        const float edge = DUST ? fast_exp2((spoke + vL + u_old) * LOG2E) : 0.f;   // spoke (o, dustbin of the other side)
+        const float edge = DUST ? fast_exp2((row.spoke + vL + row.u) * LOG2E) : 0.f;   // spoke (o, dustbin of the other side)
         tot += edge;
         float u_new = 0.f, w = 0.f;
-        [[maybe_unused]] int wexp = 0;   // TARGETS: exponent that the fragment's weights are taken less of
+        int wexp = 0;
         if (o < Le) {
-            if (u_old == -INFINITY) {
+            if (row.u == -INFINITY) {
                 u_new = -INFINITY;   // inactive token: stays so
             } else if (!(tot > 0.f && tot < INFINITY)) {
                 u_new = w = __builtin_nanf("");
             } else if constexpr (!TARGETS) {
-                const float delta = fmaf(-LN2, fast_log2(tot) + u_rest, 0.f);
-                u_new = u_old + delta;
+                const float delta = fmaf(-LN2, fast_log2(tot) + row.rest, 0.f);
+                u_new = row.u + delta;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
-                w = fmaf(w, (u_new - u_old) - delta, w);   // as u' was rounded, so that v' makes up for it
+                w = fmaf(w, (u_new - row.u) - delta, w);   // as u' was rounded, so that v' makes up for it
             } else {
-                const float nat = row_target_nat(la), delta = fmaf(-LN2, fast_log2(tot) + u_rest, la - nat), x = u_old + delta;
+                const float nat = row_target_nat(row.la), delta = fmaf(-LN2, fast_log2(tot) + row.rest, row.la - nat), x = row.u + delta;
                 u_new = nat + x;
                 w = PRE ? __builtin_amdgcn_rcpf(tot) : 1.f / tot;
-                w = fmaf(w, ((u_new - nat) - x) + ((x - u_old) - delta), w);
+                w = fmaf(w, ((u_new - nat) - x) + ((x - row.u) - delta), w);
             }
         }
         if constexpr (TARGETS) {
             // the weight is target / sum.  Where a fragment's rows all weigh little (small targets over columns of ordinary ones),
             // their entries are as large as the weights are small: a common exponent is left out until the column sums are done
-            const float lac = fmaxf(la, -1e5f), la2 = lac * LOG2E, q = rintf(la2);   // (a target below that weighs nothing either way)
+            const float lac = fmaxf(row.la, -1e5f), la2 = lac * LOG2E, q = rintf(la2);   // (a target below that weighs nothing either way)
             w *= fast_exp2((la2 - q) + base2_rest(lac));
             float top = w > 0.f ? q + fast_log2(w) : -INFINITY;
             if (!__any(top >= -40.f)) {
@@ -683,82 +766,113 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         if (h == 0) wsw[c] = PRE ? w : __builtin_amdgcn_ldexpf(w, -(int)p.up);
         if (h == 0 && g == 0 && o < Le) to_col += edge * w;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        f32x16 wv;
+        Weights wt;
+        wt.u_new = u_new; wt.exp = wexp;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float4 v4 = *reinterpret_cast<const float4 *>(wsw + 8 * q + 4 * h);
-            wv[4 * q + 0] = v4.x; wv[4 * q + 1] = v4.y; wv[4 * q + 2] = v4.z; wv[4 * q + 3] = v4.w;
+            wt.w[4 * q + 0] = v4.x; wt.w[4 * q + 1] = v4.y; wt.w[4 * q + 2] = v4.z; wt.w[4 * q + 3] = v4.w;
         }
-        // column sums of the fragment
-        float *cp = cp0 + par * NF * G * NTW * 32;
-        float *cpw = cp + (f * G * NTW + j0) * 32;
+        return wt;
+    };
+    auto add_columns = [&](float *cpw, const Weights &wt) {   // of a fragment
         auto col = [&](const f32x16 &e) {
             float x = 0.f, y = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) { x = fmaf(e[r], wv[r], x); y = fmaf(e[r + 1], wv[r + 1], y); }
-            if constexpr (TARGETS) return __builtin_amdgcn_ldexpf(x + y, wexp);
+            for (int r = 0; r < 16; r += 2) { x = fmaf(e[r], wt.w[r], x); y = fmaf(e[r + 1], wt.w[r + 1], y); }
+            if constexpr (TARGETS) return __builtin_amdgcn_ldexpf(x + y, wt.exp);
             else return x + y;
         };
 #pragma unroll
-        for (int s = 0; s + 1 < NTW; s += 2) cpw[32 * s + lane] = halves_sum(col(E[s]), col(E[s + 1]));
-        if constexpr (NTW & 1) {
-            const float x = col(E[NTW - 1]);
-            const float y = halves_sum(x, x);
-            if (h == 0) cpw[32 * (NTW - 1) + c] = y;
+        for (int s = 0; s < NTW; s += 2) {
+            const float x = col(E[s]), y = halves_sum(x, s + 1 < NTW ? col(E[s + 1 < NTW ? s + 1 : s]) : x);
+            if (lane < (s + 1 < NTW ? 64 : 32) && s + (lane >> 5) < cnt) cpw[32 * s + lane] = y;   // (tiles that are not there: zeros stay)
         }
-        if (more && tid < BM) {
-            const float v_new = finish_v(nt, nv, np[0] + (nq >= 1 ? np[1] : 0.f) + (nq >= 2 ? np[2] : 0.f), nlb, nsp);
-            int sl = 32 * (base + nwt) + tid;
-            if (sl >= 32 * RS) sl -= 32 * RS;
-            stage_v(sl, nt, v_new, nlb);
-            stage_u((LD::TWO == 2 ? par ^ 1 : 0) * BM + tid, no < Le ? nu : -INFINITY, nla);
-        }
-        if (DUST && !more) {   // the segment's last block: every thread has added its share
+    };
+    // the segment's last block: every thread has added its share of what the dustbin gets (wsw: its weights have been read)
+    auto sum_dustbin = [&]() {
+        if (!DUST) return;
 #pragma unroll
-            for (int s = 32; s >= 1; s >>= 1) { to_row += __shfl_xor(to_row, s); to_col += __shfl_xor(to_col, s); }
-            if (lane == 0) { wsw[0] = to_row; wsw[1] = to_col; }   // (its weights have been read)
-        }
-        __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
-        __syncthreads();
-        // rows' stores only now: the wait above would wait for them as well
-        if (h == 0 && g == 0 && o < L) u_out[o] = u_new;
-        if (DUST && !more && tid < 2) {
-            float s = 0.f;
+        for (int s = 32; s >= 1; s >>= 1) { to_row += __shfl_xor(to_row, s); to_col += __shfl_xor(to_col, s); }
+        if (lane == 0) { wsw[0] = to_row; wsw[1] = to_col; }
+    };
+    auto store_dustbin = [&]() {
+        if (!DUST || tid >= 2) return;
+        float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < NF * G; ++i) s += reinterpret_cast<const float *>(smem + LD::WS)[32 * i + tid];
-            dust[tid * p.nseg + seg] = s;
-        }
-        // the block's column sums onto the segment's; tiles that no later block of the segment meets are done
-        float *po = p.part_out + n * p.part_stride + (long)seg * (32 * (NF * M + 2 * hw));
-        if constexpr (!MARCH) {
+        for (int i = 0; i < NF * G; ++i) s += reinterpret_cast<const float *>(smem + LD::WS)[32 * i + tid];
+        dust[tid * p.nseg + seg] = s;
+    };
+    // column sums of the block's fragments at column i of its window
+    auto over_fragments = [&](const float *cp, int i, float s) {
+        float x[NF];
 #pragma unroll
-            for (int k = 0; k < NWIN; ++k) {
-                const int i = tid + k * NTHR, wt = i >> 5;
-                if (i >= 32 * nwt) continue;
-                float x[NF], s = 0.f;
+        for (int q = 0; q < NF; ++q) x[q] = cp[q * cps + i];
 #pragma unroll
-                for (int q = 0; q < NF; ++q) x[q] = cp[(q * G * NTW + min(max(wt - q, 0), NT - 1)) * 32 + (i & 31)];
-#pragma unroll
-                for (int q = 0; q < NF; ++q) s += (unsigned)(wt - q) < (unsigned)NT ? x[q] : 0.f;
-                po[i] = s;
-            }
-            return;
-        }
+        for (int q = 0; q < NF; ++q) s += x[q];
+        return s;
+    };
+    constexpr int NPOS = (32 * ((TIGHT ? 1 : 2) * NF + G * NTW) + NTHR - 1) / NTHR;   // ring positions of a thread, always the same ones
+    [[maybe_unused]] float acc[NPOS];   // MARCH: the segment's column sums there so far
+    // a block's column sums onto the segment's; tiles that no later block of the segment meets are done (at: ring slot of its
+    // first tile)
+    auto add_to_segment = [&](const float *cp, int b, int at) {
 #pragma unroll
         for (int k = 0; k < NPOS; ++k) {
             const int i = tid + k * NTHR;
-            int wt = (i >> 5) - base;
+            int wt = (i >> 5) - at;
             if (wt < 0) wt += RS;
             if (i >= 32 * RS || wt >= nwt) continue;
-            float s = b == b0 || wt >= nwt - NF ? 0.f : acc[k];
-            float x[NF];
-#pragma unroll
-            for (int q = 0; q < NF; ++q) x[q] = cp[(q * G * NTW + min(max(wt - q, 0), NT - 1)) * 32 + (i & 31)];
-#pragma unroll
-            for (int q = 0; q < NF; ++q) s += (unsigned)(wt - q) < (unsigned)NT ? x[q] : 0.f;
-            if (!more || wt < NF) po[32 * (k0 + wt - kseg) + (i & 31)] = s;
+            const float s = over_fragments(cp, 32 * wt + (i & 31), b == b0 || wt >= nwt - NF ? 0.f : acc[k]);
+            if (b + 1 == bv || wt < NF) po[32 * (b * NF - hw + wt - kseg) + (i & 31)] = s;
             acc[k] = s;
         }
+    };
+    float rsum[16];
+
+    for (int b = b0; b < (MARCH ? bv : b0 + 1); ++b) {
+        // what depends on the lane alone is computed again in every block: kept across the loop it would take the
+        // registers that the plan entries need
+        if constexpr (MARCH) asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        const int par = LD::TWO == 2 ? (b - b0) & 1 : 0, o = (b * NF + f) * 32 + (lane & 31);
+        const bool more = MARCH && b + 1 < bv;
+        Added next{};
+        if (more) {
+            next = request(b);
+            if constexpr (!TIGHT) request_tiles(b);
+        }
+        const Row row = row_of(b, par);
+        evaluate(b, par, row.u, rsum, [&]() {
+            if (MARCH && b > b0) add_to_segment(cp0 + (LD::TWO == 2 ? par ^ 1 : 0) * NF * cps, b - 1, base >= NF ? base - NF : base - NF + RS);
+        });
+        if (more) xf.load(reinterpret_cast<const T *>(Xb), min(((b + 1) * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
+        write_row_sums(rsum, rs);
+        if (KIND == STEP_MARCH && more) stage_added_v(next, b);   // (slots of their own)
+        if constexpr (G > 1) __syncthreads();
+        else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if constexpr (TIGHT)
+            if (more) request_tiles(b);   // (every wavefront is done with this block's)
+        const Weights wt = weights(b, row, rs);
+        float *cp = cp0 + par * NF * cps;
+        add_columns(cp + f * cps + (f + j0) * 32, wt);
+        if (TIGHT && more) stage_added_v(next, b);
+        if (more) stage_added_u(next, b, LD::TWO == 2 ? par ^ 1 : 0);
+        else sum_dustbin();
+        __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
+        __syncthreads();
+        // rows' stores only now: the wait above would wait for them as well
+        if (lane < 32 && g == 0 && o < L) u_out[o] = wt.u_new;
+        if (!more) store_dustbin();
+        if constexpr (!MARCH) {
+#pragma unroll
+            for (int k = 0; k < NWIN; ++k) {
+                const int i = tid + k * NTHR;
+                if (i < 32 * nwt) po[i] = over_fragments(cp, i, 0.f);
+            }
+            return;
+        }
+        if (!more) add_to_segment(cp, b, base);
         base += NF;
         if (base >= RS) base -= RS;
     }

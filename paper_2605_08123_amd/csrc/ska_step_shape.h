@@ -19,22 +19,24 @@ enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
 // (which go with no dustbin; a cut or none), segments cut from valid rows.
 enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS, STEP_CUT };
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> struct StepLds {   // offsets in bytes
-    static constexpr int RSUM = 0;                              // [NF][G][32] row sums
-    static constexpr int WS = RSUM + NF * G * 128;              // [wave][32] weights of the rows
-    static constexpr int US = WS + NF * G * 128;                // [TWO][32 NF] potentials of the rows
     static constexpr bool MARCH = KIND != STEP_BLOCK;
     static_assert(KIND != STEP_TIGHT || G > 1, "the exchange of row sums says that the products are done");
     // With G > 1 that exchange lies between a wavefront's reads and its next block's writes; without it there are two buffers.
     static constexpr int TWO = MARCH && G == 1 ? 2 : 1;
+    static constexpr int RSUM = 0;                              // [NF][G][32] row sums
+    static constexpr int WS = RSUM + NF * G * 128;                // [wave][32] weights of the rows
+    static constexpr int US = WS + NF * G * 128;                // [TWO][32 NF] potentials of the rows
     static constexpr int UE = US + TWO * NF * 128;              // fp32 storage: the same as the evaluation takes them
-    static constexpr int CP = UE + (sizeof(T) == 4 ? TWO * NF * 128 : 0);   // [TWO][NF][G NTW 32] column sums of a fragment
-    static constexpr int Y = CP + TWO * NF * G * NTW * 128;   // ring of the other side's tiles
+    static constexpr int CP = UE + (sizeof(T) == 4 ? TWO * NF * 128 : 0);
     static constexpr int VB = sizeof(T) == 2 || FORM == STEP_TARGETS ? 8 : 4;   // bytes of a column's potential (and weight)
-    int rs, vs, total;
+    int cp, cps, y, rs, vs, total;   // cp: [TWO][NF][cps] column sums of a fragment; y: ring of the other side's tiles
     __host__ __device__ StepLds(int hw)
     {
         rs = NF + 2 * hw + (KIND == STEP_MARCH ? NF : 0);   // ring slots: the window of a block (and the tiles the next one adds)
-        vs = Y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
+        cp = CP;
+        cps = 32 * (NF - 1 + (2 * hw + 1 > G * NTW ? 2 * hw + 1 : G * NTW));   // (the window, and tiles that the last fragment's wavefronts are short of)
+        y = cp + TWO * NF * cps * 4;
+        vs = y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
         total = vs + rs * 32 * VB;
     }
     // Ring slot of the tile `at` slots on from the ring's first.  A wavefront evaluates NTW tiles also where its band ends before:
