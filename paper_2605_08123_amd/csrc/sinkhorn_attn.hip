@@ -495,6 +495,48 @@ inline StepSums step_sums(const Problem &p, const StepShape &sh, bool one_call)
     }
     return s;
 }
+// Where a call keeps what a chain of steps needs, all of it between g_u and the end of the backward's vectors and packs (the
+// call's sweeps are not split, so that no backward writes there before the forward has ended): its state and words, cleared at the
+// call's start, and the column sums of its last step.  off 0: no room.
+struct ChainSpace { size_t off, clear, sums; long wstride; };
+inline ChainSpace chain_space(const Problem &p, const StepShape &sh, bool one_call)
+{
+    ChainSpace s{0, 0, 0, 0};
+    const size_t N = p.N(), gu = N * p.ldw() * sizeof(float), off = ((one_call ? 0 : ws_qs_bytes(p)) + gu + 255) / 256 * 256;
+    s.wstride = step_segments(sh, p.L) * 32 * (sh.NF + 2 * sh.hw);
+    s.clear = 256 + 2 * N * s.wstride * sizeof(unsigned long long);
+    s.sums = off + s.clear;
+    const size_t end = s.sums + N * step_part_stride(sh, p.L, false, false) * sizeof(float);
+    if (end <= (one_call ? ws_vec_bytes(p) : p.ws_given)) s.off = off;
+    return s;
+}
+// Chains of the device that are or may be waiting for room: all on one stream follow each other; one on another stream starts only if
+// the last one's workgroups have all started (they need nothing more then).  Otherwise the steps are launched one by one, with the
+// same results.
+struct ChainGate {
+    unsigned *started = nullptr, *started_dev = nullptr;   // host memory
+    hipStream_t last = nullptr;
+    unsigned seq = 0;
+    bool tried = false;
+};
+ChainGate g_gate[MAX_DEVICES];   // (g_mutex held)
+bool chain_may_start(int dev, hipStream_t st)
+{
+    ChainGate &g = g_gate[dev];
+    if (!g.tried) {
+        g.tried = true;
+        void *h = nullptr, *d = nullptr;
+        if (hipHostMalloc(&h, sizeof(unsigned), hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&d, h, 0) == hipSuccess) {
+            g.started = static_cast<unsigned *>(h);
+            g.started_dev = static_cast<unsigned *>(d);
+            *g.started = 0;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    if (!g.started) return false;
+    return __atomic_load_n(g.started, __ATOMIC_RELAXED) == g.seq || (st == g.last && st != hipStreamPerThread);
+}
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
 {
     p.nb_total = p.cut ? (N < p.items * p.nh ? CUT_HALF : CUT_SEGS) : p.nseg * N;
@@ -505,6 +547,23 @@ template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int lau
                                 hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
             return SKA_EHIP;
         raised[dev] = true;
+    }
+    if (p.nsteps > 1) {   // a chain's workgroups wait for each other: they must fit the device together
+        static int caps[MAX_DEVICES], caps_lds[MAX_DEVICES];   // what it holds, at which LDS size (0: not asked yet; g_mutex held)
+        if (caps_lds[dev] != lds) {
+            int per_cu = 0, cus = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, FORM>),
+                                                             64 * NF * G, lds) != hipSuccess ||
+                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+                return SKA_EHIP;
+            caps[dev] = per_cu * cus;
+            caps_lds[dev] = lds;
+        }
+        if ((p.nb_total + 7) / 8 * 8 > caps[dev]) return SKA_EUNSUPPORTED;   // (nothing has been launched)
+        ChainGate &gate = g_gate[dev];
+        p.started = gate.started_dev;
+        p.seq = ++gate.seq;
+        gate.last = st;
     }
     hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, FORM>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
@@ -635,10 +694,20 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     base.dustbin = p.dustbin; base.sdb2 = p.sdb * LOG2E;
     base.nh = p.H;
 
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+    // Whole steps after the first one: in one launch where every workgroup is a single block and all of them fit the device, the
+    // call's sweeps are not split, and nothing but lengths is added to the plain problem (see vstep_kernel).
+    const StepShape shape = step_shape<T, D>(N, L, p.W);
+    const ChainSpace room = shape.NF && ws ? chain_space(p, shape, fused) : ChainSpace{0, 0, 0, 0};
+    const int after_first = p.T + R - 1;
+    bool chained = room.off && shape.kind == STEP_BLOCK && shape.M == 1 && after_first >= 2 && !p.dustbin && !p.mask_q && !p.mask_k && !p.log_a &&
+                   !p.log_b && !p.n_stages && !p.resume_t && !cx.side && !cx.noalloc && !capturing && chain_may_start(cx.dev, st);
     // u0 = v0 = 0: the base solve starts from v = 0
     if (!p.resume_t) {
-        long tot = 2L * Lp * N;
-        hipLaunchKernelGGL(fill_kernel, dim3((tot + 255) / 256), dim3(256), 0, st, UV, 2L * Lp, us, N, 0.f);
+        const long n16 = chained ? (long)room.clear / 16 : 0, tot = 2L * Lp * N > n16 ? 2L * Lp * N : n16;
+        hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, UV, 2L * Lp, us, N,
+                           chained ? reinterpret_cast<uint4 *>(reinterpret_cast<unsigned char *>(ws) + room.off) : nullptr, n16);
         if (hipGetLastError() != hipSuccess) return SKA_EHIP;
     }
     if (p.mask_q || p.mask_k) {   // inactive tokens start, and stay, at -inf
@@ -678,8 +747,6 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     int *chain_done = nullptr;
     bool tail_now = false;
     {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
         size_t off;
         if (g_fuse && !cx.noalloc && !capturing && ws && chain_room(p, fused, &off))
             chain_done = reinterpret_cast<int *>(reinterpret_cast<unsigned char *>(ws) + off);
@@ -759,7 +826,6 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // yet; the next step's launch does so on the way, and a launch of its own (flush) where v is needed by itself.  The
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
-    const StepShape shape = step_shape<T, D>(N, L, p.W);
     const int nseg = shape.NF ? (int)step_segments(shape, L) : 0;
     const StepSums sums = step_sums(p, shape, fused);
     const long pstride = sums.stride;
@@ -787,6 +853,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         step.cut = cut;
     }
     step.nh = p.H; step.dustbin = p.dustbin;
+    step.nsteps = 1;
     if (sizeof(T) == 4) step.up = (float)ilogbf((float)(2 * base.W + 1));
     auto flush = [&]() -> int {
         if (!pend) return SKA_OK;
@@ -829,6 +896,31 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         vhome = vslot;
         return SKA_OK;
     };
+    // all steps after the first one as a chain; SKA_EUNSUPPORTED: they do not fit the device together (nothing has been launched)
+    auto chain_steps = [&]() -> int {
+        StepArgs f = step;
+        f.c2 = c2;
+        f.X = Q;
+        f.v = slot(vcur); f.u = f.u_out = slot(p.T ? 0 : 2); f.v_out = slot(vcur);
+        unsigned char *at = reinterpret_cast<unsigned char *>(ws) + room.off;
+        f.part_stride = step_part_stride(shape, L, false, false);
+        f.part_out = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + room.sums);
+        f.nsteps = after_first;
+        f.base_left = p.T ? p.T - 1 : 0; f.tail = p.T ? 1 : 2;
+        f.slots = UV; f.Lp = Lp;
+        f.chain = reinterpret_cast<StepChain *>(at);
+        f.words = reinterpret_cast<unsigned long long *>(at + 256);
+        f.wstride = room.wstride; f.wbuf = N * room.wstride;
+        f.limit = g_spin_limit;
+        f.rev = nlaunch++ & 1;
+        SKA_TRY((step_sweep<T, D>(cx, f, &shape, N)));
+        if (pt_run) pt_run->launched(2 * after_first);
+        f.v = slot(2 * R - 1); f.v_out = slot(2 * R + 1); f.u_fin = slot(2 * R);
+        f.part_in = f.part_out;
+        hipLaunchKernelGGL((vfinish_kernel<T, D>), dim3((unsigned)((L + NTHREADS - 1) / NTHREADS * N)), dim3(NTHREADS), 0, st, f, SolveArgs{p.T, R});
+        vcur = 2 * R + 1;
+        return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
+    };
     auto halves = [&]() -> int {
         // base solve: T steps at eps, or the stages of the continuation schedule (remark
         // "Fixed-Budget eps-Scaling"): stage s runs on the scores A / eps_s; between stages both
@@ -848,7 +940,14 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
                 first = true;   // the plan to the power of the ratio: its row sums are bounded by nothing (as before the first step)
             }
             stage_sdb2 = p.sdb * (p.eps / es) * LOG2E;
-            for (int t = 0; t < Ts; ++t) SKA_TRY(full(0, 0, 1, sidx + 1 < nst ? 0 : Ts - 1 - t));
+            for (int t = 0; t < Ts; ++t) {
+                SKA_TRY(full(0, 0, 1, sidx + 1 < nst ? 0 : Ts - 1 - t));
+                if (t == 0 && chained) {
+                    const int rc = chain_steps();
+                    if (rc != SKA_EUNSUPPORTED) return rc;
+                    chained = false;
+                }
+            }
             if (sidx + 1 < nst) {   // the next stage rescales both potentials in place
                 SKA_TRY(flush());
             }
@@ -859,6 +958,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         for (int t = p.resume_t ? p.resume_t : 1; t <= R; ++t) {
             if (pend && vcur == vhome) SKA_TRY(flush());
             SKA_TRY(full(2 * t - 2, 2 * t, 2 * t + 1, 0));       // u_t from v_{t-1}, v_t from u_t
+            if (t == 1 && chained) {   // (T = 0)
+                const int rc = chain_steps();
+                if (rc != SKA_EUNSUPPORTED) return rc;
+                chained = false;
+            }
         }
         SKA_TRY(flush());
         return flush_chain();

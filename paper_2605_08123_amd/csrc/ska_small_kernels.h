@@ -12,6 +12,14 @@ __global__ void fill_kernel(float *p, long per, long stride, int nprob, float va
     if (i < per * nprob) p[(i / per) * stride + (i % per)] = val;
 }
 
+// The start of a forward: zeros in `per` floats of every problem's potentials, and in a region of its own (n16 times 16 bytes).
+__global__ void clear_kernel(float *p, long per, long stride, int nprob, uint4 *q, long n16)
+{
+    const long all = (long)gridDim.x * blockDim.x, first = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    for (long i = first; i < per * nprob; i += all) p[(i / per) * stride + (i % per)] = 0.f;
+    for (long i = first; i < n16; i += all) q[i] = make_uint4(0, 0, 0, 0);
+}
+
 // g_o = <A_o, B_o> for o below the problem's valid length (len[n / nh], or L if len is null);
 // g = 0 from there to Lp.  A row is read by D * sizeof(T) / 16 neighbouring
 // lanes, 16 bytes each (whole 128-byte lines per group of lanes), and reduced across them.

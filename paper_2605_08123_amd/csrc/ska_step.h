@@ -55,6 +55,7 @@ namespace {
 // L = 65536, W = 256 1388 -> 1445 us, a forward of eight of 701, W = 64 113 -> 115; by half-steps 1674 and 211.
 //   The arguments are a struct of their own, read as a whole at a kernel's start (take_args): fetched where they are first
 // used they cost a short launch one wait of some hundred cycles after another.
+struct StepChain { unsigned started, failed; };   // zero at launch
 struct StepArgs {
     const void *X, *Y;             // row (owner) and column operand
     const float *v, *u;            // potentials before the step (with part_in: v before the step before)
@@ -81,6 +82,16 @@ struct StepArgs {
     // of L = 256, d = 32, W = 16: half-steps 2.61e-7, without 2.70e-7, with 2.52e-7; 16 of L = 4096, d = 64, W = 128: 5.44, 5.36,
     // 4.99e-7.
     float up;
+    // Several steps in one launch (single blocks; see ChainArgs)
+    int nsteps;                    // 1: one step, as everything above says
+    int base_left, tail;           // the first base_left end the base solve (slots 0 and 1), the others are the tail's from step `tail` on
+    float *slots;                  // u_t in slot 2 t, v_t in slot 2 t + 1 of a problem, Lp floats each
+    int Lp;
+    StepChain *chain;
+    unsigned long long *words;     // [2][problem][block][32 (NF + 2 hw)] column sums on their way, with the step's number
+    long wstride, wbuf;            // words between problems, buffers
+    unsigned *started;             // host memory: `seq` when all workgroups have started
+    unsigned seq, limit;           // polls of a wait before it gives up
 };
 __device__ __forceinline__ void take_args(const StepArgs &p)
 {
@@ -335,8 +346,35 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     const float *lap = TARGETS && p.log_a ? p.log_a + (long)n * p.lstride : nullptr;
     const float *lbp = TARGETS && p.log_b ? p.log_b + (long)n * p.lstride : nullptr;
     const float *spr = p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr, *spc = p.spoke_c ? p.spoke_c + (long)n * p.sstride : nullptr;
+    // A chain: steps follow each other in the same workgroups.  What a block needs of others between two steps are their column sums
+    // of its window, which go from hand to hand as 8-byte words of a sum and the step's number: a reader polls the words
+    // themselves, so nothing has to be ordered or acknowledged (relaxed accesses of agent scope).  Two buffers do: a
+    // block writes a step's words after it has read the step before's of every block that reads its own, and those have then read
+    // the words of two steps before.  A hand-over takes about 1 us where a launch takes 5 (2.3 if it is empty).  The host sees to it that the
+    // workgroups fit the device together and that no other chain is waiting for room; a wait that runs out all the same (other
+    // programs on the device) ends the launch, and the problem is solved again by the launch that follows (vfinish_kernel).
+    const bool chained = KIND == STEP_BLOCK && p.nsteps > 1;
+    __shared__ int gave_up;
+    float *slots = p.slots + n * p.us;
+    if (chained && tid == 0) {
+        gave_up = 0;
+        if (__hip_atomic_fetch_add(&p.chain->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)p.nb_total)
+            __hip_atomic_store(p.started, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    // where step st leaves its potentials (-1: nowhere)
+    auto slot_of = [&](int st) { return st + 1 < p.base_left ? -1 : st + 1 == p.base_left ? 0 : 2 * (p.tail + st - p.base_left); };
+    if (chained) {   // rows without an edge: zeros (v: from the last column with an edge on; the last block with rows has the others)
+        for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR)
+            for (int st = 0; st < p.nsteps; ++st) {
+                const int sl = slot_of(st);
+                if (sl < 0) continue;
+                slots[(long)sl * p.Lp + t] = 0.f;
+                if (t >= Lc && st + 1 < p.nsteps) slots[(long)(sl + 1) * p.Lp + t] = 0.f;
+            }
+        if (b0 >= bv) return;
+    }
     // rows without an edge: zeros, and this segment's share of v there
-    for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR) {
+    for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L) && !chained; t += NTHR) {
         u_out[t] = 0.f;
         if (part) v_out[t] = t < Lc ? column_update<true>(vp[t], column_sum(p, cut, part, t, nseg_valid), ColumnTarget(lbp ? lbp[t] : 0.f)) : 0.f;
     }
@@ -457,7 +495,10 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 #pragma unroll
             for (int q = 0; q < NSUM; ++q) sum += q < cg.n ? win_sum[k][q] : 0.f;
         }
-        if (i < 32 * nwt) stage_v(i, t, finish_v(t, win_v[k], sum, win_lb[k], win_sp[k]), win_lb[k]);   // (later columns: with their block)
+        if (i < 32 * nwt) {   // (later columns: with their block)
+            win_v[k] = finish_v(t, win_v[k], sum, win_lb[k], win_sp[k]);
+            stage_v(i, t, win_v[k], win_lb[k]);
+        }
     }
     if (tid < BM) stage_u(tid, u_first, la_first);
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
@@ -830,10 +871,10 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     };
     float rsum[16];
 
-    for (int b = b0; b < (MARCH ? bv : b0 + 1); ++b) {
+    for (int b = b0, st = 0; !MARCH || b < bv; MARCH ? ++b : ++st) {
         // what depends on the lane alone is computed again in every block: kept across the loop it would take the
         // registers that the plan entries need
-        if constexpr (MARCH) asm volatile("" : "+v"(tid));
+        asm volatile("" : "+v"(tid));
         lane = tid & 63;
         const int par = LD::TWO == 2 ? (b - b0) & 1 : 0, o = (b * NF + f) * 32 + (lane & 31);
         const bool more = MARCH && b + 1 < bv;
@@ -862,15 +903,69 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
         __syncthreads();
         // rows' stores only now: the wait above would wait for them as well
-        if (lane < 32 && g == 0 && o < L) u_out[o] = wt.u_new;
+        const int to = chained ? slot_of(st) : 0;
+        if (lane < 32 && g == 0 && o < L && to >= 0) (chained ? slots + (long)to * p.Lp : u_out)[o] = wt.u_new;
         if (!more) store_dustbin();
         if constexpr (!MARCH) {
+            float sum[NWIN];
+#pragma unroll
+            for (int k = 0; k < NWIN; ++k) sum[k] = over_fragments(cp, min(tid + k * NTHR, 32 * nwt - 1), 0.f);
+            if (st + 1 == p.nsteps) {
+#pragma unroll
+                for (int k = 0; k < NWIN; ++k)
+                    if (tid + k * NTHR < 32 * nwt) po[tid + k * NTHR] = sum[k];
+                return;
+            }
+            const unsigned tag = st + 1;
+            unsigned long long *words = p.words + (st & 1) * p.wbuf + n * p.wstride;
+#pragma unroll
+            for (int k = 0; k < NWIN; ++k)
+                if (tid + k * NTHR < 32 * nwt)
+                    __hip_atomic_store(words + (long)seg * (32 * nwt) + tid + k * NTHR, (unsigned long long)tag << 32 | __float_as_uint(sum[k]),
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane < 32 && g == 0) stage_u(32 * f + lane, o < Le ? wt.u_new : -INFINITY, row.la);
+            for (unsigned polls = 0;;) {
+                unsigned long long w[NWIN][NSUM];
+                int cn[NWIN];
+#pragma unroll
+                for (int k = 0; k < NWIN; ++k) {
+                    const ColumnSegments cg(p, cut, min(max(32 * kseg + min(tid + k * NTHR, 32 * nwt - 1), 0), L - 1), nseg_valid);
+                    cn[k] = cg.n;
+#pragma unroll
+                    for (int i = 0; i < NSUM; ++i)
+                        w[k][i] = __hip_atomic_load(words + cg.at(i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                bool ok = true;
+#pragma unroll
+                for (int k = 0; k < NWIN; ++k) {
+                    sum[k] = 0.f;
+#pragma unroll
+                    for (int i = 0; i < NSUM; ++i) {
+                        ok = ok && (unsigned)(w[k][i] >> 32) == tag;
+                        sum[k] += i < cn[k] ? __uint_as_float((unsigned)w[k][i]) : 0.f;
+                    }
+                }
+                if (__all(ok)) break;
+                if (++polls > p.limit || ((polls & 63) == 0 && __hip_atomic_load(&p.chain->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
+                    gave_up = 1;
+                    break;
+                }
+            }
+            const int own_end = b + 1 == nseg_valid ? max(bv * BM, Lc) : bv * BM;
 #pragma unroll
             for (int k = 0; k < NWIN; ++k) {
-                const int i = tid + k * NTHR;
-                if (i < 32 * nwt) po[i] = over_fragments(cp, i, 0.f);
+                const int i = tid + k * NTHR, t = 32 * kseg + i;
+                if (i >= 32 * nwt) continue;
+                win_v[k] = t < Lc ? column_update<true>(win_v[k], sum[k], ColumnTarget(TARGETS ? win_lb[k] : 0.f)) : 0.f;
+                if (to >= 0 && t >= b0 * BM && t < min(own_end, L)) slots[(long)(to + 1) * p.Lp + t] = win_v[k];
+                stage_v(i, t, win_v[k], win_lb[k]);
             }
-            return;
+            __syncthreads();
+            if (gave_up) {
+                if (tid == 0) __hip_atomic_store(&p.chain->failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return;
+            }
+            continue;
         }
         if (!more) add_to_segment(cp, b, base);
         base += NF;
@@ -926,7 +1021,7 @@ __global__ __launch_bounds__(NTHREADS) void step_cut_kernel(const CutArgs a)
 }
 
 // v from the column sums of a step that no step follows (v_out may be p.v).
-__global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
+__device__ __forceinline__ void final_columns(const StepArgs &p)
 {
     __shared__ float red[32];
     const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk, blk = blockIdx.x % nblk, t = blk * NTHREADS + threadIdx.x;
@@ -952,6 +1047,60 @@ __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p)
         out = column_update<true>(v, sum, ColumnTarget(p.log_b ? p.log_b[(long)n * p.lstride + t] : 0.f));
     }
     v_out[t] = out;
+}
+__global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p) { final_columns(p); }
+
+// One half-step of problem n by one workgroup, a wavefront per row and a lane per partner; nothing is assumed of the potentials.
+template <typename T, int D>
+__device__ __forceinline__ void plain_half_step(const T *X, const T *Y, const float *y, float *x, int L, int W, int own, int oth, float c2)
+{
+    const int lane = threadIdx.x & 63;
+    for (int o = threadIdx.x >> 6; o < L; o += NWAVES) {
+        float m = -INFINITY, sum = 0.f;
+        for (int t = max(o - W, 0) + lane; t <= min(o + W, oth - 1) && o < own; t += 64) {
+            float dot = 0.f;
+            for (int k = 0; k < D; k += 4) {
+                float a[4], b[4];
+                load4<T>(X + (long)o * D + k, a);
+                load4<T>(Y + (long)t * D + k, b);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) dot = fmaf(a[i], b[i], dot);
+            }
+            const float e = fmaf(dot, c2, y[t] * LOG2E), mn = fmaxf(m, e);
+            sum = sum * fast_exp2(m - mn) + fast_exp2(e - mn);
+            m = mn;
+        }
+        for (int s = 32; s >= 1; s >>= 1) {
+            const float mo = __shfl_xor(m, s), so = __shfl_xor(sum, s), mn = fmaxf(m, mo);
+            sum = mn > -INFINITY ? sum * fast_exp2(m - mn) + so * fast_exp2(mo - mn) : 0.f;
+            m = mn;
+        }
+        if (lane == 0) x[o] = o < own ? -LN2 * (m + fast_log2(sum)) : 0.f;
+    }
+    __syncthreads();
+}
+// After a chain: the last step's v.  If the chain has given up, one workgroup per problem does all its steps from the start
+// (milliseconds; it asks nothing of the device).
+struct SolveArgs { int T, R; };
+template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish_kernel(const StepArgs p, const SolveArgs a)
+{
+    if (!p.chain->failed) {   // (written by the launch before)
+        final_columns(p);
+        return;
+    }
+    const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk;
+    if (blockIdx.x % nblk) return;
+    const T *X = reinterpret_cast<const T *>(p.X) + (long)n * p.L * D, *Y = reinterpret_cast<const T *>(p.Y) + (long)n * p.L * D;
+    float *slots = p.slots + n * p.us;
+    auto slot = [&](int k) { return slots + (long)k * p.Lp; };
+    const StepLens ln = step_lens(p, n);
+    for (int i = threadIdx.x; i < p.L; i += NTHREADS) slot(0)[i] = slot(1)[i] = 0.f;
+    __syncthreads();
+    for (int st = 0; st < a.T + a.R; ++st) {
+        const int to = st < a.T ? 0 : 2 * (st - a.T + 1), from = st < a.T ? 1 : to - 1;
+        plain_half_step<T, D>(X, Y, slot(from), slot(to), p.L, p.W, ln.Le, ln.Lt, p.c2);
+        plain_half_step<T, D>(Y, X, slot(to), slot(to + 1), p.L, p.W, ln.Lc, ln.Le, p.c2);
+    }
 }
 
 }  // namespace

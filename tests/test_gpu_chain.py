@@ -1,0 +1,83 @@
+"""Several Sinkhorn steps in one launch, whose workgroups hand their column sums to each other, against the same steps launch by
+launch: a forward whose workspace has room for the column sums of launched steps and no more takes the latter.  The same kernel on
+the same numbers, so the same bits; and the answer where a wait for a neighbour runs out."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # kind, dtype, d, N, L, W, T, R: one block and many, one tile of band and as many as single blocks take, ragged ends
+    ("plain", "bf16", 64, 1, 31, 7, 3, 2), ("plain", "bf16", 64, 2, 65, 0, 2, 1), ("plain", "bf16", 64, 8, 701, 64, 16, 2),
+    ("plain", "bf16", 64, 5, 3001, 100, 9, 2), ("plain", "bf16", 64, 30, 1999, 128, 4, 3), ("plain", "bf16", 64, 3, 1023, 256, 5, 2),
+    ("plain", "bf16", 64, 2, 1100, 300, 4, 2), ("plain", "bf16", 64, 1, 700, 33, 0, 4), ("plain", "bf16", 64, 1, 700, 33, 1, 2),
+    ("plain", "bf16", 32, 7, 1333, 40, 5, 2), ("plain", "bf16", 128, 4, 1777, 127, 5, 2), ("plain", "bf16", 128, 2, 900, 256, 3, 2),
+    ("plain", "bf16", 64, 300, 130, 60, 3, 2), ("plain", "f32", 32, 1, 256, 16, 8, 2), ("plain", "f32", 64, 8, 2000, 128, 5, 2),
+    ("plain", "f32", 64, 2, 700, 255, 3, 1), ("plain", "f32", 128, 2, 500, 60, 3, 2), ("plain", "bf16", 64, 2, 400, 5000, 4, 2),
+    ("varlen", "bf16", 64, 6, 2048, 128, 6, 2), ("varlen", "f32", 64, 4, 500, 100, 4, 2), ("varlen", "bf16", 64, 4, 900, 200, 2, 3),
+    ("varlen", "bf16", 64, 4, 611, 20, 1, 3)]
+
+
+def _setup(case):
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    kind, dtype, d, N, L, W, T, R = case
+    td, code = (torch.float32, 0) if dtype == "f32" else (torch.bfloat16, 1)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(31)
+    Q, K, V = (torch.randn((N, 1, L, d), generator=gen, device="cuda").to(td) for _ in range(3))
+    lq = lk = None
+    if kind == "varlen":   # an item without queries, one with a single key, rows that end before and after the columns
+        lq, lk = (torch.randint(1, L + 1, (N,), generator=gen, device="cuda").int() for _ in range(2))
+        lq[0], lk[1] = 0, 1
+        lq[2], lk[2] = L // 3, L
+        lq[3], lk[3] = L, L // 4
+    plan = binding.query_step_plan(N, 1, L, d, W, T, R, False, code, lengths=kind == "varlen")
+    assert plan.whole_steps and plan.segment_blocks == 1
+    few = plan.sums_offset[1] + N * plan.sums_bytes   # launches: room for two buffers of column sums
+    assert few < ska.sinkhorn_attn_workspace_bytes(N, 1, L, d, W, T, R, False, code)
+
+    def forward(nbytes=None):
+        ws = None if nbytes is None else torch.full((nbytes,), 255, device="cuda", dtype=torch.uint8)
+        out = ska.sinkhorn_attn_fwd_varlen(Q, K, V, None, None, lq, lk, W, T, R, 0.7, False, 0.0, workspace=ws)
+        torch.cuda.synchronize()
+        return out
+
+    return forward, few
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_a_chain_has_the_bits_of_its_steps(case):
+    import torch
+    print(f"\n[case] {case}", flush=True)
+    forward, few = _setup(case)
+    O0, UV0 = forward(few)
+    assert torch.isfinite(UV0).all()
+    for _ in range(3):   # (the words of the call before lie where the next one's will)
+        O, UV = forward()
+        assert torch.equal(UV, UV0) and torch.equal(O, O0)
+
+
+@pytest.mark.parametrize("case", [CASES[2], CASES[3], CASES[7], CASES[14], CASES[18], CASES[20]], ids=lambda c: "-".join(map(str, c)))
+def test_a_wait_that_runs_out_leaves_the_answer(case):
+    """One poll and no more: some workgroup gives up, and the launch that follows solves the problem by itself.  The potentials
+    agree to rounding: (2 W + 20 + 4 M) 2^-24 per half-step on either side (see test_gpu_steps.py), M the largest exponent."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    kind, dtype, d, N, L, W, T, R = case
+    print(f"\n[case] {case}", flush=True)
+    forward, few = _setup(case)
+    O0, UV0 = forward(few)
+    try:
+        ska.sinkhorn_attn_set_fused_half_steps(0, 1)
+        O, UV = forward()
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+    M = 1.4427 * max(float(UV0.abs().max()), 6.0 * d ** 0.5 / 0.7)
+    bound = 2 * 2 * (T + R) * (2 * min(W, L) + 21 + 4 * M) * 2.0 ** -24
+    err = float((UV.double() - UV0.double()).abs().max())
+    print(f"   |UV - UV0| {err:.1e} (bound {bound:.1e})", flush=True)
+    assert err <= bound
+    rel = float((O.double() - O0.double()).norm() / O0.double().norm())
+    assert rel <= 2 * bound + (2.0 ** -8 if dtype == "bf16" else 0.0), rel
