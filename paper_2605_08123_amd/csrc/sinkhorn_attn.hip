@@ -38,14 +38,14 @@
 #include "sinkhorn_attn_query.h"
 #include "ska_common.h"
 #include "ska_small_kernels.h"
-#include "ska_step.h"
+#include "ska_step_ends.h"
+#include "ska_step_launch.h"
 #include "ska_sweep_generic.h"
 #include "ska_sweep_ring.h"
 
 namespace {
 
 // ------------------------------------------------------------------ host side
-constexpr int MAX_DEVICES = 16;   // per-device state of the library (helper stream, raised LDS limits, static scratch)
 
 struct Problem {
     int B, H, L, d, W, T, R, dustbin, dtype;
@@ -537,53 +537,20 @@ bool chain_may_start(int dev, hipStream_t st)
     if (!g.started) return false;
     return __atomic_load_n(g.started, __ATOMIC_RELAXED) == g.seq || (st == g.last && st != hipStreamPerThread);
 }
-template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int launch_vstep_n(StepArgs p, int N, hipStream_t st, int dev)
+// a step's or a chain's launch; a chain on a stream of its own is the gate's latest once it is on its way
+template <typename T, int D> int launch_vstep(StepArgs p, const StepShape &sh, int N, hipStream_t st, int dev)
 {
-    p.nb_total = p.cut ? (N < p.items * p.nh ? CUT_HALF : CUT_SEGS) : p.nseg * N;
-    const int lds = StepLds<T, D, NF, G, NTW, KIND, FORM>(p.hw).total;
-    static bool raised[MAX_DEVICES];
-    if (!raised[dev]) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, FORM>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, STEP_LDS) != hipSuccess)
-            return SKA_EHIP;
-        raised[dev] = true;
-    }
-    if (p.nsteps > 1) {   // a chain's workgroups wait for each other: they must fit the device together
-        static int caps[MAX_DEVICES], caps_lds[MAX_DEVICES];   // what it holds, at which LDS size (0: not asked yet; g_mutex held)
-        if (caps_lds[dev] != lds) {
-            int per_cu = 0, cus = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(&vstep_kernel<T, D, NF, G, NTW, KIND, FORM>),
-                                                             64 * NF * G, lds) != hipSuccess ||
-                hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-                return SKA_EHIP;
-            caps[dev] = per_cu * cus;
-            caps_lds[dev] = lds;
-        }
-        if ((p.nb_total + 7) / 8 * 8 > caps[dev]) return SKA_EUNSUPPORTED;   // (nothing has been launched)
-        ChainGate &gate = g_gate[dev];
-        p.started = gate.started_dev;
-        p.seq = ++gate.seq;
+    ChainGate &gate = g_gate[dev];
+    p.started = gate.started_dev;
+    p.seq = gate.seq + 1;
+    const auto launch = sizeof(T) == 2 ? (D == 32 ? ska_launch_steps_bf16_32 : D == 64 ? ska_launch_steps_bf16_64 : ska_launch_steps_bf16_128)
+                                       : (D == 32 ? ska_launch_steps_f32_32 : D == 64 ? ska_launch_steps_f32_64 : ska_launch_steps_f32_128);
+    const int rc = launch(&p, &sh, N, st, dev);
+    if (rc == SKA_OK && p.nsteps > 1) {
+        gate.seq = p.seq;
         gate.last = st;
     }
-    hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, FORM>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
-    return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
-}
-template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape &sh, int N, hipStream_t st, int dev)
-{
-    constexpr int TB = step_tile_bytes<T, D>;
-#define SKA_LAUNCH(COND, NF_, G_, NTW_, KIND_) \
-    if constexpr (COND) \
-        if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) { \
-            constexpr bool ANY = KIND_ == STEP_BLOCK; \
-            if (p.log_a || p.log_b) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(p, N, st, dev); \
-            if constexpr (!ANY) \
-                if (p.cut) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_CUT>(p, N, st, dev); \
-            if (!ANY && p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_DUSTBIN>(p, N, st, dev); \
-            return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_PLAIN>(p, N, st, dev); \
-        }
-    SKA_STEP_SHAPES(SKA_LAUNCH)
-#undef SKA_LAUNCH
-    return SKA_EUNSUPPORTED;
+    return rc;
 }
 inline int launch_vfinal(const StepArgs &p, int N, hipStream_t st)
 {

@@ -14,6 +14,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
+constexpr int MAX_DEVICES = 16;   // per-device state of the library (helper stream, raised LDS limits, static scratch)
 constexpr int NTHREADS = 256;
 constexpr int NWAVES = 4;
 constexpr int TT = 32;  // other-side rows per tile
