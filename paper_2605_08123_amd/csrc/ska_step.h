@@ -305,7 +305,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
     constexpr bool TARGETS = FORM == STEP_TARGETS, MAY_CUT = MARCH && (TARGETS || FORM == STEP_CUT);
-    const bool DUST = FORM == STEP_ANY ? p.dustbin != 0 : FORM == STEP_DUSTBIN;
+    const bool DUST = FORM == STEP_ANY || FORM == STEP_KEEP ? p.dustbin != 0 : FORM == STEP_DUSTBIN;
     extern __shared__ __align__(16) unsigned char smem[];
     take_args(p);
     const int bx = (int)blockIdx.x;
@@ -585,8 +585,17 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         return r;
     };
 
-    f32x16 E[NTW];   // plan entries of a block: this wavefront's
-    auto evaluate = [&](int b, int us_buf, float u_own, float (&rsum)[16], auto &&late) {
+    // KEEP: a chain's scores stay in registers from step to step, since a tile's products take 2048 cycles at d = 64.  The plan
+    // entries lie beside them where one workgroup fills a CU's LDS with four wavefronts, which may have 512 registers each, or
+    // where both are few; elsewhere they are evaluated a second time for the column sums.
+    // Chained steps, us each, products in every step -> kept: 8 problems of L = 4096, d = 64, W = 128 (4,1,9) 14.8 -> 6.4, of 8000 (8,1,9)
+    // 25.6 -> 11.9; 4 of 4000, W = 256 (2,4,5) 15.5 -> 8.4; 8 of 2000, d = 32, W = 128 (2,2,5) 7.1 -> 6.2; one of 256, W = 16 3.5 -> 2.7.
+    // (bf16: a tile's products take 160 cycles, which the exponentials partly hide.)
+    constexpr bool KEEP = FORM == STEP_KEEP;
+    constexpr bool STORE_E = !KEEP || NTW <= 3 || (NF * G <= 4 && ST::BYTES >= 8192 && NF + G * NTW > 9);
+    f32x16 E[STORE_E ? NTW : 1], S[KEEP ? NTW : 1];   // plan entries, scores of a block: this wavefront's
+    // KEEP: first, that the scores are not there yet; columns, that the entries are wanted again, by column(s, e).
+    auto evaluate = [&](int b, int us_buf, float u_own, float (&rsum)[16], auto &&late, bool first, bool columns, auto &&column) {
         const int c = lane & 31, h = lane >> 5, k0 = b * NF - hw, o_f = (b * NF + f) * 32;
         [[maybe_unused]] f32x16 ci;   // fp32 storage: the rows' potentials
         if constexpr (!PRE) {
@@ -596,8 +605,10 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                 ci[4 * q + 0] = v4.x; ci[4 * q + 1] = v4.y; ci[4 * q + 2] = v4.z; ci[4 * q + 3] = v4.w;
             }
         }
+        if (!columns) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) rsum[r] = 0.f;
+            for (int r = 0; r < 16; ++r) rsum[r] = 0.f;
+        }
         [[maybe_unused]] float bt[NTW];   // TARGETS: weight of this lane's column of each tile
         auto add_rows = [&](const f32x16 &e, int s, int r) {
             if constexpr (TARGETS) rsum[r] = fmaf(e[r], bt[s], rsum[r]);
@@ -716,29 +727,39 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
 #pragma unroll
             for (int s = 0; s < NTW; ++s) {
                 if (s == NTW / 2) late();
+                f32x16 e;
                 if (present(s)) {   // (uniform)
-                    const unsigned char *yr = smem + lds.y + slot * ST::BYTES + c * ST::ROWB;
+                    f32x16 &score = KEEP ? S[KEEP ? s : 0] : e;
+                    if (!KEEP || first) {
+                        const unsigned char *yr = smem + lds.y + slot * ST::BYTES + c * ST::ROWB;
+                        f32x16 a;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) a[r] = 0.f;
+#pragma unroll
+                        for (int q = 0; q < D / 8; ++q) {
+                            const float4 y = *reinterpret_cast<const float4 *>(yr + (((h * (D / 8) + q) ^ ST::swz(c)) << 4));
+                            a = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 0], y.x, a, 0, 0, 0);
+                            a = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 1], y.y, a, 0, 0, 0);
+                            a = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 2], y.z, a, 0, 0, 0);
+                            a = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 3], y.w, a, 0, 0, 0);
+                        }
+                        score = a;
+                    }
                     const float vt = *reinterpret_cast<const float *>(vs + (32 * slot + c) * LD::VB);
                     if constexpr (TARGETS) bt[s] = *reinterpret_cast<const float *>(vs + (32 * slot + c) * LD::VB + 4);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
+                    for (int r = 0; r < 16; ++r) e[r] = fast_exp2(fmaf(score[r], p.c2, ci[r] + vt));
+                    if (!interior(s)) mask(e, 32 * (kw + s), true);
+                    if (!columns) {
 #pragma unroll
-                    for (int q = 0; q < D / 8; ++q) {
-                        const float4 y = *reinterpret_cast<const float4 *>(yr + (((h * (D / 8) + q) ^ ST::swz(c)) << 4));
-                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 0], y.x, E[s], 0, 0, 0);
-                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 1], y.y, E[s], 0, 0, 0);
-                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 2], y.z, E[s], 0, 0, 0);
-                        E[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[4 * q + 3], y.w, E[s], 0, 0, 0);
+                        for (int r = 0; r < 16; ++r) add_rows(e, s, r);
                     }
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) E[s][r] = fast_exp2(fmaf(E[s][r], p.c2, ci[r] + vt));
-                    if (!interior(s)) mask(E[s], 32 * (kw + s), true);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) add_rows(E[s], s, r);
                 } else {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) E[s][r] = 0.f;
+                    for (int r = 0; r < 16; ++r) e[r] = 0.f;
                 }
+                if constexpr (STORE_E) E[s] = e;
+                else if (columns) column(s, e);
                 slot = lds.slot(slot + 1);
             }
         }
@@ -816,18 +837,25 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         }
         return wt;
     };
+    auto column_of = [&](const f32x16 &e, const Weights &wt) {
+        float x = 0.f, y = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) { x = fmaf(e[r], wt.w[r], x); y = fmaf(e[r + 1], wt.w[r + 1], y); }
+        if constexpr (TARGETS) return __builtin_amdgcn_ldexpf(x + y, wt.exp);
+        else return x + y;
+    };
+    // of tiles s and s + 1, if there is one (their columns' halves are in the two halves of the wavefront)
+    auto store_columns = [&](float *cpw, int s, float x, float x1) {
+        const float y = halves_sum(x, x1);
+        if (lane < (s + 1 < NTW ? 64 : 32) && s + (lane >> 5) < cnt) cpw[32 * s + lane] = y;   // (tiles that are not there: zeros stay)
+    };
     auto add_columns = [&](float *cpw, const Weights &wt) {   // of a fragment
-        auto col = [&](const f32x16 &e) {
-            float x = 0.f, y = 0.f;
+        if constexpr (STORE_E) {
 #pragma unroll
-            for (int r = 0; r < 16; r += 2) { x = fmaf(e[r], wt.w[r], x); y = fmaf(e[r + 1], wt.w[r + 1], y); }
-            if constexpr (TARGETS) return __builtin_amdgcn_ldexpf(x + y, wt.exp);
-            else return x + y;
-        };
-#pragma unroll
-        for (int s = 0; s < NTW; s += 2) {
-            const float x = col(E[s]), y = halves_sum(x, s + 1 < NTW ? col(E[s + 1 < NTW ? s + 1 : s]) : x);
-            if (lane < (s + 1 < NTW ? 64 : 32) && s + (lane >> 5) < cnt) cpw[32 * s + lane] = y;   // (tiles that are not there: zeros stay)
+            for (int s = 0; s < NTW; s += 2) {
+                const float x = column_of(E[s], wt);
+                store_columns(cpw, s, x, s + 1 < NTW ? column_of(E[s + 1 < NTW ? s + 1 : s], wt) : x);
+            }
         }
     };
     // the segment's last block: every thread has added its share of what the dustbin gets (wsw: its weights have been read)
@@ -886,7 +914,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         const Row row = row_of(b, par);
         evaluate(b, par, row.u, rsum, [&]() {
             if (MARCH && b > b0) add_to_segment(cp0 + (LD::TWO == 2 ? par ^ 1 : 0) * NF * cps, b - 1, base >= NF ? base - NF : base - NF + RS);
-        });
+        }, st == 0, false, [](int, const f32x16 &) {});
         if (more) xf.load(reinterpret_cast<const T *>(Xb), min(((b + 1) * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
         write_row_sums(rsum, rs);
         if (KIND == STEP_MARCH && more) stage_added_v(next, b);   // (slots of their own)
@@ -897,6 +925,15 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         const Weights wt = weights(b, row, rs);
         float *cp = cp0 + par * NF * cps;
         add_columns(cp + f * cps + (f + j0) * 32, wt);
+        if constexpr (!STORE_E) {
+            float before = 0.f;
+            evaluate(b, par, row.u, rsum, []() {}, false, true, [&](int s, const f32x16 &e) {
+                const float x = column_of(e, wt);
+                if (s & 1) store_columns(cp + f * cps + (f + j0) * 32, s - 1, before, x);
+                else if (s == NTW - 1) store_columns(cp + f * cps + (f + j0) * 32, s, x, x);
+                before = x;
+            });
+        }
         if (TIGHT && more) stage_added_v(next, b);
         if (more) stage_added_u(next, b, LD::TWO == 2 ? par ^ 1 : 0);
         else sum_dustbin();

@@ -42,6 +42,11 @@ template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape
             if (p.log_a || p.log_b) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(p, N, st, dev); \
             if constexpr (!ANY) \
                 if (p.cut) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_CUT>(p, N, st, dev); \
+            if constexpr (ANY && sizeof(T) == 4) \
+                if (p.nsteps > 1) { /* (more registers: fewer workgroups fit) */ \
+                    const int rc = launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_KEEP>(p, N, st, dev); \
+                    if (rc != SKA_EUNSUPPORTED) return rc; \
+                } \
             if (!ANY && p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_DUSTBIN>(p, N, st, dev); \
             return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_PLAIN>(p, N, st, dev); \
         }

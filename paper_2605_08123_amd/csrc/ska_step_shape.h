@@ -17,7 +17,8 @@ template <typename T, int D> struct StepTile {
 enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
 // What a call's steps add to the plain ones: nothing, a dustbin, a dustbin if the arguments say so, targets of rows or columns
 // (which go with no dustbin; a cut or none), segments cut from valid rows.
-enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS, STEP_CUT };
+// STEP_KEEP: STEP_ANY in a chain of steps, fp32 storage.
+enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS, STEP_CUT, STEP_KEEP };
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> struct StepLds {   // offsets in bytes
     static constexpr bool MARCH = KIND != STEP_BLOCK;
     static_assert(KIND != STEP_TIGHT || G > 1, "the exchange of row sums says that the products are done");

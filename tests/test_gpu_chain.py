@@ -12,6 +12,9 @@ CASES = [  # kind, dtype, d, N, L, W, T, R: one block and many, one tile of band
     ("plain", "bf16", 32, 7, 1333, 40, 5, 2), ("plain", "bf16", 128, 4, 1777, 127, 5, 2), ("plain", "bf16", 128, 2, 900, 256, 3, 2),
     ("plain", "bf16", 64, 300, 130, 60, 3, 2), ("plain", "f32", 32, 1, 256, 16, 8, 2), ("plain", "f32", 64, 8, 2000, 128, 5, 2),
     ("plain", "f32", 64, 2, 700, 255, 3, 1), ("plain", "f32", 128, 2, 500, 60, 3, 2), ("plain", "bf16", 64, 2, 400, 5000, 4, 2),
+    # fp32 keeps its scores over the steps: beside the plan entries or with those evaluated twice, few tiles and many
+    ("plain", "f32", 64, 4, 2000, 256, 4, 2), ("plain", "f32", 64, 8, 8000, 128, 3, 2), ("plain", "f32", 32, 8, 2000, 128, 4, 2),
+    ("plain", "f32", 64, 2, 3000, 60, 4, 2), ("plain", "f32", 128, 4, 700, 33, 4, 2), ("varlen", "f32", 64, 4, 8000, 120, 3, 2),
     ("varlen", "bf16", 64, 6, 2048, 128, 6, 2), ("varlen", "f32", 64, 4, 500, 100, 4, 2), ("varlen", "bf16", 64, 4, 900, 200, 2, 3),
     ("varlen", "bf16", 64, 4, 611, 20, 1, 3)]
 
