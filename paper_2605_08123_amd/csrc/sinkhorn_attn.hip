@@ -504,10 +504,12 @@ inline ChainSpace chain_space(const Problem &p, const StepShape &sh, bool one_ca
     ChainSpace s{0, 0, 0, 0};
     const size_t N = p.N(), gu = N * p.ldw() * sizeof(float), off = ((one_call ? 0 : ws_qs_bytes(p)) + gu + 255) / 256 * 256;
     s.wstride = step_segments(sh, p.L) * 32 * (sh.NF + 2 * sh.hw);
-    s.clear = 256 + 2 * N * s.wstride * sizeof(unsigned long long);
+    s.clear = 256 + 2 * N * (s.wstride + (p.dustbin ? 2 * step_segments(sh, p.L) : 0)) * sizeof(unsigned long long);
     s.sums = off + s.clear;
-    const size_t end = s.sums + N * step_part_stride(sh, p.L, false, false) * sizeof(float);
-    if (end <= (one_call ? ws_vec_bytes(p) : p.ws_given)) s.off = off;
+    const size_t end = s.sums + N * step_part_stride(sh, p.L, p.dustbin, false) * sizeof(float);
+    // (what follows the vectors holds the spokes of learned dustbin tokens)
+    const size_t limit = ws_vec_bytes(p) + (one_call ? 0 : ws_qs_bytes(p));
+    if (end <= limit && (one_call || end <= p.ws_given)) s.off = off;
     return s;
 }
 // Chains of the device that are or may be waiting for room: all on one stream follow each other; one on another stream starts only if
@@ -664,12 +666,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
     // Whole steps after the first one: in one launch where every workgroup is a single block and all of them fit the device, the
-    // call's sweeps are not split, and nothing but lengths is added to the plain problem (see vstep_kernel).
+    // call's sweeps are not split (see vstep_kernel).
     const StepShape shape = step_shape<T, D>(N, L, p.W);
     const ChainSpace room = shape.NF && ws ? chain_space(p, shape, fused) : ChainSpace{0, 0, 0, 0};
     const int after_first = p.T + R - 1;
-    bool chained = room.off && shape.kind == STEP_BLOCK && shape.M == 1 && after_first >= 2 && !p.dustbin && !p.mask_q && !p.mask_k && !p.log_a &&
-                   !p.log_b && !p.n_stages && !p.resume_t && !cx.side && !cx.noalloc && !capturing && chain_may_start(cx.dev, st);
+    bool chained = room.off && shape.kind == STEP_BLOCK && shape.M == 1 && after_first >= 2 && !p.n_stages && !p.resume_t && !cx.side && !cx.noalloc && !capturing && chain_may_start(cx.dev, st);
     // u0 = v0 = 0: the base solve starts from v = 0
     if (!p.resume_t) {
         const long n16 = chained ? (long)room.clear / 16 : 0, tot = 2L * Lp * N > n16 ? 2L * Lp * N : n16;
@@ -866,11 +867,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // all steps after the first one as a chain; SKA_EUNSUPPORTED: they do not fit the device together (nothing has been launched)
     auto chain_steps = [&]() -> int {
         StepArgs f = step;
-        f.c2 = c2;
+        f.c2 = c2; f.sdb = p.sdb;
         f.X = Q;
         f.v = slot(vcur); f.u = f.u_out = slot(p.T ? 0 : 2); f.v_out = slot(vcur);
         unsigned char *at = reinterpret_cast<unsigned char *>(ws) + room.off;
-        f.part_stride = step_part_stride(shape, L, false, false);
+        f.part_stride = step_part_stride(shape, L, p.dustbin, false);
         f.part_out = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + room.sums);
         f.nsteps = after_first;
         f.base_left = p.T ? p.T - 1 : 0; f.tail = p.T ? 1 : 2;

@@ -244,12 +244,9 @@ __device__ __forceinline__ bf16x4 potential_parts(float x)
 // of the segments, the same in every workgroup).  The column half-step follows the row half-step.  All threads call it;
 // red: 2 * 16 floats of LDS.
 struct DustbinPair { float u, v; };
-template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_pair(const StepArgs &p, const float *part, float corner, float *red)
+// r, c: this thread's share of the sums; u0, v0: the potentials they refer to
+template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_from(float r, float c, float u0, float v0, float corner, float *red)
 {
-    const float *q = part + (long)p.nseg * (32 * (p.NF * p.M + 2 * p.hw));
-    float r = 0.f, c = 0.f;
-    for (int i = threadIdx.x; i < p.nseg; i += NTHR) { r += q[i]; c += q[p.nseg + i]; }
-    const float u0 = q[2 * p.nseg], v0 = q[2 * p.nseg + 1];
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1) { r += __shfl_xor(r, s); c += __shfl_xor(c, s); }
     if ((threadIdx.x & 63) == 0) { red[threadIdx.x >> 6] = r; red[16 + (threadIdx.x >> 6)] = c; }
@@ -259,6 +256,13 @@ template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_pair(const St
     for (int i = 0; i < NTHR / 64; ++i) { r += red[i]; c += red[16 + i]; }
     const float u = column_update<false>(u0, r + fast_exp2((corner + v0 + u0) * LOG2E), ColumnTarget(0.f));
     return DustbinPair{u, column_update<false>(v0, c + fast_exp2((corner + u + v0) * LOG2E), ColumnTarget(0.f))};
+}
+template <int NTHR> __device__ __forceinline__ DustbinPair dustbin_pair(const StepArgs &p, const float *part, float corner, float *red)
+{
+    const float *q = part + (long)p.nseg * (32 * (p.NF * p.M + 2 * p.hw));
+    float r = 0.f, c = 0.f;
+    for (int i = threadIdx.x; i < p.nseg; i += NTHR) { r += q[i]; c += q[p.nseg + i]; }
+    return dustbin_from<NTHR>(r, c, q[2 * p.nseg], q[2 * p.nseg + 1], corner, red);
 }
 
 template <int CTRL> __device__ __forceinline__ float dpp_add(float x)
@@ -296,16 +300,19 @@ __device__ __forceinline__ float rows16_sum(float a, float b)
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Wavefronts per SIMD that the registers must allow: three short blocks of four wavefronts fit a CU's LDS (a chain of 16 problems of
+// L = 3001, W = 100 needs them all).
+template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> constexpr int step_waves = KIND == STEP_CHAIN && FORM == STEP_DUSTBIN && NF * G == 4 && NTW <= 5 && StepTile<T, D>::BYTES <= 4096 && sizeof(T) == 2 ? 3 : 1;
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM>
-__global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
+__global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FORM>)) void vstep_kernel(const StepArgs p)
 {
     using ST = StepTile<T, D>;
     using LD = StepLds<T, D, NF, G, NTW, KIND, FORM>;
-    constexpr bool MARCH = KIND != STEP_BLOCK, TIGHT = KIND == STEP_TIGHT;
+    constexpr bool TIGHT = KIND == STEP_TIGHT, MARCH = KIND == STEP_MARCH || TIGHT, CHAIN = KIND == STEP_CHAIN;
     constexpr bool PRE = (sizeof(T) == 2);
     constexpr int BM = 32 * NF, NTHR = 64 * NF * G;
     constexpr bool TARGETS = FORM == STEP_TARGETS, MAY_CUT = MARCH && (TARGETS || FORM == STEP_CUT);
-    const bool DUST = FORM == STEP_ANY || FORM == STEP_KEEP ? p.dustbin != 0 : FORM == STEP_DUSTBIN;
+    const bool DUST = FORM == STEP_ANY ? p.dustbin != 0 : FORM == STEP_DUSTBIN;
     extern __shared__ __align__(16) unsigned char smem[];
     take_args(p);
     const int bx = (int)blockIdx.x;
@@ -353,17 +360,18 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     // the words of two steps before.  A hand-over takes about 1 us where a launch takes 5 (2.3 if it is empty).  The host sees to it that the
     // workgroups fit the device together and that no other chain is waiting for room; a wait that runs out all the same (other
     // programs on the device) ends the launch, and the problem is solved again by the launch that follows (vfinish_kernel).
-    const bool chained = KIND == STEP_BLOCK && p.nsteps > 1;
+    // (A kind of its own, since what it adds costs a launched step of a call with a dustbin 4 %, and forms of its own, since a flag that is
+    // read costs a chain without a dustbin as much.)
     __shared__ int gave_up;
     float *slots = p.slots + n * p.us;
-    if (chained && tid == 0) {
+    if (CHAIN && tid == 0) {
         gave_up = 0;
         if (__hip_atomic_fetch_add(&p.chain->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)p.nb_total)
             __hip_atomic_store(p.started, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     // where step st leaves its potentials (-1: nowhere)
     auto slot_of = [&](int st) { return st + 1 < p.base_left ? -1 : st + 1 == p.base_left ? 0 : 2 * (p.tail + st - p.base_left); };
-    if (chained) {   // rows without an edge: zeros (v: from the last column with an edge on; the last block with rows has the others)
+    if constexpr (CHAIN) {   // rows without an edge: zeros (v: from the last column with an edge on; the last block with rows has the others)
         for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L); t += NTHR)
             for (int st = 0; st < p.nsteps; ++st) {
                 const int sl = slot_of(st);
@@ -374,7 +382,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         if (b0 >= bv) return;
     }
     // rows without an edge: zeros, and this segment's share of v there
-    for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L) && !chained; t += NTHR) {
+    for (int t = max(b0, bv) * BM + tid; t < min(b1 * BM, L) && !CHAIN; t += NTHR) {
         u_out[t] = 0.f;
         if (part) v_out[t] = t < Lc ? column_update<true>(vp[t], column_sum(p, cut, part, t, nseg_valid), ColumnTarget(lbp ? lbp[t] : 0.f)) : 0.f;
     }
@@ -454,15 +462,16 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         }
     }
     // Dustbin: its potentials as this step's rows see them (uL is a reference only: the row half-step replaces it)
+    auto uniform = [](float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); };
     float uL = 0.f, vL = 0.f, to_row = 0.f, to_col = 0.f;   // this thread's share of what its row and its column get
     float *dust = p.part_out + n * p.part_stride + (long)p.nseg * (32 * (NF * M + 2 * hw));
     if (DUST) {
         const float corner = spr ? spr[L] : p.sdb;
         if (part) {
             const DustbinPair d = dustbin_pair<NTHR>(p, part, corner, rs);
-            uL = d.u; vL = d.v;
+            uL = uniform(d.u); vL = uniform(d.v);
         } else {
-            uL = xsp[L]; vL = vp[L];
+            uL = uniform(xsp[L]); vL = uniform(vp[L]);
         }
         if (seg == 0 && tid == 0) {
             dust[2 * p.nseg] = uL; dust[2 * p.nseg + 1] = vL;
@@ -500,6 +509,14 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             stage_v(i, t, win_v[k], win_lb[k]);
         }
     }
+    // a chain's rows' share is known here, before the evaluation
+    __shared__ float dust_row[16];
+    auto sum_row = [&]() {
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) to_row += __shfl_xor(to_row, s);
+        if ((tid & 63) == 0) dust_row[wave] = to_row;
+    };
+    if (CHAIN && DUST) sum_row();
     if (tid < BM) stage_u(tid, u_first, la_first);
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): the LDS-direct loads have arrived
     __syncthreads();
@@ -862,15 +879,25 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     auto sum_dustbin = [&]() {
         if (!DUST) return;
 #pragma unroll
-        for (int s = 32; s >= 1; s >>= 1) { to_row += __shfl_xor(to_row, s); to_col += __shfl_xor(to_col, s); }
-        if (lane == 0) { wsw[0] = to_row; wsw[1] = to_col; }
+        for (int s = 32; s >= 1; s >>= 1) {
+            if constexpr (!CHAIN) to_row += __shfl_xor(to_row, s);
+            to_col += __shfl_xor(to_col, s);
+        }
+        if (lane == 0) {
+            if constexpr (!CHAIN) wsw[0] = to_row;
+            wsw[1] = to_col;
+        }
     };
-    auto store_dustbin = [&]() {
+    // (a chain's: as words behind the columns')
+    auto dust_words = [&](int st) { return p.words + 2 * p.wbuf + ((long)(st & 1) * p.np + n) * (2 * p.nseg); };
+    auto store_dustbin = [&](int st) {
         if (!DUST || tid >= 2) return;
         float s = 0.f;
 #pragma unroll
-        for (int i = 0; i < NF * G; ++i) s += reinterpret_cast<const float *>(smem + LD::WS)[32 * i + tid];
-        dust[tid * p.nseg + seg] = s;
+        for (int i = 0; i < NF * G; ++i) s += CHAIN && tid == 0 ? dust_row[i] : reinterpret_cast<const float *>(smem + LD::WS)[32 * i + tid];
+        if (CHAIN && st + 1 < p.nsteps)
+            __hip_atomic_store(dust_words(st) + tid * p.nseg + seg, (unsigned long long)(st + 1) << 32 | __float_as_uint(s), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else dust[tid * p.nseg + seg] = s;
     };
     // column sums of the block's fragments at column i of its window
     auto over_fragments = [&](const float *cp, int i, float s) {
@@ -899,10 +926,10 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
     };
     float rsum[16];
 
-    for (int b = b0, st = 0; !MARCH || b < bv; MARCH ? ++b : ++st) {
+    for (int b = b0, st = 0; MARCH ? b < bv : CHAIN || st == 0; MARCH ? ++b : ++st) {
         // what depends on the lane alone is computed again in every block: kept across the loop it would take the
         // registers that the plan entries need
-        asm volatile("" : "+v"(tid));
+        if constexpr (MARCH || CHAIN) asm volatile("" : "+v"(tid));
         lane = tid & 63;
         const int par = LD::TWO == 2 ? (b - b0) & 1 : 0, o = (b * NF + f) * 32 + (lane & 31);
         const bool more = MARCH && b + 1 < bv;
@@ -911,6 +938,7 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
             next = request(b);
             if constexpr (!TIGHT) request_tiles(b);
         }
+        if constexpr (CHAIN) to_col = 0.f;
         const Row row = row_of(b, par);
         evaluate(b, par, row.u, rsum, [&]() {
             if (MARCH && b > b0) add_to_segment(cp0 + (LD::TWO == 2 ? par ^ 1 : 0) * NF * cps, b - 1, base >= NF ? base - NF : base - NF + RS);
@@ -940,14 +968,14 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
         __builtin_amdgcn_s_waitcnt(0x0070);   // the next block's tiles
         __syncthreads();
         // rows' stores only now: the wait above would wait for them as well
-        const int to = chained ? slot_of(st) : 0;
-        if (lane < 32 && g == 0 && o < L && to >= 0) (chained ? slots + (long)to * p.Lp : u_out)[o] = wt.u_new;
-        if (!more) store_dustbin();
+        const int to = CHAIN ? slot_of(st) : 0;
+        if (lane < 32 && g == 0 && o < L && to >= 0) (CHAIN ? slots + (long)to * p.Lp : u_out)[o] = wt.u_new;
+        if (!more) store_dustbin(st);
         if constexpr (!MARCH) {
             float sum[NWIN];
 #pragma unroll
             for (int k = 0; k < NWIN; ++k) sum[k] = over_fragments(cp, min(tid + k * NTHR, 32 * nwt - 1), 0.f);
-            if (st + 1 == p.nsteps) {
+            if (!CHAIN || st + 1 == p.nsteps) {
 #pragma unroll
                 for (int k = 0; k < NWIN; ++k)
                     if (tid + k * NTHR < 32 * nwt) po[tid + k * NTHR] = sum[k];
@@ -961,7 +989,14 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                     __hip_atomic_store(words + (long)seg * (32 * nwt) + tid + k * NTHR, (unsigned long long)tag << 32 | __float_as_uint(sum[k]),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (lane < 32 && g == 0) stage_u(32 * f + lane, o < Le ? wt.u_new : -INFINITY, row.la);
-            for (unsigned polls = 0;;) {
+            unsigned polls = 0;
+            // whether to give up waiting
+            auto enough = [&]() {
+                if (++polls <= p.limit && ((polls & 63) || !__hip_atomic_load(&p.chain->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return false;
+                gave_up = 1;
+                return true;
+            };
+            for (;;) {
                 unsigned long long w[NWIN][NSUM];
                 int cn[NWIN];
 #pragma unroll
@@ -983,20 +1018,43 @@ __global__ __launch_bounds__(64 * NF * G) void vstep_kernel(const StepArgs p)
                     }
                 }
                 if (__all(ok)) break;
-                if (++polls > p.limit || ((polls & 63) == 0 && __hip_atomic_load(&p.chain->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) {
-                    gave_up = 1;
-                    break;
+                if (enough()) break;
+            }
+            if (DUST) {
+                const unsigned long long *q = dust_words(st);
+                float r = 0.f, c = 0.f;
+                for (int i = tid; i < p.nseg; i += NTHR) {
+                    unsigned long long a, b;
+                    do {
+                        a = __hip_atomic_load(q + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        b = __hip_atomic_load(q + p.nseg + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    } while (((unsigned)(a >> 32) != tag || (unsigned)(b >> 32) != tag) && !enough());
+                    r += __uint_as_float((unsigned)a); c += __uint_as_float((unsigned)b);
+                }
+                const DustbinPair d = dustbin_from<NTHR>(r, c, uL, vL, spr ? spr[L] : p.sdb, rs);
+                uL = uniform(d.u); vL = uniform(d.v);
+                to_row = 0.f;
+                if (seg == 0 && tid == 0) {
+                    if (to >= 0) { slots[(long)to * p.Lp + L] = uL; slots[(long)(to + 1) * p.Lp + L] = vL; }
+                    dust[2 * p.nseg] = uL; dust[2 * p.nseg + 1] = vL;   // (the last step's is what the launch after this one reads)
                 }
             }
+            // (the scores of the spokes are read again: kept over the evaluation they cost a workgroup per CU)
+            float spoke_c[NWIN];
+#pragma unroll
+            for (int k = 0; k < NWIN; ++k) spoke_c[k] = DUST && spc ? spc[min(max(32 * kseg + tid + k * NTHR, 0), L - 1)] : p.sdb;
             const int own_end = b + 1 == nseg_valid ? max(bv * BM, Lc) : bv * BM;
 #pragma unroll
             for (int k = 0; k < NWIN; ++k) {
                 const int i = tid + k * NTHR, t = 32 * kseg + i;
                 if (i >= 32 * nwt) continue;
+                if (DUST) sum[k] += fast_exp2((spoke_c[k] + uL + win_v[k]) * LOG2E);
                 win_v[k] = t < Lc ? column_update<true>(win_v[k], sum[k], ColumnTarget(TARGETS ? win_lb[k] : 0.f)) : 0.f;
+                if (DUST && t >= b0 * BM && t < min(bv * BM, L)) to_row += fast_exp2((spoke_c[k] + win_v[k] + uL) * LOG2E);
                 if (to >= 0 && t >= b0 * BM && t < min(own_end, L)) slots[(long)(to + 1) * p.Lp + t] = win_v[k];
                 stage_v(i, t, win_v[k], win_lb[k]);
             }
+            if (DUST) sum_row();
             __syncthreads();
             if (gave_up) {
                 if (tid == 0) __hip_atomic_store(&p.chain->failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -82,32 +82,45 @@ __device__ __forceinline__ void final_columns(const StepArgs &p)
 }
 __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p) { final_columns(p); }
 
-// One half-step of problem n by one workgroup, a wavefront per row and a lane per partner; nothing is assumed of the potentials.
+// One half-step of a problem by one workgroup, a wavefront per row and a lane per partner; nothing is assumed of the potentials.
+// own, oth: valid rows and partners; mark: -inf where a token is inactive; olog: log targets; dustbin: edges to and from index L,
+// scores of the owners' spokes and of the others' (null: sdb).
+struct PlainSide { const float *mark, *olog, *spoke; int valid; };
 template <typename T, int D>
-__device__ __forceinline__ void plain_half_step(const T *X, const T *Y, const float *y, float *x, int L, int W, int own, int oth, float c2)
+__device__ __forceinline__ void plain_half_step(const StepArgs &p, const T *X, const T *Y, const PlainSide own, const PlainSide oth, const float *y, float *x)
 {
-    const int lane = threadIdx.x & 63;
-    for (int o = threadIdx.x >> 6; o < L; o += NWAVES) {
+    const int lane = threadIdx.x & 63, L = p.L;
+    for (int o = threadIdx.x >> 6; o < L + (p.dustbin ? 1 : 0); o += NWAVES) {
         float m = -INFINITY, sum = 0.f;
-        for (int t = max(o - W, 0) + lane; t <= min(o + W, oth - 1) && o < own; t += 64) {
-            float dot = 0.f;
-            for (int k = 0; k < D; k += 4) {
-                float a[4], b[4];
-                load4<T>(X + (long)o * D + k, a);
-                load4<T>(Y + (long)t * D + k, b);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) dot = fmaf(a[i], b[i], dot);
-            }
-            const float e = fmaf(dot, c2, y[t] * LOG2E), mn = fmaxf(m, e);
-            sum = sum * fast_exp2(m - mn) + fast_exp2(e - mn);
+        auto add = [&](float e, float times) {
+            const float mn = fmaxf(m, e);
+            if (mn > -INFINITY) sum = sum * fast_exp2(m - mn) + times * fast_exp2(e - mn);
             m = mn;
+        };
+        if (o == L) {
+            for (int t = lane; t <= L; t += 64) add(((oth.spoke ? oth.spoke[t] : p.sdb) + y[t]) * LOG2E, 1.f);
+        } else if (o < own.valid) {
+            for (int t = max(o - p.W, 0) + lane; t <= min(o + p.W, oth.valid - 1); t += 64) {
+                float dot = 0.f;
+                for (int k = 0; k < D; k += 4) {
+                    float a[4], b[4];
+                    load4<T>(X + (long)o * D + k, a);
+                    load4<T>(Y + (long)t * D + k, b);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) dot = fmaf(a[i], b[i], dot);
+                }
+                add(fmaf(dot, p.c2, y[t] * LOG2E), 1.f);
+            }
+            if (p.dustbin && lane == 0) add(((own.spoke ? own.spoke[o] : p.sdb) + y[L]) * LOG2E, 1.f);
         }
         for (int s = 32; s >= 1; s >>= 1) {
-            const float mo = __shfl_xor(m, s), so = __shfl_xor(sum, s), mn = fmaxf(m, mo);
-            sum = mn > -INFINITY ? sum * fast_exp2(m - mn) + so * fast_exp2(mo - mn) : 0.f;
-            m = mn;
+            const float mo = __shfl_xor(m, s), so = __shfl_xor(sum, s);
+            add(mo, so);
         }
-        if (lane == 0) x[o] = o < own ? -LN2 * (m + fast_log2(sum)) : 0.f;
+        if (lane == 0) {
+            const bool active = o == L || (o < own.valid && own.mark[o] != -INFINITY && m > -INFINITY);
+            x[o] = active ? (own.olog ? own.olog[o] : 0.f) - LN2 * (m + fast_log2(sum)) : o < own.valid ? -INFINITY : 0.f;
+        }
     }
     __syncthreads();
 }
@@ -126,12 +139,15 @@ template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish
     float *slots = p.slots + n * p.us;
     auto slot = [&](int k) { return slots + (long)k * p.Lp; };
     const StepLens ln = step_lens(p, n);
-    for (int i = threadIdx.x; i < p.L; i += NTHREADS) slot(0)[i] = slot(1)[i] = 0.f;
+    const PlainSide rows{slot(0), p.log_a ? p.log_a + (long)n * p.lstride : nullptr, p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr, ln.Le};
+    const PlainSide cols{slot(1), p.log_b ? p.log_b + (long)n * p.lstride : nullptr, p.spoke_c ? p.spoke_c + (long)n * p.sstride : nullptr, ln.Lc};
+    for (int i = threadIdx.x; i < p.Lp; i += NTHREADS)   // v = 0; inactive tokens keep their mark
+        for (int k = 0; k < 2; ++k) slot(k)[i] = slot(k)[i] == -INFINITY ? -INFINITY : 0.f;
     __syncthreads();
     for (int st = 0; st < a.T + a.R; ++st) {
         const int to = st < a.T ? 0 : 2 * (st - a.T + 1), from = st < a.T ? 1 : to - 1;
-        plain_half_step<T, D>(X, Y, slot(from), slot(to), p.L, p.W, ln.Le, ln.Lt, p.c2);
-        plain_half_step<T, D>(Y, X, slot(to), slot(to + 1), p.L, p.W, ln.Lc, ln.Le, p.c2);
+        plain_half_step<T, D>(p, X, Y, rows, PlainSide{nullptr, nullptr, cols.spoke, ln.Lt}, slot(from), slot(to));
+        plain_half_step<T, D>(p, Y, X, cols, PlainSide{nullptr, nullptr, rows.spoke, ln.Le}, slot(to), slot(to + 1));
     }
 }
 

@@ -16,7 +16,7 @@ template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int lau
             return SKA_EHIP;
         raised[dev] = true;
     }
-    if (p.nsteps > 1) {   // a chain's workgroups wait for each other: they must fit the device together
+    if constexpr (KIND == STEP_CHAIN) {   // a chain's workgroups wait for each other: they must fit the device together
         static int caps[MAX_DEVICES], caps_lds[MAX_DEVICES];   // what it holds, at which LDS size (0: not asked yet; g_mutex held)
         if (caps_lds[dev] != lds) {
             int per_cu = 0, cus = 0;
@@ -28,6 +28,9 @@ template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int lau
             caps_lds[dev] = lds;
         }
         if ((p.nb_total + 7) / 8 * 8 > caps[dev]) return SKA_EUNSUPPORTED;   // (nothing has been launched)
+        // with a dustbin every step waits for the slowest block: forward of 4 problems of L = 6000, W = 64 (376 blocks) 164 us by launches,
+        // 133 as a chain; 8 of 4000, W = 128 (504) 201 / 173; 8 of 5000 (632) 200 / 208
+        if (p.dustbin && p.nb_total > 512) return SKA_EUNSUPPORTED;
     }
     hipLaunchKernelGGL((vstep_kernel<T, D, NF, G, NTW, KIND, FORM>), dim3((p.nb_total + 7) / 8 * 8), dim3(64 * NF * G), lds, st, p);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
@@ -39,14 +42,20 @@ template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape
     if constexpr (COND) \
         if (sh.NF == NF_ && sh.G == G_ && sh.NTW == NTW_ && sh.kind == KIND_) { \
             constexpr bool ANY = KIND_ == STEP_BLOCK; \
+            if constexpr (ANY) { \
+                if (p.nsteps > 1) { \
+                    if (p.log_a || p.log_b) return launch_vstep_n<T, D, NF_, G_, NTW_, STEP_CHAIN, STEP_TARGETS>(p, N, st, dev); \
+                    if (p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, STEP_CHAIN, STEP_DUSTBIN>(p, N, st, dev); \
+                    if constexpr (sizeof(T) == 4) { /* (more registers: fewer workgroups fit) */ \
+                        const int rc = launch_vstep_n<T, D, NF_, G_, NTW_, STEP_CHAIN, STEP_KEEP>(p, N, st, dev); \
+                        if (rc != SKA_EUNSUPPORTED) return rc; \
+                    } \
+                    return launch_vstep_n<T, D, NF_, G_, NTW_, STEP_CHAIN, STEP_PLAIN>(p, N, st, dev); \
+                } \
+            } \
             if (p.log_a || p.log_b) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_TARGETS>(p, N, st, dev); \
             if constexpr (!ANY) \
                 if (p.cut) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_CUT>(p, N, st, dev); \
-            if constexpr (ANY && sizeof(T) == 4) \
-                if (p.nsteps > 1) { /* (more registers: fewer workgroups fit) */ \
-                    const int rc = launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, STEP_KEEP>(p, N, st, dev); \
-                    if (rc != SKA_EUNSUPPORTED) return rc; \
-                } \
             if (!ANY && p.dustbin) return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_DUSTBIN>(p, N, st, dev); \
             return launch_vstep_n<T, D, NF_, G_, NTW_, KIND_, ANY ? STEP_ANY : STEP_PLAIN>(p, N, st, dev); \
         }

@@ -14,13 +14,14 @@ template <typename T, int D> struct StepTile {
 // products are done, into the slots that it leaves.  (8 KB tiles: a forward of eight problems of L = 16384, d = 128,
 // W = 256 1300 us block by block, 867 so, 1115 by half-steps.  Streams of tiles of each wavefront's own, which need no
 // window, expose a tile's latency in every product: 1017, and 3358 -> 5301 at L = 262144, d = 64, W = 1024.)
-enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT };
+// STEP_CHAIN: single blocks, several steps in one launch (not a choice of step_shape: the launch says so).
+enum StepKind { STEP_BLOCK, STEP_MARCH, STEP_TIGHT, STEP_CHAIN };
 // What a call's steps add to the plain ones: nothing, a dustbin, a dustbin if the arguments say so, targets of rows or columns
 // (which go with no dustbin; a cut or none), segments cut from valid rows.
-// STEP_KEEP: STEP_ANY in a chain of steps, fp32 storage.
+// STEP_KEEP: plain ones of a chain in fp32 storage.
 enum StepForm { STEP_PLAIN, STEP_DUSTBIN, STEP_ANY, STEP_TARGETS, STEP_CUT, STEP_KEEP };
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> struct StepLds {   // offsets in bytes
-    static constexpr bool MARCH = KIND != STEP_BLOCK;
+    static constexpr bool MARCH = KIND == STEP_MARCH || KIND == STEP_TIGHT;
     static_assert(KIND != STEP_TIGHT || G > 1, "the exchange of row sums says that the products are done");
     // With G > 1 that exchange lies between a wavefront's reads and its next block's writes; without it there are two buffers.
     static constexpr int TWO = MARCH && G == 1 ? 2 : 1;
