@@ -341,8 +341,7 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
     const int b0 = min(seg * M, nblk), b1 = seg + 1 == nseg ? nblk : min(b0 + M, nblk), bv = min(b1, (Le + BM - 1) / BM);
 
     unsigned char *vs = smem + lds.vs;
-    // column sums of a fragment, by column of the block's window: zeros where its band does not reach
-    const int cps = lds.cps;
+    const int cps = lds.cps, cp_own = f * (LD::PADDED ? cps + 32 : cps);   // column sums of a fragment (StepLds::PADDED); this one's first tile
     float *us = reinterpret_cast<float *>(smem + LD::US);
     float *rs = reinterpret_cast<float *>(smem + LD::RSUM), *cp0 = reinterpret_cast<float *>(smem + lds.cp);
     float *wsw = reinterpret_cast<float *>(smem + LD::WS) + 32 * wave;
@@ -494,7 +493,8 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
     OwnerFrag<T, D> xf;
     dma(kseg, nwt, 0);
     xf.load(reinterpret_cast<const T *>(Xb), min((b0 * NF + f) * 32 + (lane & 31), Le - 1), Le, lane >> 5);
-    for (int i = tid; i < LD::TWO * NF * cps; i += NTHR) cp0[i] = 0.f;   // (while the loads are on their way)
+    if constexpr (LD::PADDED)
+        for (int i = tid; i < LD::TWO * NF * cps; i += NTHR) cp0[i] = 0.f;   // (while the loads are on their way)
 #pragma unroll
     for (int k = 0; k < NWIN; ++k) {
         const int i = tid + k * NTHR, t = 32 * kseg + i;
@@ -704,16 +704,19 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
                 if (NTW > 1) rd(1, ks);
             }
             constexpr int RPS = 16 / (KS + 1) + 1;   // entries per product: KS + 1 products and sixteen entries
+            constexpr int SURE = G > 1 ? NTW - 1 : NTW;   // (with one group the last tile is there, or masked where the band is less)
 #pragma unroll
-            for (int s = 0; s + 1 < NTW; ++s) {
+            for (int s = 0; s < SURE; ++s) {
 #pragma unroll
                 for (int ks = 0; ks <= KS; ++ks) {
-                    if (ks == 0) E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
-                    else E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks - 1], y[ks - 1], E[s + 1], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (s + 2 < NTW) {
-                        if (ks == 0) rdv(s + 2);
-                        else rd(s + 2, ks - 1);
+                    if (s + 1 < NTW) {
+                        if (ks == 0) E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xv, yv, zero, 0, 0, 0);
+                        else E[s + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks - 1], y[ks - 1], E[s + 1], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (s + 2 < NTW) {
+                            if (ks == 0) rdv(s + 2);
+                            else rd(s + 2, ks - 1);
+                        }
                     }
 #pragma unroll
                     for (int r = ks * RPS; r < 16 && r < (ks + 1) * RPS; ++r) {
@@ -726,17 +729,19 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
                 if (!interior(s)) mask(E[s], 32 * (kw + s), present(s));
                 if (s == (NTW > 4 ? 3 : NTW - 2)) late();
             }
-            if (NTW > 1) {
+            if constexpr (SURE < NTW) {
+                if constexpr (NTW > 1) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) add_rows(E[NTW - 2], NTW - 2, r);
-            }
-            if (NTW - 1 < cnt) {   // (uniform)
+                    for (int r = 0; r < 16; ++r) add_rows(E[NTW - 2], NTW - 2, r);
+                }
+                if (NTW - 1 < cnt) {   // (uniform)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) E[NTW - 1][r] = fast_exp2(E[NTW - 1][r]);
-                if (!interior(NTW - 1)) mask(E[NTW - 1], 32 * (kw + NTW - 1), present(NTW - 1));
-            } else {
+                    for (int r = 0; r < 16; ++r) E[NTW - 1][r] = fast_exp2(E[NTW - 1][r]);
+                    if (!interior(NTW - 1)) mask(E[NTW - 1], 32 * (kw + NTW - 1), present(NTW - 1));
+                } else {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) E[NTW - 1][r] = 0.f;
+                    for (int r = 0; r < 16; ++r) E[NTW - 1][r] = 0.f;
+                }
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) add_rows(E[NTW - 1], NTW - 1, r);
@@ -786,17 +791,35 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
         float t[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) t[r] = rows16_sum(rsum[r], rsum[r + 8]);
-        // two registers into one each time: one in the first half of a row of lanes and one in the second, then by quarters
-        merge_add<0x128, 0xc>(t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7]);   // row_ror:8
-        merge_add<0x141, 0xa>(t[0], t[1], t[2], t[3]);                           // row_half_mirror
+        if constexpr (MARCH) {
+            // two registers into one each time: one in the first half of a row of lanes and one in the second, then by quarters.  (Fewer
+            // instructions, but each waits for the one before: with one block per workgroup, which has others beside it, the plain way is
+            // 1 % faster.)
+            merge_add<0x128, 0xc>(t[0], t[1], t[2], t[3], t[4], t[5], t[6], t[7]);   // row_ror:8
+            merge_add<0x141, 0xa>(t[0], t[1], t[2], t[3]);                           // row_half_mirror
 #pragma unroll
-        for (int r = 0; r < 2; ++r) t[r] = dpp_add<0xb1>(dpp_add<0x4e>(t[r]));   // quad_perm:[2,3,0,1], [1,0,3,2]
-        // register r of quarter q of a row of lanes is the r + 2 (q & 1) + 4 (q >> 1)-th of eight, the second row's 8 further; the
-        // i-th of sixteen is row 8 (i >> 2) + (i & 3) (+ 4 in the second half)
-        if ((lane & 3) == 0) {
-            const int q = lane >> 2;
-            d += (f * G + g) * 32 + 16 * ((q >> 2) & 1) + 8 * ((q >> 1) & 1) + 4 * (lane >> 5) + 2 * (q & 1);
-            *reinterpret_cast<float2 *>(d) = make_float2(t[0], t[1]);
+            for (int r = 0; r < 2; ++r) t[r] = dpp_add<0xb1>(dpp_add<0x4e>(t[r]));   // quad_perm:[2,3,0,1], [1,0,3,2]
+            // register r of quarter q of a row of lanes is the r + 2 (q & 1) + 4 (q >> 1)-th of eight, the second row's 8 further; the
+            // i-th of sixteen is row 8 (i >> 2) + (i & 3) (+ 4 in the second half)
+            if ((lane & 3) == 0) {
+                const int q = lane >> 2;
+                d += (f * G + g) * 32 + 16 * ((q >> 2) & 1) + 8 * ((q >> 1) & 1) + 4 * (lane >> 5) + 2 * (q & 1);
+                *reinterpret_cast<float2 *>(d) = make_float2(t[0], t[1]);
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t[r] = dpp_add<0x128>(t[r]);   // row_ror:8, 4, 2, 1
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t[r] = dpp_add<0x124>(t[r]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t[r] = dpp_add<0x122>(t[r]);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) t[r] = dpp_add<0x121>(t[r]);
+            if ((lane & 15) == 0) {   // register r of the second row of lanes is r + 8: rows 16 further
+                d += (f * G + g) * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane >> 5);
+                *reinterpret_cast<float4 *>(d) = make_float4(t[0], t[1], t[2], t[3]);
+                *reinterpret_cast<float4 *>(d + 8) = make_float4(t[4], t[5], t[6], t[7]);
+            }
         }
     };
     // From the row sums of block b: u' of this lane's row, and the weights of the fragment's rows as the column sums take them.
@@ -902,10 +925,18 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
     // column sums of the block's fragments at column i of its window
     auto over_fragments = [&](const float *cp, int i, float s) {
         float x[NF];
+        if constexpr (LD::PADDED) {
 #pragma unroll
-        for (int q = 0; q < NF; ++q) x[q] = cp[q * cps + i];
+            for (int q = 0; q < NF; ++q) x[q] = cp[q * cps + i];
 #pragma unroll
-        for (int q = 0; q < NF; ++q) s += x[q];
+            for (int q = 0; q < NF; ++q) s += x[q];
+        } else {
+            const int wt = i >> 5;
+#pragma unroll
+            for (int q = 0; q < NF; ++q) x[q] = cp[q * cps + min(max(wt - q, 0), NT - 1) * 32 + (i & 31)];
+#pragma unroll
+            for (int q = 0; q < NF; ++q) s += (unsigned)(wt - q) < (unsigned)NT ? x[q] : 0.f;
+        }
         return s;
     };
     constexpr int NPOS = (32 * ((TIGHT ? 1 : 2) * NF + G * NTW) + NTHR - 1) / NTHR;   // ring positions of a thread, always the same ones
@@ -952,13 +983,13 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
             if (more) request_tiles(b);   // (every wavefront is done with this block's)
         const Weights wt = weights(b, row, rs);
         float *cp = cp0 + par * NF * cps;
-        add_columns(cp + f * cps + (f + j0) * 32, wt);
+        add_columns(cp + cp_own + j0 * 32, wt);
         if constexpr (!STORE_E) {
             float before = 0.f;
             evaluate(b, par, row.u, rsum, []() {}, false, true, [&](int s, const f32x16 &e) {
                 const float x = column_of(e, wt);
-                if (s & 1) store_columns(cp + f * cps + (f + j0) * 32, s - 1, before, x);
-                else if (s == NTW - 1) store_columns(cp + f * cps + (f + j0) * 32, s, x, x);
+                if (s & 1) store_columns(cp + cp_own + j0 * 32, s - 1, before, x);
+                else if (s == NTW - 1) store_columns(cp + cp_own + j0 * 32, s, x, x);
                 before = x;
             });
         }

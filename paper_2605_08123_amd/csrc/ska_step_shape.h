@@ -31,12 +31,15 @@ template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> struct 
     static constexpr int UE = US + TWO * NF * 128;              // fp32 storage: the same as the evaluation takes them
     static constexpr int CP = UE + (sizeof(T) == 4 ? TWO * NF * 128 : 0);
     static constexpr int VB = sizeof(T) == 2 || FORM == STEP_TARGETS ? 8 : 4;   // bytes of a column's potential (and weight)
+    // Column sums of a fragment by column of the block's window, with zeros where its band does not reach; of a single launched block by
+    // tile of the band, which is less (d = 128, W = 32: three workgroups fit a CU instead of two).
+    static constexpr bool PADDED = KIND != STEP_BLOCK;
     int cp, cps, y, rs, vs, total;   // cp: [TWO][NF][cps] column sums of a fragment; y: ring of the other side's tiles
     __host__ __device__ StepLds(int hw)
     {
         rs = NF + 2 * hw + (KIND == STEP_MARCH ? NF : 0);   // ring slots: the window of a block (and the tiles the next one adds)
         cp = CP;
-        cps = 32 * (NF - 1 + (2 * hw + 1 > G * NTW ? 2 * hw + 1 : G * NTW));   // (the window, and tiles that the last fragment's wavefronts are short of)
+        cps = 32 * (G * NTW + (PADDED ? NF - 1 : 0));   // (the window, and tiles that the last fragment's wavefronts are short of)
         y = cp + TWO * NF * cps * 4;
         vs = y + rs * StepTile<T, D>::BYTES;   // [32 rs] potentials of the columns, base 2 (bf16 storage: an operand row each)
         total = vs + rs * 32 * VB;
