@@ -384,7 +384,8 @@ int sinkhorn_attn_set_streams(int n);
  * half-steps may be in flight on a device at a time (two such launches can hold each other's
  * workgroups out).  Every wait inside the launch is bounded by spin_limit polls (0: the default,
  * 2^18, about a tenth of a second): a wait that runs out stops waiting and writes NaN into its block of the
- * potentials, which reaches every output depending on it, and the launch ends normally.
+ * potentials, which reaches every output depending on it, and the launch ends normally.  The same bound holds for
+ * the waits of short calls' whole steps in one launch, whatever the mode; what such a launch gives up is solved again by the launch after it.
  * Process-wide.  Returns SKA_OK, or SKA_EINVAL for another mode.
  */
 int sinkhorn_attn_set_fused_half_steps(int mode, unsigned spin_limit);

@@ -30,6 +30,7 @@
 #include <stdint.h>
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 #include <new>
 #include <type_traits>
@@ -112,11 +113,9 @@ int spoke_scores(const Problem &p, const void *Qin, const void *K, float *SQ, fl
 {
     constexpr int LPR = D * (int)sizeof(T) / 16;
     const float cs = 1.f / (p.eps * sqrtf((float)p.d));
-    const dim3 grid((unsigned)(((long)(p.L + 1) * LPR + 255) / 256), p.N());
-    hipLaunchKernelGGL((spoke_scores_kernel<T, D>), grid, dim3(256), 0, st, reinterpret_cast<const T *>(Qin), p.k_db,
-                       p.q_db, SQ, p.ldw(), p.L, cs);
-    hipLaunchKernelGGL((spoke_scores_kernel<T, D>), grid, dim3(256), 0, st, reinterpret_cast<const T *>(K), p.q_db,
-                       p.k_db, SK, p.ldw(), p.L, cs);
+    const dim3 grid((unsigned)(((long)(p.L + 1) * LPR + 255) / 256), p.N(), 2);
+    hipLaunchKernelGGL((spoke_scores_kernel<T, D>), grid, dim3(256), 0, st, reinterpret_cast<const T *>(Qin), reinterpret_cast<const T *>(K),
+                       p.k_db, p.q_db, SQ, SK, p.ldw(), p.L, cs);
     return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
 }
 
@@ -643,14 +642,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // g_u = <dO_i, O_i> (Sec. 2.2), taken from its fp32 accumulators, in the backward's first
     // workspace vector, so that the backward needs no pass over O and dO for it.
     // Q below is the score operand: for bf16 storage the prescaled copy, with c2 = 1
-    const void *Q = nullptr;
-    float c2 = 0.f;
-    {
-        PhaseTimer pt(SKA_PH_PRESCALE, cx);
-        void *ws_q = fused ? reinterpret_cast<unsigned char *>(ws) + ws_vec_bytes(p) : ws;
-        SKA_TRY((make_scores_operand<T>(p, p.n_stages ? p.eps_stage[0] : p.eps, Qin, ws_q, &Q, &c2, st)));
-        pt.launched(sizeof(T) == 2 ? 1 : 0);
-    }
+    constexpr bool PRESCALED = sizeof(T) == 2;
+    void *ws_q = fused ? reinterpret_cast<unsigned char *>(ws) + ws_vec_bytes(p) : ws;
+    const float c_start = LOG2E * (1.f / ((p.n_stages ? p.eps_stage[0] : p.eps) * sqrtf((float)p.d)));
+    const void *Q = PRESCALED ? ws_q : Qin;
+    const float c2 = PRESCALED ? 1.f : c_start;
     const int N = p.N(), L = p.L, Lp = p.Lp();
     const int R = p.R;
     const long us = p.uv_us ? p.uv_us : 2L * (R + 1) * Lp;
@@ -671,12 +667,16 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     const ChainSpace room = shape.NF && ws ? chain_space(p, shape, fused) : ChainSpace{0, 0, 0, 0};
     const int after_first = p.T + R - 1;
     bool chained = room.off && shape.kind == STEP_BLOCK && shape.M == 1 && after_first >= 2 && !p.n_stages && !p.resume_t && !cx.side && !cx.noalloc && !capturing && chain_may_start(cx.dev, st);
-    // u0 = v0 = 0: the base solve starts from v = 0
-    if (!p.resume_t) {
-        const long n16 = chained ? (long)room.clear / 16 : 0, tot = 2L * Lp * N > n16 ? 2L * Lp * N : n16;
-        hipLaunchKernelGGL(clear_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, UV, 2L * Lp, us, N,
+    // the score operand, and u0 = v0 = 0: the base solve starts from v = 0
+    if (PRESCALED || !p.resume_t) {
+        PhaseTimer pt(SKA_PH_PRESCALE, cx);
+        const long n8 = PRESCALED ? (long)N * L * p.d / 8 : 0, per = p.resume_t ? 0 : 2L * Lp, n16 = chained ? (long)room.clear / 16 : 0;
+        const long tot = std::max(n8, std::max(per * N, n16));
+        hipLaunchKernelGGL(start_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, reinterpret_cast<const __bf16 *>(Qin),
+                           reinterpret_cast<__bf16 *>(ws_q), n8, c_start, UV, per, us, N,
                            chained ? reinterpret_cast<uint4 *>(reinterpret_cast<unsigned char *>(ws) + room.off) : nullptr, n16);
         if (hipGetLastError() != hipSuccess) return SKA_EHIP;
+        pt.launched(PRESCALED ? 1 : 0);
     }
     if (p.mask_q || p.mask_k) {   // inactive tokens start, and stay, at -inf
         hipLaunchKernelGGL(mask_fill_kernel, dim3((L + 255) / 256, N), dim3(256), 0, st, UV, us, Lp, L, p.mask_q,
@@ -1016,7 +1016,7 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     if (p.token()) {
         SQ = Vec{tok, ldw};
         SK = Vec{tok + nldp, ldw};
-        SKA_TRY((spoke_scores<T, D>(p, Qin, K, tok, tok + nldp, st)));
+        if (!fused) SKA_TRY((spoke_scores<T, D>(p, Qin, K, tok, tok + nldp, st)));   // (fused: the forward has left them there)
     }
 
     // g_u = <dO_i, O_i> (= (P22 . Z) 1); dustbin row has dO = 0
@@ -1042,9 +1042,9 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         if (p.token()) {
             // dv_db = sum_i P_RR(i, d_k) dO_i and vbar_R at the dustbin column = <v_db, dv_db>
             hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(WS_THREADS), 0, st, reinterpret_cast<const T *>(G),
-                               Vec{nullptr, 0}, SQ, uv(2 * R), uv(2 * R + 1), partial, L);
+                               Vec{nullptr, 0}, SQ, uv(2 * R), uv(2 * R + 1), partial, L, nullptr, Vec{nullptr, 0}, nullptr);
             hipLaunchKernelGGL((wsum_final_kernel<D>), dim3(N), dim3(D), 0, st, partial, nchunk, Vec{nullptr, 0}, 0,
-                               nullptr, 1.f, p.dv_db, p.v_db, wo(vbar(R)), L);
+                               nullptr, 1.f, p.dv_db, p.v_db, wo(vbar(R)), L, nullptr, Vec{nullptr, 0}, nullptr, nullptr);
             if (hipGetLastError() != hipSuccess) return SKA_EHIP;
         } else if (p.dustbin) {   // vbar_R at the dustbin column is 0 because V there is 0
             hipLaunchKernelGGL(fill_kernel, dim3((N + 255) / 256), dim3(256), 0, st, vbar(R) + L, 1L, ldw, N, 0.f);
@@ -1147,20 +1147,24 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         hipLaunchKernelGGL((spoke_sbar_kernel<T, D>), dim3((unsigned)(((long)Lp * LPR2 + 255) / 256), N), dim3(256), 0,
                            st, reinterpret_cast<const T *>(G), p.v_db, uv(2 * R), uv(2 * R + 1), SQ, SK, rowp, colp, nq,
                            ldw, sbr, sbc, ldw, L);
-        const dim3 agrid((unsigned)(((long)L * (D / 4) + 255) / 256), N);
+        const dim3 agrid((unsigned)(((long)L * (D / 4) + 255) / 256), N, 2);
         hipLaunchKernelGGL((spoke_axpy_kernel<T, D>), agrid, dim3(256), 0, st, reinterpret_cast<T *>(dQ), wv(sbr),
-                           p.k_db, cs, L);
-        hipLaunchKernelGGL((spoke_axpy_kernel<T, D>), agrid, dim3(256), 0, st, reinterpret_cast<T *>(dK), wv(sbc),
-                           p.q_db, cs, L);
+                           p.k_db, reinterpret_cast<T *>(dK), wv(sbc), p.q_db, cs, L);
         // dk_db = c (sum_i sbr_i q_i + sbr_L q_db), dq_db = c (sum_j sbc_j k_j + sbc_L k_db)
-        hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(WS_THREADS), 0, st, reinterpret_cast<const T *>(Qin),
-                           wv(sbr), Vec{nullptr, 0}, Vec{nullptr, 0}, Vec{nullptr, 0}, partial, L);
-        hipLaunchKernelGGL((wsum_final_kernel<D>), dim3(N), dim3(D), 0, st, partial, nchunk, wv(sbr), L, p.q_db, cs,
-                           p.dk_db, nullptr, VecOut{nullptr, 0}, 0);
-        hipLaunchKernelGGL((wsum_kernel<T, D>), dim3(nchunk, N), dim3(WS_THREADS), 0, st, reinterpret_cast<const T *>(K),
-                           wv(sbc), Vec{nullptr, 0}, Vec{nullptr, 0}, Vec{nullptr, 0}, partial, L);
-        hipLaunchKernelGGL((wsum_final_kernel<D>), dim3(N), dim3(D), 0, st, partial, nchunk, wv(sbc), L, p.k_db, cs,
-                           p.dq_db, nullptr, VecOut{nullptr, 0}, 0);
+        // Both at once where the second's partial sums fit the spokes' scores, which nothing reads any more (all but the shortest calls).
+        const bool both = 2 * ldw >= (long)nchunk * D;
+        float *partial2 = both ? tok : partial;
+        const dim3 sums(nchunk, N, both ? 2 : 1), ends(N, both ? 2 : 1);
+        const T *Qs = reinterpret_cast<const T *>(Qin), *Ks = reinterpret_cast<const T *>(K);
+        const Vec none{nullptr, 0};
+        hipLaunchKernelGGL((wsum_kernel<T, D>), sums, dim3(WS_THREADS), 0, st, Qs, wv(sbr), none, none, none, partial, L, Ks, wv(sbc), partial2);
+        hipLaunchKernelGGL((wsum_final_kernel<D>), ends, dim3(D), 0, st, partial, nchunk, wv(sbr), L, p.q_db, cs, p.dk_db, nullptr,
+                           VecOut{nullptr, 0}, 0, partial2, wv(sbc), p.k_db, p.dq_db);
+        if (!both) {
+            hipLaunchKernelGGL((wsum_kernel<T, D>), sums, dim3(WS_THREADS), 0, st, Ks, wv(sbc), none, none, none, partial, L, Ks, none, partial);
+            hipLaunchKernelGGL((wsum_final_kernel<D>), ends, dim3(D), 0, st, partial, nchunk, wv(sbc), L, p.k_db, cs, p.dq_db, nullptr,
+                               VecOut{nullptr, 0}, 0, partial, none, nullptr, nullptr);
+        }
         if (hipGetLastError() != hipSuccess) return SKA_EHIP;
     }
     return SKA_OK;

@@ -12,10 +12,24 @@ __global__ void fill_kernel(float *p, long per, long stride, int nprob, float va
     if (i < per * nprob) p[(i / per) * stride + (i % per)] = val;
 }
 
-// The start of a forward: zeros in `per` floats of every problem's potentials, and in a region of its own (n16 times 16 bytes).
-__global__ void clear_kernel(float *p, long per, long stride, int nprob, uint4 *q, long n16)
+// dst = bf16(scale * src), elements 8 i ... 8 i + 7.
+__device__ __forceinline__ void prescale8(const __bf16 *src, __bf16 *dst, long i, float scale)
+{
+    uint4 raw = reinterpret_cast<const uint4 *>(src)[i];
+    bf16x8 v = *reinterpret_cast<bf16x8 *>(&raw);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (__bf16)((float)v[e] * scale);
+    reinterpret_cast<uint4 *>(dst)[i] = *reinterpret_cast<uint4 *>(&v);
+}
+
+// The start of a forward: the prescaled operand (n8 times 8 elements; none in fp32 storage), zeros in `per` floats of every problem's
+// potentials, and in a region of its own (n16 times 16 bytes).  One launch, because each is bounded by its launch where calls are short
+// (2.3 us between dependent launches that do nothing): a forward of eight problems of L = 700, W = 64 72.0 -> 70.0 us, forward and
+// backward of six of up to 2000 238 -> 235.5.
+__global__ void start_kernel(const __bf16 *src, __bf16 *dst, long n8, float scale, float *p, long per, long stride, int nprob, uint4 *q, long n16)
 {
     const long all = (long)gridDim.x * blockDim.x, first = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    for (long i = first; i < n8; i += all) prescale8(src, dst, i, scale);
     for (long i = first; i < per * nprob; i += all) p[(i / per) * stride + (i % per)] = 0.f;
     for (long i = first; i < n16; i += all) q[i] = make_uint4(0, 0, 0, 0);
 }
@@ -122,11 +136,14 @@ __global__ __launch_bounds__(256) void issue_probe_kernel(float *out, int tiles)
 
 // ---- learned dustbin token (Sec. "Single-Active-Dustbin Bridge"): the O(L d) work on the spokes
 // out[n][o] = scale <M[n][o], x[n]> for o < L, out[n][L] = scale <x[n], xc[n]> (the corner).
-// LPR lanes per row, 16 bytes each, like rowdot_kernel.
+// LPR lanes per row, 16 bytes each, like rowdot_kernel.  Both sides in one launch (blockIdx.z: M's rows against x, M2's against xc).
+// Like the other pairs of launches below: forward and backward of eight problems of L = 5000, W = 128 351 -> 338 us (with the scores
+// of the forward taken over by a backward in the same call, and start_kernel).
 template <typename T, int D>
-__global__ void spoke_scores_kernel(const T *M, const float *x, const float *xc, float *out, long ostride, int L,
+__global__ void spoke_scores_kernel(const T *M, const T *M2, const float *x, const float *xc, float *out, float *out2, long ostride, int L,
                                     float scale)
 {
+    if (blockIdx.z) { const float *t = x; x = xc; xc = t; M = M2; out = out2; }
     constexpr int LPR = D * (int)sizeof(T) / 16, EPL = 16 / (int)sizeof(T);
     const int n = blockIdx.y;
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -154,10 +171,13 @@ __global__ void spoke_scores_kernel(const T *M, const float *x, const float *xc,
 // A workgroup takes one chunk.  The rows are few and their loads independent, so latency is what bounds
 // it: 1024 threads and eight rows requested before the first is used (256 threads, row after row:
 // 21 us per sum at L = 5000; eight problems of that length 522 -> 463 us per forward and backward).
+// blockIdx.z = 1: a second sum of the same kind, of M2 by wv2 into partial2.
 constexpr int WS_ROWS = 1024, WS_THREADS = 1024;
 template <typename T, int D>
-__global__ __launch_bounds__(WS_THREADS) void wsum_kernel(const T *M, Vec wv, Vec spoke, Vec x, Vec y, float *partial, int L)
+__global__ __launch_bounds__(WS_THREADS) void wsum_kernel(const T *M, Vec wv, Vec spoke, Vec x, Vec y, float *partial, int L,
+                                                          const T *M2, Vec wv2, float *partial2)
 {
+    if (blockIdx.z) { M = M2; wv = wv2; partial = partial2; }
     constexpr int TPR = D / 4;            // threads per row, four columns each
     constexpr int RPI = WS_THREADS / TPR; // rows per iteration
     __shared__ float red[WS_THREADS / 64][TPR][4];
@@ -197,10 +217,13 @@ __global__ __launch_bounds__(WS_THREADS) void wsum_kernel(const T *M, Vec wv, Ve
 }
 // out[n][dv] = scale (sum_chunk partial[n][chunk][dv] + wc[n] xc[n][dv]); if dotv is given also
 // dot_out[n] = <dotv[n], out[n]>.  wc_at: index of the corner weight in wc (null: no corner).
+// blockIdx.y = 1: a second sum (partial2, wc2, xc2, out2).
 template <int D>
 __global__ void wsum_final_kernel(const float *partial, int nchunk, Vec wc, int wc_at, const float *xc, float scale,
-                                  float *out, const float *dotv, VecOut dot_out, int dot_at)
+                                  float *out, const float *dotv, VecOut dot_out, int dot_at,
+                                  const float *partial2, Vec wc2, const float *xc2, float *out2)
 {
+    if (blockIdx.y) { partial = partial2; wc = wc2; xc = xc2; out = out2; }
     const int n = blockIdx.x, dv = threadIdx.x;   // D threads
     float acc = 0.f;
 #pragma unroll 8
@@ -265,10 +288,11 @@ __global__ void spoke_sbar_kernel(const T *G, const float *vdb, Vec uR, Vec vR, 
     }
 }
 
-// M[n][o][:] += scale w[n][o] x[n][:] for o < L (the spoke part of dQ / dK), storage type T
+// M[n][o][:] += scale w[n][o] x[n][:] for o < L (the spoke part of dQ / dK), storage type T.  blockIdx.z = 1: the same for M2, w2, x2.
 template <typename T, int D>
-__global__ void spoke_axpy_kernel(T *M, Vec w, const float *x, float scale, int L)
+__global__ void spoke_axpy_kernel(T *M, Vec w, const float *x, T *M2, Vec w2, const float *x2, float scale, int L)
 {
+    if (blockIdx.z) { M = M2; w = w2; x = x2; }
     constexpr int TPR = D / 4;
     const int n = blockIdx.y;
     const long p = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -350,12 +374,7 @@ __global__ void seed_kernel(const float *seed, const float *olog, float *out, lo
 __global__ void prescale_kernel(const __bf16 *src, __bf16 *dst, long n8, float scale)
 {
     long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n8) return;
-    uint4 raw = reinterpret_cast<const uint4 *>(src)[i];
-    bf16x8 v = *reinterpret_cast<bf16x8 *>(&raw);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (__bf16)((float)v[e] * scale);
-    reinterpret_cast<uint4 *>(dst)[i] = *reinterpret_cast<uint4 *>(&v);
+    if (i < n8) prescale8(src, dst, i, scale);
 }
 
 // Modifier packs of Prop. 2 for a tail of depth R.  With a_t = exp(u_t - u_R), b_t = exp(v_t - v_R)
