@@ -24,8 +24,8 @@ __device__ __forceinline__ void prescale8(const __bf16 *src, __bf16 *dst, long i
 
 // The start of a forward: the prescaled operand (n8 times 8 elements; none in fp32 storage), zeros in `per` floats of every problem's
 // potentials, and in a region of its own (n16 times 16 bytes).  One launch, because each is bounded by its launch where calls are short
-// (2.3 us between dependent launches that do nothing): a forward of eight problems of L = 700, W = 64 72.0 -> 70.0 us, forward and
-// backward of six of up to 2000 238 -> 235.5.
+// (2.3 us between dependent launches that do nothing): a forward of eight problems of L = 701, W = 64 72.0 -> 70.0 us, forward and
+// backward of 16 of L = 3001, W = 100 238 -> 235.5.
 __global__ void start_kernel(const __bf16 *src, __bf16 *dst, long n8, float scale, float *p, long per, long stride, int nprob, uint4 *q, long n16)
 {
     const long all = (long)gridDim.x * blockDim.x, first = (long)blockIdx.x * blockDim.x + threadIdx.x;

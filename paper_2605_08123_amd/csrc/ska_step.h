@@ -301,8 +301,12 @@ __device__ __forceinline__ float rows16_sum(float a, float b)
 }
 
 // Wavefronts per SIMD that the registers must allow: three short blocks of four wavefronts fit a CU's LDS (a chain of 16 problems of
-// L = 3001, W = 100 needs them all).
-template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> constexpr int step_waves = KIND == STEP_CHAIN && FORM == STEP_DUSTBIN && NF * G == 4 && NTW <= 5 && StepTile<T, D>::BYTES <= 4096 && sizeof(T) == 2 ? 3 : 1;
+// L = 3001, W = 100 needs them all).  Narrow blocks at d = 32: five (32 problems of L = 17853, W = 17, us per step: 26.1 -> 25.7,
+// forward and backward 699 -> 685).
+template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> constexpr bool step_narrow = sizeof(T) == 2 && D == 32 && NF * G == 4 && NTW <= 3 && KIND == STEP_BLOCK && FORM == STEP_ANY;
+template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> constexpr int step_waves =
+    KIND == STEP_CHAIN && FORM == STEP_DUSTBIN && NF * G == 4 && NTW <= 5 && StepTile<T, D>::BYTES <= 4096 && sizeof(T) == 2 ? 3
+    : step_narrow<T, D, NF, G, NTW, KIND, FORM> ? 5 : 1;
 template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM>
 __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FORM>)) void vstep_kernel(const StepArgs p)
 {
@@ -673,21 +677,29 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
             // LDS addresses of tile s less s tiles: the instructions add those.  Where the ring ends (of a single block: where its
-            // window does) they go back by as much.
+            // window does) they go back by as much.  (Narrow blocks make each address where it is used, which takes fewer registers.)
+            constexpr bool ADVANCE = !step_narrow<T, D, NF, G, NTW, KIND, FORM>;
             typedef __attribute__((address_space(3))) const unsigned char *lds_ptr;
-            unsigned ya[KS], va;
+            typedef __attribute__((address_space(3))) const bf16x8 *lds_row;
+            typedef __attribute__((address_space(3))) const bf16x4 *lds_parts;
+            unsigned ya[KS], va = smem_at + lds.vs + (32 * slot + c) * 8;
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) ya[ks] = smem_at + lds.y + slot * ST::BYTES + c * ST::ROWB + (((2 * ks + h) ^ ST::swz(c)) << 4);
-            va = smem_at + lds.vs + (32 * slot + c) * 8;
-            auto rd = [&](int s, int ks) { y[ks] = *reinterpret_cast<__attribute__((address_space(3))) const bf16x8 *>((lds_ptr)(ya[ks] + 0u) + s * ST::BYTES); };
+            const unsigned char *ybase = smem + lds.y + c * ST::ROWB;
+            auto rd = [&](int s, int ks) {
+                if constexpr (ADVANCE) y[ks] = *(lds_row)((lds_ptr)(ya[ks] + 0u) + s * ST::BYTES);
+                else y[ks] = *reinterpret_cast<const bf16x8 *>(ybase + slot * ST::BYTES + (((2 * ks + h) ^ ST::swz(c)) << 4));
+            };
             auto rdv = [&](int s) {   // (the first read of tile s)
-                if (s > 0 && (MARCH ? slot + s == RS : slot + s >= RS)) {
+                if constexpr (!ADVANCE) {
+                    if (s > 0) slot = lds.slot(slot + 1);
+                } else if (s > 0 && (MARCH ? slot + s == RS : slot + s >= RS)) {
                     const int back = MARCH ? RS : 1;
 #pragma unroll
                     for (int ks = 0; ks < KS; ++ks) ya[ks] -= back * ST::BYTES;
                     va -= back * 256;
                 }
-                const bf16x4 v3 = *reinterpret_cast<__attribute__((address_space(3))) const bf16x4 *>((lds_ptr)(va + 0u) + s * 256);
+                const bf16x4 v3 = ADVANCE ? *(lds_parts)((lds_ptr)(va + 0u) + s * 256) : *reinterpret_cast<const bf16x4 *>(vs + (32 * slot + c) * 8);
                 // (a zero of the row's operand meets it; an absent tile's slot may hold anything, and its zero entries stay zero)
                 if constexpr (TARGETS) bt[s] = present(s) ? (float)v3[3] : 0.f;
                 const __bf16 one = (__bf16)1.f, no = (__bf16)0.f;
