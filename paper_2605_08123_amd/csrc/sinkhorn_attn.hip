@@ -1016,7 +1016,7 @@ int bwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     if (p.token()) {
         SQ = Vec{tok, ldw};
         SK = Vec{tok + nldp, ldw};
-        if (!fused) SKA_TRY((spoke_scores<T, D>(p, Qin, K, tok, tok + nldp, st)));   // (fused: the forward has left them there)
+        SKA_TRY((spoke_scores<T, D>(p, Qin, K, tok, tok + nldp, st)));
     }
 
     // g_u = <dO_i, O_i> (= (P22 . Z) 1); dustbin row has dO = 0

@@ -137,8 +137,8 @@ __global__ __launch_bounds__(256) void issue_probe_kernel(float *out, int tiles)
 // ---- learned dustbin token (Sec. "Single-Active-Dustbin Bridge"): the O(L d) work on the spokes
 // out[n][o] = scale <M[n][o], x[n]> for o < L, out[n][L] = scale <x[n], xc[n]> (the corner).
 // LPR lanes per row, 16 bytes each, like rowdot_kernel.  Both sides in one launch (blockIdx.z: M's rows against x, M2's against xc).
-// Like the other pairs of launches below: forward and backward of eight problems of L = 5000, W = 128 351 -> 338 us (with the scores
-// of the forward taken over by a backward in the same call, and start_kernel).
+// Like the other pairs of launches below: forward and backward of eight problems of L = 5000, W = 128 351 -> 338 us (with
+// start_kernel).
 template <typename T, int D>
 __global__ void spoke_scores_kernel(const T *M, const T *M2, const float *x, const float *xc, float *out, float *out2, long ostride, int L,
                                     float scale)
