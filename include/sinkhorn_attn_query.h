@@ -34,6 +34,19 @@ typedef struct {
 int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dustbin, int lengths, int dtype,
                         size_t workspace_bytes, int one_call, ska_step_plan *plan);
 
+/*
+ * Chains: short calls run the steps after the first one in one launch, whose workgroups hand their sums to each other.  They
+ * are numbered from 1 on, per device; the device writes `started` and `given_up` (ask after a synchronisation).
+ */
+typedef struct {
+    unsigned launched;  /* number of the latest chain (0: there was none)                                             */
+    unsigned started;   /* of the latest one whose workgroups have all started                                     */
+    unsigned given_up;  /* of the latest one in which a wait has run out (its steps were solved again), 0: none      */
+} ska_chains;
+
+/* Returns SKA_OK, or SKA_EINVAL without a place for the answer or for a device number out of range. */
+int ska_query_chains(int device, ska_chains *chains);
+
 #ifdef __cplusplus
 }
 #endif

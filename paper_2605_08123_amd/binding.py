@@ -90,6 +90,8 @@ def load():
                                                           ctypes.POINTER(ctypes.c_long)]
         lib.ska_query_step_plan.restype = i
         lib.ska_query_step_plan.argtypes = [i] * 10 + [sz, i, ctypes.POINTER(StepPlan)]
+        lib.ska_query_chains.restype = i
+        lib.ska_query_chains.argtypes = [i, ctypes.POINTER(Chains)]
         lib.sinkhorn_attn_strerror.restype = ctypes.c_char_p
         lib.sinkhorn_attn_strerror.argtypes = [i]
         _lib = lib
@@ -114,6 +116,20 @@ def query_step_plan(B, H, L, d, W, T, R=2, dustbin=False, dtype=SKA_BF16, worksp
     if rc != SKA_OK:
         raise SinkhornAttnError(rc)
     return plan
+
+
+class Chains(ctypes.Structure):
+    """Numbers of the latest chain of steps launched, wholly started, given up (ska_chains, include/sinkhorn_attn_query.h)."""
+    _fields_ = [(n, ctypes.c_uint) for n in ("launched", "started", "given_up")]
+
+
+def query_chains(device=0) -> Chains:
+    """How the chains of steps of a device went so far; host only, up to date after a synchronisation."""
+    chains = Chains()
+    rc = load().ska_query_chains(int(device), chains)
+    if rc != SKA_OK:
+        raise SinkhornAttnError(rc)
+    return chains
 
 
 class SinkhornAttnError(RuntimeError):

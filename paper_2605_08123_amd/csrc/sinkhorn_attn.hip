@@ -515,7 +515,7 @@ inline ChainSpace chain_space(const Problem &p, const StepShape &sh, bool one_ca
 // the last one's workgroups have all started (they need nothing more then).  Otherwise the steps are launched one by one, with the
 // same results.
 struct ChainGate {
-    unsigned *started = nullptr, *started_dev = nullptr;   // host memory
+    unsigned *word = nullptr, *word_dev = nullptr;   // host memory: numbers of the latest chain that has started as a whole, that has given up
     hipStream_t last = nullptr;
     unsigned seq = 0;
     bool tried = false;
@@ -527,31 +527,23 @@ bool chain_may_start(int dev, hipStream_t st)
     if (!g.tried) {
         g.tried = true;
         void *h = nullptr, *d = nullptr;
-        if (hipHostMalloc(&h, sizeof(unsigned), hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&d, h, 0) == hipSuccess) {
-            g.started = static_cast<unsigned *>(h);
-            g.started_dev = static_cast<unsigned *>(d);
-            *g.started = 0;
+        if (hipHostMalloc(&h, 2 * sizeof(unsigned), hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&d, h, 0) == hipSuccess) {
+            g.word = static_cast<unsigned *>(h);
+            g.word_dev = static_cast<unsigned *>(d);
+            g.word[0] = g.word[1] = 0;
         } else {
             (void)hipGetLastError();
         }
     }
-    if (!g.started) return false;
-    return __atomic_load_n(g.started, __ATOMIC_RELAXED) == g.seq || (st == g.last && st != hipStreamPerThread);
+    if (!g.word) return false;
+    return __atomic_load_n(g.word, __ATOMIC_RELAXED) == g.seq || (st == g.last && st != hipStreamPerThread);
 }
-// a step's or a chain's launch; a chain on a stream of its own is the gate's latest once it is on its way
-template <typename T, int D> int launch_vstep(StepArgs p, const StepShape &sh, int N, hipStream_t st, int dev)
+// a step's or a chain's launch
+template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape &sh, int N, hipStream_t st, int dev)
 {
-    ChainGate &gate = g_gate[dev];
-    p.started = gate.started_dev;
-    p.seq = gate.seq + 1;
     const auto launch = sizeof(T) == 2 ? (D == 32 ? ska_launch_steps_bf16_32 : D == 64 ? ska_launch_steps_bf16_64 : ska_launch_steps_bf16_128)
                                        : (D == 32 ? ska_launch_steps_f32_32 : D == 64 ? ska_launch_steps_f32_64 : ska_launch_steps_f32_128);
-    const int rc = launch(&p, &sh, N, st, dev);
-    if (rc == SKA_OK && p.nsteps > 1) {
-        gate.seq = p.seq;
-        gate.last = st;
-    }
-    return rc;
+    return launch(&p, &sh, N, st, dev);
 }
 inline int launch_vfinal(const StepArgs &p, int N, hipStream_t st)
 {
@@ -880,8 +872,12 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         f.words = reinterpret_cast<unsigned long long *>(at + 256);
         f.wstride = room.wstride; f.wbuf = N * room.wstride;
         f.limit = g_spin_limit;
+        ChainGate &gate = g_gate[cx.dev];
+        f.gate = gate.word_dev; f.seq = gate.seq + 1;
         f.rev = nlaunch++ & 1;
         SKA_TRY((step_sweep<T, D>(cx, f, &shape, N)));
+        gate.seq = f.seq;
+        gate.last = st;
         if (pt_run) pt_run->launched(2 * after_first);
         f.v = slot(2 * R - 1); f.v_out = slot(2 * R + 1); f.u_fin = slot(2 * R);
         f.part_in = f.part_out;
@@ -1253,6 +1249,15 @@ int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dus
     using D128 = std::integral_constant<int, 128>;
     if (dtype == SKA_F32) return d == 32 ? with(0.f, D32{}) : d == 64 ? with(0.f, D64{}) : with(0.f, D128{});
     return d == 32 ? with(__bf16{}, D32{}) : d == 64 ? with(__bf16{}, D64{}) : with(__bf16{}, D128{});
+}
+
+int ska_query_chains(int device, ska_chains *chains)
+{
+    if (!chains || device < 0 || device >= MAX_DEVICES) return SKA_EINVAL;
+    std::lock_guard<std::mutex> lk(g_mutex);
+    const ChainGate &g = g_gate[device];
+    *chains = ska_chains{g.seq, g.word ? __atomic_load_n(g.word, __ATOMIC_RELAXED) : 0u, g.word ? __atomic_load_n(g.word + 1, __ATOMIC_RELAXED) : 0u};
+    return SKA_OK;
 }
 
 static int fwd_call(const Problem &p_in, const void *Q, const void *K, const void *V, void *O, float *UV,

@@ -90,8 +90,8 @@ struct StepArgs {
     StepChain *chain;
     unsigned long long *words;     // [2][problem][block][32 (NF + 2 hw)] column sums on their way, with the step's number
     long wstride, wbuf;            // words between problems, buffers
-    unsigned *started;             // host memory: `seq` when all workgroups have started
-    unsigned seq, limit;           // polls of a wait before it gives up
+    unsigned *gate;                // host memory: [0] `seq` when all workgroups have started, [1] where the chain gives up (vfinish_kernel)
+    unsigned seq, limit;           // the chain's number; polls of a wait before it gives up
 };
 __device__ __forceinline__ void take_args(const StepArgs &p)
 {
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
     if (CHAIN && tid == 0) {
         gave_up = 0;
         if (__hip_atomic_fetch_add(&p.chain->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == (unsigned)p.nb_total)
-            __hip_atomic_store(p.started, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(p.gate, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     // where step st leaves its potentials (-1: nowhere)
     auto slot_of = [&](int st) { return st + 1 < p.base_left ? -1 : st + 1 == p.base_left ? 0 : 2 * (p.tail + st - p.base_left); };

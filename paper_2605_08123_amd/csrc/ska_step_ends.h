@@ -134,6 +134,7 @@ template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish
         return;
     }
     const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk;
+    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(p.gate + 1, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (blockIdx.x % nblk) return;
     const T *X = reinterpret_cast<const T *>(p.X) + (long)n * p.L * D, *Y = reinterpret_cast<const T *>(p.Y) + (long)n * p.L * D;
     float *slots = p.slots + n * p.us;

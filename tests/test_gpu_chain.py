@@ -1,6 +1,7 @@
 """Several Sinkhorn steps in one launch, whose workgroups hand their column sums to each other, against the same steps launch by
 launch: a forward whose workspace has room for the column sums of launched steps and no more takes the latter.  The same kernel on
-the same numbers, so the same bits; and the answer where a wait for a neighbour runs out."""
+the same numbers, so the same bits; and the answer where a wait for a neighbour runs out.  Which route a call took is asked
+(query_chains), in every case."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -8,19 +9,23 @@ pytestmark = pytest.mark.gpu
 CASES = [  # kind, dtype, d, N, L, W, T, R: one block and many, one tile of band and as many as single blocks take, ragged ends
     ("plain", "bf16", 64, 1, 31, 7, 3, 2), ("plain", "bf16", 64, 2, 65, 0, 2, 1), ("plain", "bf16", 64, 8, 701, 64, 16, 2),
     ("plain", "bf16", 64, 5, 3001, 100, 9, 2), ("plain", "bf16", 64, 30, 1999, 128, 4, 3), ("plain", "bf16", 64, 3, 1023, 256, 5, 2),
-    ("plain", "bf16", 64, 2, 1100, 300, 4, 2), ("plain", "bf16", 64, 1, 700, 33, 0, 4), ("plain", "bf16", 64, 1, 700, 33, 1, 2),
+    ("plain", "bf16", 64, 2, 1100, 300, 4, 3), ("plain", "bf16", 64, 1, 700, 33, 0, 4), ("plain", "bf16", 64, 1, 700, 33, 1, 2),
     ("plain", "bf16", 32, 7, 1333, 40, 5, 2), ("plain", "bf16", 128, 4, 1777, 127, 5, 2), ("plain", "bf16", 128, 2, 900, 256, 3, 2),
     ("plain", "bf16", 64, 300, 130, 60, 3, 2), ("plain", "f32", 32, 1, 256, 16, 8, 2), ("plain", "f32", 64, 8, 2000, 128, 5, 2),
-    ("plain", "f32", 64, 2, 700, 255, 3, 1), ("plain", "f32", 128, 2, 500, 60, 3, 2), ("plain", "bf16", 64, 2, 400, 5000, 4, 2),
+    ("plain", "f32", 64, 2, 700, 255, 3, 6), ("plain", "f32", 128, 2, 500, 60, 3, 2), ("plain", "bf16", 64, 2, 400, 5000, 4, 6),
     # fp32 keeps its scores over the steps: beside the plan entries or with those evaluated twice, few tiles and many
-    ("plain", "f32", 64, 4, 2000, 256, 4, 2), ("plain", "f32", 64, 8, 8000, 128, 3, 2), ("plain", "f32", 32, 8, 2000, 128, 4, 2),
+    ("plain", "f32", 64, 4, 2000, 256, 4, 6), ("plain", "f32", 64, 8, 8000, 128, 3, 2), ("plain", "f32", 32, 8, 2000, 128, 4, 2),
     ("plain", "f32", 64, 2, 3000, 60, 4, 2), ("plain", "f32", 128, 4, 700, 33, 4, 2), ("varlen", "f32", 64, 4, 8000, 120, 3, 2),
     ("varlen", "bf16", 64, 6, 2048, 128, 6, 2), ("varlen", "f32", 64, 4, 500, 100, 4, 2), ("varlen", "bf16", 64, 4, 900, 200, 2, 3),
     ("varlen", "bf16", 64, 4, 611, 20, 1, 3),
-    ("dustbin", "bf16", 64, 2, 701, 30, 6, 2), ("dustbin", "bf16", 64, 8, 5000, 128, 5, 2), ("dustbin", "f32", 64, 2, 900, 100, 4, 2),
+    ("dustbin", "bf16", 64, 2, 701, 30, 6, 2), ("dustbin", "bf16", 64, 8, 4000, 128, 5, 2), ("dustbin", "f32", 64, 2, 900, 100, 4, 2),
     ("dustbin", "bf16", 128, 2, 600, 222, 3, 2), ("dustbin", "bf16", 32, 1, 20000, 60, 0, 4), ("dustbin", "f32", 32, 1, 40, 16, 3, 2),
     ("marginals", "bf16", 64, 3, 900, 100, 5, 2), ("marginals", "f32", 64, 2, 700, 50, 4, 2), ("small targets", "bf16", 64, 2, 900, 64, 4, 2),
     ("masked", "bf16", 64, 4, 700, 40, 5, 2), ("masked", "f32", 64, 2, 600, 128, 4, 3), ("masked", "bf16", 64, 2, 500, 1, 0, 3)]
+LAUNCHED = [   # with as large a workspace: a dustbin's 632 blocks, which are more than a chain takes; 2000 blocks, more than fit the device;
+    # windows whose words are more than the workspace of as few tail steps has room for
+    ("dustbin", "bf16", 64, 8, 5000, 128, 5, 2), ("plain", "f32", 64, 16, 16000, 60, 3, 2), ("plain", "bf16", 64, 2, 1100, 300, 4, 2),
+    ("plain", "f32", 64, 2, 700, 255, 3, 1), ("plain", "bf16", 64, 2, 400, 5000, 4, 2), ("plain", "f32", 64, 4, 2000, 256, 4, 2)]
 
 
 def _setup(case):
@@ -54,46 +59,62 @@ def _setup(case):
     assert few < ska.sinkhorn_attn_workspace_bytes(N, 1, L, d, W, T, R, db, code)
 
     def forward(nbytes=None):
+        """O, UV, and whether the steps ran as a chain"""
+        before = binding.query_chains().launched
         ws = None if nbytes is None else torch.full((nbytes,), 255, device="cuda", dtype=torch.uint8)
         if kind == "masked":
             out = ska.sinkhorn_attn_fwd_masked(Q, K, V, mq, mk, W, T, R, 0.7, workspace=ws)
         else:
             out = ska.sinkhorn_attn_fwd_varlen(Q, K, V, la, lb, lq, lk, W, T, R, 0.7, db, 0.3, workspace=ws)
         torch.cuda.synchronize()
-        return out
+        chains = binding.query_chains()
+        assert chains.started == chains.launched <= before + 1
+        return *out, chains.launched > before
 
     return forward, few
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("case", CASES + LAUNCHED, ids=lambda c: "-".join(map(str, c)))
 def test_a_chain_has_the_bits_of_its_steps(case):
     import torch
+
+    from paper_2605_08123_amd import binding
     print(f"\n[case] {case}", flush=True)
     forward, few = _setup(case)
-    O0, UV0 = forward(few)
-    assert not torch.isnan(UV0).any() and torch.isfinite(O0.float()).all()
+    O0, UV0, chained = forward(few)
+    assert not chained and not torch.isnan(UV0).any() and torch.isfinite(O0.float()).all()
+    given_up = binding.query_chains().given_up
     for _ in range(3):   # (the words of the call before lie where the next one's will)
-        O, UV = forward()
+        O, UV, chained = forward()
+        assert chained == (case not in LAUNCHED)
         assert torch.equal(UV, UV0) and torch.equal(O, O0)
+    assert binding.query_chains().given_up == given_up
 
 
 @pytest.mark.parametrize("case", [c for c in CASES if c[:5] in (
     ("plain", "bf16", 64, 8, 701), ("plain", "bf16", 64, 5, 3001), ("plain", "f32", 64, 8, 2000), ("varlen", "bf16", 64, 6, 2048),
-    ("varlen", "bf16", 64, 4, 900), ("dustbin", "bf16", 64, 8, 5000), ("dustbin", "f32", 64, 2, 900), ("marginals", "f32", 64, 2, 700),
+    ("varlen", "bf16", 64, 4, 900), ("dustbin", "bf16", 64, 8, 4000), ("dustbin", "f32", 64, 2, 900), ("marginals", "f32", 64, 2, 700),
     ("masked", "bf16", 64, 4, 700), ("masked", "f32", 64, 2, 600)) or c[3:6] == (1, 700, 33)], ids=lambda c: "-".join(map(str, c)))
 def test_a_wait_that_runs_out_leaves_the_answer(case):
-    """One poll and no more: some workgroup gives up, and the launch that follows solves the problem by itself.  The potentials
-    agree to rounding: (2 W + 20 + 4 M) 2^-24 per half-step on either side (see test_gpu_steps.py), M the largest exponent."""
+    """One poll and no more: some workgroup gives up (if by chance none has, once more), and the launch that follows solves the
+    problem by itself.  The potentials agree to rounding: (2 W + 20 + 4 M) 2^-24 per half-step on either side (see test_gpu_steps.py), M the largest exponent."""
     import torch
 
     import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
     kind, dtype, d, N, L, W, T, R = case
     print(f"\n[case] {case}", flush=True)
     forward, few = _setup(case)
-    O0, UV0 = forward(few)
+    O0, UV0, _ = forward(few)
     try:
-        ska.sinkhorn_attn_set_fused_half_steps(0, 1)
-        O, UV = forward()
+        for _ in range(20):
+            ska.sinkhorn_attn_set_fused_half_steps(0, 1)
+            O, UV, chained = forward()
+            assert chained
+            chains = binding.query_chains()
+            if chains.given_up == chains.launched:
+                break
+        assert chains.given_up == chains.launched
     finally:
         ska.sinkhorn_attn_set_fused_half_steps(0)
     assert torch.equal(torch.isneginf(UV), torch.isneginf(UV0))
@@ -108,13 +129,15 @@ def test_a_wait_that_runs_out_leaves_the_answer(case):
     assert rel <= 2 * bound + (2.0 ** -8 if dtype == "bf16" else 0.0), rel
 
 
-@pytest.mark.parametrize("B,H,L,d,W,T,R", [(2, 2, 2500, 64, 100, 6, 2), (3, 3, 446, 32, 255, 2, 1), (1, 2, 446, 64, 255, 3, 2)])
-def test_a_chain_with_learned_dustbin_tokens_is_replayed_by_launches(B, H, L, d, W, T, R):
+@pytest.mark.parametrize("B,H,L,d,W,T,R,room", [(2, 2, 2500, 64, 100, 6, 2, True), (3, 3, 446, 32, 255, 2, 1, False),
+                                                (3, 3, 446, 32, 255, 2, 2, True), (1, 2, 446, 64, 255, 3, 2, True)])
+def test_a_chain_with_learned_dustbin_tokens_is_replayed_by_launches(B, H, L, d, W, T, R, room):
     """Captured steps are launches: the same bits as the eager chain, tokens' spokes and gradients included.  (Wide bands over few
     rows take most room in the workspace, which the spokes follow.)"""
     import torch
 
     import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
     gen = torch.Generator(device="cuda")
     gen.manual_seed(7)
     eps = 0.5
@@ -126,12 +149,15 @@ def test_a_chain_with_learned_dustbin_tokens_is_replayed_by_launches(B, H, L, d,
         O, UV = ska.sinkhorn_attn_fwd_dustbin_token(Q, K, V, *tok, W, T, R, eps, workspace=ws)
         return [O, UV, *ska.sinkhorn_attn_bwd_dustbin_token(Q, K, V, *tok, O, G, UV, W, T, R, eps, workspace=ws)]
 
+    before = binding.query_chains().launched
     eager = [x.clone() for x in run()]
     torch.cuda.synchronize()
+    assert binding.query_chains().launched == before + room
     graph = torch.cuda.CUDAGraph()
     side = torch.cuda.Stream()
     with torch.cuda.graph(graph, stream=side):
         out = run()
+    assert binding.query_chains().launched == before + room
     for _ in range(3):
         for x in out:
             x.fill_(float("nan"))
