@@ -653,10 +653,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
 
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     const bool capturing = hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
-    // Whole steps after the first one: in one launch where every workgroup is a single block and all of them fit the device, the
-    // call's sweeps are not split (see vstep_kernel).
+    // Whole steps after the first one (stride 0: there is no room for their sums, and the steps are half-steps): in one launch where
+    // every workgroup is a single block and all of them fit the device, the call's sweeps are not split (see vstep_kernel).
     const StepShape shape = step_shape<T, D>(N, L, p.W);
-    const ChainSpace room = shape.NF && ws ? chain_space(p, shape, fused) : ChainSpace{0, 0, 0, 0};
+    const StepSums sums = ws ? step_sums(p, shape, fused) : StepSums{{0, 0}, 0, true};
+    const ChainSpace room = sums.stride ? chain_space(p, shape, fused) : ChainSpace{0, 0, 0, 0};
     const int after_first = p.T + R - 1;
     bool chained = room.off && shape.kind == STEP_BLOCK && shape.M == 1 && after_first >= 2 && !p.n_stages && !p.resume_t && !cx.side && !cx.noalloc && !capturing && chain_may_start(cx.dev, st);
     // the score operand, and u0 = v0 = 0: the base solve starts from v = 0
@@ -787,10 +788,9 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     // launch writes v to another slot than it reads it from: the slots 1 and 3 in turn, so that the base solve
     // ends in slot 1 (the first step's v starts in the slot that makes it so).
     const int nseg = shape.NF ? (int)step_segments(shape, L) : 0;
-    const StepSums sums = step_sums(p, shape, fused);
     const long pstride = sums.stride;
     float *part[2] = {nullptr, nullptr};
-    if (pstride && ws)
+    if (pstride)
         for (int i = 0; i < 2; ++i) part[i] = reinterpret_cast<float *>(reinterpret_cast<unsigned char *>(ws) + sums.off[i]);
     if (part[0]) chain_done = nullptr;   // a step is one launch already
     bool first = !p.resume_t, pend = false;

@@ -165,3 +165,46 @@ def test_a_chain_with_learned_dustbin_tokens_is_replayed_by_launches(B, H, L, d,
         torch.cuda.synchronize()
         for x, y in zip(out, eager):
             assert torch.isfinite(y.float()).all() and torch.equal(x, y)
+
+
+@pytest.mark.parametrize("N,dtype,R,T", [(1, "bf16", 16, 2), (16, "bf16", 13, 3), (1, "f32", 20, 0), (1, "f32", 16, 1)])
+def test_no_chain_where_launched_steps_have_no_room(N, dtype, R, T):
+    """A few rows with many tail steps: room for a chain's words and none for two buffers of launched sums.  The steps are half-steps
+    then, queued or not, and none of them is lost."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    td, code = (torch.float32, 0) if dtype == "f32" else (torch.bfloat16, 1)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    L, W, d = 4, 3, 64
+    Q, K, V = (torch.randn((N, 1, L, d), generator=gen, device="cuda").to(td) for _ in range(3))
+    assert not binding.query_step_plan(N, 1, L, d, W, T, R, False, code).whole_steps
+    before = binding.query_chains().launched
+    S = (Q.double() @ K.double().transpose(-1, -2).contiguous())[:, 0] / (0.7 * d ** 0.5)
+    v, uv = torch.zeros((N, L), device="cuda", dtype=torch.float64), []
+    for t in range(T + R):
+        u = -torch.logsumexp(S + v[:, None], 2)
+        v1 = -torch.logsumexp(S + u[:, :, None], 1)
+        if t >= T:
+            uv += [u, v1]
+        v = v1
+    try:
+        for mode in (0, 1, 2):
+            ska.sinkhorn_attn_set_fused_half_steps(mode)
+            O, UV = ska.sinkhorn_attn_fwd(Q, K, V, W, T, R, 0.7)
+            torch.cuda.synchronize()
+            if mode == 0:
+                O0, UV0 = O.clone(), UV.clone()
+            assert torch.equal(O, O0) and torch.equal(UV, UV0), mode
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+    # per half-step (2 W + 20 + 4 M) 2^-24 (see above), M the largest exponent; bf16: and the scaled operand's rounding, 2^-9 of |Q| |K|^T
+    big = float((Q.double().abs() @ K.double().abs().transpose(-1, -2).contiguous()).max()) / (0.7 * d ** 0.5)
+    M = 1.4427 * (big + float(UV0.abs().max()))
+    bound = 2 * (T + R) * ((2 * W + 20 + 4 * M) * 2.0 ** -24 + (2.0 ** -9 * big if dtype == "bf16" else 0.0))
+    err = float((UV0[:, 0, 2:].double() - torch.stack(uv, 1)).abs().max())
+    print(f"[case] {N, dtype, R, T} |UV - UV64| {err:.1e} (bound {bound:.1e})", flush=True)
+    assert err <= bound
+    assert binding.query_chains().launched == before
