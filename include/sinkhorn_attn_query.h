@@ -35,13 +35,15 @@ int ska_query_step_plan(int B, int H, int L, int d, int W, int T, int R, int dus
                         size_t workspace_bytes, int one_call, ska_step_plan *plan);
 
 /*
- * Chains: short calls run the steps after the first one in one launch, whose workgroups hand their sums to each other.  They
- * are numbered from 1 on, per device; the device writes `started` and `given_up` (ask after a synchronisation).
+ * Chains: launches whose workgroups wait for each other.  Short calls run the steps after the first one in one launch, whose
+ * workgroups hand their sums to each other; sinkhorn_attn_set_fused_half_steps runs half-steps so.  They are numbered from 1
+ * on, per device; the device writes `started` and `given_up` (ask after a synchronisation).
  */
 typedef struct {
     unsigned launched;  /* number of the latest chain (0: there was none)                                             */
     unsigned started;   /* of the latest one whose workgroups have all started                                     */
-    unsigned given_up;  /* of the latest one in which a wait has run out (its steps were solved again), 0: none      */
+    unsigned given_up;  /* of the latest one in which a wait has run out, 0: none (steps: they were solved again;    */
+                        /* half-steps: what depends on the wait is NaN)                                        */
 } ska_chains;
 
 /* Returns SKA_OK, or SKA_EINVAL without a place for the answer or for a device number out of range. */

@@ -38,6 +38,7 @@
 #include "sinkhorn_attn.h"
 #include "sinkhorn_attn_query.h"
 #include "ska_common.h"
+#include "ska_gate.h"
 #include "ska_small_kernels.h"
 #include "ska_step_ends.h"
 #include "ska_step_launch.h"
@@ -343,6 +344,27 @@ Side *side_for_device(int dev)   // (g_mutex held)
     return sd.s ? &sd : nullptr;
 }
 
+WaitGate g_gate[MAX_DEVICES];   // (g_mutex held)
+WaitStream wait_stream(hipStream_t st) { return WaitStream{st, st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()}; }
+// whether a launch whose workgroups wait for each other may go on its way (see WaitGate)
+bool chain_may_start(int dev, hipStream_t st)
+{
+    static bool tried[MAX_DEVICES];
+    WaitGate &g = g_gate[dev];
+    if (!tried[dev]) {
+        tried[dev] = true;
+        void *h = nullptr, *d = nullptr;
+        if (hipHostMalloc(&h, 2 * sizeof(unsigned), hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&d, h, 0) == hipSuccess) {
+            g.word = static_cast<unsigned *>(h);
+            g.word_dev = static_cast<unsigned *>(d);
+            g.word[0] = g.word[1] = 0;
+        } else {
+            (void)hipGetLastError();
+        }
+    }
+    return g.may_start(wait_stream(st));
+}
+
 // One library call: the stream it enqueues on, the device, and whether its sweeps are split
 // over the helper stream.  Splitting doubles the dispatches of a call, which pays only while a
 // dispatch is long against the host's cost of enqueueing it: at least 50 M band edges per
@@ -388,7 +410,7 @@ struct Call {
 };
 
 // A chain of half-steps in one cooperative launch (vchain_kernel); returns SKA_EUNSUPPORTED if the
-// device cannot hold a useful grid, so that the caller launches the half-steps one by one instead.
+// device cannot hold a useful grid, so that the caller launches the half-steps one by one instead.  (The gate has let it through.)
 template <typename T, int D, int FR> int launch_vchain(ChainArgs &c, int N, hipStream_t st, int dev)
 {
     constexpr int BM = NWAVES * FR * 32;
@@ -414,11 +436,15 @@ template <typename T, int D, int FR> int launch_vchain(ChainArgs &c, int N, hipS
     const int want = (c.base.nb_total + 7) / 8 * 8;
     const int grid = want < cap ? want : cap / 8 * 8;   // a multiple of eight: a workgroup's blocks stay on its XCD
     if (grid < 8) return SKA_EUNSUPPORTED;
+    WaitGate &gate = g_gate[dev];
+    c.gate = gate.word_dev; c.seq = gate.seq + 1; c.goal = gate.goal + grid;
     void *args[] = {&c};
     if (hipLaunchCooperativeKernel(fn, dim3(grid), dim3(NTHREADS), args, LDS, st) != hipSuccess) {
         (void)hipGetLastError();
         return SKA_EUNSUPPORTED;
     }
+    gate.goal = c.goal;
+    gate.launched(wait_stream(st));
     return SKA_OK;
 }
 
@@ -510,33 +536,6 @@ inline ChainSpace chain_space(const Problem &p, const StepShape &sh, bool one_ca
     const size_t limit = ws_vec_bytes(p) + (one_call ? 0 : ws_qs_bytes(p));
     if (end <= limit && (one_call || end <= p.ws_given)) s.off = off;
     return s;
-}
-// Chains of the device that are or may be waiting for room: all on one stream follow each other; one on another stream starts only if
-// the last one's workgroups have all started (they need nothing more then).  Otherwise the steps are launched one by one, with the
-// same results.
-struct ChainGate {
-    unsigned *word = nullptr, *word_dev = nullptr;   // host memory: numbers of the latest chain that has started as a whole, that has given up
-    hipStream_t last = nullptr;
-    unsigned seq = 0;
-    bool tried = false;
-};
-ChainGate g_gate[MAX_DEVICES];   // (g_mutex held)
-bool chain_may_start(int dev, hipStream_t st)
-{
-    ChainGate &g = g_gate[dev];
-    if (!g.tried) {
-        g.tried = true;
-        void *h = nullptr, *d = nullptr;
-        if (hipHostMalloc(&h, 2 * sizeof(unsigned), hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&d, h, 0) == hipSuccess) {
-            g.word = static_cast<unsigned *>(h);
-            g.word_dev = static_cast<unsigned *>(d);
-            g.word[0] = g.word[1] = 0;
-        } else {
-            (void)hipGetLastError();
-        }
-    }
-    if (!g.word) return false;
-    return __atomic_load_n(g.word, __ATOMIC_RELAXED) == g.seq || (st == g.last && st != hipStreamPerThread);
 }
 // a step's or a chain's launch
 template <typename T, int D> int launch_vstep(const StepArgs &p, const StepShape &sh, int N, hipStream_t st, int dev)
@@ -719,8 +718,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
     const bool chain_fr1 = small_blocks<T, D>(n_half, L, base.W);
     const int chain_stab = stab_rows<T>((long)n_half * L);
     if (chain_stab != stab_rows<T>((long)(N - n_half) * L) && N > n_half) chain_done = nullptr;
-    auto flush_chain = [&]() -> int {
-        if (chain.nsteps == 0) return SKA_OK;
+    auto launch_chain = [&]() -> int {
         SKA_TRY(cx.join());   // the chain takes all problems on the caller's stream
         chain.base = base;
         chain.base.stab = chain_stab;
@@ -728,7 +726,6 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         chain.Q = Q; chain.K = K; chain.UV = UV; chain.us = us; chain.Lp = Lp;
         chain.log_a = p.log_a; chain.log_b = p.log_b; chain.len_q = p.len_q; chain.len_k = p.len_k;
         chain.done = chain_done; chain.spin_limit = g_spin_limit;
-        chain.rev0 = nlaunch & 1;
         const bool fr1 = chain_fr1;
         const long nflag = (long)N * ((L + 127) / 128);
         hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((nflag + 255) / 256)), dim3(256), 0, st,
@@ -737,7 +734,14 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         int rc;
         if constexpr (sizeof(T) == 2) rc = fr1 ? launch_vchain<T, D, 1>(chain, N, st, cx.dev) : launch_vchain<T, D, 2>(chain, N, st, cx.dev);
         else rc = launch_vchain<T, D, 1>(chain, N, st, cx.dev);
-        if (rc == SKA_EUNSUPPORTED) {   // the device cannot hold the grid: one launch per half-step after all
+        SKA_TRY(cx.fork());
+        return rc;
+    };
+    auto flush_chain = [&]() -> int {
+        if (chain.nsteps == 0) return SKA_OK;
+        chain.rev0 = nlaunch & 1;
+        int rc = chain_may_start(cx.dev, st) ? launch_chain() : SKA_EUNSUPPORTED;
+        if (rc == SKA_EUNSUPPORTED) {   // it would have to wait for room, or the device cannot hold the grid: one launch per half-step after all
             for (int i = 0; i < chain.nsteps; ++i) {
                 const unsigned code = chain.code[i];
                 const bool row = code & 1;
@@ -748,15 +752,14 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
                 a.olog = Vec{row ? p.log_a : p.log_b, (long)Lp};
                 a.len_own = row ? p.len_q : p.len_k; a.len_oth = row ? p.len_k : p.len_q;
                 a.rev = (chain.rev0 + i) & 1;
-                SKA_TRY((sweep_one<T, D>(M_LSE, a, N, st, cx.dev)));
+                SKA_TRY((sweep<T, D>(cx, M_LSE, a, N)));
             }
             rc = SKA_OK;
         }
         nlaunch += chain.nsteps;
         if (pt_run) pt_run->launched(chain.nsteps);
         chain.nsteps = 0;
-        SKA_TRY(rc);
-        return cx.fork();
+        return rc;
     };
     auto half = [&](bool row, int yslot, int prevslot, int outslot) -> int {
         if (chain_done && cold == 0 && (g_fuse >= 2 || tail_now)) {
@@ -872,12 +875,11 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         f.words = reinterpret_cast<unsigned long long *>(at + 256);
         f.wstride = room.wstride; f.wbuf = N * room.wstride;
         f.limit = g_spin_limit;
-        ChainGate &gate = g_gate[cx.dev];
+        WaitGate &gate = g_gate[cx.dev];
         f.gate = gate.word_dev; f.seq = gate.seq + 1;
         f.rev = nlaunch++ & 1;
         SKA_TRY((step_sweep<T, D>(cx, f, &shape, N)));
-        gate.seq = f.seq;
-        gate.last = st;
+        gate.launched(wait_stream(st));
         if (pt_run) pt_run->launched(2 * after_first);
         f.v = slot(2 * R - 1); f.v_out = slot(2 * R + 1); f.u_fin = slot(2 * R);
         f.part_in = f.part_out;
@@ -1255,8 +1257,8 @@ int ska_query_chains(int device, ska_chains *chains)
 {
     if (!chains || device < 0 || device >= MAX_DEVICES) return SKA_EINVAL;
     std::lock_guard<std::mutex> lk(g_mutex);
-    const ChainGate &g = g_gate[device];
-    *chains = ska_chains{g.seq, g.word ? __atomic_load_n(g.word, __ATOMIC_RELAXED) : 0u, g.word ? __atomic_load_n(g.word + 1, __ATOMIC_RELAXED) : 0u};
+    const WaitGate &g = g_gate[device];
+    *chains = ska_chains{g.seq, g.started(), g.given_up()};
     return SKA_OK;
 }
 

@@ -436,8 +436,13 @@ struct ChainArgs {
     int rev0;                  // direction of the first half-step's walk over the blocks (alternates)
     int *done;                 // [nb_total] half-steps completed per block, zero at launch
     unsigned spin_limit;       // polls of a wait before it gives up
+    unsigned *gate;            // host memory: [0] `seq` when all workgroups have started, [1] when a wait has run out
+    unsigned seq, goal;        // this chain's number; what vchain_started then is
     unsigned code[MAXCHAIN];   // per half-step: bit 0 row step; bits 8-15, 16-23, 24-31 slots of yt, xs, out
 };
+
+// Workgroups that have started, of all such launches of the device.  (A chain starts after all of the one before have.)
+__device__ unsigned vchain_started;
 
 template <typename T, int D, int FR>
 __global__ __launch_bounds__(NTHREADS) void vchain_kernel(const ChainArgs c)
@@ -449,6 +454,8 @@ __global__ __launch_bounds__(NTHREADS) void vchain_kernel(const ChainArgs c)
     const int nb = c.base.nb_total, nbp = c.base.nbp;
     const int reach = (c.base.W + BM - 1) / BM;   // blocks on either side whose potentials a block reads
     const int slots = ((nb + 7) >> 3) * 8;
+    if (tid == 0 && __hip_atomic_fetch_add(&vchain_started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == c.goal)
+        __hip_atomic_store(c.gate, c.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     for (int hs = 0; hs < c.nsteps; ++hs) {
         const unsigned code = c.code[hs];
         const bool row = code & 1;
@@ -482,6 +489,7 @@ __global__ __launch_bounds__(NTHREADS) void vchain_kernel(const ChainArgs c)
             if (ok) {
                 vsweep_block<T, D, M_LSE, FR, true>(a, lb, smem, red);
             } else {   // gave up: poison this block's result
+                if (tid == 0) __hip_atomic_store(c.gate + 1, c.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 for (int i = tid; i < BM; i += NTHREADS)
                     if (bi * BM + i < a.L) st_pot<true>(a.out_vec.p + n * a.out_vec.stride + bi * BM + i, __builtin_nanf(""));
             }

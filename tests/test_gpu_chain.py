@@ -197,6 +197,7 @@ def test_no_chain_where_launched_steps_have_no_room(N, dtype, R, T):
             torch.cuda.synchronize()
             if mode == 0:
                 O0, UV0 = O.clone(), UV.clone()
+                assert binding.query_chains().launched == before
             assert torch.equal(O, O0) and torch.equal(UV, UV0), mode
     finally:
         ska.sinkhorn_attn_set_fused_half_steps(0)
@@ -207,4 +208,55 @@ def test_no_chain_where_launched_steps_have_no_room(N, dtype, R, T):
     err = float((UV0[:, 0, 2:].double() - torch.stack(uv, 1)).abs().max())
     print(f"[case] {N, dtype, R, T} |UV - UV64| {err:.1e} (bound {bound:.1e})", flush=True)
     assert err <= bound
-    assert binding.query_chains().launched == before
+
+
+@pytest.mark.parametrize("first,second", [(a, b) for a in ("steps", "half-steps") for b in ("steps", "half-steps")])
+def test_no_chain_beside_one_that_has_not_started(first, second):
+    """A call whose chain stands behind other work on its stream: another stream's call runs as launches, the same stream's next one as a
+    chain.  All of them have the bits of launches."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+    sizes = {"steps": (4, 700, 64, 6), "half-steps": (2, 9000, 500, 3)}
+    data = {k: [torch.randn((N, 1, L, 64), generator=gen, device="cuda").bfloat16() for _ in range(3)] for k, (N, L, _, _) in sizes.items()}
+
+    def ws(kind):
+        N, L, W, T = sizes[kind]
+        return torch.empty(ska.sinkhorn_attn_workspace_bytes(N, 1, L, 64, W, T, 2, False, 1), device="cuda", dtype=torch.uint8)
+
+    def call(kind, w):
+        N, L, W, T = sizes[kind]
+        before = binding.query_chains().launched
+        return *ska.sinkhorn_attn_fwd(*data[kind], W, T, 2, 0.6, workspace=w), binding.query_chains().launched - before
+
+    few = binding.query_step_plan(4, 1, 700, 64, 64, 6)
+    few = few.sums_offset[1] + 4 * few.sums_bytes
+    ref = {"steps": call("steps", ws("steps")[:few]), "half-steps": call("half-steps", ws("half-steps"))}
+    assert ref["steps"][2] == ref["half-steps"][2] == 0
+    A, B = torch.cuda.Stream(), torch.cuda.Stream()
+    room = [ws(first), ws(second), ws(second)]
+    try:
+        ska.sinkhorn_attn_set_fused_half_steps(2)
+        for k in sizes:
+            assert call(k, ws(k))[2] == 1   # (both kinds are chains here)
+        torch.cuda.synchronize()
+        with torch.cuda.stream(A):
+            torch.cuda._sleep(300_000_000)   # (some tenths of a second; ends by itself)
+            one = call(first, room[0])
+        chains = binding.query_chains()
+        waiting = chains.started != chains.launched
+        with torch.cuda.stream(B):
+            two = call(second, room[1])
+        with torch.cuda.stream(A):
+            three = call(second, room[2])
+        torch.cuda.synchronize()
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+    assert waiting and (one[2], two[2], three[2]) == (1, 0, 1)
+    for kind, got in ((first, one), (second, two), (second, three)):
+        assert torch.equal(got[0], ref[kind][0]) and torch.equal(got[1], ref[kind][1])
+    chains = binding.query_chains()
+    assert chains.started == chains.launched

@@ -51,6 +51,7 @@ def test_fused_half_steps_equal_separate_launches(case):
     import torch
 
     import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
     name, B, H, L, d, W, T, R, eps, dtype, kind = case
     w = Workload(name, 31, B, H, L, d, W, T, R, eps, dtype)
     print(f"\n[case] {w} ({kind})", flush=True)
@@ -73,7 +74,9 @@ def test_fused_half_steps_equal_separate_launches(case):
     try:
         for mode in (0, 1, 2):
             ska.sinkhorn_attn_set_fused_half_steps(mode)
+            before = binding.query_chains().launched
             O, UV = _forward(ska, torch, w, kind, Q, K, V, extra)
+            assert (binding.query_chains().launched > before) == (mode > 0)
             step = None
             if kind == "plain":
                 step = ska.sinkhorn_attn_step(Q, K, V, G, w.W, w.T, w.R, w.eps)

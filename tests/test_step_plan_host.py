@@ -68,6 +68,14 @@ def test_forward_alone_keeps_its_sums_inside_the_workspace():
         assert not small.whole_steps   # room for the prescaled operand alone
 
 
+def test_launches_that_wait_start_one_after_the_other(tmp_path):
+    """gate.cpp: chains of steps and of half-steps go through one gate per device."""
+    exe = str(tmp_path / "gate")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-pthread", "-I", CSRC, "-o", exe, os.path.join(HERE, "gate.cpp")], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+
+
 def test_block_shapes(tmp_path):
     """step_shapes.cpp over the shapes that the rule takes: each has an instance that fits LDS, and no wavefront reads a tile
     outside it."""
