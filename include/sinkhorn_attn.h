@@ -387,6 +387,8 @@ int sinkhorn_attn_set_streams(int n);
  * 2^18, about a tenth of a second): a wait that runs out stops waiting and writes NaN into its block of the
  * potentials, which reaches every output depending on it, and the launch ends normally.  The same bound holds for
  * the waits of short calls' whole steps in one launch, whatever the mode; what such a launch gives up is solved again by the launch after it.
+ * After a wait has run out, the next calls (256, twice as many each time that it happens soon again) run without such launches;
+ * this function forgets that, whatever its arguments.
  * Process-wide.  Returns SKA_OK, or SKA_EINVAL for another mode.
  */
 int sinkhorn_attn_set_fused_half_steps(int mode, unsigned spin_limit);

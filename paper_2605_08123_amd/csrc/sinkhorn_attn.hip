@@ -666,7 +666,8 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         const long tot = std::max(n8, std::max(per * N, n16));
         hipLaunchKernelGGL(start_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, st, reinterpret_cast<const __bf16 *>(Qin),
                            reinterpret_cast<__bf16 *>(ws_q), n8, c_start, UV, per, us, N,
-                           chained ? reinterpret_cast<uint4 *>(reinterpret_cast<unsigned char *>(ws) + room.off) : nullptr, n16);
+                           chained ? reinterpret_cast<uint4 *>(reinterpret_cast<unsigned char *>(ws) + room.off) : nullptr, n16,
+                           g_gate[cx.dev].given_up());
         if (hipGetLastError() != hipSuccess) return SKA_EHIP;
         pt.launched(PRESCALED ? 1 : 0);
     }
@@ -1696,6 +1697,7 @@ int sinkhorn_attn_set_fused_half_steps(int mode, unsigned spin_limit)
     std::lock_guard<std::mutex> lk(g_mutex);
     g_fuse = mode;
     g_spin_limit = spin_limit ? spin_limit : (1u << 18);
+    for (WaitGate &g : g_gate) g.forget();   // (waits that ran out under another limit)
     return SKA_OK;
 }
 

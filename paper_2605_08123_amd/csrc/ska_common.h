@@ -15,6 +15,12 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr int MAX_DEVICES = 16;   // per-device state of the library (helper stream, raised LDS limits, static scratch)
+// A chain of steps' own words, in the workspace; start_kernel writes them.
+struct StepChain {
+    unsigned started;   // workgroups
+    unsigned failed;    // not 0: waits give up after 64 polls
+};
+constexpr unsigned CHAIN_GAVE_UP = 1, CHAIN_HURRY = 2;   // because a workgroup has; because a chain before has
 constexpr int NTHREADS = 256;
 constexpr int NWAVES = 4;
 constexpr int TT = 32;  // other-side rows per tile

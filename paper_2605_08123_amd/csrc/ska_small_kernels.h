@@ -22,16 +22,20 @@ __device__ __forceinline__ void prescale8(const __bf16 *src, __bf16 *dst, long i
     reinterpret_cast<uint4 *>(dst)[i] = *reinterpret_cast<uint4 *>(&v);
 }
 
+// Number of the device's latest chain that has given up (WaitGate::given_up as the device knows it).  Where that has happened since the host enqueued the
+// next one (it then saw `gave`), what keeps workgroups out is not waited for again by every chain in the queue.
+__device__ unsigned chain_given_up;
+
 // The start of a forward: the prescaled operand (n8 times 8 elements; none in fp32 storage), zeros in `per` floats of every problem's
-// potentials, and in a region of its own (n16 times 16 bytes).  One launch, because each is bounded by its launch where calls are short
+// potentials, and a chain's words (n16 times 16 bytes).  One launch, because each is bounded by its launch where calls are short
 // (2.3 us between dependent launches that do nothing): a forward of eight problems of L = 701, W = 64 72.0 -> 70.0 us, forward and
 // backward of 16 of L = 3001, W = 100 238 -> 235.5.
-__global__ void start_kernel(const __bf16 *src, __bf16 *dst, long n8, float scale, float *p, long per, long stride, int nprob, uint4 *q, long n16)
+__global__ void start_kernel(const __bf16 *src, __bf16 *dst, long n8, float scale, float *p, long per, long stride, int nprob, uint4 *q, long n16, unsigned gave)
 {
     const long all = (long)gridDim.x * blockDim.x, first = (long)blockIdx.x * blockDim.x + threadIdx.x;
     for (long i = first; i < n8; i += all) prescale8(src, dst, i, scale);
     for (long i = first; i < per * nprob; i += all) p[(i / per) * stride + (i % per)] = 0.f;
-    for (long i = first; i < n16; i += all) q[i] = make_uint4(0, 0, 0, 0);
+    for (long i = first; i < n16; i += all) q[i] = make_uint4(0, i == 0 && (int)(chain_given_up - gave) > 0 ? CHAIN_HURRY : 0, 0, 0);   // (StepChain)
 }
 
 // g_o = <A_o, B_o> for o below the problem's valid length (len[n / nh], or L if len is null);

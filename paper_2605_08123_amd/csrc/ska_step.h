@@ -55,7 +55,6 @@ namespace {
 // L = 65536, W = 256 1388 -> 1445 us, a forward of eight of 701, W = 64 113 -> 115; by half-steps 1674 and 211.
 //   The arguments are a struct of their own, read as a whole at a kernel's start (take_args): fetched where they are first
 // used they cost a short launch one wait of some hundred cycles after another.
-struct StepChain { unsigned started, failed; };   // zero at launch
 struct StepArgs {
     const void *X, *Y;             // row (owner) and column operand
     const float *v, *u;            // potentials before the step (with part_in: v before the step before)
@@ -1100,7 +1099,7 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
             if (DUST) sum_row();
             __syncthreads();
             if (gave_up) {
-                if (tid == 0) __hip_atomic_store(&p.chain->failed, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (tid == 0) __hip_atomic_store(&p.chain->failed, CHAIN_GAVE_UP, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 return;
             }
             continue;

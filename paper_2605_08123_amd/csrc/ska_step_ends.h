@@ -129,12 +129,15 @@ __device__ __forceinline__ void plain_half_step(const StepArgs &p, const T *X, c
 struct SolveArgs { int T, R; };
 template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish_kernel(const StepArgs p, const SolveArgs a)
 {
-    if (!p.chain->failed) {   // (written by the launch before)
+    if (p.chain->failed != CHAIN_GAVE_UP) {   // (written by the launch before)
         final_columns(p);
         return;
     }
     const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk;
-    if (blockIdx.x == 0 && threadIdx.x == 0) __hip_atomic_store(p.gate + 1, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        chain_given_up = p.seq;
+        __hip_atomic_store(p.gate + 1, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
     if (blockIdx.x % nblk) return;
     const T *X = reinterpret_cast<const T *>(p.X) + (long)n * p.L * D, *Y = reinterpret_cast<const T *>(p.Y) + (long)n * p.L * D;
     float *slots = p.slots + n * p.us;

@@ -489,7 +489,10 @@ __global__ __launch_bounds__(NTHREADS) void vchain_kernel(const ChainArgs c)
             if (ok) {
                 vsweep_block<T, D, M_LSE, FR, true>(a, lb, smem, red);
             } else {   // gave up: poison this block's result
-                if (tid == 0) __hip_atomic_store(c.gate + 1, c.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                if (tid == 0) {
+                    chain_given_up = c.seq;
+                    __hip_atomic_store(c.gate + 1, c.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
                 for (int i = tid; i < BM; i += NTHREADS)
                     if (bi * BM + i < a.L) st_pot<true>(a.out_vec.p + n * a.out_vec.stride + bi * BM + i, __builtin_nanf(""));
             }

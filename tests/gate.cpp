@@ -39,6 +39,21 @@ int main()
     MUST(theirs.thread == other);
     g.launched(mine);
     MUST(g.may_start(mine) && !g.may_start(theirs) && !g.may_start(a));
+    // a wait that ran out: launches for a while, longer each time that it happens soon again
+    word[0] = 4;
+    for (unsigned round = 0, length = WaitGate::PAUSE; round < 14; ++round, length = length < WaitGate::LONGEST ? 2 * length : length) {
+        MUST(g.may_start(a));
+        g.launched(a);
+        word[0] = word[1] = g.seq;
+        for (unsigned i = 0; i < length; ++i) MUST(!g.may_start(i & 1 ? a : b));
+    }
+    MUST(g.may_start(a) && g.length == WaitGate::LONGEST);
+    // ... and as long as at first after many that went well
+    for (unsigned i = 0; i < 64 * WaitGate::LONGEST + 1; ++i) g.launched(a);
+    word[0] = word[1] = g.seq;
+    MUST(!g.may_start(a) && g.pause == WaitGate::PAUSE - 1);
+    g.forget();
+    MUST(g.may_start(a));
     // numbers go round
     g.seq = word[0] = ~0u;
     g.launched(b);

@@ -260,3 +260,75 @@ def test_no_chain_beside_one_that_has_not_started(first, second):
         assert torch.equal(got[0], ref[kind][0]) and torch.equal(got[1], ref[kind][1])
     chains = binding.query_chains()
     assert chains.started == chains.launched
+
+
+@pytest.mark.parametrize("kind", ["steps", "half-steps"])
+def test_after_a_wait_that_ran_out_calls_are_launched(kind):
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+    N, L, W, mode = (8, 700, 64, 0) if kind == "steps" else (2, 9000, 500, 2)
+    Q, K, V = (torch.randn((N, 1, L, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
+
+    def call():
+        before = binding.query_chains().launched
+        out = ska.sinkhorn_attn_fwd(Q, K, V, W, 6, 2, 0.6)
+        torch.cuda.synchronize()
+        return *out, binding.query_chains().launched - before
+
+    try:
+        ska.sinkhorn_attn_set_fused_half_steps(mode)
+        ref = call()
+        assert ref[2] == 1
+        for _ in range(20):   # (until a wait has run out)
+            ska.sinkhorn_attn_set_fused_half_steps(mode, 1)
+            call()
+            chains = binding.query_chains()
+            if chains.given_up == chains.launched:
+                break
+        assert chains.given_up == chains.launched
+        for _ in range(3):
+            O, UV, chained = call()
+            assert not chained and torch.equal(O, ref[0]) and torch.equal(UV, ref[1])
+        ska.sinkhorn_attn_set_fused_half_steps(mode)
+        O, UV, chained = call()
+        assert chained and torch.equal(O, ref[0]) and torch.equal(UV, ref[1])
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+
+
+def test_a_chain_behind_one_that_gave_up():
+    """In the queue when the one before gives up: it waits less long, and runs to its end where nothing keeps its workgroups out."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(13)
+    Q, K, V = (torch.randn((8, 1, 700, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    ws = [torch.empty(ska.sinkhorn_attn_workspace_bytes(8, 1, 700, 64, 64, 6, 2, False, 1), device="cuda", dtype=torch.uint8) for _ in range(2)]
+    call = lambda i: ska.sinkhorn_attn_fwd(Q, K, V, 64, 6, 2, 0.6, workspace=ws[i])
+    try:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+        O0, UV0 = call(0)
+        for _ in range(20):   # (until a wait has run out)
+            torch.cuda._sleep(20_000_000)
+            ska.sinkhorn_attn_set_fused_half_steps(0, 1)
+            first, before = call(0), binding.query_chains()
+            ska.sinkhorn_attn_set_fused_half_steps(0)
+            second = call(1)
+            torch.cuda.synchronize()
+            chains = binding.query_chains()
+            assert chains.launched == before.launched + 1 and before.started < before.launched
+            if chains.given_up == before.launched:
+                break
+        assert chains.given_up == before.launched
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+    assert torch.equal(second[0], O0) and torch.equal(second[1], UV0)
+    # (the first one's bound is that of the test of waits that run out: 2 * 2 * 8 half-steps of (2 W + 21 + 4 M) 2^-24 each)
+    M = 1.4427 * max(float(UV0.abs().max()), 6.0 * 8 / 0.6)
+    assert float((first[1] - UV0).abs().max()) <= 2 * 2 * 8 * (2 * 64 + 21 + 4 * M) * 2.0 ** -24

@@ -115,8 +115,8 @@ def test_a_wait_that_runs_out_ends_the_launch():
     O0, UV0 = ska.sinkhorn_attn_fwd(Q, K, V, w.W, w.T, w.R, w.eps)
     torch.cuda.synchronize()
     try:
-        ska.sinkhorn_attn_set_fused_half_steps(2, 1)
         for rep in range(3):
+            ska.sinkhorn_attn_set_fused_half_steps(2, 1)   # (forgets that the one before gave up)
             O, UV = ska.sinkhorn_attn_fwd(Q, K, V, w.W, w.T, w.R, w.eps)
             torch.cuda.synchronize()   # returns: the launch has ended
             bad = ~torch.isfinite(UV)
