@@ -383,7 +383,7 @@ int sinkhorn_attn_set_streams(int n);
  * The fused launch takes all problems on the caller's stream.  Two launches whose workgroups wait for
  * each other can hold each other's workgroups out.  The library keeps its own apart (these, and those that short calls run their
  * whole steps in, on any stream of this process): one starts behind the latest on the same stream, or after all workgroups
- * of the latest have started; otherwise the call runs unfused.  Other programs' it cannot know of.  Every wait inside the launch is bounded by spin_limit polls (0: the default,
+ * of the latest have started; otherwise the call runs unfused, as it does on a stream with a mask of CUs.  Other programs' it cannot know of.  Every wait inside the launch is bounded by spin_limit polls (0: the default,
  * 2^18, about a tenth of a second): a wait that runs out stops waiting and writes NaN into its block of the
  * potentials, which reaches every output depending on it, and the launch ends normally.  The same bound holds for
  * the waits of short calls' whole steps in one launch, whatever the mode; what such a launch gives up is solved again by the launch after it.

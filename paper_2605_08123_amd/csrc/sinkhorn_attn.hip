@@ -346,6 +346,20 @@ Side *side_for_device(int dev)   // (g_mutex held)
 
 WaitGate g_gate[MAX_DEVICES];   // (g_mutex held)
 WaitStream wait_stream(hipStream_t st) { return WaitStream{st, st == hipStreamPerThread ? std::this_thread::get_id() : std::thread::id()}; }
+// whether a stream's kernels run on all CUs of the device (of which hipOccupancy... knows nothing)
+bool whole_device(int dev, hipStream_t st)
+{
+    static int cus[MAX_DEVICES];   // (g_mutex held)
+    uint32_t mask[32] = {};
+    if ((!cus[dev] && hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) ||
+        hipExtStreamGetCUMask(st == hipStreamLegacy ? nullptr : st, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    int n = 0;
+    for (uint32_t m : mask) n += __builtin_popcount(m);
+    return n >= cus[dev];
+}
 // whether a launch whose workgroups wait for each other may go on its way (see WaitGate)
 bool chain_may_start(int dev, hipStream_t st)
 {
@@ -362,7 +376,7 @@ bool chain_may_start(int dev, hipStream_t st)
             (void)hipGetLastError();
         }
     }
-    return g.may_start(wait_stream(st));
+    return whole_device(dev, st) && g.may_start(wait_stream(st));
 }
 
 // One library call: the stream it enqueues on, the device, and whether its sweeps are split

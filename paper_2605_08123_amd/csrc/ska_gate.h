@@ -15,6 +15,7 @@ struct WaitStream {
 // are placed in part hold each other's workgroups out.  So one starts only behind the latest on the same stream, or
 // after all workgroups of the latest have started, which then need nothing more (and so did those of all before it).  Otherwise the
 // caller launches steps or half-steps one by one, with the same results.
+//   (A stream whose kernels do not run on all CUs has no such launches: what fits the device may not fit those.)
 //   A wait that runs out means that something this process does not know of keeps workgroups out (another program, a kernel that stays),
 // and costs a call a tenth of a second and the solve anew.  So the calls after it are launched: PAUSE of them, twice as many each
 // time that it happens soon again.  (g_mutex held)

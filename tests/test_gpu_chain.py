@@ -332,3 +332,39 @@ def test_a_chain_behind_one_that_gave_up():
     # (the first one's bound is that of the test of waits that run out: 2 * 2 * 8 half-steps of (2 W + 21 + 4 M) 2^-24 each)
     M = 1.4427 * max(float(UV0.abs().max()), 6.0 * 8 / 0.6)
     assert float((first[1] - UV0).abs().max()) <= 2 * 2 * 8 * (2 * 64 + 21 + 4 * M) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("kind", ["steps", "half-steps"])
+def test_no_chain_on_a_stream_with_some_of_the_cus(kind):
+    """What the device holds at once may not fit the CUs of such a stream: its calls are launched, with the same bits."""
+    import ctypes
+
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    torch.cuda.init()
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipExtStreamCreateWithCUMask.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_uint32, ctypes.POINTER(ctypes.c_uint32)]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(14)
+    N, L, W, mode = (8, 700, 64, 0) if kind == "steps" else (2, 9000, 500, 2)
+    Q, K, V = (torch.randn((N, 1, L, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    words = (cus + 31) // 32
+    masks = {"all": [0xffffffff] * words, "half": [0xffffffff if i < words // 2 else 0 for i in range(words)]}
+    results = {}
+    try:
+        ska.sinkhorn_attn_set_fused_half_steps(mode)
+        for name, mask in masks.items():
+            st = ctypes.c_void_p()
+            assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(st), words, (ctypes.c_uint32 * words)(*mask)) == 0
+            with torch.cuda.stream(torch.cuda.ExternalStream(st.value)):
+                before = binding.query_chains().launched
+                O, UV = ska.sinkhorn_attn_fwd(Q, K, V, W, 6, 2, 0.6)
+                torch.cuda.synchronize()
+                assert binding.query_chains().launched - before == (name == "all")
+            results[name] = O, UV
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+    assert all(torch.equal(x, y) for x, y in zip(results["all"], results["half"]))
