@@ -84,17 +84,19 @@ __global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p) { fi
 
 // One half-step of a problem by one workgroup, a wavefront per row and a lane per partner; nothing is assumed of the potentials.
 // own, oth: valid rows and partners; mark: -inf where a token is inactive; olog: log targets; dustbin: edges to and from index L,
-// scores of the owners' spokes and of the others' (null: sdb).
+// scores of the owners' spokes and of the others' (null: sdb).  A sum without an entry: marks its token while it is not `settled` who
+// is active (as the launched half-steps do with their running maximum), and is an error after that, as in the launched steps.
 struct PlainSide { const float *mark, *olog, *spoke; int valid; };
 template <typename T, int D>
-__device__ __forceinline__ void plain_half_step(const StepArgs &p, const T *X, const T *Y, const PlainSide own, const PlainSide oth, const float *y, float *x)
+__device__ __forceinline__ void plain_half_step(const StepArgs &p, const T *X, const T *Y, const PlainSide own, const PlainSide oth, bool settled, const float *y, float *x)
 {
     const int lane = threadIdx.x & 63, L = p.L;
     for (int o = threadIdx.x >> 6; o < L + (p.dustbin ? 1 : 0); o += NWAVES) {
-        float m = -INFINITY, sum = 0.f;
+        constexpr float NONE = -3e38f;   // (a number: a NaN stays in the sum, whatever comes before and after it)
+        float m = NONE, sum = 0.f;
         auto add = [&](float e, float times) {
             const float mn = fmaxf(m, e);
-            if (mn > -INFINITY) sum = sum * fast_exp2(m - mn) + times * fast_exp2(e - mn);
+            sum = sum * fast_exp2(m - mn) + times * fast_exp2(e - mn);
             m = mn;
         };
         if (o == L) {
@@ -118,15 +120,17 @@ __device__ __forceinline__ void plain_half_step(const StepArgs &p, const T *X, c
             add(mo, so);
         }
         if (lane == 0) {
-            const bool active = o == L || (o < own.valid && own.mark[o] != -INFINITY && m > -INFINITY);
-            x[o] = active ? (own.olog ? own.olog[o] : 0.f) - LN2 * (m + fast_log2(sum)) : o < own.valid ? -INFINITY : 0.f;
+            float r = 0.f;
+            if (o < own.valid && own.mark[o] == -INFINITY) r = -INFINITY;
+            else if (o == L || o < own.valid) r = m > NONE ? (own.olog ? own.olog[o] : 0.f) - LN2 * (m + fast_log2(sum)) : settled ? __builtin_nanf("") : -INFINITY;
+            x[o] = r;
         }
     }
     __syncthreads();
 }
 // After a chain: the last step's v.  If the chain has given up, one workgroup per problem does all its steps from the start
 // (milliseconds; it asks nothing of the device).
-struct SolveArgs { int T, R; };
+struct SolveArgs { int T, R, cold; };   // cold: half-steps until it is settled who is active
 template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish_kernel(const StepArgs p, const SolveArgs a)
 {
     if (p.chain->failed != CHAIN_GAVE_UP) {   // (written by the launch before)
@@ -150,8 +154,8 @@ template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish
     __syncthreads();
     for (int st = 0; st < a.T + a.R; ++st) {
         const int to = st < a.T ? 0 : 2 * (st - a.T + 1), from = st < a.T ? 1 : to - 1;
-        plain_half_step<T, D>(p, X, Y, rows, PlainSide{nullptr, nullptr, cols.spoke, ln.Lt}, slot(from), slot(to));
-        plain_half_step<T, D>(p, Y, X, cols, PlainSide{nullptr, nullptr, rows.spoke, ln.Le}, slot(to), slot(to + 1));
+        plain_half_step<T, D>(p, X, Y, rows, PlainSide{nullptr, nullptr, cols.spoke, ln.Lt}, 2 * st >= a.cold, slot(from), slot(to));
+        plain_half_step<T, D>(p, Y, X, cols, PlainSide{nullptr, nullptr, rows.spoke, ln.Le}, 2 * st + 1 >= a.cold, slot(to), slot(to + 1));
     }
 }
 

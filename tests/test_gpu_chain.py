@@ -368,3 +368,51 @@ def test_no_chain_on_a_stream_with_some_of_the_cus(kind):
     finally:
         ska.sinkhorn_attn_set_fused_half_steps(0)
     assert all(torch.equal(x, y) for x, y in zip(results["all"], results["half"]))
+
+
+@pytest.mark.parametrize("what", ["NaN", "no partner"])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_what_is_no_number_stays_none_where_a_wait_ran_out(what, dtype):
+    """One query with a NaN, or one key whose scores are all -inf (its first column sum has no entry, which is an error then): the
+    solve after a chain that gave up says NaN wherever the band carries it, as the launched steps do, and nowhere out of their reach."""
+    import torch
+
+    import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(15)
+    L, W, T, R, at = 3000, 20, 1, 2, 1500
+    td, code = (torch.float32, 0) if dtype == "f32" else (torch.bfloat16, 1)
+    Q, K, V = (torch.randn((1, 1, L, 64), generator=gen, device="cuda").to(td) for _ in range(3))
+    if what == "NaN":
+        Q[0, 0, at, 5] = float("nan")
+    else:
+        Q[..., 0], K[..., 0] = 64.0, 0.0
+        K[0, 0, at, 0] = -3e38
+    few = binding.query_step_plan(1, 1, L, 64, W, T, R, False, code)
+    few = few.sums_offset[1] + few.sums_bytes
+    full = ska.sinkhorn_attn_workspace_bytes(1, 1, L, 64, W, T, R, False, code)
+    run = lambda n: ska.sinkhorn_attn_fwd(Q, K, V, W, T, R, 0.7, workspace=torch.empty(n, device="cuda", dtype=torch.uint8))
+    results = [run(few), run(full)]
+    try:
+        for _ in range(20):
+            ska.sinkhorn_attn_set_fused_half_steps(0, 1)
+            again = run(full)
+            torch.cuda.synchronize()
+            chains = binding.query_chains()
+            if chains.given_up == chains.launched:
+                break
+        assert chains.given_up == chains.launched
+    finally:
+        ska.sinkhorn_attn_set_fused_half_steps(0)
+    results.append(again)
+    away = (torch.arange(L, device="cuda") - at).abs()
+    for route, (O, UV) in zip(("launched", "chain", "solved again"), results):
+        # (the first half-step marks a query without a score as inactive; its scores are NaN all the same)
+        # a half-step carries it W further; steps carry it to whole tiles of 32 and blocks
+        for slot in range(1, 2 * (R + 1)):
+            h = slot - (0 if what == "NaN" else 1)
+            nan = torch.isnan(UV[0, 0, slot])
+            assert nan[(away <= h * W) & ((away > 0) | (h != slot) | (slot % 2 == 1))].all(), (route, slot)
+            assert not nan[away > h * (W + 160) + 160].any(), (route, slot)
+        assert torch.isnan(O[0, 0, (away <= 3 * W) & (away > 0)]).all() and torch.isfinite(O[0, 0, away > 1200]).all(), route
