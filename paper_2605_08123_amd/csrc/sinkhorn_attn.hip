@@ -898,7 +898,7 @@ int fwd_impl(Call &cx, const Problem &p, const void *Qin, const void *K, const v
         if (pt_run) pt_run->launched(2 * after_first);
         f.v = slot(2 * R - 1); f.v_out = slot(2 * R + 1); f.u_fin = slot(2 * R);
         f.part_in = f.part_out;
-        hipLaunchKernelGGL((vfinish_kernel<T, D>), dim3((unsigned)((L + NTHREADS - 1) / NTHREADS * N)), dim3(NTHREADS), 0, st, f, SolveArgs{p.T, R, p.mask_q || p.mask_k ? 2 : 1});
+        hipLaunchKernelGGL((vfinish_kernel<T, D>), dim3((unsigned)((L + SOLVE_THREADS - 1) / SOLVE_THREADS * N)), dim3(SOLVE_THREADS), 0, st, f, SolveArgs{p.T, R, p.mask_q || p.mask_k ? 2 : 1});
         vcur = 2 * R + 1;
         return hipGetLastError() == hipSuccess ? SKA_OK : SKA_EHIP;
     };

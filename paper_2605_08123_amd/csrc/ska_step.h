@@ -1034,7 +1034,7 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
             unsigned polls = 0;
             // whether to give up waiting
             auto enough = [&]() {
-                if (++polls <= p.limit && ((polls & 63) || !__hip_atomic_load(&p.chain->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return false;
+                if (++polls < p.limit && ((polls & 63) || !__hip_atomic_load(&p.chain->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))) return false;
                 gave_up = 1;
                 return true;
             };

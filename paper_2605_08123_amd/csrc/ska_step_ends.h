@@ -52,11 +52,12 @@ __global__ __launch_bounds__(NTHREADS) void step_cut_kernel(const CutArgs a)
     }
 }
 
-// v from the column sums of a step that no step follows (v_out may be p.v).
-__device__ __forceinline__ void final_columns(const StepArgs &p)
+// v from the column sums of a step that no step follows (v_out may be p.v), by workgroups of NTHR threads.  (The dustbin's shares are
+// added up as by NTHREADS, so that its bits do not depend on who does it; more threads' sums are not used.)
+template <int NTHR> __device__ __forceinline__ void final_columns(const StepArgs &p)
 {
     __shared__ float red[32];
-    const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk, blk = blockIdx.x % nblk, t = blk * NTHREADS + threadIdx.x;
+    const int nblk = (p.L + NTHR - 1) / NTHR, n = blockIdx.x / nblk, blk = blockIdx.x % nblk, t = blk * NTHR + threadIdx.x;
     const float *part = p.part_in + n * p.part_stride, *spr = p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr;
     float *v_out = p.v_out + n * p.us;
     float uL = 0.f;
@@ -80,64 +81,101 @@ __device__ __forceinline__ void final_columns(const StepArgs &p)
     }
     v_out[t] = out;
 }
-__global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p) { final_columns(p); }
+__global__ __launch_bounds__(NTHREADS) void vfinal_kernel(const StepArgs p) { final_columns<NTHREADS>(p); }
 
-// One half-step of a problem by one workgroup, a wavefront per row and a lane per partner; nothing is assumed of the potentials.
+// One half-step of a problem by one workgroup: a wavefront takes 32 rows at a time and its band's tiles one after the other, a lane is
+// a column, its registers are rows, each with a maximum and a sum of its own.  Nothing is assumed of the potentials.
 // own, oth: valid rows and partners; mark: -inf where a token is inactive; olog: log targets; dustbin: edges to and from index L,
 // scores of the owners' spokes and of the others' (null: sdb).  A sum without an entry: marks its token while it is not `settled` who
 // is active (as the launched half-steps do with their running maximum), and is an error after that, as in the launched steps.
+constexpr int SOLVE_THREADS = 512;
 struct PlainSide { const float *mark, *olog, *spoke; int valid; };
 template <typename T, int D>
 __device__ __forceinline__ void plain_half_step(const StepArgs &p, const T *X, const T *Y, const PlainSide own, const PlainSide oth, bool settled, const float *y, float *x)
 {
-    const int lane = threadIdx.x & 63, L = p.L;
-    for (int o = threadIdx.x >> 6; o < L + (p.dustbin ? 1 : 0); o += NWAVES) {
-        constexpr float NONE = -3e38f;   // (a number: a NaN stays in the sum, whatever comes before and after it)
-        float m = NONE, sum = 0.f;
-        auto add = [&](float e, float times) {
-            const float mn = fmaxf(m, e);
-            sum = sum * fast_exp2(m - mn) + times * fast_exp2(e - mn);
-            m = mn;
-        };
-        if (o == L) {
-            for (int t = lane; t <= L; t += 64) add(((oth.spoke ? oth.spoke[t] : p.sdb) + y[t]) * LOG2E, 1.f);
-        } else if (o < own.valid) {
-            for (int t = max(o - p.W, 0) + lane; t <= min(o + p.W, oth.valid - 1); t += 64) {
-                float dot = 0.f;
-                for (int k = 0; k < D; k += 4) {
-                    float a[4], b[4];
-                    load4<T>(X + (long)o * D + k, a);
-                    load4<T>(Y + (long)t * D + k, b);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = lane & 31, h = lane >> 5, L = p.L, W = p.W;
+    constexpr float NONE = -3e38f;   // (a number: a NaN stays in the sum, whatever comes before and after it)
+    auto add = [](float &m, float &sum, float e, float times) {
+        const float mn = fmaxf(m, e);
+        sum = sum * fast_exp2(m - mn) + times * fast_exp2(e - mn);
+        m = mn;
+    };
+    auto finish = [&](int o, float m, float sum) {
+        if (m > NONE) x[o] = (own.olog ? own.olog[o] : 0.f) - LN2 * (m + fast_log2(sum));
+        else x[o] = settled ? __builtin_nanf("") : -INFINITY;
+    };
+    for (int o0 = 32 * wave; o0 < own.valid; o0 += SOLVE_THREADS / 2) {
+        float m[16], sum[16];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) dot = fmaf(a[i], b[i], dot);
-                }
-                add(fmaf(dot, p.c2, y[t] * LOG2E), 1.f);
+        for (int r = 0; r < 16; ++r) { m[r] = NONE; sum[r] = 0.f; }
+        const int first = max(o0 - W, 0) >> 5, last = min(o0 + 31 + W, oth.valid - 1) >> 5;
+        constexpr bool AHEAD = D * sizeof(T) <= 256;   // (registers)
+        OwnerFrag<T, D> xf, yf, next;
+        xf.load(X, o0 + c, own.valid, h);
+        if (AHEAD) next.load(Y, 32 * first + c, oth.valid, h);
+        for (int k = first; k <= last; ++k) {
+            if (AHEAD) yf = next;
+            (AHEAD ? next : yf).load(Y, 32 * (k + AHEAD) + c, oth.valid, h);
+            f32x16 e;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) e[r] = 0.f;
+            if constexpr (sizeof(T) == 2) {
+#pragma unroll
+                for (int ks = 0; ks < D / 16; ++ks) e = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf.v[ks], yf.v[ks], e, 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int ks = 0; ks < D / 2; ++ks) e = __builtin_amdgcn_mfma_f32_32x32x2f32(xf.v[ks], yf.v[ks], e, 0, 0, 0);
             }
-            if (p.dustbin && lane == 0) add(((own.spoke ? own.spoke[o] : p.sdb) + y[L]) * LOG2E, 1.f);
+            const int t = 32 * k + c;
+            const float yt = t < oth.valid ? y[t] * LOG2E : -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int o = o0 + 8 * (r >> 2) + (r & 3) + 4 * h;
+                add(m[r], sum[r], t < oth.valid && abs(t - o) <= W ? fmaf(e[r], p.c2, yt) : -INFINITY, 1.f);
+            }
         }
+        float mr = NONE, sr = 0.f;   // lane c < 16: of its register c
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+#pragma unroll
+            for (int s = 16; s >= 1; s >>= 1) {
+                const float mo = __shfl_xor(m[r], s), so = __shfl_xor(sum[r], s);
+                add(m[r], sum[r], mo, so);
+            }
+            if (c == r) { mr = m[r]; sr = sum[r]; }
+        }
+        const int o = o0 + 8 * (c >> 2) + (c & 3) + 4 * h;
+        if (c < 16 && o < own.valid) {
+            if (p.dustbin) add(mr, sr, ((own.spoke ? own.spoke[o] : p.sdb) + y[L]) * LOG2E, 1.f);
+            if (own.mark[o] == -INFINITY) x[o] = -INFINITY;
+            else finish(o, mr, sr);
+        }
+    }
+    if (p.dustbin && wave == SOLVE_THREADS / 64 - 1) {
+        float m = NONE, sum = 0.f;
+        for (int t = lane; t <= L; t += 64) add(m, sum, ((oth.spoke ? oth.spoke[t] : p.sdb) + y[t]) * LOG2E, 1.f);
         for (int s = 32; s >= 1; s >>= 1) {
             const float mo = __shfl_xor(m, s), so = __shfl_xor(sum, s);
-            add(mo, so);
+            add(m, sum, mo, so);
         }
-        if (lane == 0) {
-            float r = 0.f;
-            if (o < own.valid && own.mark[o] == -INFINITY) r = -INFINITY;
-            else if (o == L || o < own.valid) r = m > NONE ? (own.olog ? own.olog[o] : 0.f) - LN2 * (m + fast_log2(sum)) : settled ? __builtin_nanf("") : -INFINITY;
-            x[o] = r;
-        }
+        if (lane == 0) finish(L, m, sum);
     }
+    for (int o = own.valid + threadIdx.x; o < L; o += SOLVE_THREADS) x[o] = 0.f;
     __syncthreads();
 }
-// After a chain: the last step's v.  If the chain has given up, one workgroup per problem does all its steps from the start
-// (milliseconds; it asks nothing of the device).
+// After a chain: the last step's v.  If the chain has given up, one workgroup per problem does all its steps from the start (it asks
+// nothing of the device).  That takes as long as one CU needs for a problem's tiles (2 (T + R) times), beside
+// a spin limit of about 100 ms.  Whole forward in ms, T + R = 18, bf16, d = 64, rows dot by dot (a wavefront a row) -> so: 8 problems of
+// L = 701, W = 64 24 -> 1.6; 16 of 3001, W = 100 130 -> 8; one of 16384, W = 64 580 -> 28; fp32, 8 of 4096, W = 128 350 -> 20.  The
+// longest problems that chains take: one of 65536, W = 64 115; of 16000, W = 480, T + R = 22 134; fp32, of 14000, W = 128 69.
 struct SolveArgs { int T, R, cold; };   // cold: half-steps until it is settled who is active
-template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish_kernel(const StepArgs p, const SolveArgs a)
+template <typename T, int D> __global__ __launch_bounds__(SOLVE_THREADS) void vfinish_kernel(const StepArgs p, const SolveArgs a)
 {
     if (p.chain->failed != CHAIN_GAVE_UP) {   // (written by the launch before)
-        final_columns(p);
+        final_columns<SOLVE_THREADS>(p);
         return;
     }
-    const int nblk = (p.L + NTHREADS - 1) / NTHREADS, n = blockIdx.x / nblk;
+    const int nblk = (p.L + SOLVE_THREADS - 1) / SOLVE_THREADS, n = blockIdx.x / nblk;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         chain_given_up = p.seq;
         __hip_atomic_store(p.gate + 1, p.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -149,7 +187,7 @@ template <typename T, int D> __global__ __launch_bounds__(NTHREADS) void vfinish
     const StepLens ln = step_lens(p, n);
     const PlainSide rows{slot(0), p.log_a ? p.log_a + (long)n * p.lstride : nullptr, p.spoke_r ? p.spoke_r + (long)n * p.sstride : nullptr, ln.Le};
     const PlainSide cols{slot(1), p.log_b ? p.log_b + (long)n * p.lstride : nullptr, p.spoke_c ? p.spoke_c + (long)n * p.sstride : nullptr, ln.Lc};
-    for (int i = threadIdx.x; i < p.Lp; i += NTHREADS)   // v = 0; inactive tokens keep their mark
+    for (int i = threadIdx.x; i < p.Lp; i += SOLVE_THREADS)   // v = 0; inactive tokens keep their mark
         for (int k = 0; k < 2; ++k) slot(k)[i] = slot(k)[i] == -INFINITY ? -INFINITY : 0.f;
     __syncthreads();
     for (int st = 0; st < a.T + a.R; ++st) {

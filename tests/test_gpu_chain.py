@@ -94,7 +94,9 @@ def test_a_chain_has_the_bits_of_its_steps(case):
 @pytest.mark.parametrize("case", [c for c in CASES if c[:5] in (
     ("plain", "bf16", 64, 8, 701), ("plain", "bf16", 64, 5, 3001), ("plain", "f32", 64, 8, 2000), ("varlen", "bf16", 64, 6, 2048),
     ("varlen", "bf16", 64, 4, 900), ("dustbin", "bf16", 64, 8, 4000), ("dustbin", "f32", 64, 2, 900), ("marginals", "f32", 64, 2, 700),
-    ("masked", "bf16", 64, 4, 700), ("masked", "f32", 64, 2, 600)) or c[3:6] == (1, 700, 33)], ids=lambda c: "-".join(map(str, c)))
+    ("masked", "bf16", 64, 4, 700), ("masked", "f32", 64, 2, 600), ("plain", "bf16", 128, 4, 1777), ("plain", "f32", 128, 2, 500),
+    ("plain", "bf16", 32, 7, 1333), ("plain", "f32", 32, 1, 256), ("dustbin", "bf16", 32, 1, 20000), ("varlen", "f32", 64, 4, 500),
+    ("varlen", "bf16", 64, 4, 611), ("plain", "f32", 64, 2, 700)) or c[3:6] == (1, 700, 33)], ids=lambda c: "-".join(map(str, c)))
 def test_a_wait_that_runs_out_leaves_the_answer(case):
     """One poll and no more: some workgroup gives up (if by chance none has, once more), and the launch that follows solves the
     problem by itself.  The potentials agree to rounding: (2 W + 20 + 4 M) 2^-24 per half-step on either side (see test_gpu_steps.py), M the largest exponent."""
