@@ -360,13 +360,18 @@ bool whole_device(int dev, hipStream_t st)
     for (uint32_t m : mask) n += __builtin_popcount(m);
     return n >= cus[dev];
 }
+// For memory that a first call allocates: another thread's capture in global mode would forbid it, and be broken by it.
+struct DuringCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    DuringCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~DuringCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
 // whether a launch whose workgroups wait for each other may go on its way (see WaitGate)
 bool chain_may_start(int dev, hipStream_t st)
 {
-    static bool tried[MAX_DEVICES];
     WaitGate &g = g_gate[dev];
-    if (!tried[dev]) {
-        tried[dev] = true;
+    if (!g.word) {   // (where it cannot be had, calls are launched until it can)
+        const DuringCaptures relaxed;
         void *h = nullptr, *d = nullptr;
         if (hipHostMalloc(&h, 2 * sizeof(unsigned), hipHostMallocMapped) == hipSuccess && hipHostGetDevicePointer(&d, h, 0) == hipSuccess) {
             g.word = static_cast<unsigned *>(h);

@@ -418,3 +418,54 @@ def test_what_is_no_number_stays_none_where_a_wait_ran_out(what, dtype):
             assert nan[(away <= h * W) & ((away > 0) | (h != slot) | (slot % 2 == 1))].all(), (route, slot)
             assert not nan[away > h * (W + 160) + 160].any(), (route, slot)
         assert torch.isnan(O[0, 0, (away <= 3 * W) & (away > 0)]).all() and torch.isfinite(O[0, 0, away > 1200]).all(), route
+
+
+FIRST_CHAIN = """
+import threading
+import torch
+import paper_2605_08123_amd as ska
+from paper_2605_08123_amd import binding
+gen = torch.Generator(device="cuda")
+gen.manual_seed(16)
+N, L, W = 8, 700, 64
+Q, K, V, G = (torch.randn((N, 1, L, 64), generator=gen, device="cuda").bfloat16() for _ in range(4))
+ws = torch.empty(ska.sinkhorn_attn_workspace_bytes(N, 1, L, 64, W, 6, 2, False, 1), device="cuda", dtype=torch.uint8)
+out = {n: torch.empty_like(Q) for n in ("O", "dQ", "dK", "dV")}
+out["UV"] = torch.empty((N, 1, 6, L), device="cuda")
+step = lambda T: ska.sinkhorn_attn_step(Q, K, V, G, W, T, 2, 0.6, workspace=ws, **out)
+step(0)   # (whole steps, too few for a chain)
+torch.cuda.synchronize()
+assert binding.query_chains().launched == 0
+errors, x, other = [], torch.zeros(1 << 16, device="cuda"), torch.cuda.Stream()
+def call():
+    try:
+        with torch.cuda.stream(other):
+            step(6)
+    except Exception as e:
+        errors.append(e)
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph, stream=torch.cuda.Stream(), capture_error_mode="global"):
+    x.add_(1.0)
+    thread = threading.Thread(target=call)
+    thread.start()
+    thread.join()
+    x.mul_(2.0)
+graph.replay()
+torch.cuda.synchronize()
+assert not errors and float(x[0]) == 2.0 and binding.query_chains().launched == 1
+first = {n: t.clone() for n, t in out.items()}
+step(6)
+torch.cuda.synchronize()
+assert binding.query_chains().launched == 2 and all(torch.equal(t, first[n]) for n, t in out.items())
+print("fine")
+"""
+
+
+def test_a_first_chain_beside_another_threads_capture():
+    """A process's first chain, in a thread while another one captures in global mode (memory for the gate is allocated then)."""
+    import os
+    import subprocess
+    import sys
+    run = subprocess.run([sys.executable, "-c", FIRST_CHAIN], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
+                         capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0 and "fine" in run.stdout, run.stderr
