@@ -167,7 +167,8 @@ def sinkhorn_attn_set_streams(n: int) -> None:
 def sinkhorn_attn_set_fused_half_steps(mode: int, spin_limit: int = 0) -> None:
     """0 (default): one launch per half-step; 1: the tail's 2R half-steps in one launch; 2: all
     half-steps after the first in one launch.  Only calls whose Sinkhorn steps do not run as one launch each have
-    half-steps to fuse (query_step_plan: half_steps_fuse).  spin_limit bounds the waits inside it (0: default)."""
+    half-steps to fuse (query_step_plan: half_steps_fuse).  spin_limit bounds the waits inside it and inside the chains of
+    short calls' steps (0: default); whatever the arguments, a wait that has run out is forgotten."""
     rc = load().sinkhorn_attn_set_fused_half_steps(int(mode), int(spin_limit))
     if rc != SKA_OK:
         raise SinkhornAttnError(rc)

@@ -4,7 +4,8 @@
 
 namespace {
 
-// A stream as the host tells it from others.  The per-thread stream's handle is the same in every thread.
+// A stream as the host tells it from others.  The per-thread stream's handle is the same in every thread.  (A new stream that gets a
+// destroyed one's handle passes for it; if the latest launch still waits for room then, the two may run out of their waits.)
 struct WaitStream {
     const void *handle = nullptr;
     std::thread::id thread;   // of the per-thread stream

@@ -22,11 +22,12 @@ namespace {
 // segments, which the next launch adds up in a fixed order where it needs v' (vfinal_kernel where no step follows).
 //   Every row and every column carries its own potential as stabiliser: after one step the row sums of a
 // column-normalised plan lie between 1 / (2 W + 1) and 2 W + 1 (unit targets), and likewise the column sums.
-//   What bounds it: the instructions of a SIMD's two wavefronts, which get little from each other's gaps.  A step of two problems of
-// L = 262144, W = 256 takes 88 us (256 segments of 16 blocks, one per CU); of these, measured by leaving it out, the exponentials
-// are 20, the products of the scores 13, the request of the next block's tiles 7, the segment's column sums 7, the adds of the row
-// sums 6, the masks 6, the exchange of row sums 4, the column sums 4, the LDS reads of the operands 2.  So what is not a product, an
-// exponential or one of the two sums is kept short: LDS addresses advance by the instructions' offsets, the tiles that are not there are
+//   What bounds it: the instructions of a SIMD's two wavefronts.  A step of two problems of L = 262144, W = 256 (256 segments of 16
+// blocks, one per CU) takes 82 us; by counters the plain ALUs are busy for 72 % of its SIMD cycles, the matrix cores for 28 %, either for
+// 85 %, with about 90 instructions a tile where its exponentials and two sums are 48.  When it took 88 us, leaving one thing out saved:
+// the exponentials 20, the products of the scores 13, the request of the next block's tiles 7, the segment's column sums 7, the adds of
+// the row sums 6, the masks 6, the exchange of row sums 4, the column sums 4, the LDS reads of the operands 2.  So what is not a product,
+// an exponential or one of the two sums is kept short: LDS addresses advance by the instructions' offsets, the tiles that are not there are
 // not evaluated and lie on all SIMDs evenly, fragments' column sums lie by column with zeros around, the reduction of row sums halves
 // its registers on the way, and the column sums of a block are added up among the products of the next one: 91.4 -> 83.2 us, the
 // one-call step of the same problems 2583 -> 2424, of four of 65536 1408 -> 1308.  Taking the column sums themselves from
@@ -35,7 +36,8 @@ namespace {
 // 524288 rows, but 588 instead of 577 at 262144; at W = 256 two windows fit LDS only if the fragments' column sums
 // share their place by LDS atomics, which cost more than that (900 -> 1120).  Small calls are bound by latency from start to
 // end: a launch of short blocks is 5 us, 2.3 of them until the first product.
-//   Forward of T = 16, R = 2 steps, bf16, d = 64, us, by half-steps -> by steps: 8 problems of L = 700, W = 64 210 -> 117; 4 of
+//   Forward of T = 16, R = 2 steps, bf16, d = 64, us, by half-steps -> by a launch per step (short calls take less as chains, see
+// below): 8 problems of L = 700, W = 64 210 -> 117; 4 of
 // 3000, W = 128 266 -> 155; 32 of 4096, W = 128 460 -> 327; 4 of 65536, W = 64 702 -> 416, W = 256 1085 -> 900; 2 of 262144,
 // W = 256 1900 -> 1676.  fp32: 8 of 4096, W = 128 607 -> 370 (matrix instructions: half as many).
 //   The potentials enter through the products (potential_parts): as 16 adds per tile they took 6 % of a long call, and as
@@ -81,7 +83,7 @@ struct StepArgs {
     // of L = 256, d = 32, W = 16: half-steps 2.61e-7, without 2.70e-7, with 2.52e-7; 16 of L = 4096, d = 64, W = 128: 5.44, 5.36,
     // 4.99e-7.
     float up;
-    // Several steps in one launch (single blocks; see ChainArgs)
+    // Several steps in one launch (single blocks; see STEP_CHAIN in vstep_kernel)
     int nsteps;                    // 1: one step, as everything above says
     int base_left, tail;           // the first base_left end the base solve (slots 0 and 1), the others are the tail's from step `tail` on
     float *slots;                  // u_t in slot 2 t, v_t in slot 2 t + 1 of a problem, Lp floats each
@@ -359,9 +361,10 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
     // of its window, which go from hand to hand as 8-byte words of a sum and the step's number: a reader polls the words
     // themselves, so nothing has to be ordered or acknowledged (relaxed accesses of agent scope).  Two buffers do: a
     // block writes a step's words after it has read the step before's of every block that reads its own, and those have then read
-    // the words of two steps before.  A hand-over takes about 1 us where a launch takes 5 (2.3 if it is empty).  The host sees to it that the
-    // workgroups fit the device together and that no other chain is waiting for room; a wait that runs out all the same (other
-    // programs on the device) ends the launch, and the problem is solved again by the launch that follows (vfinish_kernel).
+    // the words of two steps before.  A hand-over by itself takes about 1 us (neighbours, 256 words; inside a step 1000 to 1600 cycles)
+    // where a launch takes 5 (2.3 if it is empty).  The host sees to it that the workgroups fit the device together and that no other
+    // launch of this process that waits is waiting for room (WaitGate); a wait that runs out all the same (other programs on the
+    // device) ends the launch, and the problem is solved again by the launch that follows (vfinish_kernel).
     // (A kind of its own, since what it adds costs a launched step of a call with a dustbin 4 %, and forms of its own, since a flag that is
     // read costs a chain without a dustbin as much.)
     __shared__ int gave_up;
@@ -526,7 +529,8 @@ __global__ __launch_bounds__(64 * NF * G, (step_waves<T, D, NF, G, NTW, KIND, FO
 
     const int klast = (Lt - 1) / TT;
     // This wavefront's tiles of the 2 hw + 1: j0 on, cnt of them.  Groups of a fragment that have one more than others are other
-    // groups in its neighbour on the same SIMD, which has the wavefronts w and w + 4: a tile that is not there is not evaluated.
+    // groups in its neighbour on the same SIMD, which has the wavefronts w and w + 4: the last of NTW is not evaluated where it is not
+    // there.  (Others are, in bf16 storage, and masked: at half-bands of 257 to 480 a wavefront has 5 to 8 tiles and evaluates 8.)
     const int turn = G == 4 ? f : f >> 1;
     int j0 = g * (NT / G), cnt = NT / G;
 #pragma unroll

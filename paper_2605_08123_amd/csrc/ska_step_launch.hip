@@ -28,7 +28,7 @@ template <typename T, int D, int NF, int G, int NTW, int KIND, int FORM> int lau
             caps_lds[dev] = lds;
         }
         if ((p.nb_total + 7) / 8 * 8 > caps[dev]) return SKA_EUNSUPPORTED;   // (nothing has been launched)
-        // with a dustbin every step waits for the slowest block: forward of 4 problems of L = 6000, W = 64 (376 blocks) 164 us by launches,
+        // with a dustbin every step waits for the slowest block of its problem (bounded by all problems' blocks, as measured): forward of 4 problems of L = 6000, W = 64 (376 blocks) 164 us by launches,
         // 133 as a chain; 8 of 4000, W = 128 (504) 201 / 173; 8 of 5000 (632) 200 / 208
         if (p.dustbin && p.nb_total > 512) return SKA_EUNSUPPORTED;
     }

@@ -76,7 +76,8 @@ template <typename T, int D> int step_lds(const StepShape &sh)   // bytes (of th
 }
 // Which shape a call takes, from the rows of the whole call (not of a launch: results do not depend on how a call is cut).
 // Short blocks while they leave CUs idle or barely fill them, large ones (less of the band read twice) beyond, one segment per
-// CU where two buffers of tiles fit LDS.  Forward of T = 16, R = 2 steps, us, at the sizes next to each line:
+// CU where two buffers of tiles fit LDS.  Forward of T = 16, R = 2 steps, us, at the sizes next to each line, by a launch per step
+// (chains take the shape that launches take, since a call's bits are the same either way):
 //   bf16, d = 64, W = 64:  48000 rows (2,2,3) 155 (4,1,5) 159; 65536 rows 175 / 163; half-steps 255 / 253
 //   W = 128: 48000 rows (2,2,5) 196 (8,1,9) 203, 65536 rows 262 / 203; 131072 rows (8,1,9) one block 364, segments 340
 //   W = 200: 5600 rows (2,4,5) 176 (4,2,9) 206; 48000 rows 408 / 336 in segments; 524288 rows 1803, half-steps 1804
@@ -87,7 +88,7 @@ template <typename T, int D> int step_lds(const StepShape &sh)   // bytes (of th
 //   rows 2701 / 2253 / 3181; 5600 rows (1,4,5) 381 (2,4,5) 436
 //   fp32 d = 128 (16 KB tiles): W = 32 32768 rows (2,2,3) 393 (4,1,5) 329; W = 128 5600 rows 539, half-steps 989; 32768 rows
 //   1532 / 995
-//   NTW is the least that the band's tiles need (absent ones cost as much as others): d = 64, W = 32: 262144 rows (4,1,5) 413
+//   NTW is the least that the band's tiles need up to W = 256 (absent ones cost as much as others): d = 64, W = 32: 262144 rows (4,1,5) 413
 //   (4,1,3) 333; W = 96: (8,1,9) 576 (8,1,7) 507; W = 160: (4,2,9) 974 (4,2,6) 738, half-steps 974; W = 192: 933, (4,2,7) 794, 888;
 //   W = 224: (4,2,9) 917 (4,2,8) 853; 16384 rows, W = 160: (2,4,5) 168 (2,4,3) 146; 32768 rows (2,4,3) 177 (4,2,7) 185, W = 192:
 //   (2,4,4) 266 (4,2,7) 190.  d = 128, W = 160: 131072 rows (2,4,5) 850 (2,4,3) 715.  fp32 d = 64, 8000 rows, W = 160: (1,4,5) 324

@@ -34,14 +34,18 @@ def test_two_threads_two_streams(split):
     import torch
 
     import paper_2605_08123_amd as ska
+    from paper_2605_08123_amd import binding
     ska.sinkhorn_attn_set_split_min_edges(0.0 if split else 5e7)   # True: both threads share the helper stream
     try:
         wa = Workload("thr_a", 11, 1, 2, 700, 64, 40, 5, 2, 0.5, "bf16")
         wb = Workload("thr_b", 12, 2, 2, 450, 32, 17, 4, 2, 1.0, "f32")
         arrs = {"a": make_inputs(wa), "b": make_inputs(wb)}
         single, multi = {}, {}
+        before = binding.query_chains().launched
         for key, w in (("a", wa), ("b", wb)):
             _run(w, arrs[key], torch.cuda.Stream(), 1, single, key)
+        # not split: chains here, and in the threads below as the other one's chain lets them
+        assert binding.query_chains().launched - before == (0 if split else 2)
         threads = [threading.Thread(target=_run, args=(w, arrs[key], torch.cuda.Stream(), 6, multi, key))
                    for key, w in (("a", wa), ("b", wb))]
         for t in threads:
@@ -49,6 +53,8 @@ def test_two_threads_two_streams(split):
         for t in threads:
             t.join(timeout=100)
         torch.cuda.synchronize()
+        chains = binding.query_chains()
+        assert chains.started == chains.launched and chains.given_up <= before and (chains.launched > before + 2) != split
         for key in ("a", "b"):
             assert not isinstance(single[key], Exception), single[key]
             assert not isinstance(multi[key], Exception), multi[key]
