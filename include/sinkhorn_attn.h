@@ -386,7 +386,8 @@ int sinkhorn_attn_set_streams(int n);
  * of the latest have started; otherwise the call runs unfused, as it does on a stream with a mask of CUs.  Other programs' it cannot know of.  Every wait inside the launch is bounded by spin_limit polls (0: the default,
  * 2^18, about a tenth of a second): a wait that runs out stops waiting and writes NaN into its block of the
  * potentials, which reaches every output depending on it, and the launch ends normally.  The same bound holds for
- * the waits of short calls' whole steps in one launch, whatever the mode; what such a launch gives up is solved again by the launch after it.
+ * the waits of short calls' whole steps in one launch, whatever the mode; what such a launch gives up is solved again by the launch after it,
+ * equal to rounding (results are those of separate launches bit for bit where no wait runs out).
  * After a wait has run out, the next calls (256, twice as many each time that it happens soon again) run without such launches;
  * this function forgets that, whatever its arguments.
  * Process-wide.  Returns SKA_OK, or SKA_EINVAL for another mode.

@@ -264,15 +264,16 @@ def test_no_chain_beside_one_that_has_not_started(first, second):
     assert chains.started == chains.launched
 
 
-@pytest.mark.parametrize("kind", ["steps", "half-steps"])
-def test_after_a_wait_that_ran_out_calls_are_launched(kind):
+@pytest.mark.parametrize("kind,split", [("steps", False), ("half-steps", False), ("half-steps", True)])
+def test_after_a_wait_that_ran_out_calls_are_launched(kind, split):
+    """(split: half-steps that were queued for one launch run on the two streams after all)"""
     import torch
 
     import paper_2605_08123_amd as ska
     from paper_2605_08123_amd import binding
     gen = torch.Generator(device="cuda")
     gen.manual_seed(12)
-    N, L, W, mode = (8, 700, 64, 0) if kind == "steps" else (2, 9000, 500, 2)
+    N, L, W, mode = (8, 700, 64, 0) if kind == "steps" else (3, 9000, 500, 2)
     Q, K, V = (torch.randn((N, 1, L, 64), generator=gen, device="cuda").bfloat16() for _ in range(3))
 
     def call():
@@ -282,6 +283,7 @@ def test_after_a_wait_that_ran_out_calls_are_launched(kind):
         return *out, binding.query_chains().launched - before
 
     try:
+        ska.sinkhorn_attn_set_split_min_edges(0.0 if split else 5e7)
         ska.sinkhorn_attn_set_fused_half_steps(mode)
         ref = call()
         assert ref[2] == 1
@@ -299,6 +301,7 @@ def test_after_a_wait_that_ran_out_calls_are_launched(kind):
         O, UV, chained = call()
         assert chained and torch.equal(O, ref[0]) and torch.equal(UV, ref[1])
     finally:
+        ska.sinkhorn_attn_set_split_min_edges(5e7)
         ska.sinkhorn_attn_set_fused_half_steps(0)
 
 
@@ -317,7 +320,7 @@ def test_a_chain_behind_one_that_gave_up():
         ska.sinkhorn_attn_set_fused_half_steps(0)
         O0, UV0 = call(0)
         for _ in range(20):   # (until a wait has run out)
-            torch.cuda._sleep(20_000_000)
+            torch.cuda._sleep(100_000_000)
             ska.sinkhorn_attn_set_fused_half_steps(0, 1)
             first, before = call(0), binding.query_chains()
             ska.sinkhorn_attn_set_fused_half_steps(0)
